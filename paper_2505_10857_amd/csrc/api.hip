@@ -1111,8 +1111,10 @@ nmg_status nmg_nested_solve(const nmg_desc *descs, int32_t ngrids, const nmg_par
             return fail(NMG_EINVAL, "the interpolation needs at least three coarse cells in each direction");
         if (descs[g].levels != ngrids - g) return fail(NMG_EINVAL, "grid g must have ngrids - g levels");
     }
-    if (ws_bytes < nmg_nested_workspace_bytes(descs, ngrids, params))
-        return fail(NMG_ENOMEM_WS, "workspace too small");
+    if (nmg_nested_workspace_bytes(descs, ngrids, params) == 0) return fail(NMG_ENOMEM_WS, "workspace too small");
+    for (int g = 0; g < ngrids; g++)
+        if (ws_bytes < (dim == 2 ? workspace2d_bytes(&descs[g], &params[g], true) : nmg_workspace_bytes(&descs[g], &params[g])))
+            return fail(NMG_ENOMEM_WS, "workspace too small");
     hipStream_t s = (hipStream_t)stream;
     for (int g = ngrids - 1; g >= 0; g--) {
         if (g < ngrids - 1) {
@@ -1223,7 +1225,7 @@ nmg_status nmg_newton_solve_static(const nmg_desc *desc, const nmg_params *param
 {
     if (!desc || !params) return fail(NMG_EINVAL, "null desc or params");
     if (!U) return fail(NMG_EINVAL, "null U");
-    const size_t need = nmg_workspace_bytes(desc, params);
+    const size_t need = desc->dim == 2 ? workspace2d_bytes(desc, params, true) : nmg_workspace_bytes(desc, params);
     if (need == 0) return NMG_EINVAL;   // the size query has set the message
     if (need > kStaticWsBytes)
         return fail(NMG_ENOMEM_WS, "the problem needs " + std::to_string(need) +
@@ -1235,7 +1237,8 @@ nmg_status nmg_newton_solve_static(const nmg_desc *desc, const nmg_params *param
     hipStream_t s = (hipStream_t)stream;
     nmg_stats local;
     nmg_stats &S = stats ? *stats : local;
-    if (desc->dim == 2) return newton2d(desc, params, ws, kStaticWsBytes, U, &S, hist, max_hist, s);
+    // need bytes: no mailbox, so no cooperative launch, whose first use may make the runtime allocate
+    if (desc->dim == 2) return newton2d(desc, params, ws, need, U, &S, hist, max_hist, s);
     nmg_plan P;
     st = build_plan(&P, desc, params, 1);
     if (st != NMG_OK) return st;

@@ -11,6 +11,8 @@
 //              in double (NMG_FP64) or float (NMG_FP32_MG), cells in the level's colour-blocked
 //              order (M_l slots, Perm2D); the caller's arrays stay in the natural order
 //   lu       : LU factors and row permutation of the coarsest operator (double [M][M], int [M])
+//   box      : mailbox of the resident levels (launch_resident2d); a workspace that ends before it
+//              is taken too, and every level then runs as separate launches
 #include <algorithm>
 #include <cstddef>
 #include <cstring>
@@ -41,8 +43,19 @@ struct Plan2D {
     int bottom_first = 0;      // first level of the one-workgroup bottom (launch_bottom2d)
     double tau = 0.0, omega = 1.0, tol = 0.0;
     std::vector<Level2D> L;
-    size_t off_state = 0, off_partial = 0, off_hist = 0, off_R = 0, off_rn = 0, off_mg = 0, off_lu = 0, total = 0;
+    size_t off_state = 0, off_partial = 0, off_hist = 0, off_R = 0, off_rn = 0, off_mg = 0, off_lu = 0;
+    size_t off_box = 0;        // = base: the workspace without the mailbox
+    size_t total = 0;
+    // resident levels (use_resident): the tiling of each launched level, tx = 0 where it has none
+    std::vector<Resident2D> res;
+    long long box_cells = 0;   // cells of the largest level that may be resident
+    bool resident = false;
+    mutable unsigned tag = 0;  // exchanges numbered so far in this call
 };
+
+// the largest level whose rows the registers of the chip can hold, by size alone (the device is
+// not asked when a workspace is sized)
+constexpr long long kResidentCells = 1LL << 18;
 
 nmg_status check2d(const nmg_desc *d, const nmg_params *p, bool need_geometry = true)
 {
@@ -170,6 +183,12 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
     const Level2D &Lc = P.L.back();
     set_bottom(P);
     P.off_lu = o; o = al256(o + coarse_lu_bytes(3 * Lc.nx * Lc.ny));
+    P.off_box = o;
+    if (!P.sweeps)
+        for (int l = 0; l < P.levels && P.box_cells == 0; l++)
+            if (P.L[l].nb != 21 && (long long)P.L[l].nx * P.L[l].ny <= kResidentCells)
+                P.box_cells = (long long)P.L[l].nx * P.L[l].ny;
+    o = al256(o + resident2d_box_bytes(P.box_cells, P.prec));
     P.total = o;
     return NMG_OK;
 }
@@ -199,18 +218,69 @@ nmg_status smooth(const Plan2D &P, char *mgb, int l, int nu, hipStream_t s)
     return NMG_OK;
 }
 
-// Algorithm 2 from level l (recursive)
-nmg_status vcycle_from(const Plan2D &P, char *mgb, int l, hipStream_t s)
+hipError_t clear_box(const Plan2D &P, char *ws, hipStream_t s)
 {
+    return launch_fill(ws + P.off_box, NMG_FP64, (long long)(resident2d_box_bytes(P.box_cells, P.prec) / 8), s);
+}
+
+// Choose the resident levels of a call and clear their mailbox.  Levels run as separate launches
+// where the workspace has no mailbox, while `s` is being captured (a graph may replay beside other
+// work, and the launches are cooperative), and where the device has too few compute units.
+nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
+{
+    P.res.assign(P.levels, Resident2D());
+    P.resident = false;
+    if (P.box_cells == 0 || ws_bytes < P.total) return NMG_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY2(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) return NMG_OK;
+    for (int l = 0; l < P.bottom_first; l++) {
+        const Level2D &L = P.L[l];
+        if (L.nb == 21 || (long long)L.nx * L.ny > P.box_cells) continue;
+        P.res[l] = resident2d_plan(L, P.prec, resident2d_max_wg(L.nb, P.prec));
+        if (P.res[l].tx > 0) P.resident = true;
+    }
+    if (P.resident) HIP_TRY2(clear_box(P, ws, s));
+    return NMG_OK;
+}
+
+nmg_status resident(const Plan2D &P, char *mgb, int l, int nu, int prolong, int restr, const NewtonState *S, hipStream_t s)
+{
+    const unsigned tag = P.tag;
+    P.tag += resident2d_exchanges(P.L[l], nu, P.res[l].m);
+    HIP_TRY2(launch_resident2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
+                               mgb - P.off_mg + P.off_box, P.box_cells, S, P.prec, s));
+    return NMG_OK;
+}
+
+// Algorithm 2 from level l (recursive), `cycles` times in a row: nothing else touches level l
+// between two cycles, so a resident level runs the post-smoothing of one and the pre-smoothing of
+// the next in one launch
+nmg_status vcycle_from(const Plan2D &P, char *mgb, int l, hipStream_t s, int cycles = 1, const NewtonState *S = nullptr)
+{
+    nmg_status st;
+    if (l < P.bottom_first && P.res[l].tx > 0) {
+        if ((st = resident(P, mgb, l, P.nu1, 0, 1, S, s)) != NMG_OK) return st;
+        for (int c = 0; c < cycles; c++) {
+            if ((st = vcycle_from(P, mgb, l + 1, s, 1, S)) != NMG_OK) return st;
+            const bool more = c + 1 < cycles;
+            if ((st = resident(P, mgb, l, P.nu2 + (more ? P.nu1 : 0), 1, more, S, s)) != NMG_OK) return st;
+        }
+        return NMG_OK;
+    }
+    if (cycles > 1) {
+        for (int c = 0; c < cycles; c++)
+            if ((st = vcycle_from(P, mgb, l, s, 1, S)) != NMG_OK) return st;
+        return NMG_OK;
+    }
     if (l >= P.bottom_first) {
         HIP_TRY2(launch_bottom2d(mgb, P.L.data(), l, P.levels, P.nu1, P.nu2, P.omega,
                                  (const double *)(mgb - P.off_mg + P.off_lu), P.prec, s, P.sweeps));
         return NMG_OK;
     }
-    nmg_status st;
     if ((st = smooth(P, mgb, l, P.nu1, s)) != NMG_OK) return st;
     HIP_TRY2(launch_restrict2d(mgb, P.L[l], P.L[l + 1], P.prec, s));
-    if ((st = vcycle_from(P, mgb, l + 1, s)) != NMG_OK) return st;
+    if ((st = vcycle_from(P, mgb, l + 1, s, 1, S)) != NMG_OK) return st;
     HIP_TRY2(launch_prolong2d(mgb, P.L[l], P.L[l + 1], P.prec, s));
     return smooth(P, mgb, l, P.nu2, s);
 }
@@ -245,8 +315,11 @@ nmg_status newton_step(const Plan2D &P, char *w, double *U, hipStream_t s)
     nmg_status st = coarsen_all(P, mgb, s);
     if (st != NMG_OK) return st;
     HIP_TRY2(launch_fill(mgb + vsz * L0.dU, P.prec, 3 * L0.P.M, s));
-    for (int m = 0; m < P.nu3; m++)
-        if ((st = vcycle_from(P, mgb, 0, s)) != NMG_OK) return st;
+    if (P.tag > (1u << 30)) {     // a step numbers fewer exchanges than this
+        HIP_TRY2(clear_box(P, w, s));
+        P.tag = 0;
+    }
+    if ((st = vcycle_from(P, mgb, 0, s, P.nu3, S)) != NMG_OK) return st;
     HIP_TRY2(launch_update2d(U, mgb, L0, P.tau, S, P.prec, s));
     HIP_TRY2(launch_residual2d(I, (double *)(w + P.off_partial), s));
     HIP_TRY2(launch_state2d((double *)(w + P.off_partial), P.ntiles, n0, P.tol, P.n_max, S,
@@ -256,11 +329,11 @@ nmg_status newton_step(const Plan2D &P, char *w, double *U, hipStream_t s)
 
 }  // namespace
 
-size_t workspace2d_bytes(const nmg_desc *d, const nmg_params *p)
+size_t workspace2d_bytes(const nmg_desc *d, const nmg_params *p, bool base)
 {
     Plan2D P;
     if (build2d(P, d, p, false) != NMG_OK) return 0;
-    return P.total;
+    return base ? P.off_box : P.total;
 }
 
 nmg_status residual2d(const nmg_desc *d, const double *U, double *R, double *rn, double *res, hipStream_t s)
@@ -302,7 +375,8 @@ nmg_status vcycle2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
     Plan2D P;
     nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
-    if (ws_bytes < P.total) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if ((st = use_resident(P, (char *)ws, ws_bytes, s)) != NMG_OK) return st;
     char *mgb = (char *)ws + P.off_mg;
     const size_t vsz = P.prec == NMG_FP32_MG ? 4 : 8;
     const Level2D &L0 = P.L[0];
@@ -333,7 +407,7 @@ nmg_status newton2d_begin(const nmg_desc *d, const nmg_params *p, void *ws, size
     Plan2D P;
     nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
-    if (ws_bytes < P.total) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;
     const Inst2D I = bound_inst(P, w, U);
     const long long n0 = (long long)P.L[0].nx * P.L[0].ny;
@@ -351,8 +425,9 @@ nmg_status newton2d_steps(const nmg_desc *d, const nmg_params *p, void *ws, size
     Plan2D P;
     nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
-    if (ws_bytes < P.total) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;
+    if (steps > 0 && (st = use_resident(P, w, ws_bytes, s)) != NMG_OK) return st;
     for (int k = 0; k < steps; k++)
         if ((st = newton_step(P, w, U, s)) != NMG_OK) return st;
     if (state_out)
@@ -371,7 +446,7 @@ nmg_status autotune2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t w
     nmg_status st = build2d(P, d, &q);
     if (st != NMG_OK) return st;
     if (P.sweeps) return set_error(NMG_EINVAL, "the schedules concern the multicolour smoother");
-    if (ws_bytes < P.total) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *mgb = (char *)ws + P.off_mg;
     const size_t vsz = P.prec == NMG_FP32_MG ? 4 : 8;
     const Level2D &L0 = P.L[0];
@@ -387,6 +462,8 @@ nmg_status autotune2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t w
     for (int c = 0; c < NMG_TUNE2D_CANDIDATES; c++) {
         P.sched = c;
         set_bottom(P);
+        if ((st = use_resident(P, (char *)ws, ws_bytes, s)) != NMG_OK) return st;
+        P.tag = 0;
         HIP_TRY2(launch_fill(mgb + vsz * L0.dU, P.prec, 3 * L0.P.M, s));
         if ((st = vcycle_from(P, mgb, 0, s)) != NMG_OK) return st;          // warm-up
         HIP_TRY2(hipEventRecord(e0, s));
@@ -410,13 +487,14 @@ nmg_status newton2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
     Plan2D P;
     nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
-    if (ws_bytes < P.total) return set_error(NMG_ENOMEM_WS, "workspace too small");
+    if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;
     const Inst2D I = bound_inst(P, w, U);
     const long long n0 = (long long)P.L[0].nx * P.L[0].ny;
     NewtonState *S = (NewtonState *)(w + P.off_state);
     HIP_TRY2(launch_residual2d(I, (double *)(w + P.off_partial), s));
     HIP_TRY2(launch_state2d((double *)(w + P.off_partial), P.ntiles, n0, P.tol, P.n_max, S, nullptr, 0, 1, s));
+    if ((st = use_resident(P, w, ws_bytes, s)) != NMG_OK) return st;
     NewtonState hs;
     memset(&hs, 0, sizeof(hs));
     HIP_TRY2(hipMemcpyAsync(&hs, S, sizeof(hs), hipMemcpyDeviceToHost, s));

@@ -487,6 +487,360 @@ __global__ void k_prolong2d(T *mg, Level2D Lf, Level2D Lc)
     prolong_cell(mg, Lf, Lc, i, j);
 }
 
+// ---- resident smoothing of a level ----------------------------------------------------------
+
+// One launch per smoothing phase of a level: each workgroup owns a tile of tx x ty cells, every
+// thread keeps the operator rows of its cells (off-diagonal blocks, D^{-1}, right-hand side) in
+// registers for all the phase's colour passes, and dU of the tile with its halo lives in LDS.
+// What bounds the launched passes below is the launch itself (4-5 us each) on small levels and
+// re-reading the operator 4 nu (C-1) + 1 times on large ones; here the operator is read once and
+// a pass costs its arithmetic and a share of an exchange.
+//
+// Exchange: after every m passes a workgroup publishes its cells within the halo width of its
+// edges in a mailbox and fetches its own halo from there.  A value travels as 64-bit words of 32
+// payload bits under the 32-bit number of the exchange, so a word is its own arrival flag: no
+// fence, no separate flag, one trip (about 1.0 us between any two workgroups of the chip, measured
+// with 16 to 256 of them).  Between exchanges the workgroup also relaxes the cells of its halo that
+// later passes of the group need (overlapped tiles: the compute region is the tile widened by
+// R (m-1) cells, R the reach of the stencil; dU is held R m cells wide), so the exchanges are
+// fewer and each result is formed from the same values by the same operations as in the
+// launched passes, bit for bit.
+//
+// Two parities of the mailbox suffice: a workgroup writes exchange e + 2 only after it has fetched
+// e + 1 from every workgroup whose cells its halo holds, which are those whose halos hold its cells, and
+// each of them published e + 1 after it had fetched e.  With m = 1 only the pass's colour is
+// exchanged and the halo's corners (which no cross stencil reads) are left out; tiles are at least
+// two cells wide, so every shared edge holds every colour.  With m >= 2 every cell is exchanged.
+//
+// The launch is cooperative, so all workgroups are resident and every wait ends; each wait is
+// bounded all the same (kWaitTicks of the 100 MHz clock), and a workgroup whose wait ran out stops
+// waiting, finishes and stores NaN.
+struct Resident2DArgs {
+    Level2D L, Lc;             // the level and the next coarser one
+    int tx, ty, gx, m;
+    int nu;                    // smoothing iterations (two phases in a row are one longer phase)
+    int prolong, restr;        // eq. (25) first; eq. (24)'s right-hand side last
+    unsigned tag;              // the launch's exchanges are numbered tag + 1, tag + 2, ...
+    double omega;
+    unsigned long long *box;   // [2][cells][words per cell]
+    long long cells;
+    const NewtonState *state;  // may be null: run regardless
+};
+
+constexpr long long kWaitTicks = 2000000000LL;   // 20 s
+
+template <typename T> struct BoxWords;
+template <> struct BoxWords<float> { static constexpr int n = 3; };
+template <> struct BoxWords<double> { static constexpr int n = 6; };
+
+__device__ __forceinline__ void box_put(unsigned long long *w, unsigned tag, unsigned payload)
+{
+    __hip_atomic_store(w, ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void box_store(unsigned long long *w, unsigned tag, const float v[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; c++) box_put(w + c, tag, __float_as_uint(v[c]));
+}
+
+__device__ __forceinline__ void box_store(unsigned long long *w, unsigned tag, const double v[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(v[c]);
+        box_put(w + 2 * c, tag, (unsigned)b);
+        box_put(w + 2 * c + 1, tag, (unsigned)(b >> 32));
+    }
+}
+
+// wait until every word carries `tag`; false if the wait ran out
+template <int NW>
+__device__ __forceinline__ bool box_wait(const unsigned long long *w, unsigned tag, unsigned long long v[NW])
+{
+    long long t0 = 0;
+    for (int spin = 0;; spin++) {
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < NW; k++) v[k] = __hip_atomic_load(w + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int k = 0; k < NW; k++) ok = ok && (unsigned)(v[k] >> 32) == tag;
+        if (ok) return true;
+        if ((spin & 255) == 255) {
+            const long long now = wall_clock64();
+            if (t0 == 0) t0 = now;
+            else if (now - t0 > kWaitTicks) return false;
+        }
+    }
+}
+
+__device__ __forceinline__ void box_value(const unsigned long long *v, int c, float &x) { x = __uint_as_float((unsigned)v[c]); }
+__device__ __forceinline__ void box_value(const unsigned long long *v, int c, double &x)
+{
+    x = __longlong_as_double((long long)((v[2 * c + 1] << 32) | (v[2 * c] & 0xffffffffULL)));
+}
+
+// LDS tile of dU: up to kResW x kResH cells (tile and halo) inside a ring of two zero cells, three
+// planes.  The strides are constants, so every neighbour of a cell is an immediate offset, and a
+// neighbour outside the grid reads a zero of the ring.
+constexpr int kResW = 48, kResH = 32, kResLD = kResW + 4, kResPL = kResLD * (kResH + 4);
+constexpr int kResNT = 512;
+constexpr int kResHalo = (kResW * kResH + kResNT - 1) / kResNT;   // halo cells a thread fetches at most
+
+// A row held in FP32 is widened where it is used: the compiler must not widen it once before the
+// passes (the FP64 copies would not fit the registers), so the value is made opaque there.
+__device__ __forceinline__ void keep_narrow(float &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_narrow(double &) {}
+
+// HT: the type the rows are held in; EPT: cells per thread.
+template <typename T, int NB, typename HT, int EPT>
+__global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
+{
+    constexpr int C = NB == 9 ? 3 : 2, R = NB == 9 ? 2 : 1, NW = BoxWords<T>::n;
+    __shared__ double lds[3 * kResPL];           // dU [3][kResH + 4][kResLD]; the restriction's summands last
+    __shared__ int dead;
+    T *const sz = (T *)lds;
+    T *const su = sz + 2 * kResLD + 2;
+    if (A.state && !A.state->active) return;     // the same for every workgroup
+    const Level2D &L = A.L;
+    const int t = threadIdx.x, nx = L.nx, ny = L.ny;
+    const int bi = blockIdx.x % A.gx, bj = blockIdx.x / A.gx;
+    const int i0 = bi * A.tx, j0 = bj * A.ty;
+    const int i1 = i0 + A.tx < nx ? i0 + A.tx : nx, j1 = j0 + A.ty < ny ? j0 + A.ty : ny;
+    const int hc = R * (A.m - 1), hd = R * A.m;
+    const int ci0 = i0 - hc > 0 ? i0 - hc : 0, ci1 = i1 + hc < nx ? i1 + hc : nx;
+    const int cj0 = j0 - hc > 0 ? j0 - hc : 0, cj1 = j1 + hc < ny ? j1 + hc : ny;
+    const int di0 = i0 - hd > 0 ? i0 - hd : 0, di1 = i1 + hd < nx ? i1 + hd : nx;
+    const int dj0 = j0 - hd > 0 ? j0 - hd : 0, dj1 = j1 + hd < ny ? j1 + hd : ny;
+    const int dw = di1 - di0, dh = dj1 - dj0;
+    const long long n = L.P.M;
+    if (t == 0) dead = 0;
+
+    // the thread's cells: the compute region colour by colour, row by row, without gaps (C rows in a
+    // row hold cw cells of every colour)
+    const int cw = ci1 - ci0, ch = cj1 - cj0;
+    auto first = [&](int c, int jr) { return ((c - (ci0 + cj0 + jr)) % C + C) % C; };   // column in the region
+    int end[C];                                  // entries of colours 0 .. c
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        int m = (ch / C) * cw;
+        for (int jr = ch - ch % C; jr < ch; jr++) m += (cw - first(c, jr) + C - 1) / C;
+        end[c] = (c > 0 ? end[c - 1] : 0) + m;
+    }
+    HT Jb[EPT][NB][9], Di[EPT][9], rh[EPT][3];
+    T own[EPT][3];
+    int col[EPT], q[EPT], slot[EPT], cell[EPT];
+    bool inside[EPT], edge[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+        const int e = k * kResNT + t;
+        int c = 0, p = e;
+#pragma unroll
+        for (int x = 0; x + 1 < C; x++)
+            if (e >= end[x]) { c = x + 1; p = e - end[x]; }
+        const bool valid = e < end[C - 1];
+        int jr = p / cw * C, rem = p % cw;
+#pragma unroll
+        for (int x = 0; x + 1 < C; x++) {
+            const int m = (cw - first(c, jr) + C - 1) / C;
+            if (rem >= m) { rem -= m; jr++; }
+            else break;
+        }
+        const int i = ci0 + first(c, jr) + C * rem, j = cj0 + jr;
+        col[k] = valid ? c : -1;
+        inside[k] = valid && i >= i0 && i < i1 && j >= j0 && j < j1;
+        edge[k] = inside[k] && ((i0 > 0 && i - i0 < hd) || (i1 < nx && i1 - 1 - i < hd) || (j0 > 0 && j - j0 < hd) ||
+                                (j1 < ny && j1 - 1 - j < hd));
+        q[k] = valid ? (j - dj0) * kResLD + (i - di0) : 0;
+        slot[k] = valid ? (int)perm2d(L.P, i, j) : 0;
+        cell[k] = valid ? j * nx + i : 0;
+        if (valid) {
+            const long long cc = slot[k];
+#pragma unroll
+            for (int b = 1; b < NB; b++) {
+                const int pi = i + stencil_dx(NB, b), pj = j + stencil_dy(NB, b);
+                const bool ok = pi >= 0 && pi < nx && pj >= 0 && pj < ny;
+#pragma unroll
+                for (int x = 0; x < 9; x++) Jb[k][b][x] = ok ? (HT)mg[L.J + (b * 9 + x) * n + cc] : (HT)0.0;
+            }
+#pragma unroll
+            for (int x = 0; x < 9; x++) Di[k][x] = (HT)mg[L.Dinv + x * n + cc];
+#pragma unroll
+            for (int x = 0; x < 3; x++) rh[k][x] = (HT)mg[L.rhs + x * n + cc];
+        } else {
+#pragma unroll
+            for (int b = 1; b < NB; b++)
+#pragma unroll
+                for (int x = 0; x < 9; x++) Jb[k][b][x] = (HT)0.0;
+#pragma unroll
+            for (int x = 0; x < 9; x++) Di[k][x] = (HT)0.0;
+#pragma unroll
+            for (int x = 0; x < 3; x++) rh[k][x] = (HT)0.0;
+        }
+    }
+
+    // the halo cells the thread fetches: the bands below and above, then left and right
+    const int below = j0 - dj0, above = dj1 - j1, left = i0 - di0, side = left + (di1 - i1);
+    const int nh = (below + above) * dw + (j1 - j0) * side;
+    int hq[kResHalo], hcell[kResHalo], hcol[kResHalo];
+#pragma unroll
+    for (int k = 0; k < kResHalo; k++) {
+        const int e = k * kResNT + t;
+        int i = 0, j = 0;
+        if (e < (below + above) * dw) {
+            const int r = e / dw;
+            i = di0 + e - r * dw;
+            j = r < below ? dj0 + r : j1 + (r - below);
+        } else if (e < nh) {
+            const int f = e - (below + above) * dw, r = f / side, s = f - r * side;
+            j = j0 + r;
+            i = s < left ? di0 + s : i1 + (s - left);
+        }
+        const bool corner = (i < i0 || i >= i1) && (j < j0 || j >= j1);
+        hcol[k] = e < nh && !(A.m == 1 && corner) ? (i + j) % C : -1;
+        hq[k] = (j - dj0) * kResLD + (i - di0);
+        hcell[k] = j * nx + i;
+    }
+
+    // dU of the tile and its halo
+    for (int e = t; e < 3 * kResPL; e += kResNT) sz[e] = (T)0.0;
+    __syncthreads();
+    for (int e = t; e < dw * dh; e += kResNT) {
+        const int r = e / dw, i = di0 + e - r * dw, j = dj0 + r;
+        const long long fc = perm2d(L.P, i, j);
+        const long long pc = A.prolong ? perm2d(A.Lc.P, i >> 1, j >> 1) : 0;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            T v = mg[L.dU + c * n + fc];
+            if (A.prolong) v = (T)((double)v + ld2(mg + A.Lc.dU, c * A.Lc.P.M + pc));
+            su[c * kResPL + r * kResLD + (i - di0)] = v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < EPT; k++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) own[k][c] = su[c * kResPL + q[k]];
+
+    // the merged colour passes: colours 0 .. C-1 .. 0 .. and so on, twice at every turn
+    const int runs = A.nu > 0 ? A.nu * 4 * (C - 1) + 1 : 0;
+    unsigned tag = A.tag;
+    int since = 0;
+    for (int s = 0; s < runs; s++) {
+        const int ph = s % (2 * (C - 1));
+        const int c = ph <= C - 1 ? ph : 2 * (C - 1) - ph;
+        const int reps = (c == 0 || c == C - 1) && s > 0 && s < runs - 1 ? 2 : 1;
+#pragma unroll
+        for (int k = 0; k < EPT; k++) {
+            if (col[k] != c) continue;
+#pragma unroll
+            for (int x = 0; x < 9; x++) {
+#pragma unroll
+                for (int b = 1; b < NB; b++) keep_narrow(Jb[k][b][x]);
+                keep_narrow(Di[k][x]);
+            }
+            T *u = su + q[k];
+            double r[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
+#pragma unroll
+            for (int b = 1; b < NB; b++) {
+                const int o = stencil_dy(NB, b) * kResLD + stencil_dx(NB, b);
+                const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
+#pragma unroll
+                for (int x = 0; x < 3; x++)
+                    r[x] = r[x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
+                                   (double)Jb[k][b][x * 3 + 2] * x2);
+            }
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const double tt = (double)Di[k][x * 3 + 0] * r[0] + (double)Di[k][x * 3 + 1] * r[1] + (double)Di[k][x * 3 + 2] * r[2];
+                T d = u[x * kResPL];
+                d = (T)((1.0 - A.omega) * (double)d - A.omega * tt);
+                if (reps == 2) d = (T)((1.0 - A.omega) * (double)d - A.omega * tt);
+                u[x * kResPL] = d;
+                own[k][x] = d;
+            }
+        }
+        since++;
+        if (since < A.m && s < runs - 1) { __syncthreads(); continue; }
+        since = 0;
+        if (s == runs - 1 && !A.restr) break;
+        tag++;
+        unsigned long long *box = A.box + (long long)(tag & 1) * A.cells * NW;
+#pragma unroll
+        for (int k = 0; k < EPT; k++)
+            if (edge[k] && (A.m > 1 || col[k] == c)) box_store(box + (long long)cell[k] * NW, tag, own[k]);
+        __syncthreads();     // every cell of the group is relaxed and read before the halo changes
+#pragma unroll
+        for (int k = 0; k < kResHalo; k++) {
+            if (hcol[k] < 0 || (A.m == 1 && hcol[k] != c) || dead) continue;
+            unsigned long long v[NW];
+            if (!box_wait<NW>(box + (long long)hcell[k] * NW, tag, v)) { dead = 1; continue; }
+#pragma unroll
+            for (int x = 0; x < 3; x++) box_value(v, x, su[x * kResPL + hq[k]]);
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    const bool bad = dead != 0;
+
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+        if (!inside[k]) continue;
+#pragma unroll
+        for (int c = 0; c < 3; c++) mg[L.dU + c * n + slot[k]] = bad ? (T)__builtin_nan("") : own[k][c];
+    }
+    if (!A.restr) return;
+    // eq. (24): rhs + J dU of every cell of the tile, then the sums over the children
+    const int tw = i1 - i0;
+    double a[EPT][3];
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+        if (!inside[k]) continue;
+        const T *u = su + q[k];
+        const double y0 = (double)u[0], y1 = (double)u[kResPL], y2 = (double)u[2 * kResPL];
+#pragma unroll
+        for (int x = 0; x < 3; x++)
+            a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, (x * 3 + 0) * n + slot[k]) * y0 +
+                                          ld2(mg + L.J, (x * 3 + 1) * n + slot[k]) * y1 +
+                                          ld2(mg + L.J, (x * 3 + 2) * n + slot[k]) * y2);
+#pragma unroll
+        for (int b = 1; b < NB; b++) {
+            const int o = stencil_dy(NB, b) * kResLD + stencil_dx(NB, b);
+            const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
+#pragma unroll
+            for (int x = 0; x < 3; x++)
+                a[k][x] = a[k][x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
+                                     (double)Jb[k][b][x * 3 + 2] * x2);
+        }
+    }
+    __syncthreads();
+    double *sa = lds;                            // [3][tile cells]
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+        if (!inside[k]) continue;
+        const int j = cell[k] / nx, i = cell[k] - j * nx;
+#pragma unroll
+        for (int x = 0; x < 3; x++) sa[x * A.tx * A.ty + (j - j0) * tw + (i - i0)] = a[k][x];
+    }
+    __syncthreads();
+    const int hw = tw / 2, hh = (j1 - j0) / 2;
+    for (int e = t; e < hw * hh; e += kResNT) {
+        const int jq = e / hw, iq = e - jq * hw;
+        double a00[3], a10[3], a01[3], a11[3];
+#pragma unroll
+        for (int x = 0; x < 3; x++) {
+            const double *p = sa + x * A.tx * A.ty + 2 * jq * tw + 2 * iq;
+            a00[x] = p[0];
+            a10[x] = p[1];
+            a01[x] = p[tw];
+            a11[x] = p[tw + 1];
+        }
+        restrict_store(mg, A.Lc, i0 / 2 + iq, j0 / 2 + jq, a00, a10, a01, a11);
+    }
+}
+
 // Coarsest level: Gaussian elimination with partial pivoting of the dense system sum J dU = -rhs
 // (unknown (j*nx + i)*3 + c), split into a factorisation done once per operator and a solve per
 // V-cycle.  The factorisation takes the pivots and eliminates exactly as the plain algorithm does
@@ -981,6 +1335,82 @@ hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps
         else smooth2d_launch<double, 5, false>((double *)mg, L, colour, reps, omega, s, alt);
     }
     return hipGetLastError();
+}
+
+// Cells a workgroup of k_resident2d holds: 512 threads have 256 registers each, a row takes 84
+// values (nine blocks) or 48 (five points).
+static int resident2d_cells(int nb, int prec) { return nb == 9 && prec != NMG_FP32_MG ? kResNT : 2 * kResNT; }
+
+static const void *resident2d_kernel(int nb, int prec)
+{
+    const bool f32 = prec == NMG_FP32_MG;
+    if (nb == 9) return f32 ? (const void *)k_resident2d<float, 9, float, 2> : (const void *)k_resident2d<double, 9, double, 1>;
+    return f32 ? (const void *)k_resident2d<float, 5, double, 2> : (const void *)k_resident2d<double, 5, double, 2>;
+}
+
+// The tiling of one resident level: the tile and the passes per exchange with the smallest
+// estimated time per pass, out of those whose compute region fits the registers, whose halo fits
+// LDS and whose workgroups are all resident at once (one per compute unit).  The estimate: an
+// exchange 1.0 us, shared by m passes; a pass `lat` plus `work` per wavefront that a SIMD has to run;
+// and a little for every workgroup, so that small levels leave compute units to other streams.
+Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
+{
+    Resident2D best;
+    if (L.nb != 9 && L.nb != 5) return best;
+    const int C = L.nb == 9 ? 3 : 2, R = L.nb == 9 ? 2 : 1, cap = resident2d_cells(L.nb, prec);
+    const double lat = 0.2, work = L.nb == 9 ? 0.28 : 0.16;
+    double cost = 1e30;
+    for (int ty = 2; ty <= kResH; ty += 2) {
+        if (ty > L.ny + 1) break;
+        for (int tx = 4; tx <= kResW; tx += 4) {
+            if (tx > L.nx + 3) break;
+            const int gx = (L.nx + tx - 1) / tx, gy = (L.ny + ty - 1) / ty;
+            if (gx * gy > max_wg) continue;
+            for (int m = 1; m <= 16; m++) {
+                const int hc = R * (m - 1), hd = R * m;
+                const int cw = std::min(tx + 2 * hc, L.nx), ch = std::min(ty + 2 * hc, L.ny);
+                if (cw * ch > cap) break;
+                if (std::min(tx + 2 * hd, L.nx) > kResW || std::min(ty + 2 * hd, L.ny) > kResH) break;
+                const double t = (gx * gy > 1 ? 1.0 / m : 0.0) + lat + work * ((cw * ch / C + 255) / 256) + 0.001 * gx * gy;
+                if (t < cost) {
+                    cost = t;
+                    best.tx = tx; best.ty = ty; best.gx = gx; best.gy = gy; best.m = m;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+int resident2d_max_wg(int nb, int prec)
+{
+    int dev = 0, cus = 0, per = 0, coop = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident2d_kernel(nb, prec), kResNT, 0) != hipSuccess) return 0;
+    return per > 0 ? cus : 0;
+}
+
+size_t resident2d_box_bytes(long long cells, int prec) { return (size_t)2 * cells * 8 * (prec == NMG_FP32_MG ? 3 : 6); }
+
+unsigned resident2d_exchanges(const Level2D &L, int nu, int m) { return (unsigned)((nu * 4LL * (L.P.C - 1) + 1) / m + 2); }
+
+hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
+                             int restr, unsigned tag, double omega, void *box, long long cells,
+                             const NewtonState *state, int prec, hipStream_t s)
+{
+    if (G.tx < 2 || L.P.C != (L.nb == 9 ? 3 : 2)) return hipErrorInvalidValue;
+    Resident2DArgs A;
+    A.L = L; A.Lc = Lc;
+    A.tx = G.tx; A.ty = G.ty; A.gx = G.gx; A.m = G.m;
+    A.nu = nu; A.prolong = prolong; A.restr = restr;
+    A.tag = tag; A.omega = omega;
+    A.box = (unsigned long long *)box;
+    A.cells = cells;
+    A.state = state;
+    void *args[] = {&mg, &A};
+    return hipLaunchCooperativeKernel(resident2d_kernel(L.nb, prec), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
 }
 
 hipError_t launch_restrict2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s)

@@ -230,6 +230,21 @@ hipError_t launch_coarsen2d(void *mg, const Level2D &Lf, const Level2D &Lc, int 
 // sched: NMG_SCHED2D_* bits (the pass form and the streaming hints; results are the same)
 hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps, double omega, int prec,
                                hipStream_t s, int sched = 0);
+// A level's smoothing phases with the operator held in registers (k_resident2d): tiles of tx x ty
+// cells, gx x gy workgroups, m colour passes between two exchanges; tx = 0: the level does not fit.
+struct Resident2D {
+    int tx = 0, ty = 0, gx = 0, gy = 0, m = 0;
+};
+Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg);
+// workgroups of k_resident2d that can be resident at once on the current device (0: none)
+int resident2d_max_wg(int nb, int prec);
+// bytes of the mailbox for levels of up to `cells` cells; exchanges a launch numbers
+size_t resident2d_box_bytes(long long cells, int prec);
+unsigned resident2d_exchanges(const Level2D &L, int nu, int m);
+// [prolongation from Lc +] nu smoothing iterations [+ restriction to Lc] in one cooperative launch
+hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
+                             int restr, unsigned tag, double omega, void *box, long long cells,
+                             const NewtonState *state, int prec, hipStream_t s);
 hipError_t launch_restrict2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s);
 hipError_t launch_prolong2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s);
 // coarsest level: LU factors with row permutation (M*M doubles then M ints, M = 3 cells) once
@@ -258,7 +273,8 @@ constexpr int kMaxCoarse2D = 40;   // cells on the coarsest 2D level (dense solv
 nmg_status set_error(nmg_status st, const char *msg);
 
 // 2D entry points (dim = 2), called by the ABI functions
-size_t workspace2d_bytes(const nmg_desc *d, const nmg_params *p);
+// base: without the mailbox of the resident levels, the least that the 2D calls accept
+size_t workspace2d_bytes(const nmg_desc *d, const nmg_params *p, bool base = false);
 nmg_status residual2d(const nmg_desc *d, const double *U, double *R, double *rn, double *res,
                       hipStream_t s);
 nmg_status jacobian2d(const nmg_desc *d, const nmg_params *p, const double *U, const double *R,
