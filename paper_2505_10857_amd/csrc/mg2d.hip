@@ -35,13 +35,10 @@ __device__ __forceinline__ void stencil_off(int nb, int b, int &di, int &dj)
     dj = stencil_dy(nb, b);
 }
 
-__device__ __forceinline__ int find_off(int nb, int di, int dj)
+__device__ constexpr int find_off(int nb, int di, int dj)
 {
-    for (int b = 0; b < nb; b++) {
-        int ox, oy;
-        stencil_off(nb, b, ox, oy);
-        if (ox == di && oy == dj) return b;
-    }
+    for (int b = 0; b < nb; b++)
+        if (stencil_dx(nb, b) == di && stencil_dy(nb, b) == dj) return b;
     return -1;
 }
 
@@ -62,48 +59,56 @@ __device__ __forceinline__ void inv3d(const double A[9], double B[9])
     B[8] = (A[0] * A[4] - A[1] * A[3]) / det;
 }
 
-// eq. (24), operator part, one thread per coarse cell: for each five-point offset, sum the fine
-// blocks of the 2x2 children rows against the 2x2 children of the neighbour; then D^{-1}.
-template <typename T>
-__global__ void k_coarsen2d(T *mg, Level2D Lf, Level2D Lc)
+// eq. (24), operator part, one thread per coarse cell and five-point offset BC: the sum of the fine
+// blocks of the 2x2 children rows against the 2x2 children of the neighbour; for the centre also D^{-1}.
+// The block of every pair of children is known at compile time, so a thread's loads (at most 16
+// blocks of nine) issue together; an offset per thread, a fifth of the row each, keeps the small
+// levels' few cells from being one long chain (37 -> 0 us for a 32 x 16 coarse level).
+template <typename T, int NB, int BC>
+__device__ __forceinline__ void coarsen_block(T *mg, const Level2D &Lf, const Level2D &Lc, int I, int Jq)
 {
-    const int I = blockIdx.x * blockDim.x + threadIdx.x;
-    const int Jq = blockIdx.y;
-    if (I >= Lc.nx || Jq >= Lc.ny) return;
+    constexpr int dP = stencil_dx(5, BC), dQ = stencil_dy(5, BC);
     const long long nf = Lf.P.M, nc = Lc.P.M;
     const long long cc = perm2d(Lc.P, I, Jq);
-    double D[9];
-    for (int bc = 0; bc < 5; bc++) {
-        int dP, dQ;
-        stencil_off(5, bc, dP, dQ);
-        const int P = I + dP, Q = Jq + dQ;
-        double blk[9];
+    const int P = I + dP, Q = Jq + dQ;
+    double blk[9];
 #pragma unroll
-        for (int e = 0; e < 9; e++) blk[e] = 0.0;
-        if (P >= 0 && P < Lc.nx && Q >= 0 && Q < Lc.ny) {
-            for (int fj = 2 * Jq; fj <= 2 * Jq + 1; fj++)
-                for (int fi = 2 * I; fi <= 2 * I + 1; fi++) {
-                    const long long fc = perm2d(Lf.P, fi, fj);
-                    for (int cj = 2 * Q; cj <= 2 * Q + 1; cj++)
-                        for (int ci = 2 * P; ci <= 2 * P + 1; ci++) {
-                            const int b = find_off(Lf.nb, ci - fi, cj - fj);
-                            if (b < 0) continue;
+    for (int e = 0; e < 9; e++) blk[e] = 0.0;
+    if (P >= 0 && P < Lc.nx && Q >= 0 && Q < Lc.ny) {
 #pragma unroll
-                            for (int e = 0; e < 9; e++)
-                                blk[e] = blk[e] + ld2(mg + Lf.J, (b * 9 + e) * nf + fc);
-                        }
-                }
-        }
+        for (int f = 0; f < 4; f++) {
+            const long long fc = perm2d(Lf.P, 2 * I + (f & 1), 2 * Jq + (f >> 1));
 #pragma unroll
-        for (int e = 0; e < 9; e++) {
-            mg[Lc.J + (bc * 9 + e) * nc + cc] = (T)blk[e];
-            if (bc == 0) D[e] = blk[e];
+            for (int g = 0; g < 4; g++) {
+                const int b = find_off(NB, 2 * dP + (g & 1) - (f & 1), 2 * dQ + (g >> 1) - (f >> 1));
+                if (b < 0) continue;
+#pragma unroll
+                for (int e = 0; e < 9; e++) blk[e] = blk[e] + ld2(mg + Lf.J, (b * 9 + e) * nf + fc);
+            }
         }
     }
-    double B[9];
-    inv3d(D, B);
 #pragma unroll
-    for (int e = 0; e < 9; e++) mg[Lc.Dinv + e * nc + cc] = (T)B[e];
+    for (int e = 0; e < 9; e++) mg[Lc.J + (BC * 9 + e) * nc + cc] = (T)blk[e];
+    if (BC == 0) {
+        double B[9];
+        inv3d(blk, B);
+#pragma unroll
+        for (int e = 0; e < 9; e++) mg[Lc.Dinv + e * nc + cc] = (T)B[e];
+    }
+}
+
+template <typename T, int NB>
+__global__ void __launch_bounds__(64) k_coarsen2d(T *mg, Level2D Lf, Level2D Lc)
+{
+    const int I = blockIdx.x * 64 + threadIdx.x, Jq = blockIdx.y;
+    if (I >= Lc.nx) return;
+    switch (blockIdx.z) {
+    case 0: coarsen_block<T, NB, 0>(mg, Lf, Lc, I, Jq); break;
+    case 1: coarsen_block<T, NB, 1>(mg, Lf, Lc, I, Jq); break;
+    case 2: coarsen_block<T, NB, 2>(mg, Lf, Lc, I, Jq); break;
+    case 3: coarsen_block<T, NB, 3>(mg, Lf, Lc, I, Jq); break;
+    default: coarsen_block<T, NB, 4>(mg, Lf, Lc, I, Jq); break;
+    }
 }
 
 // `reps` consecutive passes of eq. (22) over the cells of one colour on one level with the
@@ -508,9 +513,9 @@ __global__ void k_prolong2d(T *mg, Level2D Lf, Level2D Lc)
 //
 // Two parities of the mailbox suffice: a workgroup writes exchange e + 2 only after it has fetched
 // e + 1 from every workgroup whose cells its halo holds, which are those whose halos hold its cells, and
-// each of them published e + 1 after it had fetched e.  With m = 1 only the pass's colour is
-// exchanged and the halo's corners (which no cross stencil reads) are left out; tiles are at least
-// two cells wide, so every shared edge holds every colour.  With m >= 2 every cell is exchanged.
+// each of them published e + 1 after it had fetched e.  A halo leaves out its corners, which m
+// passes of a cross stencil do not reach.  With m = 1 only the pass's colour is exchanged (tiles are
+// at least two cells wide, so every shared edge holds every colour), with m >= 2 every cell.
 //
 // The launch is cooperative, so all workgroups are resident and every wait ends; each wait is
 // bounded all the same (kWaitTicks of the 100 MHz clock), and a workgroup whose wait ran out stops
@@ -554,67 +559,48 @@ __device__ __forceinline__ void box_store(unsigned long long *w, unsigned tag, c
     }
 }
 
-// wait until every word carries `tag`; false if the wait ran out
-template <int NW>
-__device__ __forceinline__ bool box_wait(const unsigned long long *w, unsigned tag, unsigned long long v[NW])
-{
-    long long t0 = 0;
-    for (int spin = 0;; spin++) {
-        bool ok = true;
-#pragma unroll
-        for (int k = 0; k < NW; k++) v[k] = __hip_atomic_load(w + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int k = 0; k < NW; k++) ok = ok && (unsigned)(v[k] >> 32) == tag;
-        if (ok) return true;
-        if ((spin & 255) == 255) {
-            const long long now = wall_clock64();
-            if (t0 == 0) t0 = now;
-            else if (now - t0 > kWaitTicks) return false;
-        }
-    }
-}
-
 __device__ __forceinline__ void box_value(const unsigned long long *v, int c, float &x) { x = __uint_as_float((unsigned)v[c]); }
 __device__ __forceinline__ void box_value(const unsigned long long *v, int c, double &x)
 {
     x = __longlong_as_double((long long)((v[2 * c + 1] << 32) | (v[2 * c] & 0xffffffffULL)));
 }
 
-// LDS tile of dU: up to kResW x kResH cells (tile and halo) inside a ring of two zero cells, three
-// planes.  The strides are constants, so every neighbour of a cell is an immediate offset, and a
-// neighbour outside the grid reads a zero of the ring.
-constexpr int kResW = 48, kResH = 32, kResLD = kResW + 4, kResPL = kResLD * (kResH + 4);
+// LDS tile of dU: the cells of the tile and its halo, row by row, inside a ring of two zero cells
+// (a neighbour outside the grid reads a zero of the ring); three planes at a constant stride.
+constexpr int kResPL = 1872;                     // cells of a plane, ring included (48 x 32 cells fit)
 constexpr int kResNT = 512;
-constexpr int kResHalo = (kResW * kResH + kResNT - 1) / kResNT;   // halo cells a thread fetches at most
+constexpr int kResHalo = 3;                      // halo cells a thread fetches at most
+
+// a tile of w x h cells fits the plane
+__host__ __device__ inline bool resident2d_fits(int w, int h) { return (w + 4) * (h + 4) <= kResPL; }
 
 // A row held in FP32 is widened where it is used: the compiler must not widen it once before the
 // passes (the FP64 copies would not fit the registers), so the value is made opaque there.
 __device__ __forceinline__ void keep_narrow(float &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void keep_narrow(double &) {}
 
-// HT: the type the rows are held in; EPT: cells per thread.
-template <typename T, int NB, typename HT, int EPT>
-__global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
+// One smoothing phase of one level by the workgroups that share it; this one has tile (bi, bj).
+// HT: the type the rows are held in; EPT: cells per thread; SOLO: one workgroup has the whole
+// level (no halo, no mailbox).  lds: [3 kResPL] doubles; dead: set when a wait ran out.
+template <typename T, int NB, typename HT, int EPT, bool SOLO>
+__device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, int bi, int bj, double *lds, int &dead)
 {
     constexpr int C = NB == 9 ? 3 : 2, R = NB == 9 ? 2 : 1, NW = BoxWords<T>::n;
-    __shared__ double lds[3 * kResPL];           // dU [3][kResH + 4][kResLD]; the restriction's summands last
-    __shared__ int dead;
-    T *const sz = (T *)lds;
-    T *const su = sz + 2 * kResLD + 2;
-    if (A.state && !A.state->active) return;     // the same for every workgroup
+    constexpr int KB = NW == 3 ? 3 : 2;          // halo cells whose words a thread has in flight
+    T *const sz = (T *)lds;                      // dU [3][rows + 4][ld]; the restriction's summands last
     const Level2D &L = A.L;
     const int t = threadIdx.x, nx = L.nx, ny = L.ny;
-    const int bi = blockIdx.x % A.gx, bj = blockIdx.x / A.gx;
-    const int i0 = bi * A.tx, j0 = bj * A.ty;
-    const int i1 = i0 + A.tx < nx ? i0 + A.tx : nx, j1 = j0 + A.ty < ny ? j0 + A.ty : ny;
-    const int hc = R * (A.m - 1), hd = R * A.m;
+    const int i0 = SOLO ? 0 : bi * A.tx, j0 = SOLO ? 0 : bj * A.ty;
+    const int i1 = !SOLO && i0 + A.tx < nx ? i0 + A.tx : nx, j1 = !SOLO && j0 + A.ty < ny ? j0 + A.ty : ny;
+    const int hc = SOLO ? 0 : R * (A.m - 1), hd = SOLO ? 0 : R * A.m;
     const int ci0 = i0 - hc > 0 ? i0 - hc : 0, ci1 = i1 + hc < nx ? i1 + hc : nx;
     const int cj0 = j0 - hc > 0 ? j0 - hc : 0, cj1 = j1 + hc < ny ? j1 + hc : ny;
     const int di0 = i0 - hd > 0 ? i0 - hd : 0, di1 = i1 + hd < nx ? i1 + hd : nx;
     const int dj0 = j0 - hd > 0 ? j0 - hd : 0, dj1 = j1 + hd < ny ? j1 + hd : ny;
-    const int dw = di1 - di0, dh = dj1 - dj0;
+    const int dw = di1 - di0, dh = dj1 - dj0, ld = dw + 4;
+    T *const su = sz + 2 * ld + 2;
     const long long n = L.P.M;
-    if (t == 0) dead = 0;
+    if (t == 0 && !SOLO) dead = 0;
 
     // the thread's cells: the compute region colour by colour, row by row, without gaps (C rows in a
     // row hold cw cells of every colour)
@@ -628,9 +614,14 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
         end[c] = (c > 0 ? end[c - 1] : 0) + m;
     }
     HT Jb[EPT][NB][9], Di[EPT][9], rh[EPT][3];
-    T own[EPT][3];
-    int col[EPT], q[EPT], slot[EPT], cell[EPT];
-    bool inside[EPT], edge[EPT];
+    // a cell's colour (-1: none), whether it is the tile's own and whether other tiles read it (the
+    // registers are full: its place in the level is worked out from q where it is needed)
+    int q[EPT], flags[EPT];
+    auto colour = [&](int k) { return (flags[k] & 15) - 1; };
+    auto inside = [&](int k) { return (flags[k] & 16) != 0; };
+    auto edge = [&](int k) { return (flags[k] & 32) != 0; };
+    auto cell_i = [&](int k) { return di0 + q[k] % ld; };
+    auto cell_j = [&](int k) { return dj0 + q[k] / ld; };
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         const int e = k * kResNT + t;
@@ -647,15 +638,13 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
             else break;
         }
         const int i = ci0 + first(c, jr) + C * rem, j = cj0 + jr;
-        col[k] = valid ? c : -1;
-        inside[k] = valid && i >= i0 && i < i1 && j >= j0 && j < j1;
-        edge[k] = inside[k] && ((i0 > 0 && i - i0 < hd) || (i1 < nx && i1 - 1 - i < hd) || (j0 > 0 && j - j0 < hd) ||
-                                (j1 < ny && j1 - 1 - j < hd));
-        q[k] = valid ? (j - dj0) * kResLD + (i - di0) : 0;
-        slot[k] = valid ? (int)perm2d(L.P, i, j) : 0;
-        cell[k] = valid ? j * nx + i : 0;
+        const bool own = valid && i >= i0 && i < i1 && j >= j0 && j < j1;
+        const bool read = own && ((i0 > 0 && i - i0 < hd) || (i1 < nx && i1 - 1 - i < hd) || (j0 > 0 && j - j0 < hd) ||
+                                  (j1 < ny && j1 - 1 - j < hd));
+        flags[k] = (valid ? c + 1 : 0) | (own ? 16 : 0) | (read ? 32 : 0);
+        q[k] = valid ? (j - dj0) * ld + (i - di0) : 0;
         if (valid) {
-            const long long cc = slot[k];
+            const long long cc = perm2d(L.P, i, j);
 #pragma unroll
             for (int b = 1; b < NB; b++) {
                 const int pi = i + stencil_dx(NB, b), pj = j + stencil_dy(NB, b);
@@ -679,10 +668,10 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
         }
     }
 
-    // the halo cells the thread fetches: the bands below and above, then left and right
+    // the halo cells the thread fetches (none where one workgroup has the level): the bands below and above, then left and right
     const int below = j0 - dj0, above = dj1 - j1, left = i0 - di0, side = left + (di1 - i1);
     const int nh = (below + above) * dw + (j1 - j0) * side;
-    int hq[kResHalo], hcell[kResHalo], hcol[kResHalo];
+    int hq[kResHalo], hcell[kResHalo];           // hq: place in LDS | colour + 1 << 16 (0: nothing to fetch)
 #pragma unroll
     for (int k = 0; k < kResHalo; k++) {
         const int e = k * kResNT + t;
@@ -696,10 +685,11 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
             j = j0 + r;
             i = s < left ? di0 + s : i1 + (s - left);
         }
-        const bool corner = (i < i0 || i >= i1) && (j < j0 || j >= j1);
-        hcol[k] = e < nh && !(A.m == 1 && corner) ? (i + j) % C : -1;
-        hq[k] = (j - dj0) * kResLD + (i - di0);
-        hcell[k] = j * nx + i;
+        // a pass moves information R cells along one axis: m passes read no cell farther out
+        const int ox = i < i0 ? i0 - i : (i >= i1 ? i - i1 + 1 : 0), oy = j < j0 ? j0 - j : (j >= j1 ? j - j1 + 1 : 0);
+        const bool read = e < nh && (ox + R - 1) / R + (oy + R - 1) / R <= A.m;
+        hq[k] = read ? ((j - dj0) * ld + (i - di0)) | ((i + j) % C + 1) << 16 : 0;
+        hcell[k] = read ? j * nx + i : 0;
     }
 
     // dU of the tile and its halo
@@ -713,26 +703,26 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
         for (int c = 0; c < 3; c++) {
             T v = mg[L.dU + c * n + fc];
             if (A.prolong) v = (T)((double)v + ld2(mg + A.Lc.dU, c * A.Lc.P.M + pc));
-            su[c * kResPL + r * kResLD + (i - di0)] = v;
+            su[c * kResPL + r * ld + (i - di0)] = v;
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < EPT; k++)
-#pragma unroll
-        for (int c = 0; c < 3; c++) own[k][c] = su[c * kResPL + q[k]];
+    // the rows have to be there before the first pass: a wait left to the loop would count the
+    // exchange's stores too
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
 
     // the merged colour passes: colours 0 .. C-1 .. 0 .. and so on, twice at every turn
     const int runs = A.nu > 0 ? A.nu * 4 * (C - 1) + 1 : 0;
     unsigned tag = A.tag;
+    const double keep = 1.0 - A.omega;
     int since = 0;
     for (int s = 0; s < runs; s++) {
         const int ph = s % (2 * (C - 1));
         const int c = ph <= C - 1 ? ph : 2 * (C - 1) - ph;
-        const int reps = (c == 0 || c == C - 1) && s > 0 && s < runs - 1 ? 2 : 1;
+        const bool twice = (c == 0 || c == C - 1) && s > 0 && s < runs - 1;
 #pragma unroll
         for (int k = 0; k < EPT; k++) {
-            if (col[k] != c) continue;
+            if (colour(k) != c) continue;
 #pragma unroll
             for (int x = 0; x < 9; x++) {
 #pragma unroll
@@ -740,12 +730,13 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
                 keep_narrow(Di[k][x]);
             }
             T *u = su + q[k];
+            T d[3] = {u[0], u[kResPL], u[2 * kResPL]};
             double r[3];
 #pragma unroll
             for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
 #pragma unroll
             for (int b = 1; b < NB; b++) {
-                const int o = stencil_dy(NB, b) * kResLD + stencil_dx(NB, b);
+                const int o = stencil_dy(NB, b) * ld + stencil_dx(NB, b);
                 const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
 #pragma unroll
                 for (int x = 0; x < 3; x++)
@@ -755,13 +746,12 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 #pragma unroll
             for (int x = 0; x < 3; x++) {
                 const double tt = (double)Di[k][x * 3 + 0] * r[0] + (double)Di[k][x * 3 + 1] * r[1] + (double)Di[k][x * 3 + 2] * r[2];
-                T d = u[x * kResPL];
-                d = (T)((1.0 - A.omega) * (double)d - A.omega * tt);
-                if (reps == 2) d = (T)((1.0 - A.omega) * (double)d - A.omega * tt);
-                u[x * kResPL] = d;
-                own[k][x] = d;
+                const T d1 = (T)(keep * (double)d[x] - A.omega * tt);
+                const T d2 = (T)(keep * (double)d1 - A.omega * tt);
+                u[x * kResPL] = twice ? d2 : d1;
             }
         }
+        if (SOLO) { __syncthreads(); continue; }
         since++;
         if (since < A.m && s < runs - 1) { __syncthreads(); continue; }
         since = 0;
@@ -770,26 +760,58 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
         unsigned long long *box = A.box + (long long)(tag & 1) * A.cells * NW;
 #pragma unroll
         for (int k = 0; k < EPT; k++)
-            if (edge[k] && (A.m > 1 || col[k] == c)) box_store(box + (long long)cell[k] * NW, tag, own[k]);
+            if (edge(k) && (A.m > 1 || colour(k) == c)) {
+                const T own[3] = {su[q[k]], su[kResPL + q[k]], su[2 * kResPL + q[k]]};
+                box_store(box + (long long)(cell_j(k) * nx + cell_i(k)) * NW, tag, own);
+            }
         __syncthreads();     // every cell of the group is relaxed and read before the halo changes
+        // the words of KB cells are loaded together, again until each cell's carry the tag
 #pragma unroll
-        for (int k = 0; k < kResHalo; k++) {
-            if (hcol[k] < 0 || (A.m == 1 && hcol[k] != c) || dead) continue;
-            unsigned long long v[NW];
-            if (!box_wait<NW>(box + (long long)hcell[k] * NW, tag, v)) { dead = 1; continue; }
+        for (int k0 = 0; k0 < kResHalo; k0 += KB) {
+            if (k0 * kResNT >= nh) break;
+            unsigned pend = 0;
 #pragma unroll
-            for (int x = 0; x < 3; x++) box_value(v, x, su[x * kResPL + hq[k]]);
+            for (int k = k0; k < k0 + KB && k < kResHalo; k++)
+                if (hq[k] && (A.m > 1 || hq[k] >> 16 == c + 1)) pend |= 1u << k;
+            if (dead) pend = 0;
+            long long t0 = 0;
+            for (int spin = 0; pend; spin++) {
+                unsigned long long v[KB][NW];
+#pragma unroll
+                for (int k = k0; k < k0 + KB && k < kResHalo; k++)
+                    if (k * kResNT < nh)
+#pragma unroll
+                        for (int w = 0; w < NW; w++)
+                            v[k - k0][w] = __hip_atomic_load(box + (long long)hcell[k] * NW + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int k = k0; k < k0 + KB && k < kResHalo; k++) {
+                    if (k * kResNT >= nh || !(pend >> k & 1)) continue;
+                    bool ok = true;
+#pragma unroll
+                    for (int w = 0; w < NW; w++) ok = ok && (unsigned)(v[k - k0][w] >> 32) == tag;
+                    if (!ok) continue;
+                    pend &= ~(1u << k);
+#pragma unroll
+                    for (int x = 0; x < 3; x++) box_value(v[k - k0], x, su[x * kResPL + (hq[k] & 0xffff)]);
+                }
+                if ((spin & 255) == 255) {
+                    const long long now = wall_clock64();
+                    if (t0 == 0) t0 = now;
+                    else if (now - t0 > kWaitTicks) { dead = 1; pend = 0; }
+                }
+            }
         }
         __syncthreads();
     }
     __syncthreads();
-    const bool bad = dead != 0;
+    const bool bad = !SOLO && dead != 0;
 
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
-        if (!inside[k]) continue;
+        if (!inside(k)) continue;
+        const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
 #pragma unroll
-        for (int c = 0; c < 3; c++) mg[L.dU + c * n + slot[k]] = bad ? (T)__builtin_nan("") : own[k][c];
+        for (int c = 0; c < 3; c++) mg[L.dU + c * n + cc] = bad ? (T)__builtin_nan("") : su[c * kResPL + q[k]];
     }
     if (!A.restr) return;
     // eq. (24): rhs + J dU of every cell of the tile, then the sums over the children
@@ -797,17 +819,18 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
     double a[EPT][3];
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
-        if (!inside[k]) continue;
+        if (!inside(k)) continue;
         const T *u = su + q[k];
+        const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
         const double y0 = (double)u[0], y1 = (double)u[kResPL], y2 = (double)u[2 * kResPL];
 #pragma unroll
         for (int x = 0; x < 3; x++)
-            a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, (x * 3 + 0) * n + slot[k]) * y0 +
-                                          ld2(mg + L.J, (x * 3 + 1) * n + slot[k]) * y1 +
-                                          ld2(mg + L.J, (x * 3 + 2) * n + slot[k]) * y2);
+            a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, (x * 3 + 0) * n + cc) * y0 +
+                                          ld2(mg + L.J, (x * 3 + 1) * n + cc) * y1 +
+                                          ld2(mg + L.J, (x * 3 + 2) * n + cc) * y2);
 #pragma unroll
         for (int b = 1; b < NB; b++) {
-            const int o = stencil_dy(NB, b) * kResLD + stencil_dx(NB, b);
+            const int o = stencil_dy(NB, b) * ld + stencil_dx(NB, b);
             const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
 #pragma unroll
             for (int x = 0; x < 3; x++)
@@ -819,10 +842,9 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
     double *sa = lds;                            // [3][tile cells]
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
-        if (!inside[k]) continue;
-        const int j = cell[k] / nx, i = cell[k] - j * nx;
+        if (!inside(k)) continue;
 #pragma unroll
-        for (int x = 0; x < 3; x++) sa[x * A.tx * A.ty + (j - j0) * tw + (i - i0)] = a[k][x];
+        for (int x = 0; x < 3; x++) sa[x * A.tx * A.ty + (cell_j(k) - j0) * tw + (cell_i(k) - i0)] = a[k][x];
     }
     __syncthreads();
     const int hw = tw / 2, hh = (j1 - j0) / 2;
@@ -841,6 +863,15 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
     }
 }
 
+template <typename T, int NB, typename HT, int EPT>
+__global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
+{
+    __shared__ double lds[3 * kResPL];
+    __shared__ int dead;
+    if (A.state && !A.state->active) return;     // the same for every workgroup
+    resident_level<T, NB, HT, EPT, false>(mg, A, blockIdx.x % A.gx, blockIdx.x / A.gx, lds, dead);
+}
+
 // Coarsest level: Gaussian elimination with partial pivoting of the dense system sum J dU = -rhs
 // (unknown (j*nx + i)*3 + c), split into a factorisation done once per operator and a solve per
 // V-cycle.  The factorisation takes the pivots and eliminates exactly as the plain algorithm does
@@ -849,130 +880,240 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 // interchanged whole, multipliers included) and the row permutation.  The solve then applies the
 // permutation to the right-hand side, the multipliers column by column (the same operations on
 // the same values as eliminating the right-hand side alongside), and back substitution.
+//
+// Both are chains of M <= 120 dependent steps, bound by what one step costs.  The factorisation keeps
+// the matrix in registers (lane l of wavefront w has rows l and l + 64 of the columns w, w + 16, ...),
+// so a step is the owning wavefront's pivot search and multipliers, one barrier, and every
+// wavefront's update (270 -> 0 us at M = 96 with the matrix in LDS and five barriers a step).  Rows
+// are interchanged by number only.  The solve runs in one wavefront with x in registers, without
+// barriers.
 struct CoarseLU {
-    double *A;    // [M][M]
-    int *perm;    // [M]
+    double *A;    // [M][M], column-major, rows in pivot order
+    int *perm;    // [M]: the row's place before the interchanges + (its last nonzero column << 16)
 };
 
 __device__ __forceinline__ CoarseLU coarse_lu(double *base, int M) { return CoarseLU{base, (int *)(base + (long long)M * M)}; }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_coarse_factor2d(T *mg, Level2D L, double *lu_base)
+__device__ __forceinline__ double lane_value(double v, int lane)
 {
-    constexpr int MM = 3 * kMaxCoarse2D;
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// max of v and the value CTRL lanes over (a DPP move); lanes without a source keep v
+template <int CTRL>
+__device__ __forceinline__ double dpp_max(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const int lo = (int)(unsigned)b, hi = (int)(unsigned)(b >> 32);
+    const unsigned l2 = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    const unsigned h2 = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    const double w = __longlong_as_double((long long)(((unsigned long long)h2 << 32) | l2));
+    return w > v ? w : v;
+}
+
+// the largest v of the wavefront (no NaN among them)
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = dpp_max<0x111>(v);   // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has the row's maximum
+    v = dpp_max<0x112>(v);
+    v = dpp_max<0x114>(v);
+    v = dpp_max<0x118>(v);
+    return fmax(fmax(lane_value(v, 15), lane_value(v, 31)), fmax(lane_value(v, 47), lane_value(v, 63)));
+}
+
+template <typename T>
+__global__ void __launch_bounds__(1024) k_coarse_factor2d(T *mg, Level2D L, double *lu_base)
+{
+    constexpr int MM = 3 * kMaxCoarse2D, NW = 16, NQ = (MM + NW - 1) / NW;
+    static_assert(MM <= 128, "two rows a lane");
     __shared__ double A[MM * MM];
-    __shared__ int perm[MM];
-    __shared__ int piv_s;
+    __shared__ double fcol[2][128];
+    __shared__ int piv[2][2];            // the pivot row and its place
     const int nx = L.nx, ny = L.ny, n = nx * ny, M = 3 * n;
     const long long Ms = L.P.M;
-    const int t = threadIdx.x;
-    for (int e = t; e < M * M; e += 256) A[e] = 0.0;
-    for (int r = t; r < M; r += 256) perm[r] = r;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    for (int e = t; e < M * M; e += 1024) A[e] = 0.0;
     __syncthreads();
-    for (int e = t; e < n * L.nb; e += 256) {
-        const int cell = e / L.nb, b = e % L.nb;
+    for (int e = t; e < n * L.nb * 9; e += 1024) {
+        const int cell = e % n, be = e / n, b = be / 9, rc = be - 9 * b;
         const int i = cell % nx, j = cell / nx;
         int di, dj;
         stencil_off(L.nb, b, di, dj);
         const int pi = i + di, pj = j + dj;
         if (pi < 0 || pi >= nx || pj < 0 || pj >= ny) continue;
-        const long long q = perm2d(L.P, i, j);
-        for (int r = 0; r < 3; r++)
-            for (int c = 0; c < 3; c++)
-                A[(cell * 3 + r) * M + (pj * nx + pi) * 3 + c] = ld2(mg + L.J, (b * 9 + r * 3 + c) * Ms + q);
+        A[((pj * nx + pi) * 3 + rc % 3) * M + cell * 3 + rc / 3] = ld2(mg + L.J, (long long)be * Ms + perm2d(L.P, i, j));
     }
     __syncthreads();
-    for (int k = 0; k < M; k++) {
-        if (t < 64) {            // pivot: largest |A[r][k]|, r >= k, the first one on ties
-            int p = -1;
-            double v = -1.0;
-            for (int r = k + t; r < M; r += 64) {
-                const double a = fabs(A[r * M + k]);
-                if (a > v) { v = a; p = r; }
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                const double v2 = __shfl_xor(v, off, 64);
-                const int p2 = __shfl_xor(p, off, 64);
-                if (v2 > v || (v2 == v && p2 >= 0 && (p < 0 || p2 < p))) { v = v2; p = p2; }
-            }
-            if (t == 0) piv_s = p < 0 ? k : p;      // no comparable entry: keep the row
-        }
-        __syncthreads();
-        const int p = piv_s;
-        if (p != k) {
-            for (int c = t; c < M; c += 256) {
-                const double y = A[k * M + c];
-                A[k * M + c] = A[p * M + c];
-                A[p * M + c] = y;
-            }
-            if (t == 0) { const int y = perm[k]; perm[k] = perm[p]; perm[p] = y; }
-        }
-        __syncthreads();
-        const double akk = A[k * M + k];
-        // every thread reads column k before any row is updated
-        double fr[(MM + 255) / 256];
+    double a[NQ][2];
 #pragma unroll
-        for (int q = 0; q < (MM + 255) / 256; q++) {
-            const int r = k + 1 + t + 256 * q;
-            fr[q] = r < M ? A[r * M + k] / akk : 0.0;
-        }
-        __syncthreads();
+    for (int q = 0; q < NQ; q++) {
+        const int c = wave + NW * q;
+        a[q][0] = c < M && lane < M ? A[c * M + lane] : 0.0;
+        a[q][1] = c < M && lane + 64 < M ? A[c * M + lane + 64] : 0.0;
+    }
+    // the place of rows lane and lane + 64; rows past the matrix stay behind every k
+    int p0 = lane < M ? lane : -1, p1 = lane + 64 < M ? lane + 64 : -1;
 #pragma unroll
-        for (int q = 0; q < (MM + 255) / 256; q++) {
-            const int r = k + 1 + t + 256 * q;
-            if (r < M) A[r * M + k] = fr[q];
+    for (int q = 0; q < NQ; q++) {
+        for (int w = 0; w < NW; w++) {
+            const int k = q * NW + w, buf = k & 1;
+            if (k >= M) break;
+            if (wave == w) {
+                // pivot: the largest magnitude at a place >= k, the first place on ties, place k if no
+                // entry compares
+                const double m0 = fabs(a[q][0]), m1 = fabs(a[q][1]);
+                const double v0 = p0 >= k && m0 >= 0.0 ? m0 : -1.0, v1 = p1 >= k && m1 >= 0.0 ? m1 : -1.0;
+                const double top = wave_max(v0 > v1 ? v0 : v1);
+                unsigned long long t0 = __ballot(top < 0.0 ? p0 == k : v0 == top), t1 = __ballot(top < 0.0 ? p1 == k : v1 == top);
+                int row = t0 ? __builtin_ctzll(t0) : 64 + __builtin_ctzll(t1);
+                int place = row < 64 ? __builtin_amdgcn_readlane(p0, row) : __builtin_amdgcn_readlane(p1, row - 64);
+                if (__popcll(t0) + __popcll(t1) > 1) {
+                    for (; t0; t0 &= t0 - 1) {
+                        const int r = __builtin_ctzll(t0), pl = __builtin_amdgcn_readlane(p0, r);
+                        if (pl < place) { place = pl; row = r; }
+                    }
+                    for (; t1; t1 &= t1 - 1) {
+                        const int r = __builtin_ctzll(t1), pl = __builtin_amdgcn_readlane(p1, r);
+                        if (pl < place) { place = pl; row = r + 64; }
+                    }
+                }
+                const double akk = row < 64 ? lane_value(a[q][0], row) : lane_value(a[q][1], row - 64);
+                double f0 = 0.0, f1 = 0.0;
+                if (p0 >= k && lane != row) a[q][0] = f0 = a[q][0] / akk;
+                if (p1 >= k && lane + 64 != row) a[q][1] = f1 = a[q][1] / akk;
+                fcol[buf][lane] = f0;
+                fcol[buf][lane + 64] = f1;
+                if (lane == 0) { piv[buf][0] = row; piv[buf][1] = place; }
+            }
+            __syncthreads();     // the other buffer is free again: every wavefront has passed its step
+            const int row = __builtin_amdgcn_readfirstlane(piv[buf][0]), place = __builtin_amdgcn_readfirstlane(piv[buf][1]);
+            const double f0 = fcol[buf][lane], f1 = fcol[buf][lane + 64];
+            if (p0 == k) p0 = place;
+            if (p1 == k) p1 = place;
+            if (lane == row) p0 = k;
+            if (lane + 64 == row) p1 = k;
+#pragma unroll
+            for (int x = q; x < NQ; x++) {
+                if (wave + NW * x <= k) continue;
+                const double u = row < 64 ? lane_value(a[x][0], row) : lane_value(a[x][1], row - 64);
+                if (f0 != 0.0) a[x][0] -= f0 * u;
+                if (f1 != 0.0) a[x][1] -= f1 * u;
+            }
         }
-        __syncthreads();
-        const int w = M - k - 1;
-        for (int e = t; e < w * w; e += 256) {
-            const int r = k + 1 + e / w, c = k + 1 + e % w;
-            const double f = A[r * M + k];
-            if (f != 0.0) A[r * M + c] -= f * A[k * M + c];
-        }
-        __syncthreads();
     }
     const CoarseLU lu = coarse_lu(lu_base, M);
-    for (int e = t; e < M * M; e += 256) lu.A[e] = A[e];
-    for (int r = t; r < M; r += 256) lu.perm[r] = perm[r];
+    __shared__ int ext[MM];
+    for (int r = t; r < M; r += 1024) ext[r] = r;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        const int c = wave + NW * q;
+        if (c >= M) continue;
+        if (p0 >= 0) {
+            lu.A[c * M + p0] = a[q][0];
+            if (a[q][0] != 0.0) atomicMax(&ext[p0], c);
+        }
+        if (p1 >= 0) {
+            lu.A[c * M + p1] = a[q][1];
+            if (a[q][1] != 0.0) atomicMax(&ext[p1], c);
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        if (p0 >= 0) lu.perm[p0] = lane | ext[p0] << 16;
+        if (p1 >= 0) lu.perm[p1] = (lane + 64) | ext[p1] << 16;
+    }
 }
 
-// solve with the factors of k_coarse_factor2d; A and x are LDS arrays of the calling workgroup
+// solve with the factors of k_coarse_factor2d; A ([M][M + 1]) and sum ([144]) are LDS arrays of the
+// calling workgroup of 512 threads
 template <typename T>
-__device__ __forceinline__ void coarse_apply(T *mg, const Level2D &L, const double *lu_base, double *A, double *x)
+__device__ __forceinline__ void coarse_apply(T *mg, const Level2D &L, const double *lu_base, double *A, double *sum)
 {
-    const int nx = L.nx, n = nx * L.ny, M = 3 * n;
+    constexpr int NC = (3 * kMaxCoarse2D + 7) / 8;
+    const int nx = L.nx, n = nx * L.ny, M = 3 * n, ld = M + 1;
     const long long Ms = L.P.M;
-    const int t = threadIdx.x, nt = blockDim.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const CoarseLU lu = coarse_lu(const_cast<double *>(lu_base), M);
-    for (int e = t; e < M * M; e += nt) A[e] = lu.A[e];
-    for (int r = t; r < M; r += nt) {
-        const int src = lu.perm[r], cell = src / 3;
-        x[r] = -ld2(mg + L.rhs, (src % 3) * Ms + perm2d(L.P, cell % nx, cell / nx));
-    }
-    __syncthreads();
-    for (int k = 0; k < M - 1; k++) {
-        const double xk = x[k];
-        for (int r = k + 1 + t; r < M; r += nt) {
-            const double f = A[r * M + k];
-            if (f != 0.0) x[r] -= f * xk;
+    {
+        double v[NC][2];
+#pragma unroll
+        for (int q = 0; q < NC; q++) {
+            const int c = wave + 8 * q;
+            v[q][0] = c < M && lane < M ? lu.A[c * M + lane] : 0.0;
+            v[q][1] = c < M && lane + 64 < M ? lu.A[c * M + lane + 64] : 0.0;
         }
-        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NC; q++) {
+            const int c = wave + 8 * q;
+            if (c < M && lane < M) A[c * ld + lane] = v[q][0];
+            if (c < M && lane + 64 < M) A[c * ld + lane + 64] = v[q][1];
+        }
     }
-    // back substitution row by row, each row's sum over the later unknowns in ascending column
-    // order (the order of a plain dense solve, so the result rounds like one); the rows depend on
-    // each other in sequence, so one lane does it (at most 120 unknowns)
-    if (t == 0) {
+    if (t < 144) sum[t] = 0.0;
+    __syncthreads();
+    if (t < 64) {
+        // x of rows t and t + 64 (in pivot order) in registers
+        const int i0 = t < M ? lu.perm[t] : 0, i1 = t + 64 < M ? lu.perm[t + 64] : 0;
+        auto load = [&](int src) { const int cell = src / 3; return -ld2(mg + L.rhs, (src % 3) * Ms + perm2d(L.P, cell % nx, cell / nx)); };
+        double x0 = t < M ? load(i0 & 0xffff) : 0.0, x1 = t + 64 < M ? load(i1 & 0xffff) : 0.0;
+        // rows t and t + 64 of column k, 0 where the row is not below the diagonal
+        auto below = [&](int k, double &f0, double &f1) {
+            f0 = t > k && t < M ? A[k * ld + t] : 0.0;
+            f1 = t + 64 > k && t + 64 < M ? A[k * ld + t + 64] : 0.0;
+        };
+        double f0, f1;
+        below(0, f0, f1);
+        for (int k = 0; k < M - 1; k++) {
+            double g0, g1;
+            below(k + 1, g0, g1);
+            const double xk = k < 64 ? lane_value(x0, k) : lane_value(x1, k - 64);
+            x0 = f0 != 0.0 ? x0 - f0 * xk : x0;
+            x1 = f1 != 0.0 ? x1 - f1 * xk : x1;
+            f0 = g0;
+            f1 = g1;
+        }
+        // back substitution row by row, each row's sum over the later unknowns in ascending column
+        // order (the order of a plain dense solve, so the result rounds like one): the products in
+        // parallel, through LDS, their sum a chain that ends at the row's last nonzero
+        auto row = [&](int k, double &u0, double &u1, double &akk) {
+            u0 = t < M ? A[t * ld + k] : 0.0;
+            u1 = t + 64 < M ? A[(t + 64) * ld + k] : 0.0;
+            akk = A[k * ld + k];
+        };
+        double u0, u1, akk;
+        row(M - 1, u0, u1, akk);
         for (int k = M - 1; k >= 0; k--) {
-            double s = x[k];
-            for (int c = k + 1; c < M; c++) s -= A[k * M + c] * x[c];
-            x[k] = s / A[k * M + k];
+            const int last = (k < 64 ? __builtin_amdgcn_readlane(i0, k) : __builtin_amdgcn_readlane(i1, k - 64)) >> 16;
+            sum[t] = t > k && t <= last ? u0 * x0 : 0.0;
+            sum[t + 64] = t + 64 > k && t + 64 <= last ? u1 * x1 : 0.0;
+            __builtin_amdgcn_wave_barrier();
+            double s = k < 64 ? lane_value(x0, k) : lane_value(x1, k - 64);
+            const double a = akk;
+            row(k > 0 ? k - 1 : 0, u0, u1, akk);
+            for (int c = (k + 1) & ~1; c <= last; c += 8) {      // zeros before the first and after the last term
+                double2 p[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) p[q] = *(const double2 *)(sum + c + 2 * q);
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    s -= p[q].x;
+                    s -= p[q].y;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            s = s / a;
+            if (t == k) x0 = s;
+            if (t + 64 == k) x1 = s;
         }
+        auto store = [&](int r, double v) { const int cell = r / 3; mg[L.dU + (r % 3) * Ms + perm2d(L.P, cell % nx, cell / nx)] = (T)v; };
+        if (t < M) store(t, x0);
+        if (t + 64 < M) store(t + 64, x1);
     }
     __syncthreads();
-    for (int r = t; r < M; r += nt) {
-        const int cell = r / 3;
-        mg[L.dU + (r % 3) * Ms + perm2d(L.P, cell % nx, cell / nx)] = (T)x[r];
-    }
 }
 
 // The bottom of a V-cycle in one workgroup: from level `first` (a small level) down to the
@@ -988,135 +1129,37 @@ struct Bottom2DArgs {
     int sweeps;          // smoother: 0 the multicolour schedule, 1 the directional sweeps D1-D4
 };
 
-// The merged colour passes of one five-point level of at most blockDim.x slots, with each
-// thread's operator row (the four neighbour blocks, D^{-1} and the right-hand side) held in
-// registers for all of them and dU in LDS (su, [3][M], each value rounded to the storage type as
-// in memory): a pass then reads its neighbours from LDS instead of the level's arrays.  The
-// operations of smooth_slot, in its order, so the results are the same bit for bit.
-template <typename T>
-__device__ void bottom_smooth5_resident(T *mg, const Level2D &L, int nu, double omega, double *su)
-{
-    constexpr int C = 2;
-    const int W = L.P.W;
-    const long long n = L.P.M, slots = (long long)L.P.ny * W;
-    const int t = threadIdx.x;
-    const int colour = (int)(t / slots);
-    const long long p = t - colour * slots;
-    const int j = (int)(p / W), k = (int)(p - (long long)j * W);
-    const int i = ((colour - j) % C + C) % C + C * k;
-    const bool mine = t < n && i < L.nx;
-    const long long cc = t;   // colour * ny * W + p
-    double Jb[5][9], Di[9], rh[3];
-    int q[5];
-    bool ok[5];
-    if (mine) {
-#pragma unroll
-        for (int b = 1; b < 5; b++) {
-            int di, dj;
-            stencil_off(5, b, di, dj);
-            const int pi = i + di, pj = j + dj;
-            ok[b] = pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny;
-            const int c2 = ((pi + pj) % C + C) % C;
-            const int ic = ((c2 - pj) % C + C) % C;
-            q[b] = ok[b] ? (int)((long long)c2 * L.ny * W + (long long)pj * W + (pi - ic) / C) : (int)cc;
-#pragma unroll
-            for (int e = 0; e < 9; e++) Jb[b][e] = ld2(mg + L.J, (b * 9 + e) * n + cc);
-        }
-#pragma unroll
-        for (int e = 0; e < 9; e++) Di[e] = ld2(mg + L.Dinv, e * n + cc);
-#pragma unroll
-        for (int c = 0; c < 3; c++) rh[c] = ld2(mg + L.rhs, c * n + cc);
-    }
-    for (long long e = t; e < 3 * n; e += blockDim.x) su[e] = ld2(mg + L.dU, e);
-    __syncthreads();
-    int cur = -1, run = 0;
-    for (int it = 0; it <= nu; it++) {
-        for (int half = 0; half < 4; half++)
-            for (int qq = 0; qq < C; qq++) {
-                const bool last = it == nu;
-                const int c = (half & 1) ? C - 1 - qq : qq;
-                if (!last && c == cur) { run++; continue; }
-                if (run > 0) {
-                    if (mine && colour == cur) {
-                        double x[5][3], a[5][3];
-#pragma unroll
-                        for (int b = 1; b < 5; b++)
-#pragma unroll
-                            for (int cm = 0; cm < 3; cm++) x[b][cm] = su[cm * n + q[b]];
-#pragma unroll
-                        for (int b = 1; b < 5; b++)
-#pragma unroll
-                            for (int cm = 0; cm < 3; cm++)
-                                a[b][cm] = Jb[b][cm * 3 + 0] * x[b][0] + Jb[b][cm * 3 + 1] * x[b][1] + Jb[b][cm * 3 + 2] * x[b][2];
-                        double r[3];
-#pragma unroll
-                        for (int cm = 0; cm < 3; cm++) {
-                            r[cm] = rh[cm];
-#pragma unroll
-                            for (int b = 1; b < 5; b++)
-                                if (ok[b]) r[cm] = r[cm] + a[b][cm];
-                        }
-#pragma unroll
-                        for (int cm = 0; cm < 3; cm++) {
-                            const double tt = Di[cm * 3 + 0] * r[0] + Di[cm * 3 + 1] * r[1] + Di[cm * 3 + 2] * r[2];
-                            T d = (T)su[cm * n + cc];
-                            for (int rr = 0; rr < run; rr++) d = (T)((1.0 - omega) * (double)d - omega * tt);
-                            su[cm * n + cc] = (double)d;
-                        }
-                    }
-                    __syncthreads();
-                }
-                if (last) {
-                    for (long long e = t; e < 3 * n; e += blockDim.x) mg[L.dU + e] = (T)su[e];
-                    __syncthreads();
-                    return;
-                }
-                cur = c;
-                run = 1;
-            }
-    }
-}
-
 // NBF: the stencil of the bottom's first level (the finest level when the whole hierarchy fits
 // one workgroup, else a five-point level); the levels below it have five points.  Only the
-// passes a launch can meet are compiled into it, which keeps the kernel's registers down.
-// Five-point levels that fit the workgroup keep their operator in registers (su: LDS for dU),
-// except in the kernel whose first level has the full 21-cell stencil, whose registers that
-// would overflow.
+// passes a launch can meet are compiled into it.  The five-point and cross levels (at most 512
+// cells: one a thread) keep their rows in registers (resident_level); the 21-cell level and the
+// directional sweeps read them in every pass.
 template <typename T, int NBF>
-__device__ void bottom_smooth(T *mg, const Level2D &L, int nu, double omega, int sweeps, double *su)
+__device__ __forceinline__ void bottom_smooth(T *mg, const Level2D &L, int nu, double omega, int sweeps)
 {
-    if constexpr (NBF != 21) {
-        if (!sweeps && L.nb == 5 && L.P.M <= (long long)blockDim.x) {
-            bottom_smooth5_resident<T>(mg, L, nu, omega, su);
-            return;
-        }
-    }
     if (sweeps) {
         if (NBF != 5 && L.nb == NBF) sweeps_level<T, NBF>(mg, L, nu, omega);
         else sweeps_level<T, 5>(mg, L, nu, omega);
         return;
     }
-    const int C = L.P.C;
-    const long long slots = (long long)L.P.ny * L.P.W;
-    int cur = -1, run = 0;
-    for (int it = 0; it <= nu; it++) {
-        for (int half = 0; half < 4; half++)
-            for (int q = 0; q < C; q++) {
-                const bool last = it == nu;
-                const int c = (half & 1) ? C - 1 - q : q;
-                if (!last && c == cur) { run++; continue; }
-                if (run > 0) {
-                    for (long long p = threadIdx.x; p < slots; p += blockDim.x) {
-                        if (NBF != 5 && L.nb == NBF) smooth_slot<T, NBF>(mg, L, cur, omega, run, p);
-                        else smooth_slot<T, 5>(mg, L, cur, omega, run, p);
+    if constexpr (NBF == 21) {
+        const long long slots = (long long)L.P.ny * L.P.W;
+        int cur = -1, run = 0;
+        for (int it = 0; it <= nu; it++) {
+            for (int half = 0; half < 4; half++)
+                for (int q = 0; q < 9; q++) {
+                    const bool last = it == nu;
+                    const int c = (half & 1) ? 8 - q : q;
+                    if (!last && c == cur) { run++; continue; }
+                    if (run > 0) {
+                        for (long long p = threadIdx.x; p < slots; p += blockDim.x) smooth_slot<T, 21>(mg, L, cur, omega, run, p);
+                        __syncthreads();
                     }
-                    __syncthreads();
+                    if (last) return;
+                    cur = c;
+                    run = 1;
                 }
-                if (last) return;
-                cur = c;
-                run = 1;
-            }
+        }
     }
 }
 
@@ -1124,23 +1167,45 @@ template <typename T, int NBF>
 __global__ void __launch_bounds__(512) k_bottom2d(T *mg, Bottom2DArgs B)
 {
     constexpr int MM = 3 * kMaxCoarse2D;
-    __shared__ double A[MM * MM];
-    __shared__ double x[MM];
-    __shared__ double su[3 * 512];   // dU of a five-point level held in LDS (at most 512 slots)
+    __shared__ double A[MM * (MM + 1)];
+    __shared__ __align__(16) double sum[144];
+    __shared__ double lds[3 * kResPL];
     const int last = B.levels - 1;
+    Resident2DArgs R;
+    R.m = 1;
+    R.omega = B.omega;
+    int dead = 0;
+    // a phase of level l with the rows in registers; false: the level is not of that kind
+    auto phase = [&](int l, int nu, int prolong, int restr) {
+        const Level2D &L = B.L[l];
+        if (B.sweeps || L.nb == 21 || (long long)L.nx * L.ny > kResNT) return false;
+        R.L = L;
+        R.Lc = B.L[l + 1];
+        R.tx = L.nx;
+        R.ty = L.ny;
+        R.nu = nu;
+        R.prolong = prolong;
+        R.restr = restr;
+        if (NBF == 9 && L.nb == 9) resident_level<T, 9, double, 1, true>(mg, R, 0, 0, lds, dead);
+        else resident_level<T, 5, double, 1, true>(mg, R, 0, 0, lds, dead);
+        __syncthreads();
+        return true;
+    };
     for (int l = B.first; l < last; l++) {
-        bottom_smooth<T, NBF>(mg, B.L[l], B.nu1, B.omega, B.sweeps, su);
+        if (phase(l, B.nu1, 0, 1)) continue;
+        bottom_smooth<T, NBF>(mg, B.L[l], B.nu1, B.omega, B.sweeps);
         const Level2D &Lc = B.L[l + 1];
         for (int e = threadIdx.x; e < Lc.nx * Lc.ny; e += blockDim.x) restrict_cell(mg, B.L[l], Lc, e % Lc.nx, e / Lc.nx);
         __syncthreads();
     }
-    coarse_apply(mg, B.L[last], B.lu, A, x);
+    coarse_apply(mg, B.L[last], B.lu, A, sum);
     __syncthreads();
     for (int l = last - 1; l >= B.first; l--) {
+        if (phase(l, B.nu2, 1, 0)) continue;
         const Level2D &Lf = B.L[l];
         for (int e = threadIdx.x; e < Lf.nx * Lf.ny; e += blockDim.x) prolong_cell(mg, Lf, B.L[l + 1], e % Lf.nx, e / Lf.nx);
         __syncthreads();
-        bottom_smooth<T, NBF>(mg, Lf, B.nu2, B.omega, B.sweeps, su);
+        bottom_smooth<T, NBF>(mg, Lf, B.nu2, B.omega, B.sweeps);
     }
 }
 
@@ -1283,8 +1348,20 @@ hipError_t launch_interp_a3(const double *Uc, int nxc, int nyc, double *Uf, hipS
 
 hipError_t launch_coarsen2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s)
 {
-    dim3 grid((Lc.nx + 63) / 64, Lc.ny);
-    DISPATCH(prec, k_coarsen2d, grid, dim3(64), Lf, Lc);
+    const dim3 grid((Lc.nx + 63) / 64, Lc.ny, 5);
+    const bool f32 = prec == NMG_FP32_MG;
+    float *mf = (float *)mg;
+    double *md = (double *)mg;
+    if (Lf.nb == 21) {
+        if (f32) hipLaunchKernelGGL((k_coarsen2d<float, 21>), grid, dim3(64), 0, s, mf, Lf, Lc);
+        else hipLaunchKernelGGL((k_coarsen2d<double, 21>), grid, dim3(64), 0, s, md, Lf, Lc);
+    } else if (Lf.nb == 9) {
+        if (f32) hipLaunchKernelGGL((k_coarsen2d<float, 9>), grid, dim3(64), 0, s, mf, Lf, Lc);
+        else hipLaunchKernelGGL((k_coarsen2d<double, 9>), grid, dim3(64), 0, s, md, Lf, Lc);
+    } else {
+        if (f32) hipLaunchKernelGGL((k_coarsen2d<float, 5>), grid, dim3(64), 0, s, mf, Lf, Lc);
+        else hipLaunchKernelGGL((k_coarsen2d<double, 5>), grid, dim3(64), 0, s, md, Lf, Lc);
+    }
     return hipGetLastError();
 }
 
@@ -1338,13 +1415,16 @@ hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps
 }
 
 // Cells a workgroup of k_resident2d holds: 512 threads have 256 registers each, a row takes 84
-// values (nine blocks) or 48 (five points).
-static int resident2d_cells(int nb, int prec) { return nb == 9 && prec != NMG_FP32_MG ? kResNT : 2 * kResNT; }
+// values (nine blocks) or 48 (five points).  Nine-block rows of FP32 levels are held in FP64 (one a
+// thread) or, narrow, in FP32 (two a thread, widened in every pass).
+static int resident2d_cells(int nb, int narrow) { return nb == 9 && !narrow ? kResNT : 2 * kResNT; }
 
-static const void *resident2d_kernel(int nb, int prec)
+static const void *resident2d_kernel(int nb, int prec, int narrow)
 {
     const bool f32 = prec == NMG_FP32_MG;
-    if (nb == 9) return f32 ? (const void *)k_resident2d<float, 9, float, 2> : (const void *)k_resident2d<double, 9, double, 1>;
+    if (nb == 9 && f32)
+        return narrow ? (const void *)k_resident2d<float, 9, float, 2> : (const void *)k_resident2d<float, 9, double, 1>;
+    if (nb == 9) return (const void *)k_resident2d<double, 9, double, 1>;
     return f32 ? (const void *)k_resident2d<float, 5, double, 2> : (const void *)k_resident2d<double, 5, double, 2>;
 }
 
@@ -1357,27 +1437,31 @@ Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
 {
     Resident2D best;
     if (L.nb != 9 && L.nb != 5) return best;
-    const int C = L.nb == 9 ? 3 : 2, R = L.nb == 9 ? 2 : 1, cap = resident2d_cells(L.nb, prec);
-    const double lat = 0.2, work = L.nb == 9 ? 0.28 : 0.16;
+    const int C = L.nb == 9 ? 3 : 2, R = L.nb == 9 ? 2 : 1;
     double cost = 1e30;
-    for (int ty = 2; ty <= kResH; ty += 2) {
-        if (ty > L.ny + 1) break;
-        for (int tx = 4; tx <= kResW; tx += 4) {
-            if (tx > L.nx + 3) break;
-            const int gx = (L.nx + tx - 1) / tx, gy = (L.ny + ty - 1) / ty;
-            if (gx * gy > max_wg) continue;
-            for (int m = 1; m <= 16; m++) {
-                const int hc = R * (m - 1), hd = R * m;
-                const int cw = std::min(tx + 2 * hc, L.nx), ch = std::min(ty + 2 * hc, L.ny);
-                if (cw * ch > cap) break;
-                if (std::min(tx + 2 * hd, L.nx) > kResW || std::min(ty + 2 * hd, L.ny) > kResH) break;
-                const double t = (gx * gy > 1 ? 1.0 / m : 0.0) + lat + work * ((cw * ch / C + 255) / 256) + 0.001 * gx * gy;
-                if (t < cost) {
-                    cost = t;
-                    best.tx = tx; best.ty = ty; best.gx = gx; best.gy = gy; best.m = m;
+    for (int narrow = 0; narrow <= (L.nb == 9 && prec == NMG_FP32_MG ? 1 : 0); narrow++) {
+        const int cap = resident2d_cells(L.nb, narrow);
+        const double lat = 0.2, work = (L.nb == 9 ? 0.28 : 0.16) * (narrow ? 1.5 : 1.0);
+        for (int ty = 2; ty <= 32 && ty <= L.ny + 1; ty += 2)
+            for (int tx = 4; tx <= 64 && tx <= L.nx + 3; tx += 4) {
+                const int gx = (L.nx + tx - 1) / tx, gy = (L.ny + ty - 1) / ty;
+                if (gx * gy > max_wg) continue;
+                for (int m = 1; m <= 16; m++) {
+                    const int hc = R * (m - 1), hd = R * m;
+                    const int cw = std::min(tx + 2 * hc, L.nx), ch = std::min(ty + 2 * hc, L.ny);
+                    if (cw * ch > cap) break;
+                    const int dw = std::min(tx + 2 * hd, L.nx), dh = std::min(ty + 2 * hd, L.ny);
+                    const int hw = std::min(2 * hd, L.nx), hh = std::min(2 * hd, L.ny);
+                    if (!resident2d_fits(dw, dh)) break;
+                    // (a ragged last tile has fewer cells of its own in the same region)
+                    if (std::min(dw * dh, tx * hh + ty * hw + hw * hh) > kResHalo * kResNT) break;
+                    const double t = (gx * gy > 1 ? 1.0 / m : 0.0) + lat + work * ((cw * ch / C + 255) / 256) + 0.001 * gx * gy;
+                    if (t < cost) {
+                        cost = t;
+                        best.tx = tx; best.ty = ty; best.gx = gx; best.gy = gy; best.m = m; best.narrow = narrow;
+                    }
                 }
             }
-        }
     }
     return best;
 }
@@ -1388,7 +1472,7 @@ int resident2d_max_wg(int nb, int prec)
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident2d_kernel(nb, prec), kResNT, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident2d_kernel(nb, prec, 0), kResNT, 0) != hipSuccess) return 0;
     return per > 0 ? cus : 0;
 }
 
@@ -1410,7 +1494,7 @@ hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, cons
     A.cells = cells;
     A.state = state;
     void *args[] = {&mg, &A};
-    return hipLaunchCooperativeKernel(resident2d_kernel(L.nb, prec), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
+    return hipLaunchCooperativeKernel(resident2d_kernel(L.nb, prec, G.narrow), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
 }
 
 hipError_t launch_restrict2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s)
@@ -1429,7 +1513,7 @@ hipError_t launch_prolong2d(void *mg, const Level2D &Lf, const Level2D &Lc, int 
 
 hipError_t launch_coarse_factor2d(void *mg, const Level2D &L, double *lu, int prec, hipStream_t s)
 {
-    DISPATCH(prec, k_coarse_factor2d, dim3(1), dim3(256), L, lu);
+    DISPATCH(prec, k_coarse_factor2d, dim3(1), dim3(1024), L, lu);
     return hipGetLastError();
 }
 
