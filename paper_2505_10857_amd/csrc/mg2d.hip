@@ -527,7 +527,7 @@ struct Resident2DArgs {
     int prolong, restr;        // eq. (25) first; eq. (24)'s right-hand side last
     unsigned tag;              // the launch's exchanges are numbered tag + 1, tag + 2, ...
     double omega;
-    unsigned long long *box;   // [2][cells][words per cell]
+    unsigned long long *box;   // [2][words per cell][cells]: consecutive cells' words lie together
     long long cells;
     const NewtonState *state;  // may be null: run regardless
 };
@@ -543,19 +543,19 @@ __device__ __forceinline__ void box_put(unsigned long long *w, unsigned tag, uns
     __hip_atomic_store(w, ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void box_store(unsigned long long *w, unsigned tag, const float v[3])
+__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, const float v[3])
 {
 #pragma unroll
-    for (int c = 0; c < 3; c++) box_put(w + c, tag, __float_as_uint(v[c]));
+    for (int c = 0; c < 3; c++) box_put(w + c * cells, tag, __float_as_uint(v[c]));
 }
 
-__device__ __forceinline__ void box_store(unsigned long long *w, unsigned tag, const double v[3])
+__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, const double v[3])
 {
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         const unsigned long long b = (unsigned long long)__double_as_longlong(v[c]);
-        box_put(w + 2 * c, tag, (unsigned)b);
-        box_put(w + 2 * c + 1, tag, (unsigned)(b >> 32));
+        box_put(w + 2 * c * cells, tag, (unsigned)b);
+        box_put(w + (2 * c + 1) * cells, tag, (unsigned)(b >> 32));
     }
 }
 
@@ -566,8 +566,12 @@ __device__ __forceinline__ void box_value(const unsigned long long *v, int c, do
 }
 
 // LDS tile of dU: the cells of the tile and its halo, row by row, inside a ring of two zero cells
-// (a neighbour outside the grid reads a zero of the ring); three planes at a constant stride.
-constexpr int kResPL = 1872;                     // cells of a plane, ring included (48 x 32 cells fit)
+// (a neighbour outside the grid reads a zero of the ring).  A cell's components lie together, so that
+// it is one or two LDS reads.
+constexpr int kResPL = 1872;                     // cells, ring included (48 x 32 cells fit)
+template <typename T> struct ResCell;
+template <> struct ResCell<double> { double v[3]; };
+template <> struct alignas(16) ResCell<float> { float v[4]; };
 constexpr int kResNT = 512;
 constexpr int kResHalo = 3;                      // halo cells a thread fetches at most
 
@@ -587,7 +591,8 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 {
     constexpr int C = NB == 9 ? 3 : 2, R = NB == 9 ? 2 : 1, NW = BoxWords<T>::n;
     constexpr int KB = NW == 3 ? 3 : 2;          // halo cells whose words a thread has in flight
-    T *const sz = (T *)lds;                      // dU [3][rows + 4][ld]; the restriction's summands last
+    typedef ResCell<T> Cell;
+    Cell *const sz = (Cell *)lds;                // dU [rows + 4][ld]; the restriction's summands last
     const Level2D &L = A.L;
     const int t = threadIdx.x, nx = L.nx, ny = L.ny;
     const int i0 = SOLO ? 0 : bi * A.tx, j0 = SOLO ? 0 : bj * A.ty;
@@ -598,7 +603,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     const int di0 = i0 - hd > 0 ? i0 - hd : 0, di1 = i1 + hd < nx ? i1 + hd : nx;
     const int dj0 = j0 - hd > 0 ? j0 - hd : 0, dj1 = j1 + hd < ny ? j1 + hd : ny;
     const int dw = di1 - di0, dh = dj1 - dj0, ld = dw + 4;
-    T *const su = sz + 2 * ld + 2;
+    Cell *const su = sz + 2 * ld + 2;
     const long long n = L.P.M;
     if (t == 0 && !SOLO) dead = 0;
 
@@ -693,7 +698,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     }
 
     // dU of the tile and its halo
-    for (int e = t; e < 3 * kResPL; e += kResNT) sz[e] = (T)0.0;
+    for (int e = t; e < kResPL; e += kResNT) sz[e] = Cell{};
     __syncthreads();
     for (int e = t; e < dw * dh; e += kResNT) {
         const int r = e / dw, i = di0 + e - r * dw, j = dj0 + r;
@@ -703,7 +708,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         for (int c = 0; c < 3; c++) {
             T v = mg[L.dU + c * n + fc];
             if (A.prolong) v = (T)((double)v + ld2(mg + A.Lc.dU, c * A.Lc.P.M + pc));
-            su[c * kResPL + r * ld + (i - di0)] = v;
+            su[r * ld + (i - di0)].v[c] = v;
         }
     }
     __syncthreads();
@@ -729,26 +734,44 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
                 for (int b = 1; b < NB; b++) keep_narrow(Jb[k][b][x]);
                 keep_narrow(Di[k][x]);
             }
-            T *u = su + q[k];
-            T d[3] = {u[0], u[kResPL], u[2 * kResPL]};
+            // the values are read ahead of the products: a wavefront has its SIMD almost to itself, so
+            // a read's latency is paid once (the last blocks' of a nine-block row held in FP64, for which
+            // the registers do not suffice, behind the first products)
+            constexpr int B1 = NB == 9 && sizeof(HT) == 8 ? 6 : NB;
+            Cell *u = su + q[k];
+            const Cell d = *u;
+            Cell y[NB];
             double r[3];
 #pragma unroll
             for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
-#pragma unroll
-            for (int b = 1; b < NB; b++) {
-                const int o = stencil_dy(NB, b) * ld + stencil_dx(NB, b);
-                const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
+            auto read = [&](int b) { y[b] = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)]; };
+            auto add = [&](int b) {
+                const double x0 = (double)y[b].v[0], x1 = (double)y[b].v[1], x2 = (double)y[b].v[2];
 #pragma unroll
                 for (int x = 0; x < 3; x++)
                     r[x] = r[x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
                                    (double)Jb[k][b][x * 3 + 2] * x2);
+            };
+#pragma unroll
+            for (int b = 1; b < B1; b++) read(b);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (B1 < NB) {
+                add(1);
+                add(2);
+                add(3);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int b = B1; b < NB; b++) read(b);
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int b = B1 < NB ? 4 : 1; b < NB; b++) add(b);
 #pragma unroll
             for (int x = 0; x < 3; x++) {
                 const double tt = (double)Di[k][x * 3 + 0] * r[0] + (double)Di[k][x * 3 + 1] * r[1] + (double)Di[k][x * 3 + 2] * r[2];
-                const T d1 = (T)(keep * (double)d[x] - A.omega * tt);
+                const T d1 = (T)(keep * (double)d.v[x] - A.omega * tt);
                 const T d2 = (T)(keep * (double)d1 - A.omega * tt);
-                u[x * kResPL] = twice ? d2 : d1;
+                u->v[x] = twice ? d2 : d1;
             }
         }
         if (SOLO) { __syncthreads(); continue; }
@@ -761,8 +784,8 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 #pragma unroll
         for (int k = 0; k < EPT; k++)
             if (edge(k) && (A.m > 1 || colour(k) == c)) {
-                const T own[3] = {su[q[k]], su[kResPL + q[k]], su[2 * kResPL + q[k]]};
-                box_store(box + (long long)(cell_j(k) * nx + cell_i(k)) * NW, tag, own);
+                const Cell own = su[q[k]];
+                box_store(box + (cell_j(k) * nx + cell_i(k)), A.cells, tag, own.v);
             }
         __syncthreads();     // every cell of the group is relaxed and read before the halo changes
         // the words of KB cells are loaded together, again until each cell's carry the tag
@@ -782,7 +805,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
                     if (k * kResNT < nh)
 #pragma unroll
                         for (int w = 0; w < NW; w++)
-                            v[k - k0][w] = __hip_atomic_load(box + (long long)hcell[k] * NW + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            v[k - k0][w] = __hip_atomic_load(box + hcell[k] + w * A.cells, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                 for (int k = k0; k < k0 + KB && k < kResHalo; k++) {
                     if (k * kResNT >= nh || !(pend >> k & 1)) continue;
@@ -792,7 +815,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
                     if (!ok) continue;
                     pend &= ~(1u << k);
 #pragma unroll
-                    for (int x = 0; x < 3; x++) box_value(v[k - k0], x, su[x * kResPL + (hq[k] & 0xffff)]);
+                    for (int x = 0; x < 3; x++) box_value(v[k - k0], x, su[hq[k] & 0xffff].v[x]);
                 }
                 if ((spin & 255) == 255) {
                     const long long now = wall_clock64();
@@ -811,7 +834,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         if (!inside(k)) continue;
         const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
 #pragma unroll
-        for (int c = 0; c < 3; c++) mg[L.dU + c * n + cc] = bad ? (T)__builtin_nan("") : su[c * kResPL + q[k]];
+        for (int c = 0; c < 3; c++) mg[L.dU + c * n + cc] = bad ? (T)__builtin_nan("") : su[q[k]].v[c];
     }
     if (!A.restr) return;
     // eq. (24): rhs + J dU of every cell of the tile, then the sums over the children
@@ -820,9 +843,9 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
-        const T *u = su + q[k];
+        const Cell *u = su + q[k];
         const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
-        const double y0 = (double)u[0], y1 = (double)u[kResPL], y2 = (double)u[2 * kResPL];
+        const double y0 = (double)u->v[0], y1 = (double)u->v[1], y2 = (double)u->v[2];
 #pragma unroll
         for (int x = 0; x < 3; x++)
             a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, (x * 3 + 0) * n + cc) * y0 +
@@ -831,7 +854,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 #pragma unroll
         for (int b = 1; b < NB; b++) {
             const int o = stencil_dy(NB, b) * ld + stencil_dx(NB, b);
-            const double x0 = (double)u[o], x1 = (double)u[kResPL + o], x2 = (double)u[2 * kResPL + o];
+            const double x0 = (double)u[o].v[0], x1 = (double)u[o].v[1], x2 = (double)u[o].v[2];
 #pragma unroll
             for (int x = 0; x < 3; x++)
                 a[k][x] = a[k][x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
@@ -1415,9 +1438,9 @@ hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps
 }
 
 // Cells a workgroup of k_resident2d holds: 512 threads have 256 registers each, a row takes 84
-// values (nine blocks) or 48 (five points).  Nine-block rows of FP32 levels are held in FP64 (one a
-// thread) or, narrow, in FP32 (two a thread, widened in every pass).
-static int resident2d_cells(int nb, int narrow) { return nb == 9 && !narrow ? kResNT : 2 * kResNT; }
+// values (nine blocks) or 48 (five points).  Rows are held in FP64, one a thread, or, narrow, two a
+// thread: nine-block rows of FP32 levels in FP32 (widened in every pass), five-point rows in FP64.
+static int resident2d_cells(int narrow) { return narrow ? 2 * kResNT : kResNT; }
 
 static const void *resident2d_kernel(int nb, int prec, int narrow)
 {
@@ -1425,7 +1448,9 @@ static const void *resident2d_kernel(int nb, int prec, int narrow)
     if (nb == 9 && f32)
         return narrow ? (const void *)k_resident2d<float, 9, float, 2> : (const void *)k_resident2d<float, 9, double, 1>;
     if (nb == 9) return (const void *)k_resident2d<double, 9, double, 1>;
-    return f32 ? (const void *)k_resident2d<float, 5, double, 2> : (const void *)k_resident2d<double, 5, double, 2>;
+    if (narrow)
+        return f32 ? (const void *)k_resident2d<float, 5, double, 2> : (const void *)k_resident2d<double, 5, double, 2>;
+    return f32 ? (const void *)k_resident2d<float, 5, double, 1> : (const void *)k_resident2d<double, 5, double, 1>;
 }
 
 // The tiling of one resident level: the tile and the passes per exchange with the smallest
@@ -1439,8 +1464,8 @@ Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
     if (L.nb != 9 && L.nb != 5) return best;
     const int C = L.nb == 9 ? 3 : 2, R = L.nb == 9 ? 2 : 1;
     double cost = 1e30;
-    for (int narrow = 0; narrow <= (L.nb == 9 && prec == NMG_FP32_MG ? 1 : 0); narrow++) {
-        const int cap = resident2d_cells(L.nb, narrow);
+    for (int narrow = 0; narrow <= (L.nb == 9 && prec != NMG_FP32_MG ? 0 : 1); narrow++) {
+        const int cap = resident2d_cells(narrow);
         const double lat = 0.2, work = (L.nb == 9 ? 0.28 : 0.16) * (narrow ? 1.5 : 1.0);
         for (int ty = 2; ty <= 32 && ty <= L.ny + 1; ty += 2)
             for (int tx = 4; tx <= 64 && tx <= L.nx + 3; tx += 4) {

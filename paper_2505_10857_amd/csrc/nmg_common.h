@@ -233,7 +233,7 @@ hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps
 // A level's smoothing phases with the operator held in registers (k_resident2d): tiles of tx x ty
 // cells, gx x gy workgroups, m colour passes between two exchanges; tx = 0: the level does not fit.
 struct Resident2D {
-    int tx = 0, ty = 0, gx = 0, gy = 0, m = 0, narrow = 0;   // narrow: rows held in FP32
+    int tx = 0, ty = 0, gx = 0, gy = 0, m = 0, narrow = 0;   // narrow: two cells a thread
 };
 Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg);
 // workgroups of k_resident2d that can be resident at once on the current device (0: none)
