@@ -502,7 +502,8 @@ nmg_status newton2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
     // Steps are enqueued check_every at a time; once the device state stops, the remaining
     // enqueued steps leave U unchanged (the update kernel reads the state).
     while (hs.active) {
-        for (int k = 0; k < P.check_every; k++)
+        const int left = std::max(1, P.n_max - hs.n);     // a step past n_max would change nothing
+        for (int k = 0; k < std::min(P.check_every, left); k++)
             if ((st = newton_step(P, w, U, s)) != NMG_OK) return st;
         HIP_TRY2(hipMemcpyAsync(&hs, S, sizeof(hs), hipMemcpyDeviceToHost, s));
         HIP_TRY2(hipStreamSynchronize(s));

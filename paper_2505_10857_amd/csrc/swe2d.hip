@@ -55,93 +55,125 @@ constexpr int kSlots = 36;                             // face states of one loc
 struct V3 { double c[3]; };
 struct H2 { double g[2]; };            // a depth at the two Gauss points of a face
 
-NMG2D_INL double weno_p2(double um, double u0, double up)
+// Division and square root rounded as IEEE 754 asks, for operands far from the overflow and denormal
+// limits (depths, smoothness indicators, wave speeds): the reciprocal refined by two Newton-Raphson
+// steps, the quotient corrected once by its residual (Markstein), and Goldschmidt's square root with
+// two residual corrections.  The compiler's sequences are these with range scaling and special cases
+// around them, which cost about a third of a quotient; and quotients of one divisor share its
+// reciprocal here.  A zero or negative depth still gives a non-finite result.
+struct Recip {
+    double b, r;
+    NMG2D_INL explicit Recip(double d) : b(d)
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        r = __builtin_amdgcn_rcp(d);
+        r = fma(fma(-d, r, 1.0), r, r);
+        r = fma(fma(-d, r, 1.0), r, r);
+#else
+        r = 0.0;
+#endif
+    }
+    NMG2D_INL double of(double a) const      // a / b
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        const double q = a * r;
+        return fma(fma(-b, q, a), r, q);
+#else
+        return a / b;
+#endif
+    }
+};
+
+NMG2D_INL double sqrt2(double a)
 {
-    double c0 = 1.5 * u0 - 0.5 * up;
-    double c1 = 0.5 * um + 0.5 * u0;
-    double b0 = (up - u0) * (up - u0);
-    double b1 = (u0 - um) * (u0 - um);
-    double a0 = (1.0 / 3.0) / ((kZeta + b0) * (kZeta + b0));
-    double a1 = (2.0 / 3.0) / ((kZeta + b1) * (kZeta + b1));
-    double w0 = a0 / (a0 + a1);
-    double w1 = a1 / (a0 + a1);
-    return w0 * c0 + w1 * c1;
+#ifdef __HIP_DEVICE_COMPILE__
+    const double r = __builtin_amdgcn_rsq(a);
+    double g = a * r, h = r * 0.5;
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    double d = fma(-g, g, a);
+    g = fma(d, h, g);
+    d = fma(-g, g, a);
+    return fma(d, h, g);
+#else
+    return sqrt(a);
+#endif
 }
 
+// The minus state's reconstruction: from cell u0 to the face on the side of up.  The plus state's is
+// the mirror image, the same operations on the cells in the opposite order.
 NMG2D_INL double weno_m2(double um, double u0, double up)
 {
     double c0 = 0.5 * u0 + 0.5 * up;
     double c1 = -0.5 * um + 1.5 * u0;
     double b0 = (up - u0) * (up - u0);
     double b1 = (u0 - um) * (u0 - um);
-    double a0 = (2.0 / 3.0) / ((kZeta + b0) * (kZeta + b0));
-    double a1 = (1.0 / 3.0) / ((kZeta + b1) * (kZeta + b1));
-    double w0 = a0 / (a0 + a1);
-    double w1 = a1 / (a0 + a1);
-    return w0 * c0 + w1 * c1;
+    double a0 = Recip((kZeta + b0) * (kZeta + b0)).of(2.0 / 3.0);
+    double a1 = Recip((kZeta + b1) * (kZeta + b1)).of(1.0 / 3.0);
+    const Recip sum(a0 + a1);
+    return sum.of(a0) * c0 + sum.of(a1) * c1;
 }
 
-// Characteristic WENO3 state at the face between cells a and a+1 of a line in direction DIR,
-// from the three consecutive cells S0, S1, S2 of the line that its stencil uses: cells a-1..a+1
-// for the minus state (W = 0, from cell a), a..a+2 for the plus state (W = 1, from cell a+1).
-// The basis is the eigensystem of the face-normal flux Jacobian at the mean of cells a, a+1.
+// Characteristic WENO3 state of cell S1 at the face it shares with S2, from three consecutive cells
+// of a line in either order (S0, S1, S2 along the line give the minus state of the face between S1 and
+// S2, against it the plus state); components (depth, momentum along the line, momentum across it).
+// The basis is the eigensystem of the face-normal flux Jacobian at the mean of the face's two cells.
 // SURF: the projection acts on the surfaces S_q.c[0] + z_q (z_q the cell average of b), the
 // basis on the depths.
+template <bool SURF>
+NMG2D_INL V3 face_state_line(const V3 &S0, const V3 &S1, const V3 &S2, double g, double z0 = 0.0, double z1 = 0.0,
+                             double z2 = 0.0)
+{
+    const double h = 0.5 * (S1.c[0] + S2.c[0]);
+    const Recip rh(h);
+    const double un = rh.of(0.5 * (S1.c[1] + S2.c[1]));
+    const double ut = rh.of(0.5 * (S1.c[2] + S2.c[2]));
+    const double cc = sqrt2(g * h);
+    const double i2c = Recip(2.0 * cc).of(1.0);
+    const double la = (un + cc) * i2c, lb = -(un - cc) * i2c;
+    double w[3];
+#pragma unroll
+    for (int f = 0; f < 3; f++) {
+        double W[3];
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            const V3 &Sq = q == 0 ? S0 : (q == 1 ? S1 : S2);
+            const double e = SURF ? Sq.c[0] + (q == 0 ? z0 : (q == 1 ? z1 : z2)) : Sq.c[0];
+            W[q] = f == 0 ? la * e + -i2c * Sq.c[1] : (f == 1 ? -ut * e + Sq.c[2] : lb * e + i2c * Sq.c[1]);
+        }
+        w[f] = weno_m2(W[0], W[1], W[2]);
+    }
+    V3 out;
+    out.c[0] = w[0] + w[2];
+    out.c[1] = (un - cc) * w[0] + (un + cc) * w[2];
+    out.c[2] = ut * w[0] + w[1] + ut * w[2];
+    return out;
+}
+
+// the state's components (h, hu, hv) in the order of direction DIR's line, and back
+template <int DIR>
+NMG2D_INL V3 along(const V3 &U)
+{
+    return DIR == 0 ? U : V3{{U.c[0], U.c[2], U.c[1]}};
+}
+
+// state of side W (0 minus, 1 plus) of a face in direction DIR from the cells S0, S1, S2 along the line
 template <int DIR, int W, bool SURF = false>
 NMG2D_INL V3 face_state_core(const V3 &S0, const V3 &S1, const V3 &S2, double g, double z0 = 0.0,
                              double z1 = 0.0, double z2 = 0.0)
 {
-    const V3 &Ua = W ? S0 : S1;
-    const V3 &Ub = W ? S1 : S2;
-    double Us[3];
-#pragma unroll
-    for (int c = 0; c < 3; c++) Us[c] = 0.5 * (Ua.c[c] + Ub.c[c]);
-    const double h = Us[0];
-    const double u = Us[1] / h;
-    const double v = Us[2] / h;
-    const double cc = sqrt(g * h);
-    const double un = DIR == 0 ? u : v;
-    const double i2c = 1.0 / (2.0 * cc);
-    double L[3][3], R[3][3];
-    if (DIR == 0) {
-        L[0][0] = (un + cc) * i2c; L[0][1] = -i2c; L[0][2] = 0.0;
-        L[1][0] = -v;              L[1][1] = 0.0;  L[1][2] = 1.0;
-        L[2][0] = -(un - cc) * i2c; L[2][1] = i2c; L[2][2] = 0.0;
-        R[0][0] = 1.0;     R[0][1] = 0.0; R[0][2] = 1.0;
-        R[1][0] = un - cc; R[1][1] = 0.0; R[1][2] = un + cc;
-        R[2][0] = v;       R[2][1] = 1.0; R[2][2] = v;
-    } else {
-        L[0][0] = (un + cc) * i2c; L[0][1] = 0.0; L[0][2] = -i2c;
-        L[1][0] = -u;              L[1][1] = 1.0; L[1][2] = 0.0;
-        L[2][0] = -(un - cc) * i2c; L[2][1] = 0.0; L[2][2] = i2c;
-        R[0][0] = 1.0;     R[0][1] = 0.0; R[0][2] = 1.0;
-        R[1][0] = u;       R[1][1] = 1.0; R[1][2] = u;
-        R[2][0] = un - cc; R[2][1] = 0.0; R[2][2] = un + cc;
-    }
-    double Wc[3][3], w[3];
-#pragma unroll
-    for (int q = 0; q < 3; q++) {
-        const V3 &Sq = q == 0 ? S0 : (q == 1 ? S1 : S2);
-        const double e = SURF ? Sq.c[0] + (q == 0 ? z0 : (q == 1 ? z1 : z2)) : Sq.c[0];
-#pragma unroll
-        for (int f = 0; f < 3; f++)
-            Wc[q][f] = L[f][0] * e + L[f][1] * Sq.c[1] + L[f][2] * Sq.c[2];
-    }
-#pragma unroll
-    for (int f = 0; f < 3; f++)
-        w[f] = W ? weno_p2(Wc[0][f], Wc[1][f], Wc[2][f]) : weno_m2(Wc[0][f], Wc[1][f], Wc[2][f]);
-    V3 out;
-#pragma unroll
-    for (int c = 0; c < 3; c++) out.c[c] = R[c][0] * w[0] + R[c][1] * w[1] + R[c][2] * w[2];
-    return out;
+    const V3 a = along<DIR>(W ? S2 : S0), b = along<DIR>(S1), c = along<DIR>(W ? S0 : S2);
+    return along<DIR>(face_state_line<SURF>(a, b, c, g, W ? z2 : z0, z1, W ? z0 : z2));
 }
 
 template <int DIR>
 NMG2D_INL V3 flux2(const V3 &U, double g)
 {
     const double h = U.c[0];
-    const double u = U.c[1] / h;
-    const double v = U.c[2] / h;
+    const Recip rh(h);
+    const double u = rh.of(U.c[1]);
+    const double v = rh.of(U.c[2]);
     V3 F;
     if (DIR == 0) {
         F.c[0] = U.c[1];
@@ -160,9 +192,9 @@ NMG2D_INL V3 llf2(const V3 &UL, const V3 &UR, double g)
 {
     const V3 FL = flux2<DIR>(UL, g);
     const V3 FR = flux2<DIR>(UR, g);
-    const double unL = UL.c[1 + DIR] / UL.c[0], unR = UR.c[1 + DIR] / UR.c[0];
-    const double sL = fabs(unL) + sqrt(g * UL.c[0]);
-    const double sR = fabs(unR) + sqrt(g * UR.c[0]);
+    const double unL = Recip(UL.c[0]).of(UL.c[1 + DIR]), unR = Recip(UR.c[0]).of(UR.c[1 + DIR]);
+    const double sL = fabs(unL) + sqrt2(g * UL.c[0]);
+    const double sR = fabs(unR) + sqrt2(g * UR.c[0]);
     const double a = sL > sR ? sL : sR;
     V3 F;
 #pragma unroll
