@@ -539,59 +539,6 @@ struct TableFS {
     }
 };
 
-// Face states of an interior row cell under a perturbation of component pm of the cell at the
-// offset (DX, DY) of the cross stencil: a state whose three cells include that cell is
-// recomputed from the staged state, every other one read from the tables.
-template <int DX, int DY, bool SURF>
-struct PerturbedFS {
-    static constexpr bool surf = SURF;
-    TableFS<SURF> tab;
-    LdsStateT<SURF> st;
-    int i, j, pm;
-    double eps, g;
-
-    template <int DIR, int W, int K, int A>
-    static constexpr bool hit()
-    {
-        // along the line the state uses cells A-1+W .. A+1+W; the line sits at offset K across
-        return DIR == 0 ? (K == DY && DX >= A - 1 + W && DX <= A + 1 + W)
-                        : (K == DX && DY >= A - 1 + W && DY <= A + 1 + W);
-    }
-
-    template <int DIR, int W, int K, int A, int Q>
-    NMG2D_INL V3 cell() const
-    {
-        constexpr int t = A - 1 + W + Q;                       // along the line
-        constexpr int ci = DIR == 0 ? t : K, cj = DIR == 0 ? K : t;
-        constexpr bool on = ci == DX && cj == DY;
-        V3 v;
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const double x = st(c, i + ci, j + cj);
-            v.c[c] = (on && c == pm) ? x + eps : x;
-        }
-        return v;
-    }
-
-    template <int DIR, int W, int K, int A>
-    NMG2D_INL V3 get() const
-    {
-        if constexpr (hit<DIR, W, K, A>()) {
-            constexpr int t0 = A - 1 + W;
-            double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-            if constexpr (SURF) {
-                z0 = DIR == 0 ? st.zb(i + t0, j + K) : st.zb(i + K, j + t0);
-                z1 = DIR == 0 ? st.zb(i + t0 + 1, j + K) : st.zb(i + K, j + t0 + 1);
-                z2 = DIR == 0 ? st.zb(i + t0 + 2, j + K) : st.zb(i + K, j + t0 + 2);
-            }
-            return face_state_core<DIR, W, SURF>(cell<DIR, W, K, A, 0>(), cell<DIR, W, K, A, 1>(),
-                                                 cell<DIR, W, K, A, 2>(), g, z0, z1, z2);
-        } else {
-            return tab.template get<DIR, W, K, A>();
-        }
-    }
-};
-
 // ---- residual -------------------------------------------------------------------------------
 
 NMG2D_INL void load_slopes(const Inst2D &I, int i, int j, double bx[4], double by[4])
@@ -716,120 +663,325 @@ NMG2D_INL bool border_row(const Inst2D &I, int i, int j)
     return i < 2 || j < 2 || i >= I.Nx - 2 || j >= I.Ny - 2;
 }
 
-template <int B, typename T, bool SURF>
-NMG2D_INL void interior_column(T *J, const JacOut &o, const TableFS<SURF> &tab, const LdsStateT<SURF> &st,
-                               const Inst2D &I, int i, int j, int m, const double bx[4], const double by[4],
-                               double d[3])
-{
-    const PerturbedFS<stencil_dx(21, B), stencil_dy(21, B), SURF> fs{tab, st, i, j, m, I.eps, I.g};
-    double h_own = 0.0;
-    if constexpr (SURF) {
-        const double x = st(0, i, j);
-        h_own = (B == 0 && m == 0) ? x + I.eps : x;
+// Tables of the interior kernel for a tile of TX x TY cells: the face states its rows use, three
+// components in line order (depth, momentum along the line, momentum across it).  Set p = 0, 1, 2:
+// the state with one component of the p-th of its three cells raised by eps; set 3: unperturbed.
+template <int TX, int TY>
+struct JacTile {
+    static constexpr int SX = TX + 4, SY = TY + 4;                 // staged state (halo 2)
+    static constexpr int XA = TX + 3, XL = TY + 2, YA = TY + 3, YL = TX + 2;
+    static constexpr int XS = 6 * XL * XA, SET = XS + 6 * YL * YA;
+    static constexpr int STATES = 2 * XL * (XA - 1);               // x (and, by symmetry of the count, y) states
+    static_assert(XL * (XA - 1) == YL * (YA - 1), "as many y states as x states");
+    // component 0 of the state of side W of face A on line K, relative to the row cell's base
+    template <int DIR, int W, int K, int A>
+    static constexpr int at() { return DIR == 0 ? (W * XL + 1 + K) * XA + 2 + A : XS + (W * YL + 1 + K) * YA + 2 + A; }
+    template <int DIR>
+    static constexpr int comp() { return DIR == 0 ? 2 * XL * XA : 2 * YL * YA; }
+};
+
+// A column's perturbed cell as direction DIR sees it: d along the line, k the line.  The state of side
+// W of face A on line K uses the cells A - 1 + W .. A + 1 + W of its line.
+struct Hit {
+    int d, k;
+    template <int W, int K, int A>
+    NMG2D_INL int set() const
+    {
+        const int p = d - (A - 1 + W);
+        return K == k && p >= 0 && p <= 2 ? p : 3;
     }
-    const V3 Rp = assemble_residual(fs, I, bx, by, i, j, h_own);
-    store_column(J, o, B, m, Rp, d);
+    // one of the states that the flux through face A, or the depth of side W there, is formed from
+    template <int A>
+    NMG2D_INL bool flux() const { return k >= -1 && k <= 1 && d >= A - 1 && d <= A + 2; }
+    template <int W, int A>
+    NMG2D_INL bool depth() const { return k >= -1 && k <= 1 && d >= A - 1 + W && d <= A + 1 + W; }
+};
+
+template <class TL, int DIR, int W, int K, int A>
+NMG2D_INL V3 tab_state(const double *tab, const Hit &h)
+{
+    const double *q = tab + h.set<W, K, A>() * TL::SET + TL::template at<DIR, W, K, A>();
+    return V3{{q[0], q[TL::template comp<DIR>()], q[2 * TL::template comp<DIR>()]}};
 }
 
-// the 3 NB columns of the interior row (i, j) of a tile whose state and face tables are staged
-// (the first nine blocks of the full stencil are the cross, so one offset table serves both)
-template <typename T, int NB, bool SURF>
-NMG2D_INL void jacobian_interior_row(const Inst2D &I, const Perm2D &Pm, T *J, T *rhs, T *Dinv, const double *xs,
-                                     const double *ys, const LdsStateT<SURF> &st, int i, int j)
+// flux through face A in direction DIR, line order; hm, hp and b0, b1 as in face_flux_at
+template <class TL, int DIR, int A, bool SURF>
+NMG2D_INL V3 tab_flux(const double *tab, const Hit &h, double g, H2 &hm, H2 &hp, double b0, double b1)
 {
-    const int i0 = st.i0, j0 = st.j0;
-    const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
-    JacOut o;
-    o.M = Pm.M;
-    o.slot = perm2d(Pm, i, j);
-    o.R0 = I.R[cidx];
-    o.R1 = I.R[n + cidx];
-    o.R2 = I.R[2 * n + cidx];
-    o.rn = I.rn[cidx];
-    o.alpha = I.alpha;
-    o.eps = I.eps;
-    if (rhs) {
-        rhs[o.slot] = (T)o.R0;
-        rhs[o.M + o.slot] = (T)o.R1;
-        rhs[2 * o.M + o.slot] = (T)o.R2;
+    const V3 Vm0 = tab_state<TL, DIR, 0, -1, A>(tab, h), Vm1 = tab_state<TL, DIR, 0, 0, A>(tab, h),
+             Vm2 = tab_state<TL, DIR, 0, 1, A>(tab, h);
+    const V3 Vp0 = tab_state<TL, DIR, 1, -1, A>(tab, h), Vp1 = tab_state<TL, DIR, 1, 0, A>(tab, h),
+             Vp2 = tab_state<TL, DIR, 1, 1, A>(tab, h);
+    V3 Pm0 = gauss_pt2<0>(Vm0, Vm1, Vm2), Pm1 = gauss_pt2<1>(Vm0, Vm1, Vm2);
+    V3 Pp0 = gauss_pt2<0>(Vp0, Vp1, Vp2), Pp1 = gauss_pt2<1>(Vp0, Vp1, Vp2);
+    hm.g[0] = Pm0.c[0]; hm.g[1] = Pm1.c[0];
+    hp.g[0] = Pp0.c[0]; hp.g[1] = Pp1.c[0];
+    if constexpr (SURF) {
+        Pm0.c[0] = Pm0.c[0] - b0; Pp0.c[0] = Pp0.c[0] - b0;
+        Pm1.c[0] = Pm1.c[0] - b1; Pp1.c[0] = Pp1.c[0] - b1;
     }
-    double bx[4], by[4];
-    load_slopes(I, i, j, bx, by);
-    const TableFS<SURF> tab{xs, ys, i - i0, j - j0};
-    double D[9];
+    const V3 F0 = llf2<0>(Pm0, Pp0, g), F1 = llf2<0>(Pm1, Pp1, g);
+    V3 F;
+#pragma unroll
+    for (int c = 0; c < 3; c++) F.c[c] = 0.5 * (F0.c[c] + F1.c[c]);
+    return F;
+}
+
+template <class TL, int DIR, int W, int A>
+NMG2D_INL H2 tab_depth(const double *tab, const Hit &h)
+{
+    const V3 V0 = tab_state<TL, DIR, W, -1, A>(tab, h), V1 = tab_state<TL, DIR, W, 0, A>(tab, h),
+             V2 = tab_state<TL, DIR, W, 1, A>(tab, h);
+    return H2{{gauss_pt2<0>(V0, V1, V2).c[0], gauss_pt2<1>(V0, V1, V2).c[0]}};
+}
+
+// What the residual of a row is assembled from: the fluxes through its four faces (line order) and, per
+// direction, the depths of its lines' cubics at x - 3/2, - 1/2, + 1/2, + 3/2
+struct RowParts {
+    V3 fxm, fxp, fym, fyp;
+    H2 hx[4], hy[4];
+};
+
+// the parts a perturbed cell reaches, the others from `o`
+template <class TL, bool SURF>
+NMG2D_INL void row_parts(RowParts &r, const RowParts &o, const double *tx, const double *ty, const Hit &hx, const Hit &hy,
+                         double g, const double zx[4], const double zy[4])
+{
+    H2 dum;
+    r = o;
+    if (hx.flux<-1>()) r.fxm = tab_flux<TL, 0, -1, SURF>(tx, hx, g, dum, r.hx[1], zx[0], zx[1]);
+    if (hx.flux<0>()) r.fxp = tab_flux<TL, 0, 0, SURF>(tx, hx, g, r.hx[2], dum, zx[2], zx[3]);
+    if (hy.flux<-1>()) r.fym = tab_flux<TL, 1, -1, SURF>(ty, hy, g, dum, r.hy[1], zy[0], zy[1]);
+    if (hy.flux<0>()) r.fyp = tab_flux<TL, 1, 0, SURF>(ty, hy, g, r.hy[2], dum, zy[2], zy[3]);
+    if (hx.depth<1, -2>()) r.hx[0] = tab_depth<TL, 0, 1, -2>(tx, hx);
+    if (hx.depth<0, 1>()) r.hx[3] = tab_depth<TL, 0, 0, 1>(tx, hx);
+    if (hy.depth<1, -2>()) r.hy[0] = tab_depth<TL, 1, 1, -2>(ty, hy);
+    if (hy.depth<0, 1>()) r.hy[3] = tab_depth<TL, 1, 0, 1>(ty, hy);
+}
+
+// R_ij from its parts: the operations of assemble_residual.  zx, zy: b at the Gauss points of the
+// cell's faces (lower face, then upper; surface variant), eta: the cell's surface there.
+template <bool SURF>
+NMG2D_INL V3 row_residual(const RowParts &r, const Inst2D &I, const Recip &rdx, const Recip &rdy, const Recip &rdd,
+                          const double bx[4], const double by[4], const double zx[4], const double zy[4], double eta)
+{
+    double s2 = 0.0, s3 = 0.0;
+#pragma unroll
+    for (int be = 0; be < 2; be++) {
+        const double h0 = cubic_at2<0>(r.hx[0].g[be], r.hx[1].g[be], r.hx[2].g[be], r.hx[3].g[be]);
+        s2 = s2 + I.g * (SURF ? h0 - eta : h0) * bx[2 * be + 0];
+        const double h1 = cubic_at2<1>(r.hx[0].g[be], r.hx[1].g[be], r.hx[2].g[be], r.hx[3].g[be]);
+        s2 = s2 + I.g * (SURF ? h1 - eta : h1) * bx[2 * be + 1];
+    }
+#pragma unroll
+    for (int ga = 0; ga < 2; ga++) {
+        const double h0 = cubic_at2<0>(r.hy[0].g[ga], r.hy[1].g[ga], r.hy[2].g[ga], r.hy[3].g[ga]);
+        s3 = s3 + I.g * (SURF ? h0 - eta : h0) * by[0 + ga];
+        const double h1 = cubic_at2<1>(r.hy[0].g[ga], r.hy[1].g[ga], r.hy[2].g[ga], r.hy[3].g[ga]);
+        s3 = s3 + I.g * (SURF ? h1 - eta : h1) * by[2 + ga];
+    }
+    double S2 = -(I.dx * I.dy / 4.0) * s2;
+    double S3 = -(I.dx * I.dy / 4.0) * s3;
+    if constexpr (SURF) {
+        double e2 = 0.0, e3 = 0.0;
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            e2 = e2 + I.g * (eta * (zx[2 + q] - zx[q]) - (zx[2 + q] * zx[2 + q] - zx[q] * zx[q]) / 2.0);
+            e3 = e3 + I.g * (eta * (zy[2 + q] - zy[q]) - (zy[2 + q] * zy[2 + q] - zy[q] * zy[q]) / 2.0);
+        }
+        S2 = -(I.dx * I.dy / 4.0) * s2 - (I.dy / 2.0) * e2;
+        S3 = -(I.dx * I.dy / 4.0) * s3 - (I.dx / 2.0) * e3;
+    }
+    V3 R;
+    R.c[0] = rdx.of(r.fxp.c[0] - r.fxm.c[0]) + rdy.of(r.fyp.c[0] - r.fym.c[0]);
+    R.c[1] = rdx.of(r.fxp.c[1] - r.fxm.c[1]) + rdy.of(r.fyp.c[2] - r.fym.c[2]) - rdd.of(S2);
+    R.c[2] = rdx.of(r.fxp.c[2] - r.fxm.c[2]) + rdy.of(r.fyp.c[1] - r.fym.c[1]) - rdd.of(S3);
+    return R;
+}
+
+// The blocks that column group `group` of `groups` forms (bit b: block b): blocks go, the costly ones
+// (whose cell reaches all four faces: the centre and the cells next to it, diagonals included) first, to
+// the group with the least work so far
+constexpr unsigned column_group(int nb, int groups, int group)
+{
+    unsigned mask[8] = {};
+    int load[8] = {};
+    for (int pass = 0; pass < 2; pass++)
+        for (int b = 0; b < nb; b++) {
+            const int dx = stencil_dx(21, b), dy = stencil_dy(21, b);
+            const bool near = dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1;
+            if (near != (pass == 0)) continue;
+            int best = 0;
+            for (int q = 1; q < groups; q++)
+                if (load[q] < load[best]) best = q;
+            mask[best] |= 1u << b;
+            load[best] += near ? 5 : 2;
+        }
+    return mask[group];
+}
+
+// Finite-difference Jacobian (eq. 12, 13) of the rows at least two cells inside the grid (no ghost in
+// their residual).  A perturbed face state serves up to five rows, so the tile forms each once per
+// component (3 cells x 3 components x 4 states a cell, where every row for itself re-evaluates 60 a
+// component) and the rows assemble their columns from the tables, re-forming only the fluxes
+// that the perturbed cell reaches.  What bounds it is FP64 arithmetic (divisions and square roots) at
+// two wavefronts per SIMD, which the tables' LDS allows: one workgroup of 512 threads per compute unit.
+// The columns of a row are shared by CG = 512 / (TX TY) threads (wavefronts of their own, so the column
+// is uniform): 2 on the 32 x 8 tile, 8 on the 8 x 8 tile for grids too small to fill the chip with
+// the larger one.
+// 1024 x 512, J9: 2050 us with every row re-evaluating its states, 1250 with cheaper divisions, 0 so;
+// 64 x 32: 226, 150, 0.
+constexpr int kJacNT = 512;
+
+template <typename T, int NB, bool SURF, int TX, int TY>
+__global__ void __launch_bounds__(kJacNT) k_jacobian2d(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv)
+{
+    typedef JacTile<TX, TY> TL;
+    constexpr int CG = kJacNT / (TX * TY), SX = TL::SX, SY = TL::SY;
+    static_assert(TX * TY % 64 == 0 && CG <= 8, "a wavefront forms one column at a time");
+    __shared__ double s[3 * SY * SX];
+    __shared__ double zs[SURF ? SY * SX : 1];
+    __shared__ double tab[4 * TL::SET];
+    const int i0 = blockIdx.x * TX, j0 = blockIdx.y * TY, t = threadIdx.x;
+    for (int e = t; e < 3 * SY * SX; e += kJacNT) {
+        const int c = e / (SY * SX), r = (e / SX) % SY, q = e % SX;
+        const int i = i0 - 2 + q, j = j0 - 2 + r;
+        const bool ok = i >= 0 && i < I.Nx && j >= 0 && j < I.Ny;
+        s[e] = ok ? I.U[((long long)c * I.Ny + j) * I.Nx + i] : 0.0;
+    }
+    if constexpr (SURF)
+        for (int e = t; e < SY * SX; e += kJacNT) {
+            const int i = i0 - 2 + e % SX, j = j0 - 2 + e / SX;
+            const bool ok = i >= -2 && i < I.Nx + 2 && j >= -2 && j < I.Ny + 2;
+            zs[e] = ok ? I.zavg[((long long)j + 2) * (I.Nx + 4) + i + 2] : 0.0;
+        }
+    __syncthreads();
+
+    const int cell = t % (TX * TY), xi = cell % TX, xj = cell / TX;
+    const int group = __builtin_amdgcn_readfirstlane(t / (TX * TY));
+    const int i = i0 + xi, j = j0 + xj;
+    const bool row = i < I.Nx && j < I.Ny && !border_row(I, i, j);
+    const double *tx = tab + xj * TL::XA + xi, *ty = tab + xi * TL::YA + xj;
+    unsigned blocks = 0;
+#pragma unroll
+    for (int q = 0; q < CG; q++)
+        if (group == q) blocks = column_group(NB, CG, q);
+    const Recip rdx(I.dx), rdy(I.dy), rdd(I.dx * I.dy);
+    JacOut o;
+    RowParts base;
+    double bx[4], by[4], zx[4], zy[4], D[9], zc = 0.0;
+    if (row) {
+        const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
+        o.M = Pm.M;
+        o.slot = perm2d(Pm, i, j);
+        o.R0 = I.R[cidx];
+        o.R1 = I.R[n + cidx];
+        o.R2 = I.R[2 * n + cidx];
+        o.rn = I.rn[cidx];
+        o.alpha = I.alpha;
+        o.eps = I.eps;
+        if (rhs && group == 0) {
+            rhs[o.slot] = (T)o.R0;
+            rhs[o.M + o.slot] = (T)o.R1;
+            rhs[2 * o.M + o.slot] = (T)o.R2;
+        }
+        load_slopes(I, i, j, bx, by);
+        if constexpr (SURF) {
+            const long long fx = ((long long)j * (I.Nx + 1) + i) * 2, fy = ((long long)j * I.Nx + i) * 2;
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                zx[q] = I.zfx[fx + q];
+                zx[2 + q] = I.zfx[fx + 2 + q];
+                zy[q] = I.zfy[fy + q];
+                zy[2 + q] = I.zfy[fy + 2 * I.Nx + q];
+            }
+            zc = zs[(xj + 2) * SX + xi + 2];
+        }
+    }
 #pragma unroll
     for (int e = 0; e < 9; e++) D[e] = 0.0;
-    // one column at a time (a rolled loop over the columns, the stencil offset dispatched to
-    // its compile-time form), so that only one column's values are live
+
 #pragma unroll 1
-    for (int col = 0; col < 3 * NB; col++) {
-        const int b = col / 3, m = col - 3 * b;
-        double d[3];
-        switch (b) {
-        case 0: interior_column<0>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 1: interior_column<1>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 2: interior_column<2>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 3: interior_column<3>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 4: interior_column<4>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 5: interior_column<5>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 6: interior_column<6>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 7: interior_column<7>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        case 8: interior_column<8>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-        default:
-            if constexpr (NB == 21) {
-                switch (b) {
-                case 9: interior_column<9>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 10: interior_column<10>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 11: interior_column<11>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 12: interior_column<12>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 13: interior_column<13>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 14: interior_column<14>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 15: interior_column<15>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 16: interior_column<16>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 17: interior_column<17>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 18: interior_column<18>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                case 19: interior_column<19>(J, o, tab, st, I, i, j, m, bx, by, d); break;
-                default: interior_column<20>(J, o, tab, st, I, i, j, m, bx, by, d); break;
+    for (int m = 0; m < 3; m++) {
+        // the tables of component m (with m = 0 also the unperturbed ones): states whose cells leave the
+        // grid belong to no interior row
+        for (int e = t; e < (m == 0 ? 4 : 3) * 2 * TL::STATES; e += kJacNT) {
+            const int p = e / (2 * TL::STATES), r = e - p * (2 * TL::STATES), dir = r / TL::STATES;
+            const int q = r - dir * TL::STATES, W = q / (TL::STATES / 2), f = q - W * (TL::STATES / 2);
+            const int per = dir ? TL::YA - 1 : TL::XA - 1, line = f / per, a = f - line * per + (W ? 0 : 1);
+            const int t0 = (dir ? j0 : i0) - 3 + a + W, k = (dir ? i0 : j0) - 1 + line;
+            if (t0 < 0 || t0 + 2 >= (dir ? I.Ny : I.Nx) || k < 0 || k >= (dir ? I.Nx : I.Ny)) continue;
+            const int c0 = dir ? (a + W - 1) * SX + line + 1 : (line + 1) * SX + a + W - 1, step = dir ? SX : 1;
+            V3 S[3];
+            double z[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const double *v = s + c0 + x * step;
+                double h = v[0], hu = v[SY * SX], hv = v[2 * SY * SX];
+                if (x == p) {
+                    h = m == 0 ? h + I.eps : h;
+                    hu = m == 1 ? hu + I.eps : hu;
+                    hv = m == 2 ? hv + I.eps : hv;
+                }
+                S[x] = dir ? V3{{h, hv, hu}} : V3{{h, hu, hv}};
+                if constexpr (SURF) z[x] = zs[c0 + x * step];
+            }
+            const V3 v = W ? face_state_line<SURF>(S[2], S[1], S[0], I.g, z[2], z[1], z[0])
+                           : face_state_line<SURF>(S[0], S[1], S[2], I.g, z[0], z[1], z[2]);
+            double *w = tab + p * TL::SET + (dir ? TL::XS + (W * TL::YL + line) * TL::YA : (W * TL::XL + line) * TL::XA) + a;
+            const int comp = dir ? TL::template comp<1>() : TL::template comp<0>();
+#pragma unroll
+            for (int c = 0; c < 3; c++) w[c * comp] = v.c[c];
+        }
+        __syncthreads();
+        if (row) {
+            if (m == 0) {
+                const Hit none{100, 0};
+                H2 dum;
+                base.fxm = tab_flux<TL, 0, -1, SURF>(tx, none, I.g, dum, base.hx[1], zx[0], zx[1]);
+                base.fxp = tab_flux<TL, 0, 0, SURF>(tx, none, I.g, base.hx[2], dum, zx[2], zx[3]);
+                base.fym = tab_flux<TL, 1, -1, SURF>(ty, none, I.g, dum, base.hy[1], zy[0], zy[1]);
+                base.fyp = tab_flux<TL, 1, 0, SURF>(ty, none, I.g, base.hy[2], dum, zy[2], zy[3]);
+                base.hx[0] = tab_depth<TL, 0, 1, -2>(tx, none);
+                base.hx[3] = tab_depth<TL, 0, 0, 1>(tx, none);
+                base.hy[0] = tab_depth<TL, 1, 1, -2>(ty, none);
+                base.hy[3] = tab_depth<TL, 1, 0, 1>(ty, none);
+            }
+#pragma unroll 1
+            for (int b = 0; b < NB; b++) {
+                if (!(blocks >> b & 1)) continue;
+                const int dx = stencil_dx(21, b), dy = stencil_dy(21, b);
+                RowParts r;
+                row_parts<TL, SURF>(r, base, tx, ty, Hit{dx, dy}, Hit{dy, dx}, I.g, zx, zy);
+                double eta = 0.0;
+                if constexpr (SURF) {
+                    const double x = s[(xj + 2) * SX + xi + 2];
+                    eta = (b == 0 && m == 0 ? x + I.eps : x) + zc;
+                }
+                const V3 Rp = row_residual<SURF>(r, I, rdx, rdy, rdd, bx, by, zx, zy, eta);
+                double d[3];
+                store_column(J, o, b, m, Rp, d);
+                if (b == 0) {
+#pragma unroll
+                    for (int l = 0; l < 3; l++)
+#pragma unroll
+                        for (int c = 0; c < 3; c++)
+                            if (c == m) D[l * 3 + c] = d[l];
                 }
             }
-            break;
         }
-        if (b == 0) {
-            if (m == 0) { D[0] = d[0]; D[3] = d[1]; D[6] = d[2]; }
-            else if (m == 1) { D[1] = d[0]; D[4] = d[1]; D[7] = d[2]; }
-            else { D[2] = d[0]; D[5] = d[1]; D[8] = d[2]; }
-        }
+        __syncthreads();
     }
-    if (Dinv) store_dinv(Dinv, o.M, o.slot, D);
+    if (row && Dinv && (blocks & 1)) store_dinv(Dinv, o.M, o.slot, D);
 }
 
-// Finite-difference Jacobian (eq. 12, 13) of the rows at least two cells inside the grid, one
-// thread per row: for each component m, the NB columns of the stencil.  Optionally the finest
-// right-hand side (= R) and the inverse of the diagonal block.
-template <typename T, int NB, bool SURF>
-__global__ void __launch_bounds__(kTX * kTY) k_jacobian2d(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv)
-{
-    __shared__ double s[3 * kSY * kSX];
-    __shared__ double zs[SURF ? kSY * kSX : 1];
-    __shared__ double xs[kXS], ys[kYS];
-    const int i0 = blockIdx.x * kTX, j0 = blockIdx.y * kTY;
-    const int tid = threadIdx.y * kTX + threadIdx.x;
-    stage_tile(I, i0, j0, s, tid, kTX * kTY, SURF ? zs : nullptr);
-    __syncthreads();
-    const LdsStateT<SURF> st{s, zs, i0, j0};
-    face_tables(I, st, xs, ys, tid, kTX * kTY);
-    __syncthreads();
-    const int i = i0 + threadIdx.x, j = j0 + threadIdx.y;
-    if (i >= I.Nx || j >= I.Ny || border_row(I, i, j)) return;
-    jacobian_interior_row<T, NB, SURF>(I, Pm, J, rhs, Dinv, xs, ys, st, i, j);
-}
-
-// Face states of a border row, full re-evaluation: the 36 states sit in per-thread LDS slots,
-// slot q at slots[(q*3 + c) * kBorderNT + lane].
+// Face states of one column of a border row: the state of slot q at slots[(q*3 + c) * kBorderNT + lane]
+// where the perturbed cell reaches it (bit q of hits), else the row's unperturbed one at base[q*3 + c].
 template <bool SURF>
 struct SlotFS {
     static constexpr bool surf = SURF;
-    const double *slots;
+    const double *slots, *base;
+    unsigned long long hits;
     int lane;
     // slot of a face state: per direction 18, in the order A = -1 (6: W, K), A = 0 (6),
     // A = -2 (3: K, plus side), A = 1 (3: K, minus side)
@@ -842,31 +994,81 @@ struct SlotFS {
     NMG2D_INL V3 get() const
     {
         constexpr int q = slot<DIR, W, K, A>();
+        const bool hit = hits >> q & 1;
         V3 v;
 #pragma unroll
-        for (int c = 0; c < 3; c++) v.c[c] = slots[(q * 3 + c) * kBorderNT + lane];
+        for (int c = 0; c < 3; c++) v.c[c] = hit ? slots[(q * 3 + c) * kBorderNT + lane] : base[q * 3 + c];
         return v;
     }
 };
 
-// the face state of slot q of row (i, j) under a perturbation (runtime slot decode)
-template <class ST>
-NMG2D_INL V3 slot_state(const Inst2D &I, const ST &st, int q, int i, int j, int pi, int pj, int pm, double eps)
-{
-    const int dir = q / 18, r = q - 18 * dir;
-    int w, K, A;
-    if (r < 6) { A = -1; w = r / 3; K = r % 3 - 1; }
-    else if (r < 12) { A = 0; w = (r - 6) / 3; K = (r - 6) % 3 - 1; }
-    else if (r < 15) { A = -2; w = 1; K = r - 13; }
-    else { A = 1; w = 0; K = r - 16; }
-    if (dir == 0) {
-        const int k = j + K, a = i + A;
-        return w ? face_state_general<0, 1>(I, st, k, a, pi, pj, pm, eps)
-                 : face_state_general<0, 0>(I, st, k, a, pi, pj, pm, eps);
+// slot q of the row (i, j): its direction, side, first cell along the line and line (runtime decode)
+struct SlotAt {
+    int dir, w, t0, k;
+    NMG2D_INL SlotAt(int q, int i, int j)
+    {
+        dir = q / 18;
+        const int r = q - 18 * dir;
+        int K, A;
+        if (r < 6) { A = -1; w = r / 3; K = r % 3 - 1; }
+        else if (r < 12) { A = 0; w = (r - 6) / 3; K = (r - 6) % 3 - 1; }
+        else if (r < 15) { A = -2; w = 1; K = r - 13; }
+        else { A = 1; w = 0; K = r - 16; }
+        t0 = (dir ? j : i) + A - 1 + w;
+        k = (dir ? i : j) + K;
     }
-    const int k = i + K, a = j + A;
-    return w ? face_state_general<1, 1>(I, st, k, a, pi, pj, pm, eps)
-             : face_state_general<1, 0>(I, st, k, a, pi, pj, pm, eps);
+};
+
+// the face state at a slot under the perturbation (pi, pj, pm), ghosts applied
+template <class ST>
+NMG2D_INL V3 slot_state(const Inst2D &I, const ST &st, const SlotAt &a, int pi, int pj, int pm, double eps)
+{
+    V3 S[3];
+    double z[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        const int t = a.t0 + (a.w ? 2 - q : q), i = a.dir ? a.k : t, j = a.dir ? t : a.k;
+        const V3 U = cell2(I, st, i, j, pi, pj, pm, eps);
+        S[q] = a.dir ? V3{{U.c[0], U.c[2], U.c[1]}} : U;
+        if constexpr (ST::surf) z[q] = st.zb(i, j);
+    }
+    const V3 v = face_state_line<ST::surf>(S[0], S[1], S[2], I.g, z[0], z[1], z[2]);
+    return a.dir ? V3{{v.c[0], v.c[2], v.c[1]}} : v;
+}
+
+// whether cell (i, j), ghosts included, takes its values from the cell (pi, pj) of the grid
+NMG2D_INL bool follows(const Inst2D &I, int i, int j, int pi, int pj)
+{
+    int ii = i, jj = j;
+    bool state = false;
+    if (j < 0 || j >= I.Ny) {
+        int kind = j < 0 ? I.bc_kind[2] : I.bc_kind[3];
+        if (j < 0 && kind == NMG_BC_WALL && I.wall_x > I.x0) {
+            const double xc = I.x0 + (i + 0.5) * I.dx;
+            kind = xc < I.wall_x ? NMG_BC_EXTRAP : NMG_BC_WALL;
+        }
+        if (kind == NMG_BC_WALL) jj = j < 0 ? -1 - j : 2 * I.Ny - 1 - j;
+        else jj = j < 0 ? 0 : I.Ny - 1;
+        if (kind == NMG_BC_STATE) state = true;
+    }
+    if (i < 0 || i >= I.Nx) {
+        const int kind = i < 0 ? I.bc_kind[0] : I.bc_kind[1];
+        if (kind == NMG_BC_WALL) ii = i < 0 ? -1 - i : 2 * I.Nx - 1 - i;
+        else ii = i < 0 ? 0 : I.Nx - 1;
+        if (kind == NMG_BC_STATE) state = true;
+    }
+    return !state && ii == pi && jj == pj;
+}
+
+NMG2D_INL bool slot_follows(const Inst2D &I, const SlotAt &a, int pi, int pj)
+{
+    bool hit = false;
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        const int t = a.t0 + q;
+        hit = hit || follows(I, a.dir ? a.k : t, a.dir ? t : a.k, pi, pj);
+    }
+    return hit;
 }
 
 // the cell of border row number r (rows within two cells of a side, bottom band, top band, then
@@ -892,82 +1094,109 @@ long long border_rows2d(int Nx, int Ny)
     return (long long)Nx * Ny - inner;
 }
 
-// column col (b*3 + m) of border row number r, its face states in the slot array at lane `lane`
-// (stride kBorderNT); d: the column's FP64 values.  Returns the row's output slot.
-template <typename T, bool SURF>
-NMG2D_INL long long jacobian_border_column(const Inst2D &I, const Perm2D &Pm, T *J, T *rhs, double *slots, int lane,
-                                           long long r, int col, double d[3])
-{
-    const int b = col / 3, m = col - 3 * b;
-    int i, j;
-    border_cell(I, r, i, j);
-    const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
-    JacOut o;
-    o.M = Pm.M;
-    o.slot = perm2d(Pm, i, j);
-    o.R0 = I.R[cidx];
-    o.R1 = I.R[n + cidx];
-    o.R2 = I.R[2 * n + cidx];
-    o.rn = I.rn[cidx];
-    o.alpha = I.alpha;
-    o.eps = I.eps;
-    if (rhs && col == 0) {
-        rhs[o.slot] = (T)o.R0;
-        rhs[o.M + o.slot] = (T)o.R1;
-        rhs[2 * o.M + o.slot] = (T)o.R2;
-    }
-    const int pi = i + stencil_dx(21, b), pj = j + stencil_dy(21, b);
-    if (pi < 0 || pi >= I.Nx || pj < 0 || pj >= I.Ny) {
-        store_zero_column(J, o, b, m);
-        return o.slot;
-    }
-    const GlobalStateT<SURF> st{I.U, I.zavg, I.Nx, I.Ny};
-#pragma unroll 1
-    for (int q = 0; q < kSlots; q++) {
-        const V3 v = slot_state(I, st, q, i, j, pi, pj, m, I.eps);
-#pragma unroll
-        for (int c = 0; c < 3; c++) slots[(q * 3 + c) * kBorderNT + lane] = v.c[c];
-    }
-    double bx[4], by[4];
-    load_slopes(I, i, j, bx, by);
-    const SlotFS<SURF> fs{slots, lane};
-    double h_own = 0.0;
-    if constexpr (SURF) {
-        const double x = st(0, i, j);
-        h_own = (pi == i && pj == j && m == 0) ? x + I.eps : x;
-    }
-    const V3 Rp = assemble_residual(fs, I, bx, by, i, j, h_own);
-    store_column(J, o, b, m, Rp, d);
-    return o.slot;
-}
+// Jacobian of the border rows, from the state in global memory.  A workgroup of 256 threads takes
+// kBorderNT / LPR rows: it forms their 36 unperturbed states, lists the (row, block, state) triples
+// whose state follows the perturbed cell (through a ghost or directly; about 7 of 36 per column),
+// forms those for the three components, and then assembles a column per thread.  Bound by the chain
+// of one state after another (every column's 36 in one thread: 81 us at 64 x 32, 470 us at
+// 1024 x 512; the list spread over the threads: 0 and 0 us).  A row takes LPR lanes of a wavefront
+// (32 for the 27 columns of J9, 64 for the 63 of J21), so the lanes of its three diagonal-block columns
+// can hand their FP64 values to the row's first lane, which writes the inverse of the diagonal block.
+constexpr int kBorderThreads = 256;
 
-// Jacobian of the border rows: one thread per (row, column of the stencil), each a full
-// re-evaluation of the perturbed local residual from the state in global memory.  A row takes
-// LPR lanes of a wavefront (32 for the 27 columns of J9, 64 for the 63 of J21), so the lanes of
-// its three diagonal-block columns can hand their FP64 values to the row's first lane, which
-// writes the inverse of the diagonal block.
 template <typename T, int NB, bool SURF>
-__global__ void __launch_bounds__(kBorderNT) k_jacobian2d_border(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv,
-                                                                 long long nrows)
+__global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv,
+                                                                      long long nrows)
 {
-    constexpr int LPR = NB == 9 ? 32 : 64, LOG = NB == 9 ? 5 : 6;
+    constexpr int LPR = NB == 9 ? 32 : 64, RPW = kBorderNT / LPR;
     static_assert(kBorderNT % LPR == 0, "a workgroup holds whole rows");
     __shared__ double slots[kSlots * 3 * kBorderNT];
-    const long long gid = blockIdx.x * (long long)kBorderNT + threadIdx.x;
-    const long long r = gid >> LOG;
-    const int col = (int)(gid & (LPR - 1)), b = col / 3, m = col - 3 * b;
-    const bool active = r < nrows && col < 3 * NB;
+    __shared__ double base[RPW * kSlots * 3];
+    __shared__ unsigned short list[RPW * NB * kSlots];
+    __shared__ unsigned long long hits[RPW * NB];
+    __shared__ int count;
+    const int t = threadIdx.x;
+    const long long r0 = blockIdx.x * (long long)RPW;
+    const GlobalStateT<SURF> st{I.U, I.zavg, I.Nx, I.Ny};
+    for (int e = t; e < RPW * NB; e += kBorderThreads) hits[e] = 0;
+    if (t == 0) count = 0;
+    __syncthreads();
+    for (int e = t; e < RPW * kSlots; e += kBorderThreads) {
+        const int row = e / kSlots, q = e - row * kSlots;
+        if (r0 + row >= nrows) continue;
+        int i, j;
+        border_cell(I, r0 + row, i, j);
+        const V3 v = slot_state(I, st, SlotAt(q, i, j), -1000, -1000, 0, 0.0);
+#pragma unroll
+        for (int c = 0; c < 3; c++) base[(row * kSlots + q) * 3 + c] = v.c[c];
+    }
+    for (int e = t; e < RPW * NB * kSlots; e += kBorderThreads) {
+        const int rb = e / kSlots, q = e - rb * kSlots, row = rb / NB, b = rb - row * NB;
+        if (r0 + row >= nrows) continue;
+        int i, j;
+        border_cell(I, r0 + row, i, j);
+        const int pi = i + stencil_dx(21, b), pj = j + stencil_dy(21, b);
+        if (pi < 0 || pi >= I.Nx || pj < 0 || pj >= I.Ny || !slot_follows(I, SlotAt(q, i, j), pi, pj)) continue;
+        atomicOr(&hits[rb], 1ULL << q);
+        list[atomicAdd(&count, 1)] = (unsigned short)e;      // in any order: the states are independent
+    }
+    __syncthreads();
+    for (int e = t; e < 3 * count; e += kBorderThreads) {
+        const int m = e % 3, x = list[e / 3], rb = x / kSlots, q = x - rb * kSlots, row = rb / NB, b = rb - row * NB;
+        int i, j;
+        border_cell(I, r0 + row, i, j);
+        const V3 v = slot_state(I, st, SlotAt(q, i, j), i + stencil_dx(21, b), j + stencil_dy(21, b), m, I.eps);
+#pragma unroll
+        for (int c = 0; c < 3; c++) slots[(q * 3 + c) * kBorderNT + row * LPR + b * 3 + m] = v.c[c];
+    }
+    __syncthreads();
+    if (t >= kBorderNT) return;
+    const int row = t / LPR, col = t % LPR, b = col / 3, m = col - 3 * b;
+    const bool active = r0 + row < nrows && col < 3 * NB;
     double d[3] = {0.0, 0.0, 0.0};
     long long slot = 0;
-    if (active) slot = jacobian_border_column<T, SURF>(I, Pm, J, rhs, slots, threadIdx.x, r, col, d);
+    if (active) {
+        int i, j;
+        border_cell(I, r0 + row, i, j);
+        const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
+        JacOut o;
+        o.M = Pm.M;
+        o.slot = slot = perm2d(Pm, i, j);
+        o.R0 = I.R[cidx];
+        o.R1 = I.R[n + cidx];
+        o.R2 = I.R[2 * n + cidx];
+        o.rn = I.rn[cidx];
+        o.alpha = I.alpha;
+        o.eps = I.eps;
+        if (rhs && col == 0) {
+            rhs[o.slot] = (T)o.R0;
+            rhs[o.M + o.slot] = (T)o.R1;
+            rhs[2 * o.M + o.slot] = (T)o.R2;
+        }
+        const int pi = i + stencil_dx(21, b), pj = j + stencil_dy(21, b);
+        if (pi < 0 || pi >= I.Nx || pj < 0 || pj >= I.Ny) {
+            store_zero_column(J, o, b, m);
+        } else {
+            double bx[4], by[4];
+            load_slopes(I, i, j, bx, by);
+            const SlotFS<SURF> fs{slots, base + row * kSlots * 3, hits[row * NB + b], t};
+            double h_own = 0.0;
+            if constexpr (SURF) {
+                const double x = st(0, i, j);
+                h_own = (pi == i && pj == j && m == 0) ? x + I.eps : x;
+            }
+            const V3 Rp = assemble_residual(fs, I, bx, by, i, j, h_own);
+            store_column(J, o, b, m, Rp, d);
+        }
+    }
     if (!Dinv) return;   // uniform over the launch
     // the diagonal block's columns m = 0, 1, 2 sit in lanes 0, 1, 2 of the row's LPR
-    const int base = threadIdx.x & ~(LPR - 1);
+    const int first = t & ~(LPR - 1);
     double D[9];
 #pragma unroll
     for (int mm = 0; mm < 3; mm++)
 #pragma unroll
-        for (int l = 0; l < 3; l++) D[l * 3 + mm] = __shfl(d[l], base + mm, 64);
+        for (int l = 0; l < 3; l++) D[l * 3 + mm] = __shfl(d[l], first + mm, 64);
     if (active && col == 0) store_dinv(Dinv, Pm.M, slot, D);
 }
 
@@ -993,15 +1222,20 @@ hipError_t launch_res2d_finalize(const double *partial, int ntiles, long long nc
 template <typename T, int NB, bool SURF>
 static hipError_t jacobian2d_t(const Inst2D &I, const Perm2D &P, T *J, T *rhs, T *Dinv, hipStream_t s)
 {
-    constexpr int LPR = NB == 9 ? 32 : 64;
-    dim3 grid((I.Nx + kTX - 1) / kTX, (I.Ny + kTY - 1) / kTY);
-    hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF>), grid, dim3(kTX, kTY), 0, s, I, P, J, rhs, Dinv);
+    constexpr int RPW = kBorderNT / (NB == 9 ? 32 : 64);
+    // the 32 x 8 tile once it fills every compute unit (256): below that the smaller tile spreads the
+    // same rows over four times the workgroups
+    if ((long long)I.Nx * I.Ny >= 256LL * 32 * 8)
+        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 32, 8>), dim3((I.Nx + 31) / 32, (I.Ny + 7) / 8), dim3(kJacNT), 0, s,
+                           I, P, J, rhs, Dinv);
+    else
+        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 8, 8>), dim3((I.Nx + 7) / 8, (I.Ny + 7) / 8), dim3(kJacNT), 0, s,
+                           I, P, J, rhs, Dinv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long nb = border_rows2d(I.Nx, I.Ny);
-    const long long blocks = (nb * LPR + kBorderNT - 1) / kBorderNT;
-    hipLaunchKernelGGL((k_jacobian2d_border<T, NB, SURF>), dim3((unsigned)blocks), dim3(kBorderNT), 0, s, I, P, J,
-                       rhs, Dinv, nb);
+    hipLaunchKernelGGL((k_jacobian2d_border<T, NB, SURF>), dim3((unsigned)((nb + RPW - 1) / RPW)), dim3(kBorderThreads),
+                       0, s, I, P, J, rhs, Dinv, nb);
     return hipGetLastError();
 }
 
