@@ -53,9 +53,6 @@ struct Plan2D {
     mutable unsigned tag = 0;  // exchanges numbered so far in this call
 };
 
-// the largest level whose rows the registers of the chip can hold, by size alone (the device is
-// not asked when a workspace is sized)
-constexpr long long kResidentCells = 1LL << 18;
 
 nmg_status check2d(const nmg_desc *d, const nmg_params *p, bool need_geometry = true)
 {
@@ -186,7 +183,7 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
     P.off_box = o;
     if (!P.sweeps)
         for (int l = 0; l < P.levels && P.box_cells == 0; l++)
-            if (P.L[l].nb != 21 && (long long)P.L[l].nx * P.L[l].ny <= kResidentCells)
+            if ((long long)P.L[l].nx * P.L[l].ny <= resident2d_max_cells(P.L[l].nb))
                 P.box_cells = (long long)P.L[l].nx * P.L[l].ny;
     o = al256(o + resident2d_box_bytes(P.box_cells, P.prec));
     P.total = o;
@@ -230,16 +227,20 @@ nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
 {
     P.res.assign(P.levels, Resident2D());
     P.resident = false;
+    set_bottom(P);
     if (P.box_cells == 0 || ws_bytes < P.total) return NMG_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY2(hipStreamIsCapturing(s, &cap));
     if (cap != hipStreamCaptureStatusNone) return NMG_OK;
+    // the one-workgroup bottom reads a 21-cell level's rows in every pass: the level runs by itself
+    if (P.bottom_first == 0 && P.L[0].nb == 21 && P.levels > 1) P.bottom_first = 1;
     for (int l = 0; l < P.bottom_first; l++) {
         const Level2D &L = P.L[l];
-        if (L.nb == 21 || (long long)L.nx * L.ny > P.box_cells) continue;
+        if ((long long)L.nx * L.ny > P.box_cells) continue;
         P.res[l] = resident2d_plan(L, P.prec, resident2d_max_wg(L.nb, P.prec));
         if (P.res[l].tx > 0) P.resident = true;
     }
+    if (P.L[0].nb == 21 && P.res[0].tx == 0) set_bottom(P);
     if (P.resident) HIP_TRY2(clear_box(P, ws, s));
     return NMG_OK;
 }

@@ -543,20 +543,16 @@ __device__ __forceinline__ void box_put(unsigned long long *w, unsigned tag, uns
     __hip_atomic_store(w, ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, const float v[3])
+__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, int c, float v)
 {
-#pragma unroll
-    for (int c = 0; c < 3; c++) box_put(w + c * cells, tag, __float_as_uint(v[c]));
+    box_put(w + c * cells, tag, __float_as_uint(v));
 }
 
-__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, const double v[3])
+__device__ __forceinline__ void box_store(unsigned long long *w, long long cells, unsigned tag, int c, double v)
 {
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v[c]);
-        box_put(w + 2 * c * cells, tag, (unsigned)b);
-        box_put(w + (2 * c + 1) * cells, tag, (unsigned)(b >> 32));
-    }
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    box_put(w + 2 * c * cells, tag, (unsigned)b);
+    box_put(w + (2 * c + 1) * cells, tag, (unsigned)(b >> 32));
 }
 
 __device__ __forceinline__ void box_value(const unsigned long long *v, int c, float &x) { x = __uint_as_float((unsigned)v[c]); }
@@ -583,13 +579,20 @@ __host__ __device__ inline bool resident2d_fits(int w, int h) { return (w + 4) *
 __device__ __forceinline__ void keep_narrow(float &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void keep_narrow(double &) {}
 
+// A thread has one or two cells of the five-point and cross levels; of a level with the full 21-cell
+// stencil, whose rows take 192 values, it has one of a cell's three rows, the cell's rows in adjacent
+// lanes (21 cells in 63 lanes of a wavefront), which hand each other their sums before D^{-1}.
+constexpr int kRes21Cells = kResNT / 64 * 21;    // cells a workgroup holds then
+
 // One smoothing phase of one level by the workgroups that share it; this one has tile (bi, bj).
 // HT: the type the rows are held in; EPT: cells per thread; SOLO: one workgroup has the whole
 // level (no halo, no mailbox).  lds: [3 kResPL] doubles; dead: set when a wait ran out.
 template <typename T, int NB, typename HT, int EPT, bool SOLO>
 __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, int bi, int bj, double *lds, int &dead)
 {
-    constexpr int C = NB == 9 ? 3 : 2, R = NB == 9 ? 2 : 1, NW = BoxWords<T>::n;
+    constexpr int C = NB == 21 ? 9 : (NB == 9 ? 3 : 2), R = NB == 5 ? 1 : 2, NW = BoxWords<T>::n;
+    constexpr int ROWS = NB == 21 ? 1 : 3;       // rows of a cell that a thread has
+    static_assert(ROWS == 3 || EPT == 1, "a row a thread");
     constexpr int KB = NW == 3 ? 3 : 2;          // halo cells whose words a thread has in flight
     typedef ResCell<T> Cell;
     Cell *const sz = (Cell *)lds;                // dU [rows + 4][ld]; the restriction's summands last
@@ -608,17 +611,25 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     if (t == 0 && !SOLO) dead = 0;
 
     // the thread's cells: the compute region colour by colour, row by row, without gaps (C rows in a
-    // row hold cw cells of every colour)
+    // row hold cw cells of every colour (i + j) mod C; the nine colours of the full stencil are the
+    // pairs (i mod 3, j mod 3))
     const int cw = ci1 - ci0, ch = cj1 - cj0;
     auto first = [&](int c, int jr) { return ((c - (ci0 + cj0 + jr)) % C + C) % C; };   // column in the region
-    int end[C];                                  // entries of colours 0 .. c
+    auto first3 = [](int c, int x0) { return x0 + (c + 3 - x0 % 3) % 3; };              // first x >= x0, x mod 3 = c
+    int end[C];                                  // cells of colours 0 .. c
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        int m = (ch / C) * cw;
-        for (int jr = ch - ch % C; jr < ch; jr++) m += (cw - first(c, jr) + C - 1) / C;
+        int m;
+        if constexpr (NB == 21) {
+            m = ((ci1 - first3(c % 3, ci0) + 2) / 3) * ((cj1 - first3(c / 3, cj0) + 2) / 3);
+        } else {
+            m = (ch / C) * cw;
+            for (int jr = ch - ch % C; jr < ch; jr++) m += (cw - first(c, jr) + C - 1) / C;
+        }
         end[c] = (c > 0 ? end[c - 1] : 0) + m;
     }
-    HT Jb[EPT][NB][9], Di[EPT][9], rh[EPT][3];
+    const int lane = t & 63, row = ROWS == 1 ? lane % 3 : 0;
+    HT Jb[EPT][NB][3 * ROWS], Di[EPT][3 * ROWS], rh[EPT][ROWS];
     // a cell's colour (-1: none), whether it is the tile's own and whether other tiles read it (the
     // registers are full: its place in the level is worked out from q where it is needed)
     int q[EPT], flags[EPT];
@@ -629,20 +640,28 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     auto cell_j = [&](int k) { return dj0 + q[k] / ld; };
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
-        const int e = k * kResNT + t;
+        const int e = ROWS == 1 ? (lane < 63 ? (t >> 6) * 21 + lane / 3 : 1 << 20) : k * kResNT + t;
         int c = 0, p = e;
 #pragma unroll
         for (int x = 0; x + 1 < C; x++)
             if (e >= end[x]) { c = x + 1; p = e - end[x]; }
         const bool valid = e < end[C - 1];
-        int jr = p / cw * C, rem = p % cw;
+        int i, j;
+        if constexpr (NB == 21) {
+            const int f = first3(c % 3, ci0), m = (ci1 - f + 2) / 3 > 0 ? (ci1 - f + 2) / 3 : 1;
+            i = f + 3 * (p % m);
+            j = first3(c / 3, cj0) + 3 * (p / m);
+        } else {
+            int jr = p / cw * C, rem = p % cw;
 #pragma unroll
-        for (int x = 0; x + 1 < C; x++) {
-            const int m = (cw - first(c, jr) + C - 1) / C;
-            if (rem >= m) { rem -= m; jr++; }
-            else break;
+            for (int x = 0; x + 1 < C; x++) {
+                const int m = (cw - first(c, jr) + C - 1) / C;
+                if (rem >= m) { rem -= m; jr++; }
+                else break;
+            }
+            i = ci0 + first(c, jr) + C * rem;
+            j = cj0 + jr;
         }
-        const int i = ci0 + first(c, jr) + C * rem, j = cj0 + jr;
         const bool own = valid && i >= i0 && i < i1 && j >= j0 && j < j1;
         const bool read = own && ((i0 > 0 && i - i0 < hd) || (i1 < nx && i1 - 1 - i < hd) || (j0 > 0 && j - j0 < hd) ||
                                   (j1 < ny && j1 - 1 - j < hd));
@@ -655,21 +674,21 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
                 const int pi = i + stencil_dx(NB, b), pj = j + stencil_dy(NB, b);
                 const bool ok = pi >= 0 && pi < nx && pj >= 0 && pj < ny;
 #pragma unroll
-                for (int x = 0; x < 9; x++) Jb[k][b][x] = ok ? (HT)mg[L.J + (b * 9 + x) * n + cc] : (HT)0.0;
+                for (int x = 0; x < 3 * ROWS; x++) Jb[k][b][x] = ok ? (HT)mg[L.J + (b * 9 + 3 * row + x) * n + cc] : (HT)0.0;
             }
 #pragma unroll
-            for (int x = 0; x < 9; x++) Di[k][x] = (HT)mg[L.Dinv + x * n + cc];
+            for (int x = 0; x < 3 * ROWS; x++) Di[k][x] = (HT)mg[L.Dinv + (3 * row + x) * n + cc];
 #pragma unroll
-            for (int x = 0; x < 3; x++) rh[k][x] = (HT)mg[L.rhs + x * n + cc];
+            for (int x = 0; x < ROWS; x++) rh[k][x] = (HT)mg[L.rhs + (row + x) * n + cc];
         } else {
 #pragma unroll
             for (int b = 1; b < NB; b++)
 #pragma unroll
-                for (int x = 0; x < 9; x++) Jb[k][b][x] = (HT)0.0;
+                for (int x = 0; x < 3 * ROWS; x++) Jb[k][b][x] = (HT)0.0;
 #pragma unroll
-            for (int x = 0; x < 9; x++) Di[k][x] = (HT)0.0;
+            for (int x = 0; x < 3 * ROWS; x++) Di[k][x] = (HT)0.0;
 #pragma unroll
-            for (int x = 0; x < 3; x++) rh[k][x] = (HT)0.0;
+            for (int x = 0; x < ROWS; x++) rh[k][x] = (HT)0.0;
         }
     }
 
@@ -690,9 +709,10 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
             j = j0 + r;
             i = s < left ? di0 + s : i1 + (s - left);
         }
-        // a pass moves information R cells along one axis: m passes read no cell farther out
+        // a pass of a cross stencil moves information R cells along one axis: m passes read no cell
+        // farther out (with the full stencil, every cell of the halo)
         const int ox = i < i0 ? i0 - i : (i >= i1 ? i - i1 + 1 : 0), oy = j < j0 ? j0 - j : (j >= j1 ? j - j1 + 1 : 0);
-        const bool read = e < nh && (ox + R - 1) / R + (oy + R - 1) / R <= A.m;
+        const bool read = e < nh && (NB == 21 || (ox + R - 1) / R + (oy + R - 1) / R <= A.m);
         hq[k] = read ? ((j - dj0) * ld + (i - di0)) | ((i + j) % C + 1) << 16 : 0;
         hcell[k] = read ? j * nx + i : 0;
     }
@@ -720,6 +740,9 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     const int runs = A.nu > 0 ? A.nu * 4 * (C - 1) + 1 : 0;
     unsigned tag = A.tag;
     const double keep = 1.0 - A.omega;
+    // one pass an exchange: only its colour's cells travel (not with nine colours, of which an edge
+    // between two tiles need not hold every one)
+    const bool filter = NB != 21 && A.m == 1;
     int since = 0;
     for (int s = 0; s < runs; s++) {
         const int ph = s % (2 * (C - 1));
@@ -729,49 +752,70 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         for (int k = 0; k < EPT; k++) {
             if (colour(k) != c) continue;
 #pragma unroll
-            for (int x = 0; x < 9; x++) {
+            for (int x = 0; x < 3 * ROWS; x++) {
 #pragma unroll
                 for (int b = 1; b < NB; b++) keep_narrow(Jb[k][b][x]);
                 keep_narrow(Di[k][x]);
             }
             // the values are read ahead of the products: a wavefront has its SIMD almost to itself, so
-            // a read's latency is paid once (the last blocks' of a nine-block row held in FP64, for which
-            // the registers do not suffice, behind the first products)
-            constexpr int B1 = NB == 9 && sizeof(HT) == 8 ? 6 : NB;
+            // a read's latency is paid once (or, where the registers do not suffice, partly behind the
+            // first products)
             Cell *u = su + q[k];
-            const Cell d = *u;
+            T d[ROWS];
+#pragma unroll
+            for (int x = 0; x < ROWS; x++) d[x] = u->v[row + x];
             Cell y[NB];
-            double r[3];
+            double r[ROWS];
 #pragma unroll
-            for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
-            auto read = [&](int b) { y[b] = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)]; };
-            auto add = [&](int b) {
-                const double x0 = (double)y[b].v[0], x1 = (double)y[b].v[1], x2 = (double)y[b].v[2];
+            for (int x = 0; x < ROWS; x++) r[x] = (double)rh[k][x];
+            auto read = [&](int b0, int b1) {
 #pragma unroll
-                for (int x = 0; x < 3; x++)
-                    r[x] = r[x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
-                                   (double)Jb[k][b][x * 3 + 2] * x2);
+                for (int b = b0; b <= b1; b++) y[b] = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)];
+                __builtin_amdgcn_sched_barrier(0);
             };
+            auto add = [&](int b0, int b1) {
 #pragma unroll
-            for (int b = 1; b < B1; b++) read(b);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (B1 < NB) {
-                add(1);
-                add(2);
-                add(3);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int b = b0; b <= b1; b++) {
+                    const double x0 = (double)y[b].v[0], x1 = (double)y[b].v[1], x2 = (double)y[b].v[2];
 #pragma unroll
-                for (int b = B1; b < NB; b++) read(b);
+                    for (int x = 0; x < ROWS; x++)
+                        r[x] = r[x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
+                                       (double)Jb[k][b][x * 3 + 2] * x2);
+                }
+            };
+            if constexpr (NB == 21) {
+                read(1, 10);
+                add(1, 5);
                 __builtin_amdgcn_sched_barrier(0);
+                read(11, 15);
+                add(6, 10);
+                __builtin_amdgcn_sched_barrier(0);
+                read(16, 20);
+                add(11, 20);
+            } else if constexpr (NB == 9 && sizeof(HT) == 8) {
+                read(1, 5);
+                add(1, 3);
+                __builtin_amdgcn_sched_barrier(0);
+                read(6, 8);
+                add(4, 8);
+            } else {
+                read(1, NB - 1);
+                add(1, NB - 1);
+            }
+            double f[3];
+            if constexpr (ROWS == 1) {
+#pragma unroll
+                for (int x = 0; x < 3; x++) f[x] = __shfl(r[0], lane - row + x, 64);
+            } else {
+#pragma unroll
+                for (int x = 0; x < 3; x++) f[x] = r[x];
             }
 #pragma unroll
-            for (int b = B1 < NB ? 4 : 1; b < NB; b++) add(b);
-#pragma unroll
-            for (int x = 0; x < 3; x++) {
-                const double tt = (double)Di[k][x * 3 + 0] * r[0] + (double)Di[k][x * 3 + 1] * r[1] + (double)Di[k][x * 3 + 2] * r[2];
-                const T d1 = (T)(keep * (double)d.v[x] - A.omega * tt);
+            for (int x = 0; x < ROWS; x++) {
+                const double tt = (double)Di[k][x * 3 + 0] * f[0] + (double)Di[k][x * 3 + 1] * f[1] + (double)Di[k][x * 3 + 2] * f[2];
+                const T d1 = (T)(keep * (double)d[x] - A.omega * tt);
                 const T d2 = (T)(keep * (double)d1 - A.omega * tt);
-                u->v[x] = twice ? d2 : d1;
+                u->v[row + x] = twice ? d2 : d1;
             }
         }
         if (SOLO) { __syncthreads(); continue; }
@@ -783,9 +827,12 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         unsigned long long *box = A.box + (long long)(tag & 1) * A.cells * NW;
 #pragma unroll
         for (int k = 0; k < EPT; k++)
-            if (edge(k) && (A.m > 1 || colour(k) == c)) {
-                const Cell own = su[q[k]];
-                box_store(box + (cell_j(k) * nx + cell_i(k)), A.cells, tag, own.v);
+            if (edge(k) && (!filter || colour(k) == c)) {
+                T own[ROWS];
+#pragma unroll
+                for (int x = 0; x < ROWS; x++) own[x] = su[q[k]].v[row + x];
+#pragma unroll
+                for (int x = 0; x < ROWS; x++) box_store(box + (cell_j(k) * nx + cell_i(k)), A.cells, tag, row + x, own[x]);
             }
         __syncthreads();     // every cell of the group is relaxed and read before the halo changes
         // the words of KB cells are loaded together, again until each cell's carry the tag
@@ -795,7 +842,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
             unsigned pend = 0;
 #pragma unroll
             for (int k = k0; k < k0 + KB && k < kResHalo; k++)
-                if (hq[k] && (A.m > 1 || hq[k] >> 16 == c + 1)) pend |= 1u << k;
+                if (hq[k] && (!filter || hq[k] >> 16 == c + 1)) pend |= 1u << k;
             if (dead) pend = 0;
             long long t0 = 0;
             for (int spin = 0; pend; spin++) {
@@ -834,12 +881,12 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         if (!inside(k)) continue;
         const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
 #pragma unroll
-        for (int c = 0; c < 3; c++) mg[L.dU + c * n + cc] = bad ? (T)__builtin_nan("") : su[q[k]].v[c];
+        for (int c = 0; c < ROWS; c++) mg[L.dU + (row + c) * n + cc] = bad ? (T)__builtin_nan("") : su[q[k]].v[row + c];
     }
     if (!A.restr) return;
     // eq. (24): rhs + J dU of every cell of the tile, then the sums over the children
     const int tw = i1 - i0;
-    double a[EPT][3];
+    double a[EPT][ROWS];
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
@@ -847,16 +894,16 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
         const double y0 = (double)u->v[0], y1 = (double)u->v[1], y2 = (double)u->v[2];
 #pragma unroll
-        for (int x = 0; x < 3; x++)
-            a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, (x * 3 + 0) * n + cc) * y0 +
-                                          ld2(mg + L.J, (x * 3 + 1) * n + cc) * y1 +
-                                          ld2(mg + L.J, (x * 3 + 2) * n + cc) * y2);
+        for (int x = 0; x < ROWS; x++)
+            a[k][x] = (double)rh[k][x] + (ld2(mg + L.J, ((row + x) * 3 + 0) * n + cc) * y0 +
+                                          ld2(mg + L.J, ((row + x) * 3 + 1) * n + cc) * y1 +
+                                          ld2(mg + L.J, ((row + x) * 3 + 2) * n + cc) * y2);
 #pragma unroll
         for (int b = 1; b < NB; b++) {
             const int o = stencil_dy(NB, b) * ld + stencil_dx(NB, b);
             const double x0 = (double)u[o].v[0], x1 = (double)u[o].v[1], x2 = (double)u[o].v[2];
 #pragma unroll
-            for (int x = 0; x < 3; x++)
+            for (int x = 0; x < ROWS; x++)
                 a[k][x] = a[k][x] + ((double)Jb[k][b][x * 3 + 0] * x0 + (double)Jb[k][b][x * 3 + 1] * x1 +
                                      (double)Jb[k][b][x * 3 + 2] * x2);
         }
@@ -867,7 +914,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
 #pragma unroll
-        for (int x = 0; x < 3; x++) sa[x * A.tx * A.ty + (cell_j(k) - j0) * tw + (cell_i(k) - i0)] = a[k][x];
+        for (int x = 0; x < ROWS; x++) sa[(row + x) * A.tx * A.ty + (cell_j(k) - j0) * tw + (cell_i(k) - i0)] = a[k][x];
     }
     __syncthreads();
     const int hw = tw / 2, hh = (j1 - j0) / 2;
@@ -1440,11 +1487,12 @@ hipError_t launch_smooth2d_pass(void *mg, const Level2D &L, int colour, int reps
 // Cells a workgroup of k_resident2d holds: 512 threads have 256 registers each, a row takes 84
 // values (nine blocks) or 48 (five points).  Rows are held in FP64, one a thread, or, narrow, two a
 // thread: nine-block rows of FP32 levels in FP32 (widened in every pass), five-point rows in FP64.
-static int resident2d_cells(int narrow) { return narrow ? 2 * kResNT : kResNT; }
+static int resident2d_cells(int nb, int narrow) { return nb == 21 ? kRes21Cells : (narrow ? 2 * kResNT : kResNT); }
 
 static const void *resident2d_kernel(int nb, int prec, int narrow)
 {
     const bool f32 = prec == NMG_FP32_MG;
+    if (nb == 21) return f32 ? (const void *)k_resident2d<float, 21, double, 1> : (const void *)k_resident2d<double, 21, double, 1>;
     if (nb == 9 && f32)
         return narrow ? (const void *)k_resident2d<float, 9, float, 2> : (const void *)k_resident2d<float, 9, double, 1>;
     if (nb == 9) return (const void *)k_resident2d<double, 9, double, 1>;
@@ -1461,12 +1509,12 @@ static const void *resident2d_kernel(int nb, int prec, int narrow)
 Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
 {
     Resident2D best;
-    if (L.nb != 9 && L.nb != 5) return best;
-    const int C = L.nb == 9 ? 3 : 2, R = L.nb == 9 ? 2 : 1;
+    if (L.nb != 21 && L.nb != 9 && L.nb != 5) return best;
+    const int C = L.P.C, R = L.nb == 5 ? 1 : 2;
     double cost = 1e30;
-    for (int narrow = 0; narrow <= (L.nb == 9 && prec != NMG_FP32_MG ? 0 : 1); narrow++) {
-        const int cap = resident2d_cells(narrow);
-        const double lat = 0.2, work = (L.nb == 9 ? 0.28 : 0.16) * (narrow ? 1.5 : 1.0);
+    for (int narrow = 0; narrow <= (L.nb == 21 || (L.nb == 9 && prec != NMG_FP32_MG) ? 0 : 1); narrow++) {
+        const int cap = resident2d_cells(L.nb, narrow);
+        const double lat = 0.2, work = (L.nb == 5 ? 0.16 : 0.28) * (narrow ? 1.5 : 1.0);
         for (int ty = 2; ty <= 32 && ty <= L.ny + 1; ty += 2)
             for (int tx = 4; tx <= 64 && tx <= L.nx + 3; tx += 4) {
                 const int gx = (L.nx + tx - 1) / tx, gy = (L.ny + ty - 1) / ty;
@@ -1501,6 +1549,8 @@ int resident2d_max_wg(int nb, int prec)
     return per > 0 ? cus : 0;
 }
 
+long long resident2d_max_cells(int nb) { return nb == 21 ? 256LL * kRes21Cells : 1LL << 18; }
+
 size_t resident2d_box_bytes(long long cells, int prec) { return (size_t)2 * cells * 8 * (prec == NMG_FP32_MG ? 3 : 6); }
 
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m) { return (unsigned)((nu * 4LL * (L.P.C - 1) + 1) / m + 2); }
@@ -1509,7 +1559,7 @@ hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, cons
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s)
 {
-    if (G.tx < 2 || L.P.C != (L.nb == 9 ? 3 : 2)) return hipErrorInvalidValue;
+    if (G.tx < 2 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
     Resident2DArgs A;
     A.L = L; A.Lc = Lc;
     A.tx = G.tx; A.ty = G.ty; A.gx = G.gx; A.m = G.m;

@@ -238,6 +238,9 @@ struct Resident2D {
 Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg);
 // workgroups of k_resident2d that can be resident at once on the current device (0: none)
 int resident2d_max_wg(int nb, int prec);
+// the largest level whose rows the registers of the whole chip could hold, by size alone (the device
+// is not asked when a workspace is sized)
+long long resident2d_max_cells(int nb);
 // bytes of the mailbox for levels of up to `cells` cells; exchanges a launch numbers
 size_t resident2d_box_bytes(long long cells, int prec);
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m);
