@@ -48,7 +48,9 @@ struct Plan2D {
     size_t total = 0;
     // resident levels (use_resident): the tiling of each launched level, tx = 0 where it has none
     std::vector<Resident2D> res;
-    long long box_cells = 0;   // cells of the largest level that may be resident
+    Resident2D stream;         // tiling of a finest level that is streamed (its order in memory, too)
+    bool streamed = false;     // it is in this call
+    long long box_cells = 0;   // cells of the largest level that may be resident or streamed
     bool resident = false;
     mutable unsigned tag = 0;  // exchanges numbered so far in this call
 };
@@ -161,6 +163,10 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
         L.nb = l == 0 ? d->jac : 5;
         // colours of the cross (3), the full stencil (9) or the five-point stencil (2)
         L.P = make_perm2d(L.nx, L.ny, l == 0 ? (d->jac == 21 ? 9 : 3) : 2);
+        if (l == 0 && P.levels > 1 && !P.sweeps) {
+            P.stream = streamed2d_plan(L, P.prec);
+            if (P.stream.tx > 0) L.P = make_perm2d_tiled(L.nx, L.ny, P.stream.tx, P.stream.ty);
+        }
         const long long n = L.P.M;
         L.J = e; e += (long long)L.nb * 9 * n;
         L.Dinv = e; e += 9 * n;
@@ -183,7 +189,7 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
     P.off_box = o;
     if (!P.sweeps)
         for (int l = 0; l < P.levels && P.box_cells == 0; l++)
-            if ((long long)P.L[l].nx * P.L[l].ny <= resident2d_max_cells(P.L[l].nb))
+            if ((l == 0 && P.stream.tx > 0) || (long long)P.L[l].nx * P.L[l].ny <= resident2d_max_cells(P.L[l].nb))
                 P.box_cells = (long long)P.L[l].nx * P.L[l].ny;
     o = al256(o + resident2d_box_bytes(P.box_cells, P.prec));
     P.total = o;
@@ -226,7 +232,7 @@ hipError_t clear_box(const Plan2D &P, char *ws, hipStream_t s)
 nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
 {
     P.res.assign(P.levels, Resident2D());
-    P.resident = false;
+    P.resident = P.streamed = false;
     set_bottom(P);
     if (P.box_cells == 0 || ws_bytes < P.total) return NMG_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -237,7 +243,12 @@ nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
     for (int l = 0; l < P.bottom_first; l++) {
         const Level2D &L = P.L[l];
         if ((long long)L.nx * L.ny > P.box_cells) continue;
-        P.res[l] = resident2d_plan(L, P.prec, resident2d_max_wg(L.nb, P.prec));
+        if (l == 0 && P.stream.tx > 0) {
+            P.streamed = streamed2d_max_wg(P.prec) >= P.stream.gx * P.stream.gy;
+            if (P.streamed) P.res[l] = P.stream;
+        } else {
+            P.res[l] = resident2d_plan(L, P.prec, resident2d_max_wg(L.nb, P.prec));
+        }
         if (P.res[l].tx > 0) P.resident = true;
     }
     if (P.L[0].nb == 21 && P.res[0].tx == 0) set_bottom(P);
@@ -249,7 +260,10 @@ nmg_status resident(const Plan2D &P, char *mgb, int l, int nu, int prolong, int 
 {
     const unsigned tag = P.tag;
     P.tag += resident2d_exchanges(P.L[l], nu, P.res[l].m);
-    HIP_TRY2(launch_resident2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
+    if (l == 0 && P.streamed)
+        HIP_TRY2(launch_streamed2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
+                                   mgb - P.off_mg + P.off_box, P.box_cells, S, P.prec, s));
+    else HIP_TRY2(launch_resident2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
                                mgb - P.off_mg + P.off_box, P.box_cells, S, P.prec, s));
     return NMG_OK;
 }

@@ -111,6 +111,19 @@ __global__ void __launch_bounds__(64) k_coarsen2d(T *mg, Level2D Lf, Level2D Lc)
     }
 }
 
+// cell (i, j) of slot p of a colour's block on a level in the tiled order; false: an empty slot
+__device__ __forceinline__ bool tiled_cell(const Level2D &L, int colour, long long p, int &i, int &j)
+{
+    const int tile = (int)(p / L.P.W), e = (int)(p - (long long)tile * L.P.W);
+    const int tj = tile / L.P.gx, i0 = (tile - tj * L.P.gx) * L.P.tw, j0 = tj * L.P.th;
+    const int w = L.nx - i0 < L.P.tw ? L.nx - i0 : L.P.tw, h = L.ny - j0 < L.P.th ? L.ny - j0 : L.P.th;
+    int il, jr;
+    tile3_cell(colour, i0, j0, w, e, il, jr);
+    i = i0 + il;
+    j = j0 + jr;
+    return jr < h && il < w;
+}
+
 // `reps` consecutive passes of eq. (22) over the cells of one colour on one level with the
 // NB-block stencil (C = 3 colours (i + j) mod 3 for the nine-block cross, 2 for five points, 9
 // colours (i mod 3) + 3 (j mod 3) for the full 21 cells), thread p taking slot p of that colour's
@@ -132,9 +145,14 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
     } else {
     constexpr int C = NB == 9 ? 3 : 2;
     const int W = L.P.W;
-    const int j = (int)(p / W), k = (int)(p - (long long)j * W);
-    const int i = ((colour - j) % C + C) % C + C * k;
-    if (i >= L.nx) return;
+    int i, j;
+    if (NB == 9 && L.P.tw > 0) {
+        if (!tiled_cell(L, colour, p, i, j)) return;
+    } else {
+        j = (int)(p / W);
+        i = ((colour - j) % C + C) % C + C * (int)(p - (long long)j * W);
+        if (i >= L.nx) return;
+    }
     const long long n = L.P.M, cc = (long long)colour * L.P.ny * W + p;
     const T *Jr = mg + L.J + cc;
     const T *Ur = mg + L.dU;
@@ -148,7 +166,9 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
         ok[b] = pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny;
         const int c2 = ((pi + pj) % C + C) % C;
         const int ic = ((c2 - pj) % C + C) % C;
-        const long long q = ok[b] ? (long long)c2 * L.ny * W + (long long)pj * W + (pi - ic) / C : cc;
+        const long long q = !ok[b] ? cc
+                            : NB == 9 && L.P.tw > 0 ? perm2d(L.P, pi, pj)
+                                                    : (long long)c2 * L.ny * W + (long long)pj * W + (pi - ic) / C;
 #pragma unroll
         for (int c = 0; c < 3; c++) x[b][c] = (double)Ur[c * n + q];
     }
@@ -256,9 +276,13 @@ __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level
     int i = 0, j = 0;
     if (valid) {
         const int jr = (int)(p / W), k = (int)(p - (long long)jr * W);
-        if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
-        else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
-        valid = i < L.nx && j < L.ny;
+        if (NB == 9 && L.P.tw > 0) {
+            valid = tiled_cell(L, colour, p, i, j);
+        } else {
+            if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
+            else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
+            valid = i < L.nx && j < L.ny;
+        }
     }
     const long long n = L.P.M, cc = (long long)colour * L.P.ny * W + p;
     double r = 0.0;
@@ -942,6 +966,325 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
     resident_level<T, NB, HT, EPT, false>(mg, A, blockIdx.x % A.gx, blockIdx.x / A.gx, lds, dead);
 }
 
+// ---- streamed smoothing of a level -----------------------------------------------------------
+
+// A cross-stencil level too large for the registers of the chip (1024 x 512 in FP64: 352 MB of rows, 172
+// MB of registers, of which rows can have two thirds) runs its phases in one cooperative launch too, a
+// tile per compute unit with dU in LDS and the same exchange after every pass, and part of its rows
+// held: in registers (one FP64 or two FP32 rows a thread) and kLdsRows in LDS.  The symmetric schedule
+// passes over colour 1 every other time and over colours 0 and 2 every fourth, so colour 1 is held
+// first, after as many cells of colours 0 and 2 as leave each of them one streamed cell a thread.  The
+// rest is streamed in every pass, contiguously (tiled order), and that is the bound: about 7.6 TB/s
+// from the memory-side cache, which the streamed part fits (235 MB; all rows: 6.1-6.6 TB/s).
+// 1024 x 512 FP64: 25.8 us a pass as separate launches, 0 so; FP32 13.6, 0.
+constexpr int kStrCells = 2600;                  // LDS cells of a tile with a ring of two
+constexpr int kLdsRows = 128;                    // colour 1 rows held in LDS
+constexpr int kRowValues = 84;                   // eight off-diagonal blocks, D^{-1}, right-hand side
+
+// how many of a colour's n[c] cells the registers hold (cap rows in all) and, of colour 1, LDS
+__device__ __forceinline__ void streamed_split(const int n[3], int cap, int held[3], int &in_lds)
+{
+    held[0] = n[0] > kResNT ? n[0] - kResNT : 0;
+    held[2] = n[2] > kResNT ? n[2] - kResNT : 0;
+    if (held[0] + held[2] > cap) held[0] = held[2] = 0;
+    int left = cap - held[0] - held[2];
+    held[1] = n[1] < left ? n[1] : left;
+    left -= held[1];
+    in_lds = n[1] - held[1] < kLdsRows ? n[1] - held[1] : kLdsRows;
+    const int more0 = n[0] - held[0] < left / 2 ? n[0] - held[0] : left / 2;
+    held[0] += more0;
+    left -= more0;
+    held[2] += n[2] - held[2] < left ? n[2] - held[2] : left;
+}
+
+template <typename T, int EPT>
+__global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
+{
+    constexpr int NB = 9, C = 3, NW = BoxWords<T>::n;
+    constexpr int AHEAD = sizeof(T) == 8 ? 1 : 3;          // blocks of a streamed row on their way
+    typedef ResCell<T> Cell;
+    __shared__ Cell sz[kStrCells];
+    __shared__ double rows_lds[kLdsRows * kRowValues * sizeof(T) / 8 > 3 * kStrCells ? kLdsRows * kRowValues * sizeof(T) / 8
+                                                                                     : 3 * kStrCells];
+    __shared__ int dead;
+    if (A.state && !A.state->active) return;     // the same for every workgroup
+    T *const rows = (T *)rows_lds;               // [kRowValues][kLdsRows]
+    const Level2D &L = A.L;
+    const int t = threadIdx.x, nx = L.nx, ny = L.ny;
+    const int bi = blockIdx.x % A.gx, bj = blockIdx.x / A.gx;
+    const int i0 = bi * A.tx, j0 = bj * A.ty;
+    const int i1 = i0 + A.tx < nx ? i0 + A.tx : nx, j1 = j0 + A.ty < ny ? j0 + A.ty : ny;
+    const int tw = i1 - i0, th = j1 - j0, ld = tw + 4;
+    Cell *const su = sz + 2 * ld + 2;            // cell (i0, j0); the halo's place is there at a side, too, as zeros
+    const long long n = L.P.M;
+    if (t == 0) dead = 0;
+
+    int cells[C], held[C], in_lds;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        cells[c] = th / 3 * tw;
+        for (int jr = th - th % 3; jr < th; jr++) cells[c] += (tw - tile3_first(c, i0, j0, jr) + 2) / 3;
+    }
+    streamed_split(cells, EPT * kResNT, held, in_lds);
+    // place in LDS of cell e of colour c, with bit 16 set where other tiles read it
+    auto place = [&](int c, int e) {
+        int il, jr;
+        tile3_cell(c, i0, j0, tw, e, il, jr);
+        const bool read = (i0 > 0 && il < 2) || (i1 < nx && tw - 1 - il < 2) || (j0 > 0 && jr < 2) || (j1 < ny && th - 1 - jr < 2);
+        return (jr * ld + il) | (read ? 1 << 16 : 0);
+    };
+    auto slot_of = [&](int c, int e) { return ((long long)c * L.P.ny + bj * A.gx + bi) * L.P.W + e; };
+
+    // rows in registers: the slots k * 512 + t take colour 1's cells, then colour 0's, then colour 2's
+    T Jb[EPT][NB][9], Di[EPT][9], rh[EPT][3];
+    int q[EPT], col[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+        const int r = k * kResNT + t;
+        int c = 1, e = r;
+        if (e >= held[1]) { c = 0; e -= held[1]; if (e >= held[0]) { c = 2; e -= held[0]; } }
+        const bool valid = e < held[c];
+        col[k] = valid ? c : -1;
+        q[k] = valid ? place(c, e) : 0;
+        const long long cc = valid ? slot_of(c, e) : 0;
+#pragma unroll
+        for (int b = 1; b < NB; b++)
+#pragma unroll
+            for (int x = 0; x < 9; x++) Jb[k][b][x] = valid ? mg[L.J + (b * 9 + x) * n + cc] : (T)0;
+#pragma unroll
+        for (int x = 0; x < 9; x++) Di[k][x] = valid ? mg[L.Dinv + x * n + cc] : (T)0;
+#pragma unroll
+        for (int x = 0; x < 3; x++) rh[k][x] = valid ? mg[L.rhs + x * n + cc] : (T)0;
+    }
+    for (int e = t; e < in_lds * kRowValues; e += kResNT) {
+        const int v = e / in_lds, r = e - v * in_lds;
+        const long long cc = slot_of(1, held[1] + r);
+        rows[v * kLdsRows + r] = v < 72 ? mg[L.J + (v + 9) * n + cc] : (v < 81 ? mg[L.Dinv + (v - 72) * n + cc] : mg[L.rhs + (v - 81) * n + cc]);
+    }
+    // the thread's first streamed cell of each colour, and its row in LDS (the last threads', which
+    // have no streamed cell of colour 1 while there are few)
+    int sq[C], start[C];
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        start[c] = held[c] + (c == 1 ? in_lds : 0);
+        sq[c] = start[c] + t < cells[c] ? place(c, start[c] + t) : 0;
+    }
+    const int lr = kResNT - 1 - t;
+    const int lq = lr < in_lds ? place(1, held[1] + lr) : 0;
+
+    // the halo cell the thread fetches (at most 512: 2 x 2 rows and columns): place | colour + 1 << 16
+    int hq = 0, hcell = 0;
+    {
+        const int dj0 = j0 - 2 > 0 ? j0 - 2 : 0, dj1 = j1 + 2 < ny ? j1 + 2 : ny;
+        const int di0 = i0 - 2 > 0 ? i0 - 2 : 0, di1 = i1 + 2 < nx ? i1 + 2 : nx;
+        const int below = j0 - dj0, above = dj1 - j1, left = i0 - di0, side = left + (di1 - i1);
+        int i = -1, j = -1;
+        if (t < (below + above) * tw) {
+            const int r = t / tw;
+            i = i0 + t - r * tw;
+            j = r < below ? dj0 + r : j1 + (r - below);
+        } else if (t < (below + above) * tw + th * side) {
+            const int f = t - (below + above) * tw, r = f / side, x = f - r * side;
+            j = j0 + r;
+            i = x < left ? di0 + x : i1 + (x - left);
+        }
+        if (i >= 0) {
+            hq = ((j - j0 + 2) * ld + (i - i0 + 2)) | ((i + j) % C + 1) << 16;
+            hcell = j * nx + i;
+        }
+    }
+
+    for (int e = t; e < (tw + 4) * (th + 4); e += kResNT) {
+        const int r = e / ld, i = i0 - 2 + e - r * ld, j = j0 - 2 + r;
+        Cell v = Cell{};
+        if (i >= 0 && i < nx && j >= 0 && j < ny) {
+            const long long fc = perm2d(L.P, i, j);
+            const long long pc = A.prolong ? perm2d(A.Lc.P, i >> 1, j >> 1) : 0;
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                v.v[c] = mg[L.dU + c * n + fc];
+                if (A.prolong) v.v[c] = (T)((double)v.v[c] + ld2(mg + A.Lc.dU, c * A.Lc.P.M + pc));
+            }
+        }
+        sz[e] = v;
+    }
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+
+    const int runs = A.nu > 0 ? A.nu * 4 * (C - 1) + 1 : 0;
+    const double keep = 1.0 - A.omega;
+    unsigned tag = A.tag;
+    for (int s = 0; s < runs; s++) {
+        const int ph = s % (2 * (C - 1));
+        const int c = ph <= C - 1 ? ph : 2 * (C - 1) - ph;
+        const bool twice = (c == 0 || c == C - 1) && s > 0 && s < runs - 1, send = s < runs - 1 || A.restr;
+        if (send) tag++;
+        unsigned long long *box = A.box + (long long)(tag & 1) * A.cells * NW;
+        // relax the cell at place p from its off-diagonal sum r and its D^{-1}, and publish it
+        auto relax = [&](int p, const double r[3], const T *D) {
+            Cell *u = su + (p & 0xffff);
+            T v[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const double tt = (double)D[x * 3 + 0] * r[0] + (double)D[x * 3 + 1] * r[1] + (double)D[x * 3 + 2] * r[2];
+                const T d1 = (T)(keep * (double)u->v[x] - A.omega * tt);
+                const T d2 = (T)(keep * (double)d1 - A.omega * tt);
+                v[x] = twice ? d2 : d1;
+                u->v[x] = v[x];
+            }
+            if (send && p >> 16) {
+                const int il = (p & 0xffff) % ld, jr = (p & 0xffff) / ld;
+#pragma unroll
+                for (int x = 0; x < 3; x++) box_store(box + ((j0 + jr) * nx + i0 + il), A.cells, tag, x, v[x]);
+            }
+        };
+        auto add = [&](double r[3], const Cell &y, const T *J) {
+            const double x0 = (double)y.v[0], x1 = (double)y.v[1], x2 = (double)y.v[2];
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = r[x] + ((double)J[x * 3 + 0] * x0 + (double)J[x * 3 + 1] * x1 + (double)J[x * 3 + 2] * x2);
+        };
+        // a row read from memory (stride n) in this pass
+        for (int e = start[c] + t, first = 1; e < cells[c]; e += kResNT, first = 0) {
+            const int p = first ? sq[c] : place(c, e);
+            const long long cc = slot_of(c, e);
+            const Cell *u = su + (p & 0xffff);
+            const T *Jr = mg + L.J + cc;
+            T v[AHEAD + 1][9], D[9];
+            double r[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = (double)mg[L.rhs + x * n + cc];
+#pragma unroll
+            for (int b = 1; b <= AHEAD; b++)
+#pragma unroll
+                for (int x = 0; x < 9; x++) v[b % (AHEAD + 1)][x] = Jr[(b * 9 + x) * n];
+#pragma unroll
+            for (int b = 1; b < NB; b++) {
+                const int g = b + AHEAD;
+                if (g < NB) {
+#pragma unroll
+                    for (int x = 0; x < 9; x++) v[g % (AHEAD + 1)][x] = Jr[(g * 9 + x) * n];
+                } else if (g == NB) {
+#pragma unroll
+                    for (int x = 0; x < 9; x++) D[x] = mg[L.Dinv + x * n + cc];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], v[b % (AHEAD + 1)]);
+            }
+            relax(p, r, D);
+        }
+#pragma unroll
+        for (int k = 0; k < EPT; k++) {
+            if (col[k] != c) continue;
+#pragma unroll
+            for (int x = 0; x < 9; x++) {
+#pragma unroll
+                for (int b = 1; b < NB; b++) keep_narrow(Jb[k][b][x]);
+                keep_narrow(Di[k][x]);
+            }
+            const Cell *u = su + (q[k] & 0xffff);
+            double r[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
+#pragma unroll
+            for (int b = 1; b < NB; b++) add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], Jb[k][b]);
+            relax(q[k], r, Di[k]);
+        }
+        if (c == 1 && lr < in_lds) {
+            const Cell *u = su + (lq & 0xffff);
+            double r[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = (double)rows[(81 + x) * kLdsRows + lr];
+            T D[9];
+#pragma unroll
+            for (int b = 1; b < NB; b++) {
+                T J[9];
+#pragma unroll
+                for (int x = 0; x < 9; x++) J[x] = rows[((b - 1) * 9 + x) * kLdsRows + lr];
+                add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], J);
+            }
+#pragma unroll
+            for (int x = 0; x < 9; x++) D[x] = rows[(72 + x) * kLdsRows + lr];
+            relax(lq, r, D);
+        }
+        if (!send) break;
+        __syncthreads();
+        if (hq >> 16 == c + 1 && !dead) {
+            long long t0 = 0;
+            for (int spin = 0;; spin++) {
+                unsigned long long v[NW];
+                bool ok = true;
+#pragma unroll
+                for (int w = 0; w < NW; w++) v[w] = __hip_atomic_load(box + hcell + w * A.cells, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int w = 0; w < NW; w++) ok = ok && (unsigned)(v[w] >> 32) == tag;
+                if (ok) {
+#pragma unroll
+                    for (int x = 0; x < 3; x++) box_value(v, x, sz[hq & 0xffff].v[x]);
+                    break;
+                }
+                if ((spin & 255) == 255) {
+                    const long long now = wall_clock64();
+                    if (t0 == 0) t0 = now;
+                    else if (now - t0 > kWaitTicks) { dead = 1; break; }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    const bool bad = dead != 0;
+
+    // dU of the tile's cells and, for eq. (24), rhs + J dU (rows read from memory once more)
+    double *sa = rows_lds;                       // [3][tile cells]
+#pragma unroll 1
+    for (int c = 0; c < C; c++)
+        for (int e = t; e < cells[c]; e += kResNT) {
+            const int p = place(c, e) & 0xffff, il = p % ld, jr = p / ld;
+            const long long cc = slot_of(c, e);
+            const Cell *u = su + p;
+#pragma unroll
+            for (int x = 0; x < 3; x++) mg[L.dU + x * n + cc] = bad ? (T)__builtin_nan("") : u->v[x];
+            if (!A.restr) continue;
+            double a[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) a[x] = (double)mg[L.rhs + x * n + cc];
+            T v[2][9];
+#pragma unroll
+            for (int x = 0; x < 9; x++) v[0][x] = mg[L.J + x * n + cc];
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                if (b + 1 < NB) {
+#pragma unroll
+                    for (int x = 0; x < 9; x++) v[(b + 1) & 1][x] = mg[L.J + ((b + 1) * 9 + x) * n + cc];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const Cell y = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)];
+                const double x0 = (double)y.v[0], x1 = (double)y.v[1], x2 = (double)y.v[2];
+#pragma unroll
+                for (int x = 0; x < 3; x++)
+                    a[x] = a[x] + ((double)v[b & 1][x * 3 + 0] * x0 + (double)v[b & 1][x * 3 + 1] * x1 + (double)v[b & 1][x * 3 + 2] * x2);
+            }
+#pragma unroll
+            for (int x = 0; x < 3; x++) sa[x * tw * th + jr * tw + il] = a[x];
+        }
+    if (!A.restr) return;
+    __syncthreads();
+    const int hw = tw / 2, hh = th / 2;
+    for (int e = t; e < hw * hh; e += kResNT) {
+        const int jq = e / hw, iq = e - jq * hw;
+        double a00[3], a10[3], a01[3], a11[3];
+#pragma unroll
+        for (int x = 0; x < 3; x++) {
+            const double *p = sa + x * tw * th + 2 * jq * tw + 2 * iq;
+            a00[x] = p[0];
+            a10[x] = p[1];
+            a01[x] = p[tw];
+            a11[x] = p[tw + 1];
+        }
+        restrict_store(mg, A.Lc, i0 / 2 + iq, j0 / 2 + jq, a00, a10, a01, a11);
+    }
+}
+
 // Coarsest level: Gaussian elimination with partial pivoting of the dense system sum J dU = -rhs
 // (unknown (j*nx + i)*3 + c), split into a factorisation done once per operator and a solve per
 // V-cycle.  The factorisation takes the pivots and eliminates exactly as the plain algorithm does
@@ -1539,15 +1882,18 @@ Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
     return best;
 }
 
-int resident2d_max_wg(int nb, int prec)
+// workgroups of the kernel that can be resident at once on the current device: one a compute unit
+static int cooperative_max_wg(const void *kernel)
 {
     int dev = 0, cus = 0, per = 0, coop = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, resident2d_kernel(nb, prec, 0), kResNT, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kResNT, 0) != hipSuccess) return 0;
     return per > 0 ? cus : 0;
 }
+
+int resident2d_max_wg(int nb, int prec) { return cooperative_max_wg(resident2d_kernel(nb, prec, 0)); }
 
 long long resident2d_max_cells(int nb) { return nb == 21 ? 256LL * kRes21Cells : 1LL << 18; }
 
@@ -1555,11 +1901,9 @@ size_t resident2d_box_bytes(long long cells, int prec) { return (size_t)2 * cell
 
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m) { return (unsigned)((nu * 4LL * (L.P.C - 1) + 1) / m + 2); }
 
-hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
-                             int restr, unsigned tag, double omega, void *box, long long cells,
-                             const NewtonState *state, int prec, hipStream_t s)
+static Resident2DArgs resident_args(const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong, int restr,
+                                    unsigned tag, double omega, void *box, long long cells, const NewtonState *state)
 {
-    if (G.tx < 2 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
     Resident2DArgs A;
     A.L = L; A.Lc = Lc;
     A.tx = G.tx; A.ty = G.ty; A.gx = G.gx; A.m = G.m;
@@ -1568,8 +1912,53 @@ hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, cons
     A.box = (unsigned long long *)box;
     A.cells = cells;
     A.state = state;
+    return A;
+}
+
+hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
+                             int restr, unsigned tag, double omega, void *box, long long cells,
+                             const NewtonState *state, int prec, hipStream_t s)
+{
+    if (G.tx < 2 || L.P.tw > 0 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
+    Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
     void *args[] = {&mg, &A};
     return hipLaunchCooperativeKernel(resident2d_kernel(L.nb, prec, G.narrow), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
+}
+
+Resident2D streamed2d_plan(const Level2D &L, int prec)
+{
+    Resident2D best;
+    if (L.nb != 9 || L.nx % 2 || L.ny % 2 || resident2d_plan(L, prec, 256).tx > 0) return best;
+    // the tiling of at most 256 workgroups with the fewest cells a tile; at equal cells the squarest, whose halo is smallest
+    long long cost = 1LL << 60;
+    for (int ty = 4; ty <= 64 && ty <= L.ny + 1; ty += 2)
+        for (int tx = 16; tx <= 96 && tx <= L.nx + 1; tx += 2) {
+            const int gx = (L.nx + tx - 1) / tx, gy = (L.ny + ty - 1) / ty;
+            if (gx * gy > 256 || (tx + 4) * (ty + 4) > kStrCells || 4 * (tx + ty) > kResNT) continue;
+            const long long t = (long long)tx * ty * 1024 + 4 * (tx + ty);
+            if (t < cost) {
+                cost = t;
+                best.tx = tx; best.ty = ty; best.gx = gx; best.gy = gy; best.m = 1;
+            }
+        }
+    return best;
+}
+
+static const void *streamed2d_kernel(int prec)
+{
+    return prec == NMG_FP32_MG ? (const void *)k_streamed2d<float, 2> : (const void *)k_streamed2d<double, 1>;
+}
+
+int streamed2d_max_wg(int prec) { return cooperative_max_wg(streamed2d_kernel(prec)); }
+
+hipError_t launch_streamed2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
+                             int restr, unsigned tag, double omega, void *box, long long cells,
+                             const NewtonState *state, int prec, hipStream_t s)
+{
+    if (G.tx < 2 || L.P.tw != G.tx || L.P.th != G.ty || L.P.gx != G.gx) return hipErrorInvalidValue;
+    Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
+    void *args[] = {&mg, &A};
+    return hipLaunchCooperativeKernel(streamed2d_kernel(prec), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
 }
 
 hipError_t launch_restrict2d(void *mg, const Level2D &Lf, const Level2D &Lc, int prec, hipStream_t s)

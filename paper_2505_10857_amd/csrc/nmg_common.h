@@ -120,15 +120,48 @@ struct Inst2D {
 // colour c in row j and W = ceil(nx / C) slots per row and colour.  C = 9 (the full 21-cell
 // stencil): colour c = (i mod 3) + 3 (j mod 3), cell (i, j) at c*ceil(ny/3)*W + (j/3)*W + i/3 with
 // W = ceil(nx / 3).  C = 1 is the natural order j*nx + i.
+// Tiled order (tw > 0, C = 3): a colour's cells lie together tile by tile (tiles of tw x th cells, gx in
+// a row, W = ceil(tw th / 3) slots per tile and colour, ny = the number of tiles), within a tile row
+// by row without gaps, so that a workgroup that streams its tile's rows reads them contiguously.
 struct Perm2D {
     int C, W, ny, pad;  // ny: rows per colour (ny of the level, ceil(ny / 3) when C = 9)
     long long M;       // slots per array: C * ny * W
+    int tw, th, gx, nx;
 };
+
+// Cells of one colour in a tile of w columns whose first cell is (i0, j0), C = 3: three rows in a row
+// hold w of them.  tile3_first: the first column (from i0) of colour c in row jr (from j0);
+// tile3_pos: the place of the cell (il, jr) among its colour's cells.
+__host__ __device__ inline int tile3_first(int c, int i0, int j0, int jr) { return ((c - (i0 + j0 + jr)) % 3 + 3) % 3; }
+__host__ __device__ inline int tile3_pos(int c, int i0, int j0, int w, int il, int jr)
+{
+    int pos = jr / 3 * w;
+    for (int r = jr - jr % 3; r < jr; r++) pos += (w - tile3_first(c, i0, j0, r) + 2) / 3;
+    return pos + (il - tile3_first(c, i0, j0, jr)) / 3;
+}
+// the cell at place p of colour c (the inverse); jr past the tile's last row when there is none
+__host__ __device__ inline void tile3_cell(int c, int i0, int j0, int w, int p, int &il, int &jr)
+{
+    jr = p / w * 3;
+    int rem = p % w;
+    for (int x = 0; x < 2; x++) {
+        const int m = (w - tile3_first(c, i0, j0, jr) + 2) / 3;
+        if (rem < m) break;
+        rem -= m;
+        jr++;
+    }
+    il = tile3_first(c, i0, j0, jr) + 3 * rem;
+}
 
 __host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
 {
     if (P.C == 9) return (long long)(i % 3 + 3 * (j % 3)) * P.ny * P.W + (long long)(j / 3) * P.W + i / 3;
     const int c = (i + j) % P.C;
+    if (P.tw > 0) {
+        const int ti = i / P.tw, tj = j / P.th, i0 = ti * P.tw, j0 = tj * P.th;
+        const int w = P.nx - i0 < P.tw ? P.nx - i0 : P.tw;
+        return ((long long)c * P.ny + tj * P.gx + ti) * P.W + tile3_pos(c, i0, j0, w, i - i0, j - j0);
+    }
     const int ic = ((c - j) % P.C + P.C) % P.C;
     return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
 }
@@ -141,6 +174,23 @@ inline Perm2D make_perm2d(int nx, int ny, int C)
     P.ny = C == 9 ? (ny + 2) / 3 : ny;
     P.pad = 0;
     P.M = (long long)C * P.ny * P.W;
+    P.tw = P.th = P.gx = 0;
+    P.nx = nx;
+    return P;
+}
+
+inline Perm2D make_perm2d_tiled(int nx, int ny, int tw, int th)
+{
+    Perm2D P;
+    P.C = 3;
+    P.W = (tw * th + 2) / 3;
+    P.gx = (nx + tw - 1) / tw;
+    P.ny = P.gx * ((ny + th - 1) / th);
+    P.pad = 0;
+    P.M = 3LL * P.ny * P.W;
+    P.tw = tw;
+    P.th = th;
+    P.nx = nx;
     return P;
 }
 
@@ -238,6 +288,14 @@ struct Resident2D {
 Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg);
 // workgroups of k_resident2d that can be resident at once on the current device (0: none)
 int resident2d_max_wg(int nb, int prec);
+// A cross-stencil level whose rows the registers of the chip do not hold all: the tiles of
+// launch_streamed2d (by size alone; tx = 0: the level is resident, or too large for it).  Such a level
+// is stored in the tiled order.
+Resident2D streamed2d_plan(const Level2D &L, int prec);
+int streamed2d_max_wg(int prec);
+hipError_t launch_streamed2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
+                             int restr, unsigned tag, double omega, void *box, long long cells,
+                             const NewtonState *state, int prec, hipStream_t s);
 // the largest level whose rows the registers of the whole chip could hold, by size alone (the device
 // is not asked when a workspace is sized)
 long long resident2d_max_cells(int nb);
