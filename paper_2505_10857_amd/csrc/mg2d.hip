@@ -978,7 +978,7 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 // from the memory-side cache, which the streamed part fits (235 MB; all rows: 6.1-6.6 TB/s).
 // 1024 x 512 FP64: 25.8 us a pass as separate launches, 0 so; FP32 13.6, 0.
 constexpr int kStrCells = 2600;                  // LDS cells of a tile with a ring of two
-constexpr int kLdsRows = 128;                    // colour 1 rows held in LDS
+constexpr int kLdsRows = 64;                     // colour 1 rows held in LDS
 constexpr int kRowValues = 84;                   // eight off-diagonal blocks, D^{-1}, right-hand side
 
 // how many of a colour's n[c] cells the registers hold (cap rows in all) and, of colour 1, LDS
@@ -1001,14 +1001,18 @@ template <typename T, int EPT>
 __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
 {
     constexpr int NB = 9, C = 3, NW = BoxWords<T>::n;
-    constexpr int AHEAD = sizeof(T) == 8 ? 1 : 3;          // blocks of a streamed row on their way
+    constexpr int RING = sizeof(T) == 8 ? 5 : 9;           // triples of a streamed row that registers hold
     typedef ResCell<T> Cell;
     __shared__ Cell sz[kStrCells];
-    __shared__ double rows_lds[kLdsRows * kRowValues * sizeof(T) / 8 > 3 * kStrCells ? kLdsRows * kRowValues * sizeof(T) / 8
-                                                                                     : 3 * kStrCells];
+    // rows in LDS, and for FP64 rows in registers their D^{-1} and right-hand sides (with them the rows
+    // themselves would not stay in registers; read from memory, they are late while the rest streams)
+    constexpr bool HOLD = sizeof(T) == 4;
+    constexpr int POOL = kLdsRows * kRowValues + (HOLD ? 0 : 12 * kResNT);
+    __shared__ double rows_lds[POOL > 3 * kStrCells ? POOL : 3 * kStrCells];
     __shared__ int dead;
     if (A.state && !A.state->active) return;     // the same for every workgroup
     T *const rows = (T *)rows_lds;               // [kRowValues][kLdsRows]
+    T *const dr = rows + kLdsRows * kRowValues;  // [12][512]
     const Level2D &L = A.L;
     const int t = threadIdx.x, nx = L.nx, ny = L.ny;
     const int bi = blockIdx.x % A.gx, bj = blockIdx.x / A.gx;
@@ -1026,18 +1030,26 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         for (int jr = th - th % 3; jr < th; jr++) cells[c] += (tw - tile3_first(c, i0, j0, jr) + 2) / 3;
     }
     streamed_split(cells, EPT * kResNT, held, in_lds);
-    // place in LDS of cell e of colour c, with bit 16 set where other tiles read it
+    // place in LDS of cell e of colour c, with bit 16 set where other tiles read it and bit 16 + b where
+    // its neighbour of block b lies outside the grid
     auto place = [&](int c, int e) {
         int il, jr;
         tile3_cell(c, i0, j0, tw, e, il, jr);
         const bool read = (i0 > 0 && il < 2) || (i1 < nx && tw - 1 - il < 2) || (j0 > 0 && jr < 2) || (j1 < ny && th - 1 - jr < 2);
-        return (jr * ld + il) | (read ? 1 << 16 : 0);
+        int p = (jr * ld + il) | (read ? 1 << 16 : 0);
+#pragma unroll
+        for (int b = 1; b < NB; b++) {
+            const int pi = i0 + il + stencil_dx(NB, b), pj = j0 + jr + stencil_dy(NB, b);
+            if (pi < 0 || pi >= nx || pj < 0 || pj >= ny) p |= 1 << (16 + b);
+        }
+        return p;
     };
     auto slot_of = [&](int c, int e) { return ((long long)c * L.P.ny + bj * A.gx + bi) * L.P.W + e; };
 
     // rows in registers: the slots k * 512 + t take colour 1's cells, then colour 0's, then colour 2's
-    T Jb[EPT][NB][9], Di[EPT][9], rh[EPT][3];
+    T Jb[EPT][NB][9], Di[HOLD ? EPT : 1][9], rh[HOLD ? EPT : 1][3];
     int q[EPT], col[EPT];
+    unsigned own_off[EPT];                       // byte offset of the cell in the level's arrays
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         const int r = k * kResNT + t;
@@ -1046,20 +1058,13 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         const bool valid = e < held[c];
         col[k] = valid ? c : -1;
         q[k] = valid ? place(c, e) : 0;
-        const long long cc = valid ? slot_of(c, e) : 0;
-#pragma unroll
-        for (int b = 1; b < NB; b++)
-#pragma unroll
-            for (int x = 0; x < 9; x++) Jb[k][b][x] = valid ? mg[L.J + (b * 9 + x) * n + cc] : (T)0;
-#pragma unroll
-        for (int x = 0; x < 9; x++) Di[k][x] = valid ? mg[L.Dinv + x * n + cc] : (T)0;
-#pragma unroll
-        for (int x = 0; x < 3; x++) rh[k][x] = valid ? mg[L.rhs + x * n + cc] : (T)0;
+        own_off[k] = valid ? (unsigned)(slot_of(c, e) * (int)sizeof(T)) : 0;
     }
     for (int e = t; e < in_lds * kRowValues; e += kResNT) {
         const int v = e / in_lds, r = e - v * in_lds;
         const long long cc = slot_of(1, held[1] + r);
-        rows[v * kLdsRows + r] = v < 72 ? mg[L.J + (v + 9) * n + cc] : (v < 81 ? mg[L.Dinv + (v - 72) * n + cc] : mg[L.rhs + (v - 81) * n + cc]);
+        const bool out = v < 72 && (place(1, held[1] + r) >> (17 + v / 9) & 1);
+        rows[v * kLdsRows + r] = out ? (T)0 : v < 72 ? mg[L.J + (v + 9) * n + cc] : (v < 81 ? mg[L.Dinv + (v - 72) * n + cc] : mg[L.rhs + (v - 81) * n + cc]);
     }
     // the thread's first streamed cell of each colour, and its row in LDS (the last threads', which
     // have no streamed cell of colour 1 while there are few)
@@ -1108,6 +1113,32 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         }
         sz[e] = v;
     }
+    // value v of the arrays at `base` for the slot at byte offset `off` (the base and the stride are
+    // uniform: no address registers)
+    auto fetch = [&](long long base, int v, unsigned off) {
+        return *(const T *)((const char *)(mg + base + v * n) + off);
+    };
+#pragma unroll
+    for (int k = 0; k < EPT; k++) {
+#pragma unroll
+        for (int b = 1; b < NB; b++)
+#pragma unroll
+            for (int x = 0; x < 9; x++) {
+                const T v = fetch(L.J, b * 9 + x, own_off[k]);
+                Jb[k][b][x] = q[k] >> (16 + b) & 1 ? (T)0 : v;
+            }
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int x = 0; x < 9; x++) Di[k][x] = fetch(L.Dinv, x, own_off[k]);
+#pragma unroll
+            for (int x = 0; x < 3; x++) rh[k][x] = fetch(L.rhs, x, own_off[k]);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 9; x++) dr[x * kResNT + t] = fetch(L.Dinv, x, own_off[k]);
+#pragma unroll
+            for (int x = 0; x < 3; x++) dr[(9 + x) * kResNT + t] = fetch(L.rhs, x, own_off[k]);
+        }
+    }
     __syncthreads();
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
 
@@ -1120,58 +1151,32 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         const bool twice = (c == 0 || c == C - 1) && s > 0 && s < runs - 1, send = s < runs - 1 || A.restr;
         if (send) tag++;
         unsigned long long *box = A.box + (long long)(tag & 1) * A.cells * NW;
-        // relax the cell at place p from its off-diagonal sum r and its D^{-1}, and publish it
-        auto relax = [&](int p, const double r[3], const T *D) {
+        // relax the cell at place p by D^{-1} r = tt, and publish it
+        auto relax = [&](int p, const double tt[3]) {
             Cell *u = su + (p & 0xffff);
             T v[3];
 #pragma unroll
             for (int x = 0; x < 3; x++) {
-                const double tt = (double)D[x * 3 + 0] * r[0] + (double)D[x * 3 + 1] * r[1] + (double)D[x * 3 + 2] * r[2];
-                const T d1 = (T)(keep * (double)u->v[x] - A.omega * tt);
-                const T d2 = (T)(keep * (double)d1 - A.omega * tt);
+                const T d1 = (T)(keep * (double)u->v[x] - A.omega * tt[x]);
+                const T d2 = (T)(keep * (double)d1 - A.omega * tt[x]);
                 v[x] = twice ? d2 : d1;
                 u->v[x] = v[x];
             }
-            if (send && p >> 16) {
+            if (send && (p >> 16 & 1)) {
                 const int il = (p & 0xffff) % ld, jr = (p & 0xffff) / ld;
 #pragma unroll
                 for (int x = 0; x < 3; x++) box_store(box + ((j0 + jr) * nx + i0 + il), A.cells, tag, x, v[x]);
             }
+        };
+        auto apply = [&](const T *D, const double r[3], double tt[3]) {
+#pragma unroll
+            for (int x = 0; x < 3; x++) tt[x] = (double)D[x * 3 + 0] * r[0] + (double)D[x * 3 + 1] * r[1] + (double)D[x * 3 + 2] * r[2];
         };
         auto add = [&](double r[3], const Cell &y, const T *J) {
             const double x0 = (double)y.v[0], x1 = (double)y.v[1], x2 = (double)y.v[2];
 #pragma unroll
             for (int x = 0; x < 3; x++) r[x] = r[x] + ((double)J[x * 3 + 0] * x0 + (double)J[x * 3 + 1] * x1 + (double)J[x * 3 + 2] * x2);
         };
-        // a row read from memory (stride n) in this pass
-        for (int e = start[c] + t, first = 1; e < cells[c]; e += kResNT, first = 0) {
-            const int p = first ? sq[c] : place(c, e);
-            const long long cc = slot_of(c, e);
-            const Cell *u = su + (p & 0xffff);
-            const T *Jr = mg + L.J + cc;
-            T v[AHEAD + 1][9], D[9];
-            double r[3];
-#pragma unroll
-            for (int x = 0; x < 3; x++) r[x] = (double)mg[L.rhs + x * n + cc];
-#pragma unroll
-            for (int b = 1; b <= AHEAD; b++)
-#pragma unroll
-                for (int x = 0; x < 9; x++) v[b % (AHEAD + 1)][x] = Jr[(b * 9 + x) * n];
-#pragma unroll
-            for (int b = 1; b < NB; b++) {
-                const int g = b + AHEAD;
-                if (g < NB) {
-#pragma unroll
-                    for (int x = 0; x < 9; x++) v[g % (AHEAD + 1)][x] = Jr[(g * 9 + x) * n];
-                } else if (g == NB) {
-#pragma unroll
-                    for (int x = 0; x < 9; x++) D[x] = mg[L.Dinv + x * n + cc];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], v[b % (AHEAD + 1)]);
-            }
-            relax(p, r, D);
-        }
 #pragma unroll
         for (int k = 0; k < EPT; k++) {
             if (col[k] != c) continue;
@@ -1179,15 +1184,60 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
             for (int x = 0; x < 9; x++) {
 #pragma unroll
                 for (int b = 1; b < NB; b++) keep_narrow(Jb[k][b][x]);
-                keep_narrow(Di[k][x]);
+                if constexpr (HOLD) keep_narrow(Di[k][x]);
             }
             const Cell *u = su + (q[k] & 0xffff);
-            double r[3];
+            double r[3], tt[3];
 #pragma unroll
-            for (int x = 0; x < 3; x++) r[x] = (double)rh[k][x];
+            for (int x = 0; x < 3; x++) r[x] = (double)(HOLD ? rh[HOLD ? k : 0][x] : dr[(9 + x) * kResNT + t]);
 #pragma unroll
-            for (int b = 1; b < NB; b++) add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], Jb[k][b]);
-            relax(q[k], r, Di[k]);
+            for (int b = 1; b < NB; b++) {
+                if (b == 5) __builtin_amdgcn_sched_barrier(0);
+                add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], Jb[k][b]);
+            }
+            T D[9];
+#pragma unroll
+            for (int x = 0; x < 9; x++) D[x] = HOLD ? Di[HOLD ? k : 0][x] : dr[x * kResNT + t];
+            apply(D, r, tt);
+            relax(q[k], tt);
+        }
+        for (int e = start[c] + t, p = sq[c]; e < cells[c];) {
+            // the row as 27 triples (a row of each block, then of D^{-1}), RING - 1 of them on their way
+            const unsigned off = (unsigned)(slot_of(c, e) * (int)sizeof(T));
+            const Cell *u = su + (p & 0xffff);
+            T v[RING][3];
+            double r[3], tt[3];
+            auto triple = [&](int g) {
+#pragma unroll
+                for (int x = 0; x < 3; x++)
+                    v[g % RING][x] = g < 24 ? fetch(L.J, 9 + 3 * g + x, off) : fetch(L.Dinv, 3 * (g - 24) + x, off);
+            };
+#pragma unroll
+            for (int x = 0; x < 3; x++) r[x] = (double)fetch(L.rhs, x, off);
+#pragma unroll
+            for (int g = 0; g < RING - 1; g++) triple(g);
+#pragma unroll
+            for (int b = 1; b < NB; b++) {
+                const Cell y = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)];
+                const double x0 = (double)y.v[0], x1 = (double)y.v[1], x2 = (double)y.v[2];
+#pragma unroll
+                for (int x = 0; x < 3; x++) {
+                    const int g = (b - 1) * 3 + x;
+                    if (g + RING - 1 < 27) triple(g + RING - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const T *J = v[g % RING];
+                    const double a = (double)J[0] * x0 + (double)J[1] * x1 + (double)J[2] * x2;
+                    if (!(p >> (16 + b) & 1)) r[x] = r[x] + a;
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const T *D = v[(24 + x) % RING];
+                tt[x] = (double)D[0] * r[0] + (double)D[1] * r[1] + (double)D[2] * r[2];
+            }
+            relax(p, tt);
+            e += kResNT;
+            if (e < cells[c]) p = place(c, e);
         }
         if (c == 1 && lr < in_lds) {
             const Cell *u = su + (lq & 0xffff);
@@ -1200,11 +1250,14 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
                 T J[9];
 #pragma unroll
                 for (int x = 0; x < 9; x++) J[x] = rows[((b - 1) * 9 + x) * kLdsRows + lr];
+                if (b & 1) __builtin_amdgcn_sched_barrier(0);    // two blocks at a time: the registers are full
                 add(r, u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)], J);
             }
 #pragma unroll
             for (int x = 0; x < 9; x++) D[x] = rows[(72 + x) * kLdsRows + lr];
-            relax(lq, r, D);
+            double tt[3];
+            apply(D, r, tt);
+            relax(lq, tt);
         }
         if (!send) break;
         __syncthreads();
@@ -1239,7 +1292,7 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
 #pragma unroll 1
     for (int c = 0; c < C; c++)
         for (int e = t; e < cells[c]; e += kResNT) {
-            const int p = place(c, e) & 0xffff, il = p % ld, jr = p / ld;
+            const int f = place(c, e), p = f & 0xffff, il = p % ld, jr = p / ld;
             const long long cc = slot_of(c, e);
             const Cell *u = su + p;
 #pragma unroll
@@ -1261,8 +1314,10 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
                 const Cell y = u[stencil_dy(NB, b) * ld + stencil_dx(NB, b)];
                 const double x0 = (double)y.v[0], x1 = (double)y.v[1], x2 = (double)y.v[2];
 #pragma unroll
-                for (int x = 0; x < 3; x++)
-                    a[x] = a[x] + ((double)v[b & 1][x * 3 + 0] * x0 + (double)v[b & 1][x * 3 + 1] * x1 + (double)v[b & 1][x * 3 + 2] * x2);
+                for (int x = 0; x < 3; x++) {
+                    const double w = (double)v[b & 1][x * 3 + 0] * x0 + (double)v[b & 1][x * 3 + 1] * x1 + (double)v[b & 1][x * 3 + 2] * x2;
+                    if (b == 0 || !(f >> (16 + b) & 1)) a[x] = a[x] + w;
+                }
             }
 #pragma unroll
             for (int x = 0; x < 3; x++) sa[x * tw * th + jr * tw + il] = a[x];
