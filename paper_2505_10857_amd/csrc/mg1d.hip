@@ -28,9 +28,24 @@ __device__ __forceinline__ bool active_of(const MGArgs &mg, int inst)
     return mg.state == nullptr || mg.state[mg.insts[inst].active_idx].active;
 }
 
+// The inverse of a 2x2 block.  The four quotients share the divisor's reciprocal where that is far
+// from overflow and denormals: refined by two Newton-Raphson steps, each quotient corrected once by
+// its residual (Markstein), which rounds as the division does.
 __device__ __forceinline__ void inv2(const double A[4], double B[4])
 {
     double det = A[0] * A[3] - A[1] * A[2];
+    if (fabs(det) > 0x1p-400 && fabs(det) < 0x1p400) {
+        double r = __builtin_amdgcn_rcp(det);
+        r = fma(fma(-det, r, 1.0), r, r);
+        r = fma(fma(-det, r, 1.0), r, r);
+        const double N[4] = {A[3], -A[1], -A[2], A[0]};
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const double q = N[e] * r;
+            B[e] = fma(fma(-det, q, N[e]), r, q);
+        }
+        return;
+    }
     B[0] = A[3] / det;
     B[1] = -A[1] / det;
     B[2] = -A[2] / det;
@@ -306,293 +321,527 @@ __device__ __forceinline__ void mul2(const double A[4], const double B[4], doubl
 }
 
 // ---- bottom of the V-cycle -----------------------------------------------------------------
-// Every level with at most 2 NT cells (always including the coarsest; the plan picks the first
+// Every level with at most 2 K NT cells (always including the coarsest; the plan picks the first
 // such level) is handled by one NT-thread workgroup per instance in a single launch:
 // pre-smoothing and restriction down to the coarsest level, the cyclic-reduction solve there,
-// prolongation and post-smoothing back up.  Thread t owns cells t and t + NT of every level;
-// dU of the current level lives in LDS,
-// the restricted right-hand sides of all levels below the first stay in LDS, and the
-// pre-smoothed dU of each level goes to HBM and comes back to the thread that wrote it.
+// prolongation and post-smoothing back up.
+//
+// A thread owns the two children 2p and 2p + 1 of one coarse cell (K such pairs on the first
+// level): every lane has a cell to relax in each half-sweep, one neighbour of each cell is the
+// thread's own, the restriction adds the thread's own two sums and the prolongation reads one
+// parent.  A level's rows are read as pairs while the level before it is being smoothed, so the
+// chain of levels waits for memory once; the rhs and the pre-smoothed dU of all levels but the
+// first stay in LDS, rounded to the storage type.  What is left is the chain itself: about 400
+// cycles a half-sweep (a barrier, one LDS round trip and the dependent FP64 operations of a
+// cell), 2 nu + 1 of them a level each way, and 500 a reduction step.
 // Same arithmetic, in the same order, as the per-level kernels.
 
-template <typename T>
-__device__ __forceinline__ void bottom_load(const T *base, const Level1D &L, int c, double Jr[12], double D[4])
+constexpr int kBottomNT = 512;
+
+// vectors of two neighbouring cells, readable at the alignment of one value
+template <typename T> struct Two;
+template <> struct Two<double> { typedef double v __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct Two<float> { typedef float v __attribute__((ext_vector_type(2), aligned(4))); };
+
+template <typename T> __device__ __forceinline__ typename Two<T>::v ld2(const T *p)
 {
-#pragma unroll
-    for (int e = 0; e < 12; e++) Jr[e] = ld(base + L.J, e * (long long)L.n + c);
-    inv2(&Jr[4], D);   // the inverse of the diagonal block, as in the tiled smoother
+    return *reinterpret_cast<const typename Two<T>::v *>(p);
+}
+template <typename T> __device__ __forceinline__ void st2(T *p, T a, T b)
+{
+    typename Two<T>::v x;
+    x.x = a;
+    x.y = b;
+    *reinterpret_cast<typename Two<T>::v *>(p) = x;
 }
 
-template <typename T, int NT>
-__global__ void __launch_bounds__(NT) k_bottom(MGArgs mg, const int *inst_list, int zero_init0,
-                                               int final_update)
+template <typename T> struct PairRows { typename Two<T>::v j[12]; };   // W, D, E of two cells
+
+struct Vec2d { double a, b; };             // the two components of one cell in LDS
+
+template <typename T>
+__device__ __forceinline__ void load_rows(PairRows<T> &R, const T *J, int n, int p)
 {
-    static_assert(2 * NT >= kMaxCoarse, "the coarsest level needs one thread per cell");
-    __shared__ double u0[2 * NT + 2], u1[2 * NT + 2];   // dU of the current level, index c+1
-    __shared__ double q0[2 * NT], q1[2 * NT];           // rhs of the levels below the first
-    __shared__ double sW[kMaxCoarse][4], sD[kMaxCoarse][4], sE[kMaxCoarse][4], sDi[kMaxCoarse][4];
+#pragma unroll
+    for (int e = 0; e < 12; e++) R.j[e] = ld2(J + e * (long long)n + 2 * p);
+}
+
+// the value of the lane before (0 in lane 0) or after (0 in lane 63), DPP wave_shr:1 / wave_shl:1
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double x)
+{
+    const unsigned long long v = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ Vec2d lane_before(double a, double b) { return Vec2d{lane_shift<0x138>(a), lane_shift<0x138>(b)}; }
+__device__ __forceinline__ Vec2d lane_after(double a, double b) { return Vec2d{lane_shift<0x130>(a), lane_shift<0x130>(b)}; }
+
+__device__ __forceinline__ double of_lane(double x, int lane)
+{
+    const unsigned long long v = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned)v, lane), hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Where a level's np pairs lie: wavefront v holds the 64 K pairs from p0 on, and its own ones, whose
+// results are used, are the first to last of them.  Windows: neighbouring wavefronts overlap by g
+// pairs each way, as far as wrong values travel from a window's edge in the steps of one level, so
+// that no half-sweep waits for another wavefront (620 cycles one with a barrier and the edge cells
+// through LDS, 320 so).  A level too large for windows is split without overlap.
+struct PairPlace {
+    int np, p0, first, last, nw, wave, lane;
+    bool sync;
+
+    __device__ __forceinline__ PairPlace(int n, int K, int g, int t)
+    {
+        np = n / 2;
+        lane = t & 63;
+        wave = __builtin_amdgcn_readfirstlane(t >> 6);
+        const int own = 64 * K - 2 * g;
+        const bool window = np > 64 * K && own > 0 && np <= own * (kBottomNT / 64);
+        const int stride = window ? own : 64 * K;
+        nw = (np + stride - 1) / stride;
+        first = window ? g : 0;
+        last = first + stride;
+        p0 = wave * stride - first;
+        sync = nw > 1 && !window;
+    }
+    __device__ __forceinline__ int pair(int k) const { return p0 + 64 * k + lane; }
+    // the pair exists / is this wavefront's to write
+    __device__ __forceinline__ bool in(int k) const { return wave < nw && pair(k) >= 0 && pair(k) < np; }
+    __device__ __forceinline__ bool own(int k) const
+    {
+        return in(k) && 64 * k + lane >= first && 64 * k + lane < last;
+    }
+};
+
+// Pairs of a level in registers: r and du are (cell 2p: 0, 1; cell 2p + 1: 2, 3), zero where there
+// is no pair.  Neighbours come from the adjacent lanes; without windows, what crosses two wavefronts
+// goes through LDS: sl[v] is the last cell before wavefront v's, sr[v] the first cell of wavefront v.
+template <typename T, int K>
+struct PairLevel {
+    double D[K][2][4], r[K][4], du[K][4];
+
+    __device__ __forceinline__ void inverses(const PairRows<T> (&R)[K], const PairPlace &P)
+    {
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (!P.in(k)) continue;
+            const double A0[4] = {(double)R[k].j[4].x, (double)R[k].j[5].x, (double)R[k].j[6].x, (double)R[k].j[7].x};
+            const double A1[4] = {(double)R[k].j[4].y, (double)R[k].j[5].y, (double)R[k].j[6].y, (double)R[k].j[7].y};
+            inv2(A0, D[k][0]);
+            inv2(A1, D[k][1]);
+        }
+    }
+
+    // a + W x (+ D c) + E y of one cell of a pair
+    template <int S, bool DIAG>
+    static __device__ __forceinline__ void row(const PairRows<T> &R, Vec2d x, Vec2d c, Vec2d y, double &a0, double &a1)
+    {
+        auto J = [&](int e) { return (double)(S ? R.j[e].y : R.j[e].x); };
+        a0 = a0 + (J(0) * x.a + J(1) * x.b);
+        a1 = a1 + (J(2) * x.a + J(3) * x.b);
+        if (DIAG) {
+            a0 = a0 + (J(4) * c.a + J(5) * c.b);
+            a1 = a1 + (J(6) * c.a + J(7) * c.b);
+        }
+        a0 = a0 + (J(8) * y.a + J(9) * y.b);
+        a1 = a1 + (J(10) * y.a + J(11) * y.b);
+    }
+
+    template <int S>
+    __device__ __forceinline__ void relax(int k, const PairRows<T> &R, Vec2d x, Vec2d y, double w, bool twice)
+    {
+        double a0 = r[k][2 * S], a1 = r[k][2 * S + 1];
+        row<S, false>(R, x, x, y, a0, a1);
+        const double t0 = D[k][S][0] * a0 + D[k][S][1] * a1;
+        const double t1 = D[k][S][2] * a0 + D[k][S][3] * a1;
+        const double v = 1.0 - w, s0 = w * t0, s1 = w * t1;
+        du[k][2 * S] = v * du[k][2 * S] - s0;
+        du[k][2 * S + 1] = v * du[k][2 * S + 1] - s1;
+        if (twice) {
+            du[k][2 * S] = v * du[k][2 * S] - s0;
+            du[k][2 * S + 1] = v * du[k][2 * S + 1] - s1;
+        }
+    }
+
+    // the odd cell before pair(k), the even cell after it
+    __device__ __forceinline__ Vec2d before(int k, Vec2d edge, int lane) const
+    {
+        Vec2d x = lane_before(du[k][2], du[k][3]);
+        const Vec2d e = k > 0 ? Vec2d{of_lane(du[k > 0 ? k - 1 : 0][2], 63), of_lane(du[k > 0 ? k - 1 : 0][3], 63)} : edge;
+        return lane == 0 ? e : x;
+    }
+    __device__ __forceinline__ Vec2d after(int k, Vec2d edge, int lane) const
+    {
+        Vec2d y = lane_after(du[k][0], du[k][1]);
+        const Vec2d e = k < K - 1 ? Vec2d{of_lane(du[k < K - 1 ? k + 1 : 0][0], 0), of_lane(du[k < K - 1 ? k + 1 : 0][1], 0)} : edge;
+        return lane == 63 ? e : y;
+    }
+
+    template <bool SYNC, bool TWICE>
+    __device__ __forceinline__ void even(const PairRows<T> (&R)[K], const PairPlace &P, double w, const Vec2d *sl, Vec2d *sr)
+    {
+        if (!SYNC || P.wave < P.nw) {
+            Vec2d edge = Vec2d{0.0, 0.0};
+            if (SYNC) edge = sl[P.wave];
+            Vec2d x[K];
+#pragma unroll
+            for (int k = 0; k < K; k++) x[k] = before(k, edge, P.lane);
+#pragma unroll
+            for (int k = K - 1; k >= 0; k--)
+                if (P.in(k)) relax<0>(k, R[k], x[k], Vec2d{du[k][2], du[k][3]}, w, TWICE);
+            if (SYNC && P.lane == 0) sr[P.wave] = Vec2d{du[0][0], du[0][1]};
+        }
+        if (SYNC) __syncthreads();
+    }
+    template <bool SYNC>
+    __device__ __forceinline__ void odd(const PairRows<T> (&R)[K], const PairPlace &P, double w, Vec2d *sl, const Vec2d *sr)
+    {
+        if (!SYNC || P.wave < P.nw) {
+            Vec2d edge = Vec2d{0.0, 0.0};
+            if (SYNC) edge = sr[P.wave + 1];
+            Vec2d y[K];
+#pragma unroll
+            for (int k = 0; k < K; k++) y[k] = after(k, edge, P.lane);
+#pragma unroll
+            for (int k = 0; k < K; k++)
+                if (P.in(k)) relax<1>(k, R[k], Vec2d{du[k][0], du[k][1]}, y[k], w, true);
+            if (SYNC && P.lane == 63) sl[P.wave + 1] = Vec2d{du[K - 1][2], du[K - 1][3]};
+        }
+        if (SYNC) __syncthreads();
+    }
+
+    // nu symmetric steps from the dU in the registers.  Half-sweeps 0 1 1 0 per step: runs 0,
+    // (1 1), (0 0), ..., (1 1), 0 of one colour share the neighbour values and so one
+    // off-diagonal sum.
+    template <bool SYNC>
+    __device__ __forceinline__ void sweeps(int nu, double w, const PairRows<T> (&R)[K], const PairPlace &P, Vec2d *sl, Vec2d *sr)
+    {
+        if (nu <= 0) return;
+        even<SYNC, false>(R, P, w, sl, sr);
+        for (int i = 1; i < nu; i++) {
+            odd<SYNC>(R, P, w, sl, sr);
+            even<SYNC, true>(R, P, w, sl, sr);
+        }
+        odd<SYNC>(R, P, w, sl, sr);
+        even<SYNC, false>(R, P, w, sl, sr);
+    }
+    __device__ __forceinline__ void smooth(int nu, double w, const PairRows<T> (&R)[K], const PairPlace &P, Vec2d *sl, Vec2d *sr)
+    {
+        if (!P.sync) {
+            if (P.wave < P.nw) sweeps<false>(nu, w, R, P, sl, sr);
+            return;
+        }
+        if (P.wave < P.nw) {
+            if (P.lane == 63) sl[P.wave + 1] = Vec2d{du[K - 1][2], du[K - 1][3]};
+            if (P.lane == 0) {
+                sr[P.wave] = Vec2d{du[0][0], du[0][1]};
+                if (P.wave == 0) sl[0] = Vec2d{0.0, 0.0};
+                if (P.wave == P.nw - 1) sr[P.nw] = Vec2d{0.0, 0.0};
+            }
+        }
+        __syncthreads();
+        sweeps<true>(nu, w, R, P, sl, sr);
+    }
+
+    // restriction to the child (eq. 17): rhs + J dU summed over the pair, rounded to the value
+    // type as the tiled kernels round it in HBM, so the result does not depend on which levels
+    // run here
+    __device__ __forceinline__ void restrict_to(T *q0, T *q1, const PairRows<T> (&R)[K], const PairPlace &P, const Vec2d *sl, const Vec2d *sr)
+    {
+        if (P.wave >= P.nw) return;
+        Vec2d el = Vec2d{0.0, 0.0}, er = Vec2d{0.0, 0.0};
+        if (P.sync) { el = sl[P.wave]; er = sr[P.wave + 1]; }
+        Vec2d x[K], y[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) { x[k] = before(k, el, P.lane); y[k] = after(k, er, P.lane); }
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int p = P.pair(k);
+            if (!P.own(k)) continue;
+            double a[4] = {r[k][0], r[k][1], r[k][2], r[k][3]};
+            const Vec2d e = Vec2d{du[k][0], du[k][1]}, o = Vec2d{du[k][2], du[k][3]};
+            row<0, true>(R[k], x[k], e, o, a[0], a[1]);
+            row<1, true>(R[k], e, o, y[k], a[2], a[3]);
+            q0[p] = (T)(a[0] + a[2]);
+            q1[p] = (T)(a[1] + a[3]);
+        }
+    }
+};
+
+template <typename T, int K>
+__global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst_list, int zero_init0,
+                                                      int final_update)
+{
+    constexpr int NP = kBottomNT * K;          // pairs of the first level
+    constexpr int MC = kMaxCoarse;
+    static_assert(kBottomNT >= MC, "the coarsest level needs one thread per cell");
+    // cyclic reduction: D^{-1}, W, E and the right-hand side of every cell, in two buffers where
+    // half the capacity is enough (a step then needs one barrier)
+    __shared__ Vec2d cr[7 * MC];
+    __shared__ Vec2d sl[kBottomNT / 64 + 1], sr[kBottomNT / 64 + 1];
+    // rhs and dU of the levels below the first, one level after the other; dU of the first behind
+    __shared__ T q0[2 * NP], q1[2 * NP], d0[4 * NP], d1[4 * NP];
     const int inst = inst_list[blockIdx.x];
-    if (!active_of(mg, inst)) return;
     const Inst1D &I = mg.insts[inst];
     T *base = reinterpret_cast<T *>(mg.mg);
     const int t = threadIdx.x;
     const int lb = I.lev0 + I.lbot;           // level-table index of the first bottom level
+    const int nl = I.levc - lb + 1;           // levels handled here
     const double w = I.omega;
-    if (t == 0) { u0[0] = u1[0] = 0.0; }
-    {   // the coarsest operator, staged once (read at the end of the descent)
-        const Level1D Lc = mg.levs[I.levc];
-        if (t < Lc.n) {
+    const int nu1 = I.nu1, nu2 = I.nu2, N = I.N;
+    double *const U0 = I.U;
+    const double tau = I.tau;
+    const bool finest = I.lbot == 0, update = finest && final_update;
+    const Level1D &L0 = mg.levs[lb];
+    const int n0 = L0.n;                      // level k of this kernel has n0 >> k cells
+    T *const rhs0 = base + L0.rhs, *const dU0 = base + L0.dU;
+    // the levels' operators, level k's offset in lane k: read once here, since a later scalar read
+    // would be waited for with the LDS reads
+    static_assert(kMaxLevels <= 64, "a lane per level");
+    const long long Jk = (t & 63) < nl ? mg.levs[lb + (t & 63)].J : 0;
+    auto rows_of = [&](int k) -> const T * {
+        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)Jk, k);
+        const int hi = __builtin_amdgcn_readlane((int)(Jk >> 32), k);
+        return base + (((long long)hi << 32) | lo);
+    };
+    if (!active_of(mg, inst)) return;
+    // pairs of overlap: 2 nu + 1 runs and the restriction each move information one cell
+    const int g = max(nu1, nu2) + 1;
+
+    PairRows<T> nxt;                          // rows of the next level; the coarsest: one cell a thread
+    PairRows<T> cur[1];
+    PairLevel<T, 1> lev;
+    auto fetch = [&](int k) {
+        const int n = n0 >> k;
+        const T *J = rows_of(k);
+        if (k == nl - 1) {
+            if (t < n) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                sW[t][e] = ld(base + Lc.J, (0 * 4 + e) * (long long)Lc.n + t);
-                sD[t][e] = ld(base + Lc.J, (1 * 4 + e) * (long long)Lc.n + t);
-                sE[t][e] = ld(base + Lc.J, (2 * 4 + e) * (long long)Lc.n + t);
+                for (int e = 0; e < 12; e++) nxt.j[e].x = J[e * (long long)n + t];
             }
+        } else {
+            const PairPlace P(n, 1, g, t);
+            if (P.in(0)) load_rows(nxt, J, n, P.pair(0));
         }
-    }
+    };
 
     // ---- down: pre-smoothing and restriction -------------------------------------------
-    int li = lb, qoff = 0;                    // qoff: LDS offset of this level's rhs (levels > lb)
-    while (true) {
-        const Level1D L = mg.levs[li];
-        if (L.coarsest) break;
-        const int n = L.n;
-        double Jr[2][12], D[2][4], r[2][2], du[2][2];
+    T r0[K][4];                               // rhs of the first level
+    if (nl == 1) {
+        fetch(0);
+    } else {
+        PairRows<T> R[K];
+        PairLevel<T, K> L;
+        const PairPlace P(n0, K, g, t);
+        const bool from_du = finest && !zero_init0;
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int c = t + k * NT;
-            du[k][0] = du[k][1] = 0.0;
-            r[k][0] = r[k][1] = 0.0;
-            if (c < n) {
-                bottom_load(base, L, c, Jr[k], D[k]);
-                if (li == lb) {
-                    r[k][0] = ld(base + L.rhs, c);
-                    r[k][1] = ld(base + L.rhs, n + (long long)c);
-                    if (li == I.lev0 && !zero_init0) {
-                        du[k][0] = ld(base + L.dU, c);
-                        du[k][1] = ld(base + L.dU, n + (long long)c);
-                    }
-                } else {
-                    r[k][0] = q0[qoff + c];
-                    r[k][1] = q1[qoff + c];
+        for (int k = 0; k < K; k++) {
+            const int p = P.pair(k);
+#pragma unroll
+            for (int e = 0; e < 4; e++) { r0[k][e] = T(0); L.du[k][e] = 0.0; }
+            if (P.in(k)) {
+                load_rows(R[k], rows_of(0), n0, p);
+                const auto x = ld2(rhs0 + 2 * p), y = ld2(rhs0 + n0 + 2 * p);
+                r0[k][0] = x.x; r0[k][1] = y.x; r0[k][2] = x.y; r0[k][3] = y.y;
+                if (from_du) {
+                    const auto u = ld2(dU0 + 2 * p), v = ld2(dU0 + n0 + 2 * p);
+                    L.du[k][0] = u.x; L.du[k][1] = v.x; L.du[k][2] = u.y; L.du[k][3] = v.y;
                 }
-                u0[c + 1] = du[k][0];
-                u1[c + 1] = du[k][1];
             }
         }
-        if (t == 0) { u0[n + 1] = 0.0; u1[n + 1] = 0.0; }
-        __syncthreads();
-        // half-sweeps 0 1 1 0 per step: runs 0, (1 1), (0 0), ..., (1 1), 0 of one colour
-        // share the neighbour values and so one off-diagonal sum
-        for (int run = 0; I.nu1 > 0 && run <= 2 * I.nu1; run++) {
-            const int col = run & 1, reps = (run == 0 || run == 2 * I.nu1) ? 1 : 2;
+        fetch(1);
+        L.inverses(R, P);
 #pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int c = t + k * NT;
-                if (c < n && (c & 1) == col) {
-                    const double x0 = u0[c], x1 = u1[c], y0 = u0[c + 2], y1 = u1[c + 2];
-                    double a0 = r[k][0], a1 = r[k][1];
-                    a0 = a0 + (Jr[k][0] * x0 + Jr[k][1] * x1);
-                    a1 = a1 + (Jr[k][2] * x0 + Jr[k][3] * x1);
-                    a0 = a0 + (Jr[k][8] * y0 + Jr[k][9] * y1);
-                    a1 = a1 + (Jr[k][10] * y0 + Jr[k][11] * y1);
-                    const double t0 = D[k][0] * a0 + D[k][1] * a1;
-                    const double t1 = D[k][2] * a0 + D[k][3] * a1;
-                    for (int q = 0; q < reps; q++) {
-                        du[k][0] = (1.0 - w) * du[k][0] - w * t0;
-                        du[k][1] = (1.0 - w) * du[k][1] - w * t1;
-                    }
-                    u0[c + 1] = du[k][0];
-                    u1[c + 1] = du[k][1];
-                }
-            }
-            __syncthreads();
-        }
-        // restriction to the child (eq. 17) into LDS; pre-smoothed dU to HBM
-        const int qn = li == lb ? 0 : qoff + n;
+        for (int k = 0; k < K; k++)
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int c = t + k * NT;
-            double a0 = r[k][0], a1 = r[k][1];
-            if (c < n) {
-                const double x0 = u0[c], x1 = u1[c], y0 = u0[c + 2], y1 = u1[c + 2];
-                a0 = a0 + (Jr[k][0] * x0 + Jr[k][1] * x1);
-                a1 = a1 + (Jr[k][2] * x0 + Jr[k][3] * x1);
-                a0 = a0 + (Jr[k][4] * du[k][0] + Jr[k][5] * du[k][1]);
-                a1 = a1 + (Jr[k][6] * du[k][0] + Jr[k][7] * du[k][1]);
-                a0 = a0 + (Jr[k][8] * y0 + Jr[k][9] * y1);
-                a1 = a1 + (Jr[k][10] * y0 + Jr[k][11] * y1);
-            }
-            const double p0 = __shfl_xor(a0, 1, 64), p1 = __shfl_xor(a1, 1, 64);
-            if (c < n) {
-                // rounded to the value type as the tiled kernels round it in HBM, so the result
-                // does not depend on which levels run here
-                if ((c & 1) == 0) {
-                    q0[qn + (c >> 1)] = (double)(T)(a0 + p0);
-                    q1[qn + (c >> 1)] = (double)(T)(a1 + p1);
-                }
-                base[L.dU + c] = (T)du[k][0];
-                base[L.dU + n + (long long)c] = (T)du[k][1];
-            }
+            for (int e = 0; e < 4; e++) L.r[k][e] = (double)r0[k][e];
+        L.smooth(nu1, w, R, P, sl, sr);
+        L.restrict_to(q0, q1, R, P, sl, sr);
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (!P.own(k)) continue;
+            st2(d0 + 2 * NP + 2 * P.pair(k), (T)L.du[k][0], (T)L.du[k][2]);
+            st2(d1 + 2 * NP + 2 * P.pair(k), (T)L.du[k][1], (T)L.du[k][3]);
         }
         __syncthreads();
-        qoff = qn;
-        li = L.child;
+    }
+    int qo = 0;                               // offset of level k in q0, q1, d0, d1
+    for (int k = 1; k < nl - 1; k++) {
+        const int n = n0 >> k;
+        const PairPlace P(n, 1, g, t);
+        const int c = qo + 2 * P.pair(0);
+        cur[0] = nxt;
+        fetch(k + 1);
+#pragma unroll
+        for (int e = 0; e < 4; e++) lev.r[0][e] = lev.du[0][e] = 0.0;
+        if (P.in(0)) {
+            const auto x = ld2(q0 + c), y = ld2(q1 + c);
+            lev.r[0][0] = x.x; lev.r[0][1] = y.x; lev.r[0][2] = x.y; lev.r[0][3] = y.y;
+        }
+        lev.inverses(cur, P);
+        lev.smooth(nu1, w, cur, P, sl, sr);
+        lev.restrict_to(q0 + qo + n, q1 + qo + n, cur, P, sl, sr);
+        if (P.own(0)) {
+            st2(d0 + c, (T)lev.du[0][0], (T)lev.du[0][2]);
+            st2(d1 + c, (T)lev.du[0][1], (T)lev.du[0][3]);
+        }
+        __syncthreads();
+        qo += n;
     }
 
-    // ---- coarsest: block parallel cyclic reduction on the staged operator ---------------------
+    // ---- coarsest: block parallel cyclic reduction ----------------------------------------------
     {
-        const Level1D L = mg.levs[li];
-        const int n = L.n;
+        const int n = n0 >> (nl - 1);
+        const bool mine = t < n;
         double W[4] = {0, 0, 0, 0}, Dm[4] = {1, 0, 0, 1}, E[4] = {0, 0, 0, 0};
         double b0 = 0.0, b1 = 0.0;
-        if (t < n) {
+        if (mine) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) { W[e] = sW[t][e]; Dm[e] = sD[t][e]; E[e] = sE[t][e]; }
-            if (li == lb) { b0 = -ld(base + L.rhs, t); b1 = -ld(base + L.rhs, n + (long long)t); }
-            else { b0 = -q0[qoff + t]; b1 = -q1[qoff + t]; }
+            for (int e = 0; e < 4; e++) {
+                // a row without the neighbour has no coupling to it: the steps below then need
+                // no case for it (its W or E stays zero)
+                W[e] = t > 0 ? (double)nxt.j[e].x : 0.0;
+                Dm[e] = (double)nxt.j[4 + e].x;
+                E[e] = t < n - 1 ? (double)nxt.j[8 + e].x : 0.0;
+            }
+            if (nl == 1) { b0 = -ld(rhs0, t); b1 = -ld(rhs0, n + (long long)t); }
+            else { b0 = -(double)q0[qo + t]; b1 = -(double)q1[qo + t]; }
         }
+        const bool two = n <= MC / 2;
+        int buf = 0;
         for (int st = 1; st < n; st <<= 1) {
-            double Di[4];
-            inv2(Dm, Di);
-            __syncthreads();
-            if (t < n) {
-#pragma unroll
-                for (int e = 0; e < 4; e++) { sW[t][e] = W[e]; sD[t][e] = Dm[e]; sE[t][e] = E[e]; sDi[t][e] = Di[e]; }
-                u0[t + 1] = b0;
-                u1[t + 1] = b1;
+            if (!two) __syncthreads();
+            Vec2d *const P = cr + buf;
+            if (mine) {
+                double Di[4];
+                inv2(Dm, Di);
+                P[0 * MC + t] = Vec2d{Di[0], Di[1]};
+                P[1 * MC + t] = Vec2d{Di[2], Di[3]};
+                P[2 * MC + t] = Vec2d{W[0], W[1]};
+                P[3 * MC + t] = Vec2d{W[2], W[3]};
+                P[4 * MC + t] = Vec2d{E[0], E[1]};
+                P[5 * MC + t] = Vec2d{E[2], E[3]};
+                P[6 * MC + t] = Vec2d{b0, b1};
             }
             __syncthreads();
-            if (t < n) {
-                double Wn[4] = {0, 0, 0, 0}, En[4] = {0, 0, 0, 0}, Dn[4], a[4], g[4], tm[4];
+            if (two) buf ^= MC / 2;
+            if (mine) {
+                struct Cell { Vec2d v[7]; };
+                Cell l, h;                     // the cells at distance st before and after
+                const int xl = t >= st ? t - st : t, xh = t + st < n ? t + st : t;
 #pragma unroll
-                for (int e = 0; e < 4; e++) Dn[e] = Dm[e];
-                double bn0 = b0, bn1 = b1;
-                if (t - st >= 0) {
-                    mul2(W, sDi[t - st], tm);
+                for (int e = 0; e < 7; e++) { l.v[e] = P[e * MC + xl]; h.v[e] = P[e * MC + xh]; }
+                // M <- a M', D <- D + a O', b <- b + a b', a = -M D'^{-1}
+                auto fold = [&](double M[4], const Cell &c, int own, int oth) {
+                    const double Bi[4] = {c.v[0].a, c.v[0].b, c.v[1].a, c.v[1].b};
+                    const double Bm[4] = {c.v[own].a, c.v[own].b, c.v[own + 1].a, c.v[own + 1].b};
+                    const double Bo[4] = {c.v[oth].a, c.v[oth].b, c.v[oth + 1].a, c.v[oth + 1].b};
+                    double a[4], tm[4];
+                    mul2(M, Bi, tm);
 #pragma unroll
                     for (int e = 0; e < 4; e++) a[e] = -tm[e];
-                    mul2(a, sW[t - st], Wn);
-                    mul2(a, sE[t - st], tm);
+                    mul2(a, Bm, M);
+                    mul2(a, Bo, tm);
 #pragma unroll
-                    for (int e = 0; e < 4; e++) Dn[e] = Dn[e] + tm[e];
-                    const double c0 = u0[t - st + 1], c1 = u1[t - st + 1];
-                    bn0 = bn0 + (a[0] * c0 + a[1] * c1);
-                    bn1 = bn1 + (a[2] * c0 + a[3] * c1);
-                }
-                if (t + st < n) {
-                    mul2(E, sDi[t + st], tm);
-#pragma unroll
-                    for (int e = 0; e < 4; e++) g[e] = -tm[e];
-                    mul2(g, sE[t + st], En);
-                    mul2(g, sW[t + st], tm);
-#pragma unroll
-                    for (int e = 0; e < 4; e++) Dn[e] = Dn[e] + tm[e];
-                    const double c0 = u0[t + st + 1], c1 = u1[t + st + 1];
-                    bn0 = bn0 + (g[0] * c0 + g[1] * c1);
-                    bn1 = bn1 + (g[2] * c0 + g[3] * c1);
-                }
-#pragma unroll
-                for (int e = 0; e < 4; e++) { W[e] = Wn[e]; E[e] = En[e]; Dm[e] = Dn[e]; }
-                b0 = bn0;
-                b1 = bn1;
+                    for (int e = 0; e < 4; e++) Dm[e] = Dm[e] + tm[e];
+                    b0 = b0 + (a[0] * c.v[6].a + a[1] * c.v[6].b);
+                    b1 = b1 + (a[2] * c.v[6].a + a[3] * c.v[6].b);
+                };
+                fold(W, l, 2, 4);
+                fold(E, h, 4, 2);
             }
         }
-        __syncthreads();
-        if (t < n) {
+        if (mine) {
             double Di[4];
             inv2(Dm, Di);
             const double x0 = Di[0] * b0 + Di[1] * b1;
             const double x1 = Di[2] * b0 + Di[3] * b1;
-            u0[t + 1] = x0;
-            u1[t + 1] = x1;
-            if (li == I.lev0 && final_update) {   // one-level hierarchy: the Newton update, eq. (14)
-                I.U[t] = I.U[t] + I.tau * x0;
-                I.U[I.N + t] = I.U[I.N + t] + I.tau * x1;
-            } else if (li == lb) {   // the bottom is the coarsest level only
-                base[L.dU + t] = (T)x0;
-                base[L.dU + n + (long long)t] = (T)x1;
+            if (nl > 1) {
+                d0[qo + t] = (T)x0;
+                d1[qo + t] = (T)x1;
+            } else if (update) {   // one-level hierarchy: the Newton update, eq. (14)
+                U0[t] = U0[t] + tau * x0;
+                U0[N + t] = U0[N + t] + tau * x1;
+            } else {                          // the bottom is the coarsest level only
+                dU0[t] = (T)x0;
+                dU0[n + (long long)t] = (T)x1;
             }
         }
         __syncthreads();
     }
+    if (nl == 1) return;
 
     // ---- up: prolongation and post-smoothing ------------------------------------------------
-    while (li > lb) {
-        li -= 1;
-        const Level1D L = mg.levs[li];
-        const int n = L.n;
-        // rhs offset of this level: walk the offsets again (levels above lb only)
-        int qo = 0;
-        for (int x = lb + 1; x < li; x++) qo += mg.levs[x].n;
-        double par[2][2];
+    auto climb = [&](int k) {                 // level k >= 1, its rows in cur; the child's dU at qo
+        const int n = n0 >> k;
+        const PairPlace P(n, 1, g, t);
+        const int p = P.pair(0), c = qo - n + 2 * p;
+        lev.inverses(cur, P);
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int c = t + k * NT;
-            par[k][0] = par[k][1] = 0.0;
-            if (c < n) { par[k][0] = (double)(T)u0[(c >> 1) + 1]; par[k][1] = (double)(T)u1[(c >> 1) + 1]; }
+        for (int e = 0; e < 4; e++) lev.r[0][e] = lev.du[0][e] = 0.0;
+        if (P.in(0)) {
+            const double p0 = (double)d0[qo + p], p1 = (double)d1[qo + p];
+            const auto x = ld2(q0 + c), y = ld2(q1 + c), u = ld2(d0 + c), v = ld2(d1 + c);
+            lev.r[0][0] = x.x; lev.r[0][1] = y.x; lev.r[0][2] = x.y; lev.r[0][3] = y.y;
+            lev.du[0][0] = (double)u.x + p0;
+            lev.du[0][1] = (double)v.x + p1;
+            lev.du[0][2] = (double)u.y + p0;
+            lev.du[0][3] = (double)v.y + p1;
+        }
+        __syncthreads();                      // windows read their neighbours' pairs of d0, d1 too
+        lev.smooth(nu2, w, cur, P, sl, sr);
+        if (P.own(0)) {
+            st2(d0 + c, (T)lev.du[0][0], (T)lev.du[0][2]);
+            st2(d1 + c, (T)lev.du[0][1], (T)lev.du[0][3]);
         }
         __syncthreads();
-        double Jr[2][12], D[2][4], r[2][2], du[2][2];
+        qo -= n;
+    };
+    for (int k = nl - 2; k >= 2; k--) {       // the lowest level's rows are still in cur
+        const PairPlace P(n0 >> (k - 1), 1, g, t);
+        if (P.in(0)) load_rows(nxt, rows_of(k - 1), n0 >> (k - 1), P.pair(0));
+        climb(k);
+        cur[0] = nxt;
+    }
+    PairRows<T> R[K];
+    PairLevel<T, K> L;
+    const PairPlace P(n0, K, g, t);
 #pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int c = t + k * NT;
-            du[k][0] = du[k][1] = 0.0;
-            r[k][0] = r[k][1] = 0.0;
-            if (c < n) {
-                bottom_load(base, L, c, Jr[k], D[k]);
-                if (li == lb) {
-                    r[k][0] = ld(base + L.rhs, c);
-                    r[k][1] = ld(base + L.rhs, n + (long long)c);
-                } else {
-                    r[k][0] = q0[qo + c];
-                    r[k][1] = q1[qo + c];
-                }
-                du[k][0] = ld(base + L.dU, c) + par[k][0];
-                du[k][1] = ld(base + L.dU, n + (long long)c) + par[k][1];
-                u0[c + 1] = du[k][0];
-                u1[c + 1] = du[k][1];
-            }
+    for (int k = 0; k < K; k++)
+        if (P.in(k)) load_rows(R[k], rows_of(0), n0, P.pair(k));
+    if (nl > 2) climb(1);
+    L.inverses(R, P);
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int p = P.pair(k);
+#pragma unroll
+        for (int e = 0; e < 4; e++) { L.r[k][e] = (double)r0[k][e]; L.du[k][e] = 0.0; }
+        if (P.in(k)) {
+            const double p0 = (double)d0[p], p1 = (double)d1[p];
+            const auto u = ld2(d0 + 2 * NP + 2 * p), v = ld2(d1 + 2 * NP + 2 * p);
+            L.du[k][0] = (double)u.x + p0;
+            L.du[k][1] = (double)v.x + p1;
+            L.du[k][2] = (double)u.y + p0;
+            L.du[k][3] = (double)v.y + p1;
         }
-        if (t == 0) { u0[n + 1] = 0.0; u1[n + 1] = 0.0; }
-        __syncthreads();
-        // half-sweeps 0 1 1 0 per step: runs 0, (1 1), (0 0), ..., (1 1), 0 of one colour
-        // share the neighbour values and so one off-diagonal sum
-        for (int run = 0; I.nu2 > 0 && run <= 2 * I.nu2; run++) {
-            const int col = run & 1, reps = (run == 0 || run == 2 * I.nu2) ? 1 : 2;
+    }
+    L.smooth(nu2, w, R, P, sl, sr);
 #pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int c = t + k * NT;
-                if (c < n && (c & 1) == col) {
-                    const double x0 = u0[c], x1 = u1[c], y0 = u0[c + 2], y1 = u1[c + 2];
-                    double a0 = r[k][0], a1 = r[k][1];
-                    a0 = a0 + (Jr[k][0] * x0 + Jr[k][1] * x1);
-                    a1 = a1 + (Jr[k][2] * x0 + Jr[k][3] * x1);
-                    a0 = a0 + (Jr[k][8] * y0 + Jr[k][9] * y1);
-                    a1 = a1 + (Jr[k][10] * y0 + Jr[k][11] * y1);
-                    const double t0 = D[k][0] * a0 + D[k][1] * a1;
-                    const double t1 = D[k][2] * a0 + D[k][3] * a1;
-                    for (int q = 0; q < reps; q++) {
-                        du[k][0] = (1.0 - w) * du[k][0] - w * t0;
-                        du[k][1] = (1.0 - w) * du[k][1] - w * t1;
-                    }
-                    u0[c + 1] = du[k][0];
-                    u1[c + 1] = du[k][1];
-                }
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int c = t + k * NT;
-            if (c >= n) continue;
-            if (li == I.lev0 && final_update) {
-                I.U[c] = I.U[c] + I.tau * du[k][0];
-                I.U[I.N + c] = I.U[I.N + c] + I.tau * du[k][1];
-            } else if (li == lb) {
-                base[L.dU + c] = (T)du[k][0];
-                base[L.dU + n + (long long)c] = (T)du[k][1];
-            }
+    for (int k = 0; k < K; k++) {
+        const int p = P.pair(k);
+        if (!P.own(k)) continue;
+        if (update) {
+            double *U = U0 + 2 * p, *V = U0 + N + 2 * p;
+            const auto u = ld2(U), v = ld2(V);
+            st2(U, u.x + tau * L.du[k][0], u.y + tau * L.du[k][2]);
+            st2(V, v.x + tau * L.du[k][1], v.y + tau * L.du[k][3]);
+        } else {
+            st2(dU0 + 2 * p, (T)L.du[k][0], (T)L.du[k][2]);
+            st2(dU0 + n0 + 2 * p, (T)L.du[k][1], (T)L.du[k][3]);
         }
     }
 }
@@ -977,12 +1226,11 @@ template <typename T>
 static void launch_bottom_t(const MGArgs &mg, const int *inst_list, int n, int zero_init0, int final_update,
                             int nt, hipStream_t s)
 {
-    if (nt <= 256)
-        hipLaunchKernelGGL((k_bottom<T, 256>), dim3(n), dim3(256), 0, s, mg, inst_list, zero_init0, final_update);
-    else if (nt <= 512)
-        hipLaunchKernelGGL((k_bottom<T, 512>), dim3(n), dim3(512), 0, s, mg, inst_list, zero_init0, final_update);
+    // nt = half the cells of the largest first level: one pair a thread up to 1024 cells, else two
+    if (nt <= kBottomNT)
+        hipLaunchKernelGGL((k_bottom<T, 1>), dim3(n), dim3(kBottomNT), 0, s, mg, inst_list, zero_init0, final_update);
     else
-        hipLaunchKernelGGL((k_bottom<T, 1024>), dim3(n), dim3(1024), 0, s, mg, inst_list, zero_init0, final_update);
+        hipLaunchKernelGGL((k_bottom<T, 2>), dim3(n), dim3(kBottomNT), 0, s, mg, inst_list, zero_init0, final_update);
 }
 
 hipError_t launch_bottom(const MGArgs &mg, const int *inst_list, int n, int zero_init0, int final_update,
