@@ -169,6 +169,8 @@ struct nmg_plan {
     // finest-level tiles of the launch that runs one V-cycle's post-smoothing and the next one's
     // pre-smoothing (nu3 >= 2, every instance on three-block rows); count 0 when not used
     std::pair<int, int> fused0 = {0, 0};
+    bool grouped = false;                     // the levels above the bottom go kGroupLevels a launch
+    std::vector<std::pair<int, int>> groups;  // (t0, nt) per group of levels, the finest first
     int jac_mask = 0;
     int depth = 0;
     size_t off_insts = 0, off_levs = 0, off_tiles = 0, off_list = 0, off_state = 0, off_partial = 0,
@@ -226,6 +228,38 @@ struct nmg_plan {
 };
 
 namespace {
+
+// First level of the bottom kernel: the first of three-block rows with at most `cells` cells.
+int bottom_level(const Inst1D &I, int cells)
+{
+    for (int l = 0; l < I.levels; l++)
+        if ((I.N >> l) <= cells && (l > 0 || I.nb == 3)) return l;
+    return I.levels - 1;
+}
+
+// Whether the levels above the bottom go kGroupLevels a launch.  That pays where launches are what a
+// cycle costs, one round of workgroups on the device: one channel of 12800 cells takes 0 us a cycle
+// so and 0 with a launch per level; with more cells than that, windows reread their margins and the
+// deeper levels leave wavefronts idle.  Only with the default options (the others ask for launches
+// per level), and where the margins leave a quarter of a tile.
+bool group_levels(const nmg_plan *P)
+{
+    if (P->linear != NMG_LINEAR_MG || P->bottom_cells != kBottomCellsMax || P->smooth_tile != kSmoothTile || P->split_finest)
+        return false;
+    const int nb = P->insts.empty() ? 3 : P->insts[0].nb;
+    long long tiles = 0;
+    bool above = false;
+    for (const Inst1D &I : P->insts) {
+        if (I.nb != nb) return false;
+        const int l = nb == 5, left = bottom_level(I, kGroupCells) - l;
+        above = above || I.lbot > l;
+        if (left <= 0) continue;
+        const Group1D G = group_window(std::max(I.nu1, I.nu2), left);
+        if (G.own < G.cells / 4 || G.own <= 0) return false;
+        tiles += ((I.N >> l) + G.own - 1) / G.own;
+    }
+    return above && tiles <= kGroupTiles;
+}
 
 nmg_status build_plan(nmg_plan *P, const nmg_desc *descs, const nmg_params *params, int n,
                       bool need_geometry = true)
@@ -293,12 +327,14 @@ nmg_status build_plan(nmg_plan *P, const nmg_desc *descs, const nmg_params *para
         }
         I.levc = (int)P->levs.size() - 1;
         // bottom kernel: from the first three-block level with at most bottom_cells cells
-        I.lbot = I.levels - 1;
-        for (int l = 0; l < I.levels; l++)
-            if ((I.N >> l) <= P->bottom_cells && (l > 0 || I.nb == 3)) { I.lbot = l; break; }
+        I.lbot = bottom_level(I, P->bottom_cells);
         I.max_hist = std::min(params[k].n_max, 100000);
         P->insts.push_back(I);
     }
+    // few cells: several levels a launch, and the bottom from a level that one workgroup reads soon
+    P->grouped = group_levels(P);
+    if (P->grouped)
+        for (auto &I : P->insts) I.lbot = bottom_level(I, kGroupCells);
     // residual / Jacobian tiles
     P->res_t0 = 0;
     P->jac_mask = 0;
@@ -350,7 +386,7 @@ nmg_status build_plan(nmg_plan *P, const nmg_desc *descs, const nmg_params *para
     for (int d = 0; d < P->depth; d++) {
         int t0 = (int)P->tiles.size(), mask = 0;
         for (int k = 0; k < n; k++) {
-            if (d >= P->insts[k].lbot) continue;
+            if (d >= P->insts[k].lbot || (P->grouped && d >= (P->insts[k].nb == 5))) continue;
             const Level1D &L = P->levs[lev_index[k][d]];
             if (L.V < 2) return fail(NMG_EINVAL, "smoothing halo exceeds the tile");
             for (int a = 0; a < L.n; a += L.V) P->tiles.push_back({lev_index[k][d], a});
@@ -358,6 +394,19 @@ nmg_status build_plan(nmg_plan *P, const nmg_desc *descs, const nmg_params *para
         }
         P->smooth.push_back({t0, (int)P->tiles.size() - t0});
         P->smooth_mask.push_back(mask);
+    }
+    P->groups.clear();
+    for (int j = 0; P->grouped; j++) {
+        int t0 = (int)P->tiles.size();
+        for (int k = 0; k < n; k++) {
+            const Inst1D &I = P->insts[k];
+            const int l = (I.nb == 5) + kGroupLevels * j;
+            if (l >= I.lbot) continue;
+            const int own = group_window(std::max(I.nu1, I.nu2), I.lbot - l).own;
+            for (int a = 0; a < I.N >> l; a += own) P->tiles.push_back({lev_index[k][l], a});
+        }
+        if ((int)P->tiles.size() == t0) break;
+        P->groups.push_back({t0, (int)P->tiles.size() - t0});
     }
     P->fused0 = {0, 0};
     if (P->linear == NMG_LINEAR_MG && P->nu3 >= 2 && P->jac_mask == 1 && P->depth > 0 && !P->split_finest) {
@@ -510,7 +559,28 @@ nmg_status enqueue_vcycle(nmg_plan *P, char *ws, const MGArgs &mg, bool zero_ini
                                 0, s));
         if (d == 0) src0 = 1 - src;
     }
-    HIP_TRY(launch_bottom(mg, list, P->n, zero_init0 ? 1 : 0, final_update ? 1 : 0, P->prec, P->bottom_nt, s));
+    // with grouped levels, the groups lie between the finest level of five-block rows (if any) and the
+    // bottom; a group's first level is the finest one for three-block rows
+    const bool five = (P->jac_mask & 2) != 0;
+    auto group = [&](size_t j, int mode) -> nmg_status {
+        const bool finest = j == 0 && !five;
+        ProfScope ps(P, j > 0 ? -1 : mode == 0 ? NMG_K_SMOOTH_PRE : NMG_K_SMOOTH_POST, s, cap);
+        HIP_TRY(launch_group1d(mg, tiles_at(P, ws, P->groups[j].first), P->groups[j].second, mode,
+                               (!finest || zero_init0) ? 1 : 0, (finest && final_update) ? 1 : 0,
+                               finest ? src0 : mode, P->prec, s));
+        if (finest) src0 = 1 - src0;
+        return NMG_OK;
+    };
+    for (size_t j = 0; j < P->groups.size(); j++) {
+        nmg_status st = group(j, 0);
+        if (st != NMG_OK) return st;
+    }
+    const int bottom_nt = P->grouped ? std::min(P->bottom_nt, kGroupCells / 2) : P->bottom_nt;
+    HIP_TRY(launch_bottom(mg, list, P->n, zero_init0 ? 1 : 0, final_update ? 1 : 0, P->prec, bottom_nt, s));
+    for (size_t j = P->groups.size(); j-- > 0;) {
+        nmg_status st = group(j, 1);
+        if (st != NMG_OK) return st;
+    }
     // Passes alternate direction over data that a recent pass streamed, so that each begins in
     // the memory-side cache: the residual runs in tile order and the Jacobian after it in
     // reverse (k_jacobian_batch), so the finest pre-smoothing after that runs in order; a coarse
@@ -583,7 +653,7 @@ nmg_status enqueue_step(nmg_plan *P, char *ws, hipStream_t s, bool cap = false)
     if (P->linear == NMG_LINEAR_MG) {
         // with fused finest-level tiles, the post-smoothing of a cycle and the pre-smoothing of
         // the next run in one launch (nothing else touches the finest level between them)
-        const bool fuse = P->fused0.second > 0;
+        const bool fuse = P->fused0.second > 0 && !P->grouped;
         int src0 = 0;
         for (int v = 0; v < P->nu3; v++) {
             st = enqueue_vcycle(P, ws, mg, v == 0, v == P->nu3 - 1, s, cap, src0, fuse && v > 0,
@@ -842,6 +912,7 @@ nmg_status nmg_plan_create(const nmg_desc *descs, const nmg_params *params, int3
     P->bottom_nt = 1024;
     st = build_plan(P, descs, params, n);
     if (st != NMG_OK) { delete P; return st; }
+    P->tile_cap = std::max(P->tile_cap, P->tiles.size());
     *out = P;
     return NMG_OK;
 }

@@ -391,26 +391,27 @@ __device__ __forceinline__ double of_lane(double x, int lane)
 // that no half-sweep waits for another wavefront (620 cycles one with a barrier and the edge cells
 // through LDS, 320 so).  A level too large for windows is split without overlap.
 struct PairPlace {
-    int np, p0, first, last, nw, wave, lane;
+    int p0, lo, hi, first, last, lane, wave, nw;
     bool sync;
 
-    __device__ __forceinline__ PairPlace(int n, int K, int g, int t)
+    // np pairs on nwaves wavefronts from w0 on; those from lo to hi - 1 exist
+    __device__ __forceinline__ PairPlace(int np, int lo_, int hi_, int K, int g, int t, int w0, int nwaves) : lo(lo_), hi(hi_)
     {
-        np = n / 2;
         lane = t & 63;
-        wave = __builtin_amdgcn_readfirstlane(t >> 6);
+        wave = __builtin_amdgcn_readfirstlane(t >> 6) - w0;
         const int own = 64 * K - 2 * g;
-        const bool window = np > 64 * K && own > 0 && np <= own * (kBottomNT / 64);
+        const bool window = np > 64 * K && own > 0 && np <= own * nwaves;
         const int stride = window ? own : 64 * K;
-        nw = (np + stride - 1) / stride;
+        nw = window ? nwaves : (np + 64 * K - 1) / (64 * K);
         first = window ? g : 0;
         last = first + stride;
         p0 = wave * stride - first;
         sync = nw > 1 && !window;
     }
     __device__ __forceinline__ int pair(int k) const { return p0 + 64 * k + lane; }
+    __device__ __forceinline__ bool on() const { return wave >= 0 && wave < nw; }
     // the pair exists / is this wavefront's to write
-    __device__ __forceinline__ bool in(int k) const { return wave < nw && pair(k) >= 0 && pair(k) < np; }
+    __device__ __forceinline__ bool in(int k) const { return on() && pair(k) >= lo && pair(k) < hi; }
     __device__ __forceinline__ bool own(int k) const
     {
         return in(k) && 64 * k + lane >= first && 64 * k + lane < last;
@@ -484,7 +485,7 @@ struct PairLevel {
     template <bool SYNC, bool TWICE>
     __device__ __forceinline__ void even(const PairRows<T> (&R)[K], const PairPlace &P, double w, const Vec2d *sl, Vec2d *sr)
     {
-        if (!SYNC || P.wave < P.nw) {
+        if (!SYNC || P.on()) {
             Vec2d edge = Vec2d{0.0, 0.0};
             if (SYNC) edge = sl[P.wave];
             Vec2d x[K];
@@ -500,7 +501,7 @@ struct PairLevel {
     template <bool SYNC>
     __device__ __forceinline__ void odd(const PairRows<T> (&R)[K], const PairPlace &P, double w, Vec2d *sl, const Vec2d *sr)
     {
-        if (!SYNC || P.wave < P.nw) {
+        if (!SYNC || P.on()) {
             Vec2d edge = Vec2d{0.0, 0.0};
             if (SYNC) edge = sr[P.wave + 1];
             Vec2d y[K];
@@ -532,10 +533,10 @@ struct PairLevel {
     __device__ __forceinline__ void smooth(int nu, double w, const PairRows<T> (&R)[K], const PairPlace &P, Vec2d *sl, Vec2d *sr)
     {
         if (!P.sync) {
-            if (P.wave < P.nw) sweeps<false>(nu, w, R, P, sl, sr);
+            if (P.on()) sweeps<false>(nu, w, R, P, sl, sr);
             return;
         }
-        if (P.wave < P.nw) {
+        if (P.on()) {
             if (P.lane == 63) sl[P.wave + 1] = Vec2d{du[K - 1][2], du[K - 1][3]};
             if (P.lane == 0) {
                 sr[P.wave] = Vec2d{du[0][0], du[0][1]};
@@ -552,7 +553,7 @@ struct PairLevel {
     // run here
     __device__ __forceinline__ void restrict_to(T *q0, T *q1, const PairRows<T> (&R)[K], const PairPlace &P, const Vec2d *sl, const Vec2d *sr)
     {
-        if (P.wave >= P.nw) return;
+        if (!P.on()) return;
         Vec2d el = Vec2d{0.0, 0.0}, er = Vec2d{0.0, 0.0};
         if (P.sync) { el = sl[P.wave]; er = sr[P.wave + 1]; }
         Vec2d x[K], y[K];
@@ -583,6 +584,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
     // half the capacity is enough (a step then needs one barrier)
     __shared__ Vec2d cr[7 * MC];
     __shared__ Vec2d sl[kBottomNT / 64 + 1], sr[kBottomNT / 64 + 1];
+    __shared__ long long Js[kMaxLevels];       // where the levels' operators begin
     // rhs and dU of the levels below the first, one level after the other; dU of the first behind
     __shared__ T q0[2 * NP], q1[2 * NP], d0[4 * NP], d1[4 * NP];
     const int inst = inst_list[blockIdx.x];
@@ -598,19 +600,20 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
     const bool finest = I.lbot == 0, update = finest && final_update;
     const Level1D &L0 = mg.levs[lb];
     const int n0 = L0.n;                      // level k of this kernel has n0 >> k cells
+    const long long J0 = L0.J;
     T *const rhs0 = base + L0.rhs, *const dU0 = base + L0.dU;
-    // the levels' operators, level k's offset in lane k: read once here, since a later scalar read
-    // would be waited for with the LDS reads
-    static_assert(kMaxLevels <= 64, "a lane per level");
-    const long long Jk = (t & 63) < nl ? mg.levs[lb + (t & 63)].J : 0;
-    auto rows_of = [&](int k) -> const T * {
-        const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)Jk, k);
-        const int hi = __builtin_amdgcn_readlane((int)(Jk >> 32), k);
-        return base + (((long long)hi << 32) | lo);
-    };
     if (!active_of(mg, inst)) return;
     // pairs of overlap: 2 nu + 1 runs and the restriction each move information one cell
     const int g = max(nu1, nu2) + 1;
+    // read once here: a later scalar read would be waited for with the LDS reads
+    if (t < nl) Js[t] = mg.levs[lb + t].J;
+    auto rows_of = [&](int k) -> const T * {
+        const unsigned long long v = Js[k];
+        const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)v);
+        const int hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+        return base + (((long long)hi << 32) | lo);
+    };
+    auto place = [&](int n, int k) { return PairPlace(n / 2, 0, n / 2, k, g, t, 0, kBottomNT / 64); };
 
     PairRows<T> nxt;                          // rows of the next level; the coarsest: one cell a thread
     PairRows<T> cur[1];
@@ -624,7 +627,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
                 for (int e = 0; e < 12; e++) nxt.j[e].x = J[e * (long long)n + t];
             }
         } else {
-            const PairPlace P(n, 1, g, t);
+            const PairPlace P = place(n, 1);
             if (P.in(0)) load_rows(nxt, J, n, P.pair(0));
         }
     };
@@ -632,11 +635,12 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
     // ---- down: pre-smoothing and restriction -------------------------------------------
     T r0[K][4];                               // rhs of the first level
     if (nl == 1) {
+        __syncthreads();
         fetch(0);
     } else {
         PairRows<T> R[K];
         PairLevel<T, K> L;
-        const PairPlace P(n0, K, g, t);
+        const PairPlace P = place(n0, K);
         const bool from_du = finest && !zero_init0;
 #pragma unroll
         for (int k = 0; k < K; k++) {
@@ -644,7 +648,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
 #pragma unroll
             for (int e = 0; e < 4; e++) { r0[k][e] = T(0); L.du[k][e] = 0.0; }
             if (P.in(k)) {
-                load_rows(R[k], rows_of(0), n0, p);
+                load_rows(R[k], base + J0, n0, p);
                 const auto x = ld2(rhs0 + 2 * p), y = ld2(rhs0 + n0 + 2 * p);
                 r0[k][0] = x.x; r0[k][1] = y.x; r0[k][2] = x.y; r0[k][3] = y.y;
                 if (from_du) {
@@ -653,6 +657,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
                 }
             }
         }
+        __syncthreads();                      // Js
         fetch(1);
         L.inverses(R, P);
 #pragma unroll
@@ -672,7 +677,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
     int qo = 0;                               // offset of level k in q0, q1, d0, d1
     for (int k = 1; k < nl - 1; k++) {
         const int n = n0 >> k;
-        const PairPlace P(n, 1, g, t);
+        const PairPlace P = place(n, 1);
         const int c = qo + 2 * P.pair(0);
         cur[0] = nxt;
         fetch(k + 1);
@@ -778,7 +783,7 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
     // ---- up: prolongation and post-smoothing ------------------------------------------------
     auto climb = [&](int k) {                 // level k >= 1, its rows in cur; the child's dU at qo
         const int n = n0 >> k;
-        const PairPlace P(n, 1, g, t);
+        const PairPlace P = place(n, 1);
         const int p = P.pair(0), c = qo - n + 2 * p;
         lev.inverses(cur, P);
 #pragma unroll
@@ -802,17 +807,16 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
         qo -= n;
     };
     for (int k = nl - 2; k >= 2; k--) {       // the lowest level's rows are still in cur
-        const PairPlace P(n0 >> (k - 1), 1, g, t);
-        if (P.in(0)) load_rows(nxt, rows_of(k - 1), n0 >> (k - 1), P.pair(0));
+        fetch(k - 1);
         climb(k);
         cur[0] = nxt;
     }
     PairRows<T> R[K];
     PairLevel<T, K> L;
-    const PairPlace P(n0, K, g, t);
+    const PairPlace P = place(n0, K);
 #pragma unroll
     for (int k = 0; k < K; k++)
-        if (P.in(k)) load_rows(R[k], rows_of(0), n0, P.pair(k));
+        if (P.in(k)) load_rows(R[k], base + J0, n0, P.pair(k));
     if (nl > 2) climb(1);
     L.inverses(R, P);
 #pragma unroll
@@ -842,6 +846,151 @@ __global__ void __launch_bounds__(kBottomNT) k_bottom(MGArgs mg, const int *inst
         } else {
             st2(dU0 + 2 * p, (T)L.du[k][0], (T)L.du[k][2]);
             st2(dU0 + n0 + 2 * p, (T)L.du[k][1], (T)L.du[k][3]);
+        }
+    }
+}
+
+// ---- levels above the bottom, several in one launch ----------------------------------------------
+// Few cells in all (one channel, a handful of small ones): a launch per level costs its start, the
+// chain of table reads and one wait for memory, 5 to 6 us, for under 1 us of smoothing.  Here one
+// 256-thread workgroup takes up to kGroupLevels levels of a tile: the tile has a margin from which
+// the levels' windows shrink (down) or grow (up), and everything the levels need is read at the
+// start, the first level on all four wavefronts, the second on two, the third and fourth on one
+// each.  MODE 0: pre-smoothing and restriction from the first level of the group to the child of its
+// last; MODE 1: prolongation and post-smoothing back up to the first.
+// Same arithmetic, in the same order, as a launch per level.
+
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kGroupNT) k_group(MGArgs mg, const Tile *tiles, int zero_init, int final_update,
+                                                    int src_out)
+{
+    constexpr int NW = kGroupNT / 64, CAP = 2 * 64 * NW;     // cells of the first level
+    static_assert(NW == 4 && kGroupLevels == 4, "levels 1, 2 and 3 lie on wavefronts 0-1, 2 and 3");
+    // rhs (down) and dU of the levels, level l's at offset CAP (2 - 2^(1-l))
+    __shared__ T q0[2 * CAP], q1[2 * CAP], d0[2 * CAP], d1[2 * CAP];
+    const Tile tl = tiles[blockIdx.x];
+    const int t = threadIdx.x;
+    const int inst = mg.levs[tl.lev].inst, n0 = mg.levs[tl.lev].n, top = mg.levs[tl.lev].l;
+    const Inst1D &I = mg.insts[inst];
+    const int nu = MODE == 0 ? I.nu1 : I.nu2;
+    const Group1D G = group_window(max(I.nu1, I.nu2), I.lbot - top);
+    const Level1D *const lev = mg.levs + tl.lev;             // of the group's levels and the child of its last
+    // the wavefront's other level; none (level 0 again, unused) where the group is shorter
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6), lw = wv < 2 ? 1 : wv;
+    const bool other = lw < G.levels;
+    const Level1D L0 = lev[0], L1 = lev[other ? lw : 0];
+    const long long dUc = lev[G.levels].dU;
+    const double w = I.omega, tau = I.tau;
+    double *const U0 = I.U;
+    const int N = I.N;
+    if (!active_of(mg, inst)) return;
+    T *const base = reinterpret_cast<T *>(mg.mg);
+    const int s0 = tl.a - G.margin;                          // first cell of the window, level 0
+    auto place = [&](int l) {
+        const int org = (s0 >> l) / 2, np = (G.cells >> l) / 2;
+        return PairPlace(np, max(0, -org), min(np, (n0 >> l) / 2 - org), 1, G.g, t, l < 2 ? 0 : l, l == 0 ? NW : l == 1 ? 2 : 1);
+    };
+    auto off = [&](int l) { return 2 * CAP - (2 * CAP >> l); };
+
+    // ---- reads: level 0 in a, the wavefront's other level in b ---------------------------------
+    PairRows<T> Ra[1], Rb[1];
+    PairLevel<T, 1> A, B;
+    auto read = [&](int l, const Level1D &V, bool there, PairRows<T> &R, PairLevel<T, 1> &L) {
+        const PairPlace P = place(l);
+        const int n = n0 >> l, p = (s0 >> l) / 2 + P.pair(0);
+#pragma unroll
+        for (int e = 0; e < 4; e++) L.r[0][e] = L.du[0][e] = 0.0;
+        const T *const f = base + V.rhs + 2 * (long long)p;
+        const T *const d = base + ((l == 0 ? src_out : 1) ? V.dUo : V.dU) + 2 * (long long)p;
+        if (!there || !P.in(0)) return;
+        load_rows(R, base + V.J, n, p);
+        if (MODE == 1 || l == 0) {
+            const auto x = ld2(f), y = ld2(f + n);
+            L.r[0][0] = x.x; L.r[0][1] = y.x; L.r[0][2] = x.y; L.r[0][3] = y.y;
+        }
+        if (MODE == 1 || (l == 0 && !zero_init)) {
+            const auto x = ld2(d), y = ld2(d + n);
+            L.du[0][0] = x.x; L.du[0][1] = y.x; L.du[0][2] = x.y; L.du[0][3] = y.y;
+        }
+    };
+    read(0, L0, true, Ra[0], A);
+    read(lw, L1, other, Rb[0], B);
+    auto store = [&](int l, PairLevel<T, 1> &L, const PairPlace &P) {
+        if (!P.own(0)) return;
+        st2(d0 + off(l) + 2 * P.pair(0), (T)L.du[0][0], (T)L.du[0][2]);
+        st2(d1 + off(l) + 2 * P.pair(0), (T)L.du[0][1], (T)L.du[0][3]);
+    };
+
+    if (MODE == 0) {
+        const PairPlace P0 = place(0), P1 = place(lw);
+        A.inverses(Ra, P0);
+        if (other) B.inverses(Rb, P1);
+        A.smooth(nu, w, Ra, P0, nullptr, nullptr);
+        A.restrict_to(q0 + off(1), q1 + off(1), Ra, P0, nullptr, nullptr);
+        store(0, A, P0);
+        __syncthreads();
+        for (int l = 1; l < G.levels; l++) {
+            if (lw == l) {
+                if (P1.in(0)) {
+                    const auto x = ld2(q0 + off(l) + 2 * P1.pair(0)), y = ld2(q1 + off(l) + 2 * P1.pair(0));
+                    B.r[0][0] = x.x; B.r[0][1] = y.x; B.r[0][2] = x.y; B.r[0][3] = y.y;
+                }
+                B.smooth(nu, w, Rb, P1, nullptr, nullptr);
+                B.restrict_to(q0 + off(l + 1), q1 + off(l + 1), Rb, P1, nullptr, nullptr);
+                store(l, B, P1);
+            }
+            __syncthreads();
+        }
+        // the tile's own cells: dU of each level and the rhs of its child
+        for (int l = 0; l < G.levels; l++) {
+            const int m = G.margin >> l, n = n0 >> l, a = tl.a >> l, v = min(G.own >> l, n - a);
+            T *du = base + ((l == 0 ? !src_out : 1) ? lev[l].dUo : lev[l].dU) + a, *f = base + lev[l + 1].rhs + a / 2;
+            const int o = off(l) + m, c = off(l + 1) + m / 2;
+            for (int i = t; i < v; i += kGroupNT) { du[i] = d0[o + i]; du[n + i] = d1[o + i]; }
+            for (int i = t; i < v / 2; i += kGroupNT) { f[i] = q0[c + i]; f[n / 2 + i] = q1[c + i]; }
+        }
+    } else {
+        const PairPlace P0 = place(0), P1 = place(lw);
+        A.inverses(Ra, P0);
+        if (other) B.inverses(Rb, P1);
+        // dU of the child of the last level, cells of the window
+        const int lc = G.levels, nc = n0 >> lc, sc = s0 >> lc;
+        const T *f = base + dUc;
+        for (int i = t; i < (G.cells >> lc); i += kGroupNT) {
+            const bool in = sc + i >= 0 && sc + i < nc;
+            d0[off(lc) + i] = in ? f[sc + i] : T(0);
+            d1[off(lc) + i] = in ? f[nc + sc + i] : T(0);
+        }
+        __syncthreads();
+        auto add_parent = [&](int l, PairLevel<T, 1> &L, const PairPlace &P) {
+            if (!P.in(0)) return;
+            const double c0 = (double)d0[off(l + 1) + P.pair(0)], c1 = (double)d1[off(l + 1) + P.pair(0)];
+            L.du[0][0] = L.du[0][0] + c0;
+            L.du[0][1] = L.du[0][1] + c1;
+            L.du[0][2] = L.du[0][2] + c0;
+            L.du[0][3] = L.du[0][3] + c1;
+        };
+        for (int l = G.levels - 1; l >= 1; l--) {
+            if (lw == l) {
+                add_parent(l, B, P1);
+                B.smooth(nu, w, Rb, P1, nullptr, nullptr);
+                store(l, B, P1);
+            }
+            __syncthreads();
+        }
+        add_parent(0, A, P0);
+        A.smooth(nu, w, Ra, P0, nullptr, nullptr);
+        const int c = 2 * P0.pair(0), j = s0 + c;            // cell in the window, in the level
+        if (P0.own(0) && c >= G.margin && c < G.margin + G.own) {
+            if (final_update) {                              // eq. (14)
+                const auto u = ld2(U0 + j), v = ld2(U0 + N + j);
+                st2(U0 + j, u.x + tau * A.du[0][0], u.y + tau * A.du[0][2]);
+                st2(U0 + N + j, v.x + tau * A.du[0][1], v.y + tau * A.du[0][3]);
+            } else {
+                T *du = base + (src_out ? L0.dU : L0.dUo) + j;
+                st2(du, (T)A.du[0][0], (T)A.du[0][2]);
+                st2(du + n0, (T)A.du[0][1], (T)A.du[0][3]);
+            }
         }
     }
 }
@@ -1279,6 +1428,21 @@ hipError_t launch_smooth1d(const MGArgs &mg, const Tile *tiles, int ntiles, int 
     } else {
         if (nb_mask & 1) launch_smooth_t<double, 3>(mg, tiles, ntiles, mode, zero_init, final_update, src_out, tile, reverse, s);
         if (nb_mask & 2) launch_smooth_t<double, 5>(mg, tiles, ntiles, mode, zero_init, final_update, src_out, tile, reverse, s);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_group1d(const MGArgs &mg, const Tile *tiles, int ntiles, int mode, int zero_init, int final_update,
+                          int src_out, int prec, hipStream_t s)
+{
+    if (ntiles == 0) return hipSuccess;
+    const dim3 g(ntiles), b(kGroupNT);
+    if (prec == NMG_FP32_MG) {
+        if (mode == 0) hipLaunchKernelGGL((k_group<float, 0>), g, b, 0, s, mg, tiles, zero_init, final_update, src_out);
+        else hipLaunchKernelGGL((k_group<float, 1>), g, b, 0, s, mg, tiles, zero_init, final_update, src_out);
+    } else {
+        if (mode == 0) hipLaunchKernelGGL((k_group<double, 0>), g, b, 0, s, mg, tiles, zero_init, final_update, src_out);
+        else hipLaunchKernelGGL((k_group<double, 1>), g, b, 0, s, mg, tiles, zero_init, final_update, src_out);
     }
     return hipGetLastError();
 }

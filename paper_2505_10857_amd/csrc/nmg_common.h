@@ -90,6 +90,29 @@ __host__ __device__ inline int smooth_halo(int nb, int nu_a, int nu_b)
     return (h + 1) & ~1;
 }
 
+// Tile of a launch that takes up to kGroupLevels levels of three-block rows (k_group), `left` of them
+// above the bottom of the cycle: its wavefronts' windows overlap by g pairs (2 nu + 1 runs and the
+// restriction).  Going down, a level's first and last i pairs are wrong where the level before it
+// was wrong in i cells, i <- (i + 2 g) / 2, never more than 2 g; going up, u cells become
+// 2 u + 2 g.  margin covers both on the last level and is a whole number of its pairs.
+constexpr int kGroupNT = 256, kGroupLevels = 4;
+constexpr int kGroupCells = 1024;    // the bottom's largest level under grouped levels
+constexpr int kGroupTiles = 512;     // most tiles of a group of the finest level
+
+struct Group1D { int levels, g, cells, margin, own; };
+
+__host__ __device__ inline Group1D group_window(int nu, int left)
+{
+    Group1D G;
+    G.g = nu + 1;
+    G.levels = left < kGroupLevels ? left : kGroupLevels;
+    G.margin = (2 * G.g) << G.levels;
+    G.cells = 2 * (kGroupNT / 64) * (64 - 2 * G.g);
+    G.cells = G.cells > 0 ? G.cells >> G.levels << G.levels : 0;
+    G.own = G.cells - 2 * G.margin;
+    return G;
+}
+
 __host__ __device__ inline int halo_cells(int nb, int nu)
 {
     // one symmetric step = 2C half-sweeps; each moves information nb/2 cells
@@ -241,6 +264,8 @@ hipError_t launch_jacobian1d(const Inst1D *insts_dev, const Tile *tiles, int nti
                              int nb_mask, int recon, hipStream_t s, double *fused_partial = nullptr);
 hipError_t launch_coarsen1d(const MGArgs &mg, const Tile *tiles, int ntiles, int prec, hipStream_t s);
 // nt: threads of the bottom workgroup (256, 512 or 1024); it handles levels of up to 2 nt cells
+hipError_t launch_group1d(const MGArgs &mg, const Tile *tiles, int ntiles, int mode, int zero_init, int final_update,
+                          int src_out, int prec, hipStream_t s);
 hipError_t launch_bottom(const MGArgs &mg, const int *inst_list, int n, int zero_init0, int final_update,
                          int prec, int nt, hipStream_t s);
 // mode 0: pre-smoothing + restriction; 1: prolongation + post-smoothing (+ update); 2: both,
