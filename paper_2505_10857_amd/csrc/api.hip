@@ -238,8 +238,8 @@ int bottom_level(const Inst1D &I, int cells)
 }
 
 // Whether the levels above the bottom go kGroupLevels a launch.  That pays where launches are what a
-// cycle costs, one round of workgroups on the device: one channel of 12800 cells takes 0 us a cycle
-// so and 0 with a launch per level; with more cells than that, windows reread their margins and the
+// cycle costs, one round of workgroups on the device: one channel of 12800 cells takes 34 us a cycle
+// so and 60 with a launch per level; with more cells than that, windows reread their margins and the
 // deeper levels leave wavefronts idle.  Only with the default options (the others ask for launches
 // per level), and where the margins leave a quarter of a tile.
 bool group_levels(const nmg_plan *P)

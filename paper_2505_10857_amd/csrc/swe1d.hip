@@ -636,6 +636,40 @@ __device__ __forceinline__ void face_extra(const Inst1D &I, const double *sH, co
     }
 }
 
+// Rows of the cells within two of a side come from full re-evaluations with ghosts, 2 NB perturbed
+// ones and (FUSED) the unperturbed one a cell, four cells an instance.  Lane by lane in one
+// wavefront, all at once: done one after the other by the lanes of those cells they were the longest
+// chain of a small launch (k_jacobian_single at 200 cells 0 us, 0 so; one channel of 12800 cells in
+// the Newton loop 18.3, 11.5).  Item of slot c (cells 0, 1, N - 2, N - 1) and state v (0: unperturbed,
+// 1 + 2 b + m: cell j + b - NB / 2, component m): c (1 + 2 NB) + v.
+template <int NB> constexpr int kBorderStates = 1 + 2 * NB;
+
+template <int NB, bool SURF, bool FUSED>
+__device__ __forceinline__ void border_item(const Inst1D &I, const double *sH, const double *sQ, int a, int item,
+                                            double eps, double (*out)[2])
+{
+    const int c = item / kBorderStates<NB>, v = item % kBorderStates<NB>;
+    const int j = c < 2 ? c : I.N - 4 + c, t = j - a;
+    if (c >= 4 || j < 0 || j >= I.N || t < 0 || t >= kTile || (!FUSED && v == 0)) return;
+    const int pp = v == 0 ? -1 : 2 + (v - 1) / 2 - NB / 2, m = (v - 1) & 1;   // the perturbed position
+    if (v > 0 && (j + pp - 2 < 0 || j + pp - 2 >= I.N)) return;
+    double H[5], Q[5], R0, R1;
+#pragma unroll
+    for (int p = 0; p < 5; p++) {
+        H[p] = sH[t + p];
+        Q[p] = sQ[t + p];
+        if (p == pp && m == 0) H[p] = H[p] + eps;
+        if (p == pp && m == 1) Q[p] = Q[p] + eps;
+    }
+    stencil_ghosts<SURF>(H, Q, j, I);
+    if (SURF) to_surface(H, I, j);
+    const CellGeom G = load_geom<SURF>(I, j);
+    const CubicGauss W;
+    local_residual<SURF>(H, Q, G, W, I.dx, I.g, R0, R1);
+    out[item][0] = R0;
+    out[item][1] = R1;
+}
+
 // a wavefront-wide shift of v by one lane with a DPP move on each 32-bit half: CTRL 0x130 gives
 // every lane the value of lane + 1, 0x138 that of lane - 1 (the lane past the end receives 0)
 template <int CTRL>
@@ -742,6 +776,7 @@ __device__ void jacobian_tile(const Inst1D &I, int a, T *J, int stride, T *rhs,
     __shared__ FaceVals next_face[kTile / 64];       // the face after each wavefront's last face
     __shared__ double next_hl2[kTile / 64][4];       // left H states of the face after that
     __shared__ double prev_hr[kTile / 64][4];        // right H states of the face before the first
+    __shared__ double border[4 * kBorderStates<NB>][2];   // residuals of the border cells' states
     stage_state<true>(I, a, sH, sQ);   // the state, geometry and residual: last use this step
     // the coarse levels inside the tile (up to eight below the finest; an instance's levels are
     // consecutive in the level table, level l holding N / 2^l cells): their sizes and operator
@@ -786,6 +821,9 @@ __device__ void jacobian_tile(const Inst1D &I, int a, T *J, int stride, T *rhs,
     }
     if (wv == kTile / 64 - 1 && lane < kFaceExtras)
         face_extra<SURF>(I, sH, sQ, a, lane, eps, next_face[kTile / 64 - 1], next_hl2[kTile / 64 - 1], prev_hr[0]);
+    // (the last wavefront has the extra faces and the first two the coarse operators)
+    static_assert(4 * kBorderStates<NB> <= 64 && kTile / 64 == 4, "one border item a lane of wavefront 2");
+    if (wv == 2 && (a == 0 || a + kTile > I.N - 2)) border_item<NB, SURF, FUSED>(I, sH, sQ, a, lane, eps, border);
     __syncthreads();
 
     const bool valid = j < I.N;
@@ -870,41 +908,24 @@ __device__ void jacobian_tile(const Inst1D &I, int a, T *J, int stride, T *rhs,
         }
     }
     if (valid) {
-        if (!interior) {   // within two cells of a side: full re-evaluation with ghosts
-            double H[5], Q[5];
-#pragma unroll
-            for (int p = 0; p < 5; p++) { H[p] = sH[t + p]; Q[p] = sQ[t + p]; }
+        if (!interior) {   // within two cells of a side
+            const double (*const P)[2] = border + (j < 2 ? j : j - I.N + 4) * kBorderStates<NB>;
             if (FUSED) {   // R from the ghost-complete unperturbed stencil
-                double Hb[5], Qb[5];
-#pragma unroll
-                for (int p = 0; p < 5; p++) { Hb[p] = H[p]; Qb[p] = Q[p]; }
-                stencil_ghosts<SURF>(Hb, Qb, j, I);
-                if (SURF) to_surface(Hb, I, j);
-                local_residual<SURF>(Hb, Qb, G, W, I.dx, I.g, R0, R1);
+                R0 = P[0][0];
+                R1 = P[0][1];
                 n1 = fabs(R0) + fabs(R1);
                 rn = n1;
             }
-#pragma unroll 1
+#pragma unroll
             for (int b = 0; b < NB; b++) {
                 const int i = j + b - HW;
                 const bool col_ok = i >= 0 && i < I.N;
-                const int pp = 2 + b - HW;  // stencil position of the perturbed cell
-#pragma unroll 1
+#pragma unroll
                 for (int m = 0; m < 2; m++) {
                     double e0 = 0.0, e1 = 0.0;
                     if (col_ok) {
-                        double Hp[5], Qp[5];
-#pragma unroll
-                        for (int p = 0; p < 5; p++) {
-                            Hp[p] = (p == pp && m == 0) ? H[p] + eps : H[p];
-                            Qp[p] = (p == pp && m == 1) ? Q[p] + eps : Q[p];
-                        }
-                        stencil_ghosts<SURF>(Hp, Qp, j, I);
-                        if (SURF) to_surface(Hp, I, j);
-                        double P0, P1;
-                        local_residual<SURF>(Hp, Qp, G, W, I.dx, I.g, P0, P1);
-                        e0 = (P0 - R0) * ieps;
-                        e1 = (P1 - R1) * ieps;
+                        e0 = (P[1 + 2 * b + m][0] - R0) * ieps;
+                        e1 = (P[1 + 2 * b + m][1] - R1) * ieps;
                         if (b == HW) {
                             if (m == 0) e0 += I.alpha * rn;
                             else e1 += I.alpha * rn;
