@@ -697,16 +697,22 @@ struct Hit {
     NMG2D_INL bool depth() const { return k >= -1 && k <= 1 && d >= A - 1 + W && d <= A + 1 + W; }
 };
 
-template <class TL, int DIR, int W, int K, int A>
-NMG2D_INL V3 tab_state(const double *tab, const Hit &h)
+// tables of the unperturbed states alone
+struct NoHit {
+    template <int W, int K, int A>
+    NMG2D_INL int set() const { return 0; }
+};
+
+template <class TL, int DIR, int W, int K, int A, class H>
+NMG2D_INL V3 tab_state(const double *tab, const H &h)
 {
-    const double *q = tab + h.set<W, K, A>() * TL::SET + TL::template at<DIR, W, K, A>();
+    const double *q = tab + h.template set<W, K, A>() * TL::SET + TL::template at<DIR, W, K, A>();
     return V3{{q[0], q[TL::template comp<DIR>()], q[2 * TL::template comp<DIR>()]}};
 }
 
 // flux through face A in direction DIR, line order; hm, hp and b0, b1 as in face_flux_at
-template <class TL, int DIR, int A, bool SURF>
-NMG2D_INL V3 tab_flux(const double *tab, const Hit &h, double g, H2 &hm, H2 &hp, double b0, double b1)
+template <class TL, int DIR, int A, bool SURF, class H>
+NMG2D_INL V3 tab_flux(const double *tab, const H &h, double g, H2 &hm, H2 &hp, double b0, double b1)
 {
     const V3 Vm0 = tab_state<TL, DIR, 0, -1, A>(tab, h), Vm1 = tab_state<TL, DIR, 0, 0, A>(tab, h),
              Vm2 = tab_state<TL, DIR, 0, 1, A>(tab, h);
@@ -727,8 +733,8 @@ NMG2D_INL V3 tab_flux(const double *tab, const Hit &h, double g, H2 &hm, H2 &hp,
     return F;
 }
 
-template <class TL, int DIR, int W, int A>
-NMG2D_INL H2 tab_depth(const double *tab, const Hit &h)
+template <class TL, int DIR, int W, int A, class H>
+NMG2D_INL H2 tab_depth(const double *tab, const H &h)
 {
     const V3 V0 = tab_state<TL, DIR, W, -1, A>(tab, h), V1 = tab_state<TL, DIR, W, 0, A>(tab, h),
              V2 = tab_state<TL, DIR, W, 1, A>(tab, h);
@@ -829,20 +835,22 @@ constexpr unsigned column_group(int nb, int groups, int group)
 // The columns of a row are shared by CG = 512 / (TX TY) threads (wavefronts of their own, so the column
 // is uniform): 2 on the 32 x 8 tile, 8 on the 8 x 8 tile for grids too small to fill the chip with
 // the larger one.
-// 1024 x 512, J9: 2050 us with every row re-evaluating its states, 1250 with cheaper divisions, 0 so;
-// 64 x 32: 226, 150, 0.
+// 1024 x 512, J9: 2050 us with every row re-evaluating its states, 1250 with cheaper divisions, 832 so;
+// 64 x 32: 226, 150, 35.
 constexpr int kJacNT = 512;
 
+template <int TX, int TY>
+constexpr int kJacLds = 4 * JacTile<TX, TY>::SET + 4 * JacTile<TX, TY>::SX * JacTile<TX, TY>::SY;
+
 template <typename T, int NB, bool SURF, int TX, int TY>
-__global__ void __launch_bounds__(kJacNT) k_jacobian2d(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv)
+__device__ __forceinline__ void interior_rows(const Inst2D &I, const Perm2D &Pm, T *J, T *rhs, T *Dinv, int i0, int j0,
+                                              double *lds)
 {
     typedef JacTile<TX, TY> TL;
     constexpr int CG = kJacNT / (TX * TY), SX = TL::SX, SY = TL::SY;
     static_assert(TX * TY % 64 == 0 && CG <= 8, "a wavefront forms one column at a time");
-    __shared__ double s[3 * SY * SX];
-    __shared__ double zs[SURF ? SY * SX : 1];
-    __shared__ double tab[4 * TL::SET];
-    const int i0 = blockIdx.x * TX, j0 = blockIdx.y * TY, t = threadIdx.x;
+    double *const tab = lds, *const s = lds + 4 * TL::SET, *const zs = s + 3 * SY * SX;
+    const int t = threadIdx.x;
     for (int e = t; e < 3 * SY * SX; e += kJacNT) {
         const int c = e / (SY * SX), r = (e / SX) % SY, q = e % SX;
         const int i = i0 - 2 + q, j = j0 - 2 + r;
@@ -975,6 +983,13 @@ __global__ void __launch_bounds__(kJacNT) k_jacobian2d(Inst2D I, Perm2D Pm, T *J
     if (row && Dinv && (blocks & 1)) store_dinv(Dinv, o.M, o.slot, D);
 }
 
+template <typename T, int NB, bool SURF, int TX, int TY>
+__global__ void __launch_bounds__(kJacNT) k_jacobian2d(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv)
+{
+    __shared__ double lds[kJacLds<TX, TY>];
+    interior_rows<T, NB, SURF, TX, TY>(I, Pm, J, rhs, Dinv, blockIdx.x * TX, blockIdx.y * TY, lds);
+}
+
 // Face states of one column of a border row: the state of slot q at slots[(q*3 + c) * kBorderNT + lane]
 // where the perturbed cell reaches it (bit q of hits), else the row's unperturbed one at base[q*3 + c].
 template <bool SURF>
@@ -1005,6 +1020,7 @@ struct SlotFS {
 // slot q of the row (i, j): its direction, side, first cell along the line and line (runtime decode)
 struct SlotAt {
     int dir, w, t0, k;
+    SlotAt() = default;
     NMG2D_INL SlotAt(int q, int i, int j)
     {
         dir = q / 18;
@@ -1099,29 +1115,37 @@ long long border_rows2d(int Nx, int Ny)
 // whose state follows the perturbed cell (through a ghost or directly; about 7 of 36 per column),
 // forms those for the three components, and then assembles a column per thread.  Bound by the chain
 // of one state after another (every column's 36 in one thread: 81 us at 64 x 32, 470 us at
-// 1024 x 512; the list spread over the threads: 0 and 0 us).  A row takes LPR lanes of a wavefront
+// 1024 x 512; the list spread over the threads: 20 and 115 us).  A row takes LPR lanes of a wavefront
 // (32 for the 27 columns of J9, 64 for the 63 of J21), so the lanes of its three diagonal-block columns
 // can hand their FP64 values to the row's first lane, which writes the inverse of the diagonal block.
 constexpr int kBorderThreads = 256;
 
-template <typename T, int NB, bool SURF>
-__global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv,
-                                                                      long long nrows)
+template <int NB>
+struct BorderLds {
+    static constexpr int LPR = NB == 9 ? 32 : 64, RPW = kBorderNT / LPR;
+    double slots[kSlots * 3 * kBorderNT];
+    double base[RPW * kSlots * 3];
+    unsigned long long hits[RPW * NB];
+    unsigned short list[RPW * NB * kSlots];
+    int count;
+};
+
+template <typename T, int NB, bool SURF, int NT>
+__device__ __forceinline__ void border_rows(const Inst2D &I, const Perm2D &Pm, T *J, T *rhs, T *Dinv, long long r0,
+                                            long long nrows, BorderLds<NB> &B)
 {
-    constexpr int LPR = NB == 9 ? 32 : 64, RPW = kBorderNT / LPR;
-    static_assert(kBorderNT % LPR == 0, "a workgroup holds whole rows");
-    __shared__ double slots[kSlots * 3 * kBorderNT];
-    __shared__ double base[RPW * kSlots * 3];
-    __shared__ unsigned short list[RPW * NB * kSlots];
-    __shared__ unsigned long long hits[RPW * NB];
-    __shared__ int count;
+    constexpr int LPR = BorderLds<NB>::LPR, RPW = BorderLds<NB>::RPW;
+    static_assert(kBorderNT % LPR == 0 && NT >= kBorderNT, "a workgroup holds whole rows");
+    double *const slots = B.slots, *const base = B.base;
+    unsigned long long *const hits = B.hits;
+    unsigned short *const list = B.list;
+    int &count = B.count;
     const int t = threadIdx.x;
-    const long long r0 = blockIdx.x * (long long)RPW;
     const GlobalStateT<SURF> st{I.U, I.zavg, I.Nx, I.Ny};
-    for (int e = t; e < RPW * NB; e += kBorderThreads) hits[e] = 0;
+    for (int e = t; e < RPW * NB; e += NT) hits[e] = 0;
     if (t == 0) count = 0;
     __syncthreads();
-    for (int e = t; e < RPW * kSlots; e += kBorderThreads) {
+    for (int e = t; e < RPW * kSlots; e += NT) {
         const int row = e / kSlots, q = e - row * kSlots;
         if (r0 + row >= nrows) continue;
         int i, j;
@@ -1130,7 +1154,7 @@ __global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, 
 #pragma unroll
         for (int c = 0; c < 3; c++) base[(row * kSlots + q) * 3 + c] = v.c[c];
     }
-    for (int e = t; e < RPW * NB * kSlots; e += kBorderThreads) {
+    for (int e = t; e < RPW * NB * kSlots; e += NT) {
         const int rb = e / kSlots, q = e - rb * kSlots, row = rb / NB, b = rb - row * NB;
         if (r0 + row >= nrows) continue;
         int i, j;
@@ -1141,7 +1165,7 @@ __global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, 
         list[atomicAdd(&count, 1)] = (unsigned short)e;      // in any order: the states are independent
     }
     __syncthreads();
-    for (int e = t; e < 3 * count; e += kBorderThreads) {
+    for (int e = t; e < 3 * count; e += NT) {
         const int m = e % 3, x = list[e / 3], rb = x / kSlots, q = x - rb * kSlots, row = rb / NB, b = rb - row * NB;
         int i, j;
         border_cell(I, r0 + row, i, j);
@@ -1200,12 +1224,143 @@ __global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, 
     if (active && col == 0) store_dinv(Dinv, Pm.M, slot, D);
 }
 
+template <typename T, int NB, bool SURF>
+__global__ void __launch_bounds__(kBorderThreads) k_jacobian2d_border(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv,
+                                                                      long long nrows)
+{
+    __shared__ BorderLds<NB> B;
+    border_rows<T, NB, SURF, kBorderThreads>(I, Pm, J, rhs, Dinv, blockIdx.x * (long long)BorderLds<NB>::RPW, nrows, B);
+}
+
+// The whole Jacobian of a grid too small to fill the chip, in one launch: the interior rows' 8 x 8 tiles
+// in the first workgroups, the border rows in the others, side by side (64 x 32: 55 us one after the
+// other, 35 so).
+template <typename T, int NB, bool SURF>
+__global__ void __launch_bounds__(kJacNT) k_jacobian2d_small(Inst2D I, Perm2D Pm, T *J, T *rhs, T *Dinv, int gx, int ntiles,
+                                                             long long nrows)
+{
+    __shared__ union Lds {
+        double d[kJacLds<8, 8>];
+        BorderLds<NB> b;
+    } lds;
+    const int g = blockIdx.x;
+    if (g < ntiles) interior_rows<T, NB, SURF, 8, 8>(I, Pm, J, rhs, Dinv, g % gx * 8, g / gx * 8, lds.d);
+    else border_rows<T, NB, SURF, kJacNT>(I, Pm, J, rhs, Dinv, (g - ntiles) * (long long)BorderLds<NB>::RPW, nrows, lds.b);
+}
+
+// ---- residual of a small grid ---------------------------------------------------------------
+// The tile and the order of its sums are k_residual2d's, on four times the threads: the face states
+// spread over them, each cell's four face fluxes side by side.  A grid too small to fill the chip waits
+// for the chain in one thread (64 x 32: 23.5 us with a cell a thread, 12.7 so).
+constexpr int kWideNT = 4 * kTX * kTY;
+
+template <bool SURF>
+__global__ void __launch_bounds__(kWideNT) k_residual2d_wide(Inst2D I, double *partial)
+{
+    typedef JacTile<kTX, kTY> TL;
+    constexpr int CELLS = kTX * kTY, NW = CELLS / 64;
+    __shared__ double s[3 * kSY * kSX];
+    __shared__ double zs[SURF ? kSY * kSX : 1];
+    __shared__ double tab[TL::SET];
+    __shared__ double part[4][5][CELLS];       // per face: its flux, the depths at it
+    __shared__ double red[NW];
+    const int i0 = blockIdx.x * kTX, j0 = blockIdx.y * kTY, t = threadIdx.x;
+    stage_tile(I, i0, j0, s, t, kWideNT, SURF ? zs : nullptr);
+    __syncthreads();
+    const LdsStateT<SURF> st{s, zs, i0, j0};
+    for (int e = t; e < 2 * TL::STATES; e += kWideNT) {
+        const int dir = e / TL::STATES, q = e - dir * TL::STATES, W = q / (TL::STATES / 2), f = q - W * (TL::STATES / 2);
+        const int per = dir ? TL::YA - 1 : TL::XA - 1, line = f / per, a = f - line * per + (W ? 0 : 1);
+        const int t0 = (dir ? j0 : i0) - 3 + a + W, k = (dir ? i0 : j0) - 1 + line;
+        if (t0 + 2 > (dir ? I.Ny : I.Nx) + 1 || k > (dir ? I.Nx : I.Ny)) continue;   // of no cell of the grid
+        SlotAt at;
+        at.dir = dir; at.w = W; at.t0 = t0; at.k = k;
+        const V3 v = slot_state(I, st, at, -1000, -1000, 0, 0.0);
+        double *w = tab + (dir ? TL::XS + (W * TL::YL + line) * TL::YA : (W * TL::XL + line) * TL::XA) + a;
+        const int comp = dir ? TL::template comp<1>() : TL::template comp<0>();
+        w[0] = v.c[0];
+        w[comp] = v.c[dir ? 2 : 1];
+        w[2 * comp] = v.c[dir ? 1 : 2];
+    }
+    __syncthreads();
+    const int cell = t % CELLS, face = __builtin_amdgcn_readfirstlane(t / CELLS);
+    const int xi = cell % kTX, xj = cell / kTX, i = i0 + xi, j = j0 + xj;
+    const bool in = i < I.Nx && j < I.Ny;
+    double zx[4] = {}, zy[4] = {}, zc = 0.0;
+    if (SURF && in) {
+        const long long fx = ((long long)j * (I.Nx + 1) + i) * 2, fy = ((long long)j * I.Nx + i) * 2;
+#pragma unroll
+        for (int q = 0; q < 2; q++) {
+            zx[q] = I.zfx[fx + q];
+            zx[2 + q] = I.zfx[fx + 2 + q];
+            zy[q] = I.zfy[fy + q];
+            zy[2 + q] = I.zfy[fy + 2 * I.Nx + q];
+        }
+        zc = zs[(xj + 2) * kSX + xi + 2];
+    }
+    const double *const tx = tab + xj * TL::XA + xi, *const ty = tab + xi * TL::YA + xj;
+    const NoHit none;
+    if (in) {
+        V3 F;
+        H2 dum, at;
+        if (face == 0) F = tab_flux<TL, 0, -1, SURF>(tx, none, I.g, dum, at, zx[0], zx[1]);
+        else if (face == 1) F = tab_flux<TL, 0, 0, SURF>(tx, none, I.g, at, dum, zx[2], zx[3]);
+        else if (face == 2) F = tab_flux<TL, 1, -1, SURF>(ty, none, I.g, dum, at, zy[0], zy[1]);
+        else F = tab_flux<TL, 1, 0, SURF>(ty, none, I.g, at, dum, zy[2], zy[3]);
+#pragma unroll
+        for (int c = 0; c < 3; c++) part[face][c][cell] = F.c[c];
+#pragma unroll
+        for (int c = 0; c < 2; c++) part[face][3 + c][cell] = at.g[c];
+    }
+    __syncthreads();
+    if (t >= CELLS) return;                    // the cells' own threads are the first ones
+    double n1 = 0.0;
+    if (in) {
+        double bx[4], by[4];
+        load_slopes(I, i, j, bx, by);
+        RowParts r;
+        auto flux = [&](int f) { return V3{{part[f][0][cell], part[f][1][cell], part[f][2][cell]}}; };
+        auto depth = [&](int f) { return H2{{part[f][3][cell], part[f][4][cell]}}; };
+        r.fxm = flux(0); r.fxp = flux(1); r.fym = flux(2); r.fyp = flux(3);
+        r.hx[1] = depth(0); r.hx[2] = depth(1); r.hy[1] = depth(2); r.hy[2] = depth(3);
+        r.hx[0] = tab_depth<TL, 0, 1, -2>(tx, none);
+        r.hx[3] = tab_depth<TL, 0, 0, 1>(tx, none);
+        r.hy[0] = tab_depth<TL, 1, 1, -2>(ty, none);
+        r.hy[3] = tab_depth<TL, 1, 0, 1>(ty, none);
+        const double eta = SURF ? st(0, i, j) + zc : 0.0;
+        const V3 R = row_residual<SURF>(r, I, Recip(I.dx), Recip(I.dy), Recip(I.dx * I.dy), bx, by, zx, zy, eta);
+        const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
+        I.R[cidx] = R.c[0];
+        I.R[n + cidx] = R.c[1];
+        I.R[2 * n + cidx] = R.c[2];
+        n1 = fabs(R.c[0]) + fabs(R.c[1]) + fabs(R.c[2]);
+        I.rn[cidx] = n1;
+    }
+    for (int off = 32; off > 0; off >>= 1) n1 += __shfl_down(n1, off, 64);
+    if ((t & 63) == 0) red[t >> 6] = n1;
+    __syncthreads();
+    if (t == 0 && partial) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; w++) sum += red[w];
+        partial[blockIdx.y * gridDim.x + blockIdx.x] = sum;
+    }
+}
+
 // ---- launchers ---------------------------------------------------------------------------
+
+// fewer cells than fill every compute unit (256) with a 32 x 8 tile: what one workgroup waits for is
+// spread over more threads or workgroups instead
+static bool few_cells(const Inst2D &I) { return (long long)I.Nx * I.Ny < 256LL * kTX * kTY; }
 
 hipError_t launch_residual2d(const Inst2D &I, double *partial, hipStream_t s)
 {
     dim3 grid((I.Nx + kTX - 1) / kTX, (I.Ny + kTY - 1) / kTY);
-    if (I.recon == NMG_RECON_SURFACE) hipLaunchKernelGGL(k_residual2d<true>, grid, dim3(kTX, kTY), 0, s, I, partial);
+    const bool surf = I.recon == NMG_RECON_SURFACE;
+    if (few_cells(I)) {
+        if (surf) hipLaunchKernelGGL(k_residual2d_wide<true>, grid, dim3(kWideNT), 0, s, I, partial);
+        else hipLaunchKernelGGL(k_residual2d_wide<false>, grid, dim3(kWideNT), 0, s, I, partial);
+    } else if (surf) hipLaunchKernelGGL(k_residual2d<true>, grid, dim3(kTX, kTY), 0, s, I, partial);
     else hipLaunchKernelGGL(k_residual2d<false>, grid, dim3(kTX, kTY), 0, s, I, partial);
     return hipGetLastError();
 }
@@ -1222,20 +1377,25 @@ hipError_t launch_res2d_finalize(const double *partial, int ntiles, long long nc
 template <typename T, int NB, bool SURF>
 static hipError_t jacobian2d_t(const Inst2D &I, const Perm2D &P, T *J, T *rhs, T *Dinv, hipStream_t s)
 {
-    constexpr int RPW = kBorderNT / (NB == 9 ? 32 : 64);
-    // the 32 x 8 tile once it fills every compute unit (256): below that the smaller tile spreads the
-    // same rows over four times the workgroups
-    if ((long long)I.Nx * I.Ny >= 256LL * 32 * 8)
-        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 32, 8>), dim3((I.Nx + 31) / 32, (I.Ny + 7) / 8), dim3(kJacNT), 0, s,
-                           I, P, J, rhs, Dinv);
+    const long long nb = border_rows2d(I.Nx, I.Ny);
+    const unsigned groups = (unsigned)((nb + BorderLds<NB>::RPW - 1) / BorderLds<NB>::RPW);
+    const int gx = (I.Nx + 7) / 8, tiles = gx * ((I.Ny + 7) / 8);
+    // interior and border rows in one launch while their workgroups are at most two rounds of two a
+    // compute unit: beyond that the border rows' own launch, of smaller workgroups, is the faster one
+    // (256 x 128, J21, 1264 workgroups: 223 us in one launch, 210 in two; J9, 888: 155 and 161)
+    if (few_cells(I) && tiles + (long long)groups <= 1024) {
+        hipLaunchKernelGGL((k_jacobian2d_small<T, NB, SURF>), dim3(tiles + groups), dim3(kJacNT), 0, s, I, P, J, rhs, Dinv,
+                           gx, tiles, nb);
+        return hipGetLastError();
+    }
+    if (few_cells(I))
+        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 8, 8>), dim3(gx, (I.Ny + 7) / 8), dim3(kJacNT), 0, s, I, P, J, rhs, Dinv);
     else
-        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 8, 8>), dim3((I.Nx + 7) / 8, (I.Ny + 7) / 8), dim3(kJacNT), 0, s,
+        hipLaunchKernelGGL((k_jacobian2d<T, NB, SURF, 32, 8>), dim3((I.Nx + 31) / 32, (I.Ny + 7) / 8), dim3(kJacNT), 0, s,
                            I, P, J, rhs, Dinv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long nb = border_rows2d(I.Nx, I.Ny);
-    hipLaunchKernelGGL((k_jacobian2d_border<T, NB, SURF>), dim3((unsigned)((nb + RPW - 1) / RPW)), dim3(kBorderThreads),
-                       0, s, I, P, J, rhs, Dinv, nb);
+    hipLaunchKernelGGL((k_jacobian2d_border<T, NB, SURF>), dim3(groups), dim3(kBorderThreads), 0, s, I, P, J, rhs, Dinv, nb);
     return hipGetLastError();
 }
 
