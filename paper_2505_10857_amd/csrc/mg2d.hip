@@ -63,7 +63,7 @@ __device__ __forceinline__ void inv3d(const double A[9], double B[9])
 // blocks of the 2x2 children rows against the 2x2 children of the neighbour; for the centre also D^{-1}.
 // The block of every pair of children is known at compile time, so a thread's loads (at most 16
 // blocks of nine) issue together; an offset per thread, a fifth of the row each, keeps the small
-// levels' few cells from being one long chain (37 -> 0 us for a 32 x 16 coarse level).
+// levels' few cells from being one long chain (37 -> 6.5 us for a 32 x 16 coarse level).
 template <typename T, int NB, int BC>
 __device__ __forceinline__ void coarsen_block(T *mg, const Level2D &Lf, const Level2D &Lc, int I, int Jq)
 {
@@ -692,7 +692,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         flags[k] = (valid ? c + 1 : 0) | (own ? 16 : 0) | (read ? 32 : 0);
         q[k] = valid ? (j - dj0) * ld + (i - di0) : 0;
         if (valid) {
-            const long long cc = perm2d(L.P, i, j);
+            const long long cc = perm2d_rows(L.P, i, j);
 #pragma unroll
             for (int b = 1; b < NB; b++) {
                 const int pi = i + stencil_dx(NB, b), pj = j + stencil_dy(NB, b);
@@ -746,8 +746,8 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     __syncthreads();
     for (int e = t; e < dw * dh; e += kResNT) {
         const int r = e / dw, i = di0 + e - r * dw, j = dj0 + r;
-        const long long fc = perm2d(L.P, i, j);
-        const long long pc = A.prolong ? perm2d(A.Lc.P, i >> 1, j >> 1) : 0;
+        const long long fc = perm2d_rows(L.P, i, j);
+        const long long pc = A.prolong ? perm2d_rows(A.Lc.P, i >> 1, j >> 1) : 0;
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             T v = mg[L.dU + c * n + fc];
@@ -903,7 +903,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
-        const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
+        const long long cc = perm2d_rows(L.P, cell_i(k), cell_j(k));
 #pragma unroll
         for (int c = 0; c < ROWS; c++) mg[L.dU + (row + c) * n + cc] = bad ? (T)__builtin_nan("") : su[q[k]].v[row + c];
     }
@@ -915,7 +915,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
         const Cell *u = su + q[k];
-        const long long cc = perm2d(L.P, cell_i(k), cell_j(k));
+        const long long cc = perm2d_rows(L.P, cell_i(k), cell_j(k));
         const double y0 = (double)u->v[0], y1 = (double)u->v[1], y2 = (double)u->v[2];
 #pragma unroll
         for (int x = 0; x < ROWS; x++)
@@ -976,7 +976,7 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 // first, after as many cells of colours 0 and 2 as leave each of them one streamed cell a thread.  The
 // rest is streamed in every pass, contiguously (tiled order), and that is the bound: about 7.6 TB/s
 // from the memory-side cache, which the streamed part fits (235 MB; all rows: 6.1-6.6 TB/s).
-// 1024 x 512 FP64: 25.8 us a pass as separate launches, 0 so; FP32 13.6, 0.
+// 1024 x 512 FP64: 25.8 us a pass as separate launches, 14.2 so; FP32 13.6, 5.7.
 constexpr int kStrCells = 2600;                  // LDS cells of a tile with a ring of two
 constexpr int kLdsRows = 64;                     // colour 1 rows held in LDS
 constexpr int kRowValues = 84;                   // eight off-diagonal blocks, D^{-1}, right-hand side
@@ -1352,7 +1352,7 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
 // Both are chains of M <= 120 dependent steps, bound by what one step costs.  The factorisation keeps
 // the matrix in registers (lane l of wavefront w has rows l and l + 64 of the columns w, w + 16, ...),
 // so a step is the owning wavefront's pivot search and multipliers, one barrier, and every
-// wavefront's update (270 -> 0 us at M = 96 with the matrix in LDS and five barriers a step).  Rows
+// wavefront's update (270 -> 104 us at M = 96, before with the matrix in LDS and five barriers a step).  Rows
 // are interchanged by number only.  The solve runs in one wavefront with x in registers, without
 // barriers.
 struct CoarseLU {

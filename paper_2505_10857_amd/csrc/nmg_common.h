@@ -176,17 +176,25 @@ __host__ __device__ inline void tile3_cell(int c, int i0, int j0, int w, int p, 
     il = tile3_first(c, i0, j0, jr) + 3 * rem;
 }
 
-__host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
+// the orders without tiles (a level that a resident or one-workgroup kernel holds never has the tiled
+// one; without that case the kernels need fewer registers)
+__host__ __device__ inline long long perm2d_rows(const Perm2D &P, int i, int j)
 {
     if (P.C == 9) return (long long)(i % 3 + 3 * (j % 3)) * P.ny * P.W + (long long)(j / 3) * P.W + i / 3;
     const int c = (i + j) % P.C;
+    const int ic = ((c - j) % P.C + P.C) % P.C;
+    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
+}
+
+__host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
+{
     if (P.tw > 0) {
+        const int c = (i + j) % P.C;
         const int ti = i / P.tw, tj = j / P.th, i0 = ti * P.tw, j0 = tj * P.th;
         const int w = P.nx - i0 < P.tw ? P.nx - i0 : P.tw;
         return ((long long)c * P.ny + tj * P.gx + ti) * P.W + tile3_pos(c, i0, j0, w, i - i0, j - j0);
     }
-    const int ic = ((c - j) % P.C + P.C) % P.C;
-    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
+    return perm2d_rows(P, i, j);
 }
 
 inline Perm2D make_perm2d(int nx, int ny, int C)
