@@ -492,22 +492,38 @@ MGArgs mg_args(const nmg_plan *P, char *ws, bool with_state)
 // from pinned memory.
 nmg_status upload_tables(nmg_plan *P, char *ws, double *const *U, hipStream_t s)
 {
-    if (P->tables_ws != ws) {
-        std::vector<char> h(P->off_state - P->off_levs, 0);
-        const size_t b = P->off_levs;
-        memcpy(h.data() + P->off_levs - b, P->levs.data(), sizeof(Level1D) * P->levs.size());
-        if (!P->tiles.empty())
-            memcpy(h.data() + P->off_tiles - b, P->tiles.data(), sizeof(Tile) * P->tiles.size());
-        std::vector<int> list(P->n);
-        for (int k = 0; k < P->n; k++) list[k] = k;
-        memcpy(h.data() + P->off_list - b, list.data(), sizeof(int) * P->n);
-        HIP_TRY(hipMemcpyAsync(ws + b, h.data(), h.size(), hipMemcpyHostToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        P->tables_ws = ws;
-    }
     const size_t isz = sizeof(Inst1D) * P->n;
-    if (!P->host_tables) HIP_TRY(pinned_get((void **)&P->host_tables, isz));
-    else HIP_TRY(hipStreamSynchronize(s));   // the previous upload from this buffer has landed
+    auto static_tables = [&](char *to, size_t base) {   // at their offsets less base
+        memcpy(to + P->off_levs - base, P->levs.data(), sizeof(Level1D) * P->levs.size());
+        if (!P->tiles.empty()) memcpy(to + P->off_tiles - base, P->tiles.data(), sizeof(Tile) * P->tiles.size());
+        int *list = reinterpret_cast<int *>(to + P->off_list - base);
+        for (int k = 0; k < P->n; k++) list[k] = k;
+    };
+    // the first use of a workspace: everything in one copy from one pinned block, without a wait, where
+    // that is small (a single V-cycle call is a plan's first use: 90 us with two copies, 70 so)
+    const bool whole = P->tables_ws != ws && !P->host_borrowed && P->off_state <= (size_t(1) << 20);
+    if (whole) {
+        char *h = nullptr;
+        HIP_TRY(pinned_get((void **)&h, P->off_state));
+        if (P->host_tables) {
+            const hipError_t e = hipStreamSynchronize(s);   // the previous upload from it has landed
+            pinned_put(P->host_tables);
+            P->host_tables = h;
+            HIP_TRY(e);
+        }
+        P->host_tables = h;
+        static_tables(h, 0);
+    } else {
+        if (P->tables_ws != ws) {
+            std::vector<char> h(P->off_state - P->off_levs, 0);
+            static_tables(h.data(), P->off_levs);
+            HIP_TRY(hipMemcpyAsync(ws + P->off_levs, h.data(), h.size(), hipMemcpyHostToDevice, s));
+            HIP_TRY(hipStreamSynchronize(s));
+            P->tables_ws = ws;
+        }
+        if (!P->host_tables) HIP_TRY(pinned_get((void **)&P->host_tables, isz));
+        else HIP_TRY(hipStreamSynchronize(s));   // the previous upload from this buffer has landed
+    }
     for (int k = 0; k < P->n; k++) {
         Inst1D I = P->insts[k];
         I.U = U ? U[k] : nullptr;
@@ -515,9 +531,11 @@ nmg_status upload_tables(nmg_plan *P, char *ws, double *const *U, hipStream_t s)
         I.rn = I.R + 2 * (size_t)I.N;
         I.hist = reinterpret_cast<double *>(ws + P->off_hist) + (size_t)k * std::max(1, P->max_hist);
         I.n_start = P->n_start.empty() ? 0 : P->n_start[k];
-        memcpy(P->host_tables + sizeof(Inst1D) * k, &I, sizeof(Inst1D));
+        memcpy(P->host_tables + P->off_insts + sizeof(Inst1D) * k, &I, sizeof(Inst1D));
     }
-    HIP_TRY(hipMemcpyAsync(ws + P->off_insts, P->host_tables, isz, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(ws + P->off_insts, P->host_tables + P->off_insts, whole ? P->off_state : isz,
+                           hipMemcpyHostToDevice, s));
+    if (whole) P->tables_ws = ws;
     return NMG_OK;
 }
 

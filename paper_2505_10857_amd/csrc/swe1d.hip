@@ -639,7 +639,7 @@ __device__ __forceinline__ void face_extra(const Inst1D &I, const double *sH, co
 // Rows of the cells within two of a side come from full re-evaluations with ghosts, 2 NB perturbed
 // ones and (FUSED) the unperturbed one a cell, four cells an instance.  Lane by lane in one
 // wavefront, all at once: done one after the other by the lanes of those cells they were the longest
-// chain of a small launch (k_jacobian_single at 200 cells 0 us, 0 so; one channel of 12800 cells in
+// chain of a small launch (k_jacobian_single at 200 cells 17.0 us, 8.2 so; one channel of 12800 cells in
 // the Newton loop 18.3, 11.5).  Item of slot c (cells 0, 1, N - 2, N - 1) and state v (0: unperturbed,
 // 1 + 2 b + m: cell j + b - NB / 2, component m): c (1 + 2 NB) + v.
 template <int NB> constexpr int kBorderStates = 1 + 2 * NB;
