@@ -10,6 +10,7 @@
 //   mg       : per instance and level: J [nb*4][n_l], rhs [2][n_l], dU [2][n_l]
 //              in double (NMG_FP64) or float (NMG_FP32_MG)
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -737,13 +738,27 @@ nmg_status read_state(nmg_plan *P, char *ws, hipStream_t s)
     return NMG_OK;
 }
 
+// A plan's own stream.  The runtime opens a hardware queue a stream, four in all, and one for
+// cooperative launches (the 2D solver's resident levels) at the first of those; opened after the four,
+// it makes every cooperative launch of the process about 70 us longer (160 x 96, FP32, three cycles:
+// 4.9 ms, 3.1 with the queue opened before).  So the first own stream of a device opens it.
+hipError_t make_own_stream(hipStream_t *s)
+{
+    static std::atomic<unsigned long long> opened{0};
+    hipError_t e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+    int dev = 0;
+    if (e == hipSuccess && hipGetDevice(&dev) == hipSuccess && dev < 64 && !(opened.fetch_or(1ULL << dev) >> dev & 1))
+        if (open_cooperative_queue(*s) != hipSuccess) (void)hipGetLastError();   // no such launches then
+    return e;
+}
+
 nmg_status plan_steps(nmg_plan *P, char *ws, int steps, int use_graph, hipStream_t s)
 {
     if (use_graph) {
         if (!P->gexec || P->g_ws != ws) {
             hipStream_t cs = s;
             if (cs == nullptr) {   // the null stream cannot be captured: capture on the plan's own
-                if (!P->own_stream) HIP_TRY(hipStreamCreateWithFlags(&P->own_stream, hipStreamNonBlocking));
+                if (!P->own_stream) HIP_TRY(make_own_stream(&P->own_stream));
                 cs = P->own_stream;
             }
             HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));

@@ -1970,6 +1970,13 @@ static Resident2DArgs resident_args(const Level2D &L, const Level2D &Lc, const R
     return A;
 }
 
+__global__ void k_nothing() {}
+
+hipError_t open_cooperative_queue(hipStream_t s)
+{
+    return hipLaunchCooperativeKernel(reinterpret_cast<void *>(k_nothing), dim3(1), dim3(64), nullptr, 0, s);
+}
+
 hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s)

@@ -336,6 +336,8 @@ long long resident2d_max_cells(int nb);
 size_t resident2d_box_bytes(long long cells, int prec);
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m);
 // [prolongation from Lc +] nu smoothing iterations [+ restriction to Lc] in one cooperative launch
+// an empty cooperative launch
+hipError_t open_cooperative_queue(hipStream_t s);
 hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s);
