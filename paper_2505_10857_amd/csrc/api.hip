@@ -1113,8 +1113,8 @@ nmg_status nmg_residual(const nmg_desc *desc, const double *U, double *R, double
     I.R = R;
     I.rn = rn;
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(launch_residual1d(nullptr, nullptr, 0, &I, nullptr, nullptr, I.recon, s));
-    if (res_dev) HIP_TRY(launch_sum_res(rn, I.N, res_dev, s));
+    HIP_TRY(launch_residual1d(nullptr, nullptr, 0, &I, nullptr, res_dev, I.recon, s));
+    if (res_dev && !residual1d_sums(I.N)) HIP_TRY(launch_sum_res(rn, I.N, res_dev, s));
     return NMG_OK;
 }
 

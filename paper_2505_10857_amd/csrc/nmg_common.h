@@ -257,6 +257,8 @@ struct Level2D {
 
 // residual over tiles (batched: tiles index instances) or one instance (tiles == null)
 // recon: the reconstruction of every instance in the launch (NMG_RECON_*)
+// whether a single instance's residual launch writes res itself (its `partial`)
+bool residual1d_sums(int N);
 hipError_t launch_residual1d(const Inst1D *insts_dev, const Tile *tiles, int ntiles,
                              const Inst1D *single, NewtonState *state, double *partial, int recon,
                              hipStream_t s);

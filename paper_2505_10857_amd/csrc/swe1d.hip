@@ -377,11 +377,11 @@ __device__ __forceinline__ void to_surface(double H[5], const Inst1D &I, int j)
     for (int p = 0; p < 5; p++) H[p] = H[p] + I.z_avg[j + p];
 }
 
+// the residual of a tile's cells; returns the thread's cell's ||R_j||_1
 template <bool SURF>
-__device__ void residual_tile(const Inst1D &I, int a, double *partial_out)
+__device__ double residual_tile(const Inst1D &I, int a)
 {
     __shared__ double sH[kTile + 4], sQ[kTile + 4];
-    __shared__ double red[kTile / 64];
     stage_state(I, a, sH, sQ);
     __syncthreads();
     const int j = a + threadIdx.x;
@@ -401,8 +401,7 @@ __device__ void residual_tile(const Inst1D &I, int a, double *partial_out)
         n1 = fabs(R0) + fabs(R1);
         I.rn[j] = n1;
     }
-    double s = block_sum(n1, red);
-    if (threadIdx.x == 0 && partial_out) *partial_out = s;
+    return n1;
 }
 
 template <bool SURF>
@@ -412,13 +411,28 @@ __global__ void __launch_bounds__(kTile) k_residual_batch(const Inst1D *insts, c
     const Tile t = tiles[blockIdx.x];
     const Inst1D &I = insts[t.lev];
     if (!inst_active(state, I)) return;
-    residual_tile<SURF>(I, t.a, partial + blockIdx.x);
+    __shared__ double red[kTile / 64];
+    const double s = block_sum(residual_tile<SURF>(I, t.a), red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// One workgroup may take all tiles, one after the other: its sum in k_sum_res's order then is res, and
+// the call is one launch.  Up to kResTiles tiles that is the cheaper way: the host's launches are what
+// such a call costs (residual and Jacobian, 200 cells: 23.8 us with a launch for the sum, 20.5 without).
+constexpr int kResTiles = 4;
+
 template <bool SURF>
-__global__ void __launch_bounds__(kTile) k_residual_single(Inst1D I)
+__global__ void __launch_bounds__(kTile) k_residual_single(Inst1D I, double *res)
 {
-    residual_tile<SURF>(I, blockIdx.x * kTile, nullptr);
+    __shared__ double red[kTile / 64];
+    double v = 0.0;
+    for (int a = blockIdx.x * kTile; a < I.N; a += gridDim.x * kTile) {
+        v += residual_tile<SURF>(I, a);
+        __syncthreads();
+    }
+    if (gridDim.x > 1) return;
+    const double s = block_sum(v, red);
+    if (threadIdx.x == 0 && res) *res = s / I.N;
 }
 
 // res = (1/N) sum_j rn_j for a single instance: one workgroup, fixed order (thread t adds cells t,
@@ -1039,8 +1053,9 @@ hipError_t launch_residual1d(const Inst1D *insts_dev, const Tile *tiles, int nti
     const bool surf = recon == NMG_RECON_SURFACE;
     if (single) {
         int nt = (single->N + kTile - 1) / kTile;
-        if (surf) hipLaunchKernelGGL(k_residual_single<true>, dim3(nt), dim3(kTile), 0, s, *single);
-        else hipLaunchKernelGGL(k_residual_single<false>, dim3(nt), dim3(kTile), 0, s, *single);
+        if (nt <= kResTiles) nt = 1;
+        if (surf) hipLaunchKernelGGL(k_residual_single<true>, dim3(nt), dim3(kTile), 0, s, *single, partial);
+        else hipLaunchKernelGGL(k_residual_single<false>, dim3(nt), dim3(kTile), 0, s, *single, partial);
     } else {
         if (ntiles == 0) return hipSuccess;
         if (surf)
@@ -1060,6 +1075,8 @@ hipError_t launch_res_finalize(const Inst1D *insts_dev, int ninst, NewtonState *
                        partial, init);
     return hipGetLastError();
 }
+
+bool residual1d_sums(int N) { return N <= kResTiles * kTile; }
 
 hipError_t launch_sum_res(const double *rn, int N, double *res, hipStream_t s)
 {
