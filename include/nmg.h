@@ -339,9 +339,11 @@ nmg_status nmg_plan_profile_read(nmg_plan *plan, double *ms, int32_t *launches);
  * selects the defaults.
  *   bottom_cells: the levels of each instance with at most this many cells (256, 512, 1024 or
  *     2048; the coarsest level always) run in the one-workgroup-per-instance bottom-of-cycle
- *     kernel, whose workgroup size follows (bottom_cells / 2, at least 256, at most 1024); the
- *     larger levels run in the tiled smoothers.  A small value spreads more levels over the
- *     whole GPU, a large one saves launches and synchronisation.  Default 2048.
+ *     kernel, with two or four cells a thread; the larger levels run in the tiled smoothers.  A
+ *     small value spreads more levels over the whole GPU, a large one saves launches and
+ *     synchronisation.  Default 2048.  With every tunable at its default, a plan whose finest levels
+ *     are covered by one round of workgroups takes several levels a launch above a bottom of at
+ *     most 1024 cells instead.
  *   smooth_tile: cells (= threads) per tile of the tiled smoother, 256 or 512 (0: 256).
  *   split_finest: 0 (default) runs the finest level's post-smoothing of one V-cycle and the
  *     pre-smoothing of the next in one launch where the plan allows it (multigrid plans with

@@ -738,17 +738,23 @@ nmg_status read_state(nmg_plan *P, char *ws, hipStream_t s)
     return NMG_OK;
 }
 
-// A plan's own stream.  The runtime opens a hardware queue a stream, four in all, and one for
-// cooperative launches (the 2D solver's resident levels) at the first of those; opened after the four,
-// it makes every cooperative launch of the process about 70 us longer (160 x 96, FP32, three cycles:
-// 4.9 ms, 3.1 with the queue opened before).  So the first own stream of a device opens it.
-hipError_t make_own_stream(hipStream_t *s)
+// The runtime opens a hardware queue a stream, four in all (one more for each stream with a mask of
+// compute units), and one for cooperative launches (the 2D solver's resident levels) at the first of
+// those; opened after the others, it makes every cooperative launch of the process about 70 us longer
+// (160 x 96, FP32, three cycles: 4.9 ms, 3.1 with the queue opened before).  So the first stream
+// that the library makes on a device opens it.
+void first_stream(hipStream_t s)
 {
     static std::atomic<unsigned long long> opened{0};
-    hipError_t e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
     int dev = 0;
-    if (e == hipSuccess && hipGetDevice(&dev) == hipSuccess && dev < 64 && !(opened.fetch_or(1ULL << dev) >> dev & 1))
-        if (open_cooperative_queue(*s) != hipSuccess) (void)hipGetLastError();   // no such launches then
+    if (hipGetDevice(&dev) == hipSuccess && dev < 64 && !(opened.fetch_or(1ULL << dev) >> dev & 1))
+        if (open_cooperative_queue(s) != hipSuccess) (void)hipGetLastError();   // no such launches then
+}
+
+hipError_t make_own_stream(hipStream_t *s)
+{
+    const hipError_t e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+    if (e == hipSuccess) first_stream(*s);
     return e;
 }
 
@@ -916,6 +922,7 @@ nmg_status nmg_lane_stream_create(void **stream)
     if (cus % 32) mask.back() = (1u << (cus % 32)) - 1u;
     hipStream_t s = nullptr;
     HIP_TRY(hipExtStreamCreateWithCUMask(&s, (uint32_t)mask.size(), mask.data()));
+    first_stream(s);
     *stream = s;
     return NMG_OK;
 }

@@ -13,9 +13,12 @@
 //    right-hand side of eq. (17), the post-smoothing kernel first adds the prolongation of
 //    eq. (18) (and, at the finest level after the last cycle, applies the Newton update of
 //    eq. 14).  HBM traffic per level and phase is one read of the operator.
+//  * k_group: the same for up to four levels of a tile in one launch, for few cells in all.
 //  * k_bottom: all small levels of one instance in one workgroup: smoothing and restriction
 //    down, the coarsest system solved exactly (up to rounding) by block parallel cyclic
 //    reduction, prolongation and smoothing back up.
+// The last two hold a level as pairs of cells with one parent (PairLevel), neighbours in adjacent
+// lanes.
 #include "nmg_common.h"
 
 namespace nmg {

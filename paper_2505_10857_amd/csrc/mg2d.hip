@@ -1,7 +1,12 @@
 // Geometric multigrid for the 2D regularised Newton systems (section 4.2, eq. 22-25) on gfx950:
 // coarse operators of eq. (24) (cross stencil -> five points on level 1, five points -> five
 // points below), multicolour block SOR passes (eq. 22), restriction, injection prolongation,
-// and Gaussian elimination with partial pivoting on the coarsest grid (dense, in LDS).
+// and Gaussian elimination with partial pivoting on the coarsest grid (dense, in registers).
+//
+// A smoothing phase of a level (all its colour passes) is one cooperative launch wherever the level's
+// rows fit the registers of the chip (k_resident2d), or most of them do (k_streamed2d); launches per
+// pass (k_smooth2d_pass) take its place where a cooperative launch is not possible.  Levels of
+// at most 512 cells run in one workgroup (k_bottom2d).
 //
 // Every level keeps its per-cell arrays in colour-blocked order (Perm2D): a colour pass of the
 // smoother touches only the cells of one colour, and with the colours stored apart it reads them

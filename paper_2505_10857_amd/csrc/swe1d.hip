@@ -6,7 +6,7 @@
 // thread; the Jacobian kernel evaluates one face per thread (the unperturbed state and every
 // column perturbation that reaches it) and assembles each row from its faces, taken from the
 // neighbouring lanes (rows within two cells of a side re-evaluate their own stencil with
-// ghosts).  FP64 division is the costly operation here (a reciprocal
+// ghosts, one lane an evaluation).  FP64 division is the costly operation here (a reciprocal
 // and several dependent FMAs each), so the formulas are evaluated in algebraically equal forms
 // with few divisions: one per WENO3 reconstruction (the normalised weights combined over a
 // common denominator), one reciprocal per depth and wave-speed difference in the HLL flux,

@@ -12,13 +12,13 @@
 // cell and the inner states of the next faces out, which the source's cubics need).  A face state
 // depends only on three consecutive cells of its line, so a 32x8 tile computes every face state
 // its cells use once, into LDS tables, and each cell assembles its residual from them.  For the
-// Jacobian a perturbation of cell p changes only the face states whose three cells include p;
-// for a row at least two cells inside the grid (no ghost in its residual) and a column at a fixed
-// offset of the stencil, which of the row's 36 states those are is known at compile time,
-// so the interior kernel recomputes just those (at most 12) and reads the rest from the tables.
-// The values equal a full re-evaluation of the perturbed local residual bit for bit.  Rows within
-// two cells of a side, whose ghosts also follow the perturbed cell, take a separate kernel that
-// re-evaluates all 36 face states per column.
+// Jacobian a perturbation of cell p changes only the face states whose three cells include p, and
+// a face state perturbed in one of its cells serves every row that has it: the interior kernel's
+// tables hold each state with each of its three cells raised, component by component, and a row (at
+// least two cells inside the grid, so without a ghost in its residual) re-forms only the fluxes
+// and depths that the perturbed cell reaches.  The values equal a full re-evaluation of the
+// perturbed local residual bit for bit.  Rows within two cells of a side, whose ghosts also follow
+// the perturbed cell, list the states that do and re-form those.
 //
 // Surface variant (recon = NMG_RECON_SURFACE, template flag SURF of the state accessors): the
 // reconstructions act on (eta, hu, hv), eta = h + zbar (zbar the cell average of b), in the
@@ -30,7 +30,7 @@
 // Register discipline: every helper is force-inlined and passes values as small structs by
 // value, indexed only by compile-time constants; boundary data of a side is selected by
 // comparisons, never by a runtime array index.  The kernels keep their state in registers and
-// LDS: no stack frame, no calls, no generic pointers into private memory.
+// LDS: no calls, no generic pointers into private memory.
 #include "nmg_common.h"
 
 namespace nmg {
