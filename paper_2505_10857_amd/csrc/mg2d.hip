@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level
 template <typename T, int NB, int TEAM>
 __device__ __forceinline__ void relax_cell_team(T *mg, const Level2D &L, int i, int j, double omega, int m)
 {
-    const long long n = L.P.M, cc = perm2d(L.P, i, j);
+    const long long n = L.P.M, cc = perm2d_of<colours2d(NB)>(L.P, i, j);
     const int b = m + 1;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
     if (b < NB) {
@@ -340,7 +340,7 @@ __device__ __forceinline__ void relax_cell_team(T *mg, const Level2D &L, int i, 
         if (pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny) {
             const T *Jr = mg + L.J + cc;
             const T *Ur = mg + L.dU;
-            const long long q = perm2d(L.P, pi, pj);
+            const long long q = perm2d_of<colours2d(NB)>(L.P, pi, pj);
             const double x0 = (double)Ur[q], x1 = (double)Ur[n + q], x2 = (double)Ur[2 * n + q];
             a0 = (double)Jr[(b * 9 + 0) * n] * x0 + (double)Jr[(b * 9 + 1) * n] * x1 + (double)Jr[(b * 9 + 2) * n] * x2;
             a1 = (double)Jr[(b * 9 + 3) * n] * x0 + (double)Jr[(b * 9 + 4) * n] * x1 + (double)Jr[(b * 9 + 5) * n] * x2;
@@ -697,7 +697,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         flags[k] = (valid ? c + 1 : 0) | (own ? 16 : 0) | (read ? 32 : 0);
         q[k] = valid ? (j - dj0) * ld + (i - di0) : 0;
         if (valid) {
-            const long long cc = perm2d_rows(L.P, i, j);
+            const long long cc = perm2d_of<C>(L.P, i, j);
 #pragma unroll
             for (int b = 1; b < NB; b++) {
                 const int pi = i + stencil_dx(NB, b), pj = j + stencil_dy(NB, b);
@@ -751,8 +751,8 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     __syncthreads();
     for (int e = t; e < dw * dh; e += kResNT) {
         const int r = e / dw, i = di0 + e - r * dw, j = dj0 + r;
-        const long long fc = perm2d_rows(L.P, i, j);
-        const long long pc = A.prolong ? perm2d_rows(A.Lc.P, i >> 1, j >> 1) : 0;
+        const long long fc = perm2d_of<C>(L.P, i, j);
+        const long long pc = A.prolong ? perm2d_of<2>(A.Lc.P, i >> 1, j >> 1) : 0;
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             T v = mg[L.dU + c * n + fc];
@@ -908,7 +908,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
-        const long long cc = perm2d_rows(L.P, cell_i(k), cell_j(k));
+        const long long cc = perm2d_of<C>(L.P, cell_i(k), cell_j(k));
 #pragma unroll
         for (int c = 0; c < ROWS; c++) mg[L.dU + (row + c) * n + cc] = bad ? (T)__builtin_nan("") : su[q[k]].v[row + c];
     }
@@ -920,7 +920,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
         const Cell *u = su + q[k];
-        const long long cc = perm2d_rows(L.P, cell_i(k), cell_j(k));
+        const long long cc = perm2d_of<C>(L.P, cell_i(k), cell_j(k));
         const double y0 = (double)u->v[0], y1 = (double)u->v[1], y2 = (double)u->v[2];
 #pragma unroll
         for (int x = 0; x < ROWS; x++)

@@ -186,6 +186,17 @@ __host__ __device__ inline long long perm2d_rows(const Perm2D &P, int i, int j)
     return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
 }
 
+// the same where the number of colours is known: 9 for the full stencil's level, 3 for the cross's, 2 below
+constexpr int colours2d(int nb) { return nb == 21 ? 9 : (nb == 9 ? 3 : 2); }
+
+template <int C>
+__host__ __device__ inline long long perm2d_of(const Perm2D &P, int i, int j)
+{
+    if (C == 9) return (long long)(i % 3 + 3 * (j % 3)) * P.ny * P.W + (long long)(j / 3) * P.W + i / 3;
+    const int c = (i + j) % C, ic = ((c - j) % C + C) % C;
+    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / C;
+}
+
 __host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
 {
     if (P.tw > 0) {
