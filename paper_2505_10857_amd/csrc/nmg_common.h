@@ -176,17 +176,9 @@ __host__ __device__ inline void tile3_cell(int c, int i0, int j0, int w, int p, 
     il = tile3_first(c, i0, j0, jr) + 3 * rem;
 }
 
-// the orders without tiles (a level that a resident or one-workgroup kernel holds never has the tiled
-// one; without that case the kernels need fewer registers)
-__host__ __device__ inline long long perm2d_rows(const Perm2D &P, int i, int j)
-{
-    if (P.C == 9) return (long long)(i % 3 + 3 * (j % 3)) * P.ny * P.W + (long long)(j / 3) * P.W + i / 3;
-    const int c = (i + j) % P.C;
-    const int ic = ((c - j) % P.C + P.C) % P.C;
-    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
-}
-
-// the same where the number of colours is known: 9 for the full stencil's level, 3 for the cross's, 2 below
+// The orders without tiles where the number of colours is known: 9 for the full stencil's level, 3 for
+// the cross's, 2 below.  A level that a resident or one-workgroup kernel holds never has the tiled order;
+// without that case the kernels need fewer registers.
 constexpr int colours2d(int nb) { return nb == 21 ? 9 : (nb == 9 ? 3 : 2); }
 
 template <int C>
@@ -205,7 +197,9 @@ __host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
         const int w = P.nx - i0 < P.tw ? P.nx - i0 : P.tw;
         return ((long long)c * P.ny + tj * P.gx + ti) * P.W + tile3_pos(c, i0, j0, w, i - i0, j - j0);
     }
-    return perm2d_rows(P, i, j);
+    if (P.C == 9) return perm2d_of<9>(P, i, j);
+    const int c = (i + j) % P.C, ic = ((c - j) % P.C + P.C) % P.C;
+    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
 }
 
 inline Perm2D make_perm2d(int nx, int ny, int C)

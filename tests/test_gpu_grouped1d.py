@@ -26,7 +26,7 @@ CASES = [(57 << 5, 6), (33 << 6, 7), (4096, 5), (81 << 6, 7), (12800, 8), (37 <<
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("jac,nu1,nu2", [(3, 2, 2), (5, 2, 2), (3, 1, 3), (3, 4, 4), (3, 0, 2)])
+@pytest.mark.parametrize("jac,nu1,nu2", [(3, 2, 2), (5, 2, 2), (3, 1, 3), (3, 4, 4), (3, 0, 2), (3, 8, 8), (3, 8, 1)])
 def test_grouped_levels_equal_a_launch_per_level(jac, nu1, nu2, prec):
     from paper_2505_10857_amd import BatchSolver1D
     probs = []
