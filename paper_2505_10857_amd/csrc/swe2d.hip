@@ -11,8 +11,8 @@
 // (x faces on rows j-1..j+1, y faces on columns i-1..i+1, both sides of the four faces of the
 // cell and the inner states of the next faces out, which the source's cubics need).  A face state
 // depends only on three consecutive cells of its line, so a 32x8 tile computes every face state
-// its cells use once, into LDS tables, and each cell assembles its residual from them.  For the
-// Jacobian a perturbation of cell p changes only the face states whose three cells include p, and
+// its cells use once, into LDS tables, then the flux through every face once, and each cell assembles
+// its residual from them.  For the Jacobian a perturbation of cell p changes only the face states whose three cells include p, and
 // a face state perturbed in one of its cells serves every row that has it: the interior kernel's
 // tables hold each state with each of its three cells raised, component by component, and a row (at
 // least two cells inside the grid, so without a ghost in its residual) re-forms only the fluxes
@@ -37,11 +37,6 @@ namespace nmg {
 
 constexpr int kTX = 32, kTY = 8;                       // tile of cells
 constexpr int kSX = kTX + 4, kSY = kTY + 4;            // staged state (halo 2)
-// face-state tables of a tile: x faces a in [i0-2, i0+kTX] on rows [j0-1, j0+kTY]; y faces
-// a in [j0-2, j0+kTY] on columns [i0-1, i0+kTX]; both sides, three components
-constexpr int kXA = kTX + 3, kXL = kTY + 2;
-constexpr int kYA = kTY + 3, kYL = kTX + 2;
-constexpr int kXS = 3 * 2 * kXL * kXA, kYS = 3 * 2 * kYL * kYA;
 constexpr int kBorderNT = 64;                          // threads of a border-kernel workgroup
 constexpr int kSlots = 36;                             // face states of one local residual
 
@@ -149,22 +144,6 @@ NMG2D_INL V3 face_state_line(const V3 &S0, const V3 &S1, const V3 &S2, double g,
     out.c[1] = (un - cc) * w[0] + (un + cc) * w[2];
     out.c[2] = ut * w[0] + w[1] + ut * w[2];
     return out;
-}
-
-// the state's components (h, hu, hv) in the order of direction DIR's line, and back
-template <int DIR>
-NMG2D_INL V3 along(const V3 &U)
-{
-    return DIR == 0 ? U : V3{{U.c[0], U.c[2], U.c[1]}};
-}
-
-// state of side W (0 minus, 1 plus) of a face in direction DIR from the cells S0, S1, S2 along the line
-template <int DIR, int W, bool SURF = false>
-NMG2D_INL V3 face_state_core(const V3 &S0, const V3 &S1, const V3 &S2, double g, double z0 = 0.0,
-                             double z1 = 0.0, double z2 = 0.0)
-{
-    const V3 a = along<DIR>(W ? S2 : S0), b = along<DIR>(S1), c = along<DIR>(W ? S0 : S2);
-    return along<DIR>(face_state_line<SURF>(a, b, c, g, W ? z2 : z0, z1, W ? z0 : z2));
 }
 
 template <int DIR>
@@ -445,35 +424,6 @@ NMG2D_INL V3 cell2(const Inst2D &I, const ST &st, int i, int j, int pi, int pj, 
     return out;
 }
 
-// face state of side W of face a (between cells a, a+1) on line k in direction DIR, any
-// position within two cells of the grid, ghosts applied, under the perturbation (pi, pj, pm)
-template <int DIR, int W, class ST>
-NMG2D_INL V3 face_state_general(const Inst2D &I, const ST &st, int k, int a, int pi, int pj, int pm, double eps)
-{
-    V3 S[3];
-    double z[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < 3; q++) {
-        const int t = a - 1 + W + q;
-        S[q] = DIR == 0 ? cell2(I, st, t, k, pi, pj, pm, eps) : cell2(I, st, k, t, pi, pj, pm, eps);
-        if constexpr (ST::surf) z[q] = DIR == 0 ? st.zb(t, k) : st.zb(k, t);
-    }
-    return face_state_core<DIR, W, ST::surf>(S[0], S[1], S[2], I.g, z[0], z[1], z[2]);
-}
-
-// ---- face-state tables of a tile ----------------------------------------------------------
-
-NMG2D_INL int xs_index(int c, int w, int line, int a)   // line, a relative to the table origin
-{
-    NMG2D_CHECK(line >= 0 && line < kXL && a >= (w ? 0 : 1) && a < kXA - (w ? 1 : 0));
-    return ((c * 2 + w) * kXL + line) * kXA + a;
-}
-NMG2D_INL int ys_index(int c, int w, int line, int a)
-{
-    NMG2D_CHECK(line >= 0 && line < kYL && a >= (w ? 0 : 1) && a < kYA - (w ? 1 : 0));
-    return ((c * 2 + w) * kYL + line) * kYA + a;
-}
-
 // thread t of n stages its share of the tile's state (and, for the surface variant, the cell
 // averages of b of the same cells, ghosts included, into z)
 NMG2D_INL void stage_tile(const Inst2D &I, int i0, int j0, double *s, int t, int n, double *z = nullptr)
@@ -493,52 +443,6 @@ NMG2D_INL void stage_tile(const Inst2D &I, int i0, int j0, double *s, int t, int
         }
 }
 
-// every face state the tile's cells use, unperturbed (after stage_tile and a barrier): the minus
-// states (W = 0) of faces i0-1 .. i0+kTX, the plus states (W = 1) of faces i0-2 .. i0+kTX-1 (and
-// the same along y), whose three cells all lie in the staged region
-template <int W, class ST>
-NMG2D_INL void face_tables_side(const Inst2D &I, const ST &st, double *xs, double *ys, int t, int n)
-{
-    constexpr int xa = kXA - 1, ya = kYA - 1;      // faces per line used on this side
-    for (int e = t; e < kXL * xa; e += n) {
-        const int line = e / xa, a = e - line * xa + (W ? 0 : 1);
-        const V3 v = face_state_general<0, W>(I, st, st.j0 - 1 + line, st.i0 - 2 + a, -1000, -1000, 0, 0.0);
-#pragma unroll
-        for (int c = 0; c < 3; c++) xs[xs_index(c, W, line, a)] = v.c[c];
-    }
-    for (int e = t; e < kYL * ya; e += n) {
-        const int line = e / ya, a = e - line * ya + (W ? 0 : 1);
-        const V3 v = face_state_general<1, W>(I, st, st.i0 - 1 + line, st.j0 - 2 + a, -1000, -1000, 0, 0.0);
-#pragma unroll
-        for (int c = 0; c < 3; c++) ys[ys_index(c, W, line, a)] = v.c[c];
-    }
-}
-
-template <class ST>
-NMG2D_INL void face_tables(const Inst2D &I, const ST &st, double *xs, double *ys, int t, int n)
-{
-    face_tables_side<0>(I, st, xs, ys, t, n);
-    face_tables_side<1>(I, st, xs, ys, t, n);
-}
-
-// face states of the row cell (i, j) read from the tables
-template <bool SURF>
-struct TableFS {
-    static constexpr bool surf = SURF;
-    const double *xs, *ys;
-    int xi, xj;        // the row cell relative to the tables' origins: i - i0, j - j0
-    template <int DIR, int W, int K, int A>
-    NMG2D_INL V3 get() const
-    {
-        V3 v;
-#pragma unroll
-        for (int c = 0; c < 3; c++)
-            v.c[c] = DIR == 0 ? xs[xs_index(c, W, xj + 1 + K, xi + 2 + A)]
-                              : ys[ys_index(c, W, xi + 1 + K, xj + 2 + A)];
-        return v;
-    }
-};
-
 // ---- residual -------------------------------------------------------------------------------
 
 NMG2D_INL void load_slopes(const Inst2D &I, int i, int j, double bx[4], double by[4])
@@ -548,47 +452,6 @@ NMG2D_INL void load_slopes(const Inst2D &I, int i, int j, double bx[4], double b
     for (int e = 0; e < 4; e++) {
         bx[e] = I.bx[g + e];
         by[e] = I.by[g + e];
-    }
-}
-
-template <bool SURF>
-__global__ void __launch_bounds__(kTX * kTY) k_residual2d(Inst2D I, double *partial)
-{
-    __shared__ double s[3 * kSY * kSX];
-    __shared__ double zs[SURF ? kSY * kSX : 1];
-    __shared__ double xs[kXS], ys[kYS];
-    __shared__ double red[kTX * kTY / 64];
-    const int i0 = blockIdx.x * kTX, j0 = blockIdx.y * kTY;
-    const int tid = threadIdx.y * kTX + threadIdx.x;
-    stage_tile(I, i0, j0, s, tid, kTX * kTY, SURF ? zs : nullptr);
-    __syncthreads();
-    const LdsStateT<SURF> st{s, zs, i0, j0};
-    face_tables(I, st, xs, ys, tid, kTX * kTY);
-    __syncthreads();
-    const int i = i0 + threadIdx.x, j = j0 + threadIdx.y;
-    double n1 = 0.0;
-    if (i < I.Nx && j < I.Ny) {
-        double bx[4], by[4];
-        load_slopes(I, i, j, bx, by);
-        const TableFS<SURF> fs{xs, ys, i - i0, j - j0};
-        const V3 R = assemble_residual(fs, I, bx, by, i, j, st(0, i, j));
-        const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
-        I.R[cidx] = R.c[0];
-        I.R[n + cidx] = R.c[1];
-        I.R[2 * n + cidx] = R.c[2];
-        n1 = fabs(R.c[0]) + fabs(R.c[1]) + fabs(R.c[2]);
-        I.rn[cidx] = n1;
-    }
-    // per-tile partial sum of ||R||_1 (fixed order)
-    const int t = threadIdx.y * kTX + threadIdx.x;
-    for (int off = 32; off > 0; off >>= 1) n1 += __shfl_down(n1, off, 64);
-    if ((t & 63) == 0) red[t >> 6] = n1;
-    __syncthreads();
-    if (t == 0 && partial) {
-        double sum = 0.0;
-#pragma unroll
-        for (int w = 0; w < kTX * kTY / 64; w++) sum += red[w];
-        partial[blockIdx.y * gridDim.x + blockIdx.x] = sum;
     }
 }
 
@@ -1248,27 +1111,28 @@ __global__ void __launch_bounds__(kJacNT) k_jacobian2d_small(Inst2D I, Perm2D Pm
     else border_rows<T, NB, SURF, kJacNT>(I, Pm, J, rhs, Dinv, (g - ntiles) * (long long)BorderLds<NB>::RPW, nrows, lds.b);
 }
 
-// ---- residual of a small grid ---------------------------------------------------------------
-// The tile and the order of its sums are k_residual2d's, on four times the threads: the face states
-// spread over them, each cell's four face fluxes side by side.  A grid too small to fill the chip waits
-// for the chain in one thread (64 x 32: 23.5 us with a cell a thread, 12.7 so).
-constexpr int kWideNT = 4 * kTX * kTY;
-
-template <bool SURF>
-__global__ void __launch_bounds__(kWideNT) k_residual2d_wide(Inst2D I, double *partial)
+// ---- residual with each face's flux formed once ---------------------------------------------
+// The face states of a tile are spread over the workgroup's threads, then the faces: a flux serves the
+// cells on both sides of its face.  The tile's sum is that of four wavefronts of 64 cells.  NT = 1024
+// for a grid too small to fill the chip, which waits for the chain in one thread (64 x 32: 23.5 us
+// with a cell a thread, 12.5 so); 512 otherwise, two workgroups a compute unit (1024 x 512: 83 us with a
+// cell a thread that forms its four fluxes itself, 69 so).
+template <bool SURF, int NT>
+__global__ void __launch_bounds__(NT) k_residual2d(Inst2D I, double *partial)
 {
     typedef JacTile<kTX, kTY> TL;
     constexpr int CELLS = kTX * kTY, NW = CELLS / 64;
+    constexpr int FX = (kTX + 1) * kTY, FY = kTX * (kTY + 1);    // faces of the tile's cells
     __shared__ double s[3 * kSY * kSX];
     __shared__ double zs[SURF ? kSY * kSX : 1];
     __shared__ double tab[TL::SET];
-    __shared__ double part[4][5][CELLS];       // per face: its flux, the depths at it
+    __shared__ double part[7][FX + FY];        // per face: its flux, the depths on its lower and upper side
     __shared__ double red[NW];
     const int i0 = blockIdx.x * kTX, j0 = blockIdx.y * kTY, t = threadIdx.x;
-    stage_tile(I, i0, j0, s, t, kWideNT, SURF ? zs : nullptr);
+    stage_tile(I, i0, j0, s, t, NT, SURF ? zs : nullptr);
     __syncthreads();
     const LdsStateT<SURF> st{s, zs, i0, j0};
-    for (int e = t; e < 2 * TL::STATES; e += kWideNT) {
+    for (int e = t; e < 2 * TL::STATES; e += NT) {
         const int dir = e / TL::STATES, q = e - dir * TL::STATES, W = q / (TL::STATES / 2), f = q - W * (TL::STATES / 2);
         const int per = dir ? TL::YA - 1 : TL::XA - 1, line = f / per, a = f - line * per + (W ? 0 : 1);
         const int t0 = (dir ? j0 : i0) - 3 + a + W, k = (dir ? i0 : j0) - 1 + line;
@@ -1283,51 +1147,68 @@ __global__ void __launch_bounds__(kWideNT) k_residual2d_wide(Inst2D I, double *p
         w[2 * comp] = v.c[dir ? 1 : 2];
     }
     __syncthreads();
-    const int cell = t % CELLS, face = __builtin_amdgcn_readfirstlane(t / CELLS);
-    const int xi = cell % kTX, xj = cell / kTX, i = i0 + xi, j = j0 + xj;
-    const bool in = i < I.Nx && j < I.Ny;
-    double zx[4] = {}, zy[4] = {}, zc = 0.0;
-    if (SURF && in) {
-        const long long fx = ((long long)j * (I.Nx + 1) + i) * 2, fy = ((long long)j * I.Nx + i) * 2;
-#pragma unroll
-        for (int q = 0; q < 2; q++) {
-            zx[q] = I.zfx[fx + q];
-            zx[2 + q] = I.zfx[fx + 2 + q];
-            zy[q] = I.zfy[fy + q];
-            zy[2 + q] = I.zfy[fy + 2 * I.Nx + q];
-        }
-        zc = zs[(xj + 2) * kSX + xi + 2];
-    }
-    const double *const tx = tab + xj * TL::XA + xi, *const ty = tab + xi * TL::YA + xj;
     const NoHit none;
-    if (in) {
+    for (int e = t; e < FX + FY; e += NT) {
+        // the lower face of cell (xi, xj); the last column's or row's upper face is that of the cell after it
+        const bool dir = e >= FX;
+        const int f = dir ? e - FX : e, xi = dir ? f % kTX : f % (kTX + 1), xj = dir ? f / kTX : f / (kTX + 1);
+        const int i = i0 + xi, j = j0 + xj;
+        if (i > I.Nx - (dir ? 1 : 0) || j > I.Ny - (dir ? 0 : 1)) continue;
+        double z0 = 0.0, z1 = 0.0;
         V3 F;
-        H2 dum, at;
-        if (face == 0) F = tab_flux<TL, 0, -1, SURF>(tx, none, I.g, dum, at, zx[0], zx[1]);
-        else if (face == 1) F = tab_flux<TL, 0, 0, SURF>(tx, none, I.g, at, dum, zx[2], zx[3]);
-        else if (face == 2) F = tab_flux<TL, 1, -1, SURF>(ty, none, I.g, dum, at, zy[0], zy[1]);
-        else F = tab_flux<TL, 1, 0, SURF>(ty, none, I.g, at, dum, zy[2], zy[3]);
+        H2 hm, hp;
+        if (!dir) {
+            if constexpr (SURF) {
+                const long long x = ((long long)j * (I.Nx + 1) + i) * 2;
+                z0 = I.zfx[x];
+                z1 = I.zfx[x + 1];
+            }
+            F = tab_flux<TL, 0, -1, SURF>(tab + xj * TL::XA + xi, none, I.g, hm, hp, z0, z1);
+        } else {
+            if constexpr (SURF) {
+                const long long y = ((long long)j * I.Nx + i) * 2;
+                z0 = I.zfy[y];
+                z1 = I.zfy[y + 1];
+            }
+            F = tab_flux<TL, 1, -1, SURF>(tab + xi * TL::YA + xj, none, I.g, hm, hp, z0, z1);
+        }
 #pragma unroll
-        for (int c = 0; c < 3; c++) part[face][c][cell] = F.c[c];
+        for (int c = 0; c < 3; c++) part[c][e] = F.c[c];
 #pragma unroll
-        for (int c = 0; c < 2; c++) part[face][3 + c][cell] = at.g[c];
+        for (int c = 0; c < 2; c++) { part[3 + c][e] = hm.g[c]; part[5 + c][e] = hp.g[c]; }
     }
     __syncthreads();
     if (t >= CELLS) return;                    // the cells' own threads are the first ones
+    const int xi = t % kTX, xj = t / kTX, i = i0 + xi, j = j0 + xj;
     double n1 = 0.0;
-    if (in) {
-        double bx[4], by[4];
+    if (i < I.Nx && j < I.Ny) {
+        double bx[4], by[4], zx[4] = {}, zy[4] = {}, eta = 0.0;
         load_slopes(I, i, j, bx, by);
+        if constexpr (SURF) {
+            const long long fx = ((long long)j * (I.Nx + 1) + i) * 2, fy = ((long long)j * I.Nx + i) * 2;
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                zx[q] = I.zfx[fx + q];
+                zx[2 + q] = I.zfx[fx + 2 + q];
+                zy[q] = I.zfy[fy + q];
+                zy[2 + q] = I.zfy[fy + 2 * I.Nx + q];
+            }
+            eta = st(0, i, j) + zs[(xj + 2) * kSX + xi + 2];
+        }
+        const double *const tx = tab + xj * TL::XA + xi, *const ty = tab + xi * TL::YA + xj;
+        const int ex = xj * (kTX + 1) + xi, ey = FX + xj * kTX + xi;
         RowParts r;
-        auto flux = [&](int f) { return V3{{part[f][0][cell], part[f][1][cell], part[f][2][cell]}}; };
-        auto depth = [&](int f) { return H2{{part[f][3][cell], part[f][4][cell]}}; };
-        r.fxm = flux(0); r.fxp = flux(1); r.fym = flux(2); r.fyp = flux(3);
-        r.hx[1] = depth(0); r.hx[2] = depth(1); r.hy[1] = depth(2); r.hy[2] = depth(3);
+        auto flux = [&](int e) { return V3{{part[0][e], part[1][e], part[2][e]}}; };
+        auto depth = [&](int e, int c) { return H2{{part[c][e], part[c + 1][e]}}; };
+        r.fxm = flux(ex); r.fxp = flux(ex + 1); r.fym = flux(ey); r.fyp = flux(ey + kTX);
         r.hx[0] = tab_depth<TL, 0, 1, -2>(tx, none);
+        r.hx[1] = depth(ex, 5);
+        r.hx[2] = depth(ex + 1, 3);
         r.hx[3] = tab_depth<TL, 0, 0, 1>(tx, none);
         r.hy[0] = tab_depth<TL, 1, 1, -2>(ty, none);
+        r.hy[1] = depth(ey, 5);
+        r.hy[2] = depth(ey + kTX, 3);
         r.hy[3] = tab_depth<TL, 1, 0, 1>(ty, none);
-        const double eta = SURF ? st(0, i, j) + zc : 0.0;
         const V3 R = row_residual<SURF>(r, I, Recip(I.dx), Recip(I.dy), Recip(I.dx * I.dy), bx, by, zx, zy, eta);
         const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
         I.R[cidx] = R.c[0];
@@ -1357,11 +1238,9 @@ hipError_t launch_residual2d(const Inst2D &I, double *partial, hipStream_t s)
 {
     dim3 grid((I.Nx + kTX - 1) / kTX, (I.Ny + kTY - 1) / kTY);
     const bool surf = I.recon == NMG_RECON_SURFACE;
-    if (few_cells(I)) {
-        if (surf) hipLaunchKernelGGL(k_residual2d_wide<true>, grid, dim3(kWideNT), 0, s, I, partial);
-        else hipLaunchKernelGGL(k_residual2d_wide<false>, grid, dim3(kWideNT), 0, s, I, partial);
-    } else if (surf) hipLaunchKernelGGL(k_residual2d<true>, grid, dim3(kTX, kTY), 0, s, I, partial);
-    else hipLaunchKernelGGL(k_residual2d<false>, grid, dim3(kTX, kTY), 0, s, I, partial);
+    auto launch = [&](auto kernel, int nt) { hipLaunchKernelGGL(kernel, grid, dim3(nt), 0, s, I, partial); };
+    if (few_cells(I)) surf ? launch(k_residual2d<true, 1024>, 1024) : launch(k_residual2d<false, 1024>, 1024);
+    else surf ? launch(k_residual2d<true, 512>, 512) : launch(k_residual2d<false, 512>, 512);
     return hipGetLastError();
 }
 
