@@ -55,7 +55,6 @@ struct Plan2D {
     mutable unsigned tag = 0;  // exchanges numbered so far in this call
 };
 
-
 nmg_status check2d(const nmg_desc *d, const nmg_params *p, bool need_geometry = true)
 {
     if (!d || !p) return set_error(NMG_EINVAL, "null desc or params");
@@ -270,15 +269,24 @@ nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
     return NMG_OK;
 }
 
-nmg_status resident(const Plan2D &P, char *mgb, int l, int nu, int prolong, int restr, const NewtonState *S, hipStream_t s)
+// one phase of level l: [prolongation,] nu smoothing iterations [, restriction]; in one cooperative
+// launch on a resident level, unless there is nothing to smooth
+nmg_status phase(const Plan2D &P, char *mgb, int l, int nu, int prolong, int restr, const NewtonState *S, hipStream_t s)
 {
-    const unsigned tag = P.tag;
-    P.tag += resident2d_exchanges(P.L[l], nu, P.res[l].m);
-    if (l == 0 && P.streamed)
-        HIP_TRY2(launch_streamed2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
-                                   mgb - P.off_mg + P.off_box, P.box_cells, S, P.prec, s));
-    else HIP_TRY2(launch_resident2d(mgb, P.L[l], P.L[l + 1], P.res[l], nu, prolong, restr, tag, P.omega,
-                               mgb - P.off_mg + P.off_box, P.box_cells, S, P.prec, s));
+    const Level2D &L = P.L[l];
+    if (P.res[l].tx > 0 && nu > 0) {
+        const Resident2D G = phase2d(L, P.res[l], nu, restr);
+        const unsigned tag = P.tag;
+        P.tag += resident2d_exchanges(L, nu, G.m);
+        const auto launch = l == 0 && P.streamed ? launch_streamed2d : launch_resident2d;
+        HIP_TRY2(launch(mgb, L, P.L[l + 1], G, nu, prolong, restr, tag, P.omega, mgb - P.off_mg + P.off_box, P.box_cells, S,
+                        P.prec, s));
+        return NMG_OK;
+    }
+    if (prolong) HIP_TRY2(launch_prolong2d(mgb, L, P.L[l + 1], P.prec, s));
+    const nmg_status st = smooth(P, mgb, l, nu, s);
+    if (st != NMG_OK) return st;
+    if (restr) HIP_TRY2(launch_restrict2d(mgb, L, P.L[l + 1], P.prec, s));
     return NMG_OK;
 }
 
@@ -288,30 +296,20 @@ nmg_status resident(const Plan2D &P, char *mgb, int l, int nu, int prolong, int 
 nmg_status vcycle_from(const Plan2D &P, char *mgb, int l, hipStream_t s, int cycles = 1, const NewtonState *S = nullptr)
 {
     nmg_status st;
-    if (l < P.bottom_first && P.res[l].tx > 0) {
-        if ((st = resident(P, mgb, l, P.nu1, 0, 1, S, s)) != NMG_OK) return st;
-        for (int c = 0; c < cycles; c++) {
-            if ((st = vcycle_from(P, mgb, l + 1, s, 1, S)) != NMG_OK) return st;
-            const bool more = c + 1 < cycles;
-            if ((st = resident(P, mgb, l, P.nu2 + (more ? P.nu1 : 0), 1, more, S, s)) != NMG_OK) return st;
-        }
-        return NMG_OK;
-    }
-    if (cycles > 1) {
-        for (int c = 0; c < cycles; c++)
-            if ((st = vcycle_from(P, mgb, l, s, 1, S)) != NMG_OK) return st;
-        return NMG_OK;
-    }
     if (l >= P.bottom_first) {
-        HIP_TRY2(launch_bottom2d(mgb, P.L.data(), l, P.levels, P.nu1, P.nu2, P.omega,
-                                 (const double *)(mgb - P.off_mg + P.off_lu), P.prec, s, P.sweeps));
+        for (int c = 0; c < cycles; c++)
+            HIP_TRY2(launch_bottom2d(mgb, P.L.data(), l, P.levels, P.nu1, P.nu2, P.omega,
+                                     (const double *)(mgb - P.off_mg + P.off_lu), P.prec, s, P.sweeps));
         return NMG_OK;
     }
-    if ((st = smooth(P, mgb, l, P.nu1, s)) != NMG_OK) return st;
-    HIP_TRY2(launch_restrict2d(mgb, P.L[l], P.L[l + 1], P.prec, s));
-    if ((st = vcycle_from(P, mgb, l + 1, s, 1, S)) != NMG_OK) return st;
-    HIP_TRY2(launch_prolong2d(mgb, P.L[l], P.L[l + 1], P.prec, s));
-    return smooth(P, mgb, l, P.nu2, s);
+    const bool merge = P.res[l].tx > 0;
+    for (int c = 0; c < cycles; c++) {
+        if ((c == 0 || !merge) && (st = phase(P, mgb, l, P.nu1, 0, 1, S, s)) != NMG_OK) return st;
+        if ((st = vcycle_from(P, mgb, l + 1, s, 1, S)) != NMG_OK) return st;
+        const bool more = merge && c + 1 < cycles;
+        if ((st = phase(P, mgb, l, P.nu2 + (more ? P.nu1 : 0), 1, more, S, s)) != NMG_OK) return st;
+    }
+    return NMG_OK;
 }
 
 // coarse operators of every level below the finest, then the factors of the coarsest

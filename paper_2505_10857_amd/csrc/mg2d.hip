@@ -542,7 +542,12 @@ __global__ void k_prolong2d(T *mg, Level2D Lf, Level2D Lc)
 //
 // Two parities of the mailbox suffice: a workgroup writes exchange e + 2 only after it has fetched
 // e + 1 from every workgroup whose cells its halo holds, which are those whose halos hold its cells, and
-// each of them published e + 1 after it had fetched e.  A halo leaves out its corners, which m
+// each of them published e + 1 after it had fetched e.  The exchanges also order the phase's memory: a
+// workgroup loads dU of its tile and halo (and the parents' dU) at the start and writes its tile's dU
+// (and clears its parents') in place at the end, so between the two it has to have heard from every
+// neighbour, which each has loaded before it publishes.  Hence a phase has at least one exchange: one
+// that ends without (no restriction) exchanges before its last pass at the latest (phase2d), and one
+// without passes is not run here.  A halo leaves out its corners, which m
 // passes of a cross stencil do not reach.  With m = 1 only the pass's colour is exchanged (tiles are
 // at least two cells wide, so every shared edge holds every colour), with m >= 2 every cell.
 //
@@ -1961,6 +1966,24 @@ size_t resident2d_box_bytes(long long cells, int prec) { return (size_t)2 * cell
 
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m) { return (unsigned)((nu * 4LL * (L.P.C - 1) + 1) / m + 2); }
 
+// colour passes of nu smoothing iterations
+static int phase_runs(const Level2D &L, int nu) { return nu > 0 ? nu * 4 * (L.P.C - 1) + 1 : 0; }
+
+Resident2D phase2d(const Level2D &L, const Resident2D &G, int nu, int restr)
+{
+    // fewer passes an exchange than planned only narrow the regions and the halo
+    Resident2D H = G;
+    if (!restr) H.m = std::max(1, std::min(G.m, phase_runs(L, nu) - 1));
+    return H;
+}
+
+// every workgroup hears from its neighbours between its first loads and its last stores
+static bool phase_exchanges(const Level2D &L, const Resident2D &G, int nu, int restr)
+{
+    const int runs = phase_runs(L, nu);
+    return runs > 0 && (restr || G.m < runs);
+}
+
 static Resident2DArgs resident_args(const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong, int restr,
                                     unsigned tag, double omega, void *box, long long cells, const NewtonState *state)
 {
@@ -1987,6 +2010,7 @@ hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, cons
                              const NewtonState *state, int prec, hipStream_t s)
 {
     if (G.tx < 2 || L.P.tw > 0 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
+    if (!phase_exchanges(L, G, nu, restr)) return hipErrorInvalidValue;
     Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
     void *args[] = {&mg, &A};
     return hipLaunchCooperativeKernel(resident2d_kernel(L.nb, prec, G.narrow), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);
@@ -2023,6 +2047,7 @@ hipError_t launch_streamed2d(void *mg, const Level2D &L, const Level2D &Lc, cons
                              const NewtonState *state, int prec, hipStream_t s)
 {
     if (G.tx < 2 || L.P.tw != G.tx || L.P.th != G.ty || L.P.gx != G.gx) return hipErrorInvalidValue;
+    if (!phase_exchanges(L, G, nu, restr)) return hipErrorInvalidValue;
     Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
     void *args[] = {&mg, &A};
     return hipLaunchCooperativeKernel(streamed2d_kernel(prec), dim3(G.gx * G.gy), dim3(kResNT), args, 0, s);

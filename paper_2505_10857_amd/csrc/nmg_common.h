@@ -342,6 +342,8 @@ long long resident2d_max_cells(int nb);
 // bytes of the mailbox for levels of up to `cells` cells; exchanges a launch numbers
 size_t resident2d_box_bytes(long long cells, int prec);
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m);
+// the tiling of one phase of nu >= 1 iterations: G with as many passes an exchange as leave the phase one
+Resident2D phase2d(const Level2D &L, const Resident2D &G, int nu, int restr);
 // [prolongation from Lc +] nu smoothing iterations [+ restriction to Lc] in one cooperative launch
 // an empty cooperative launch
 hipError_t open_cooperative_queue(hipStream_t s);
