@@ -1222,10 +1222,11 @@ nmg_status nmg_nested_solve(const nmg_desc *descs, int32_t ngrids, const nmg_par
             return fail(NMG_EINVAL, "the interpolation needs at least three coarse cells in each direction");
         if (descs[g].levels != ngrids - g) return fail(NMG_EINVAL, "grid g must have ngrids - g levels");
     }
-    if (nmg_nested_workspace_bytes(descs, ngrids, params) == 0) return fail(NMG_ENOMEM_WS, "workspace too small");
-    for (int g = 0; g < ngrids; g++)
-        if (ws_bytes < (dim == 2 ? workspace2d_bytes(&descs[g], &params[g], true) : nmg_workspace_bytes(&descs[g], &params[g])))
-            return fail(NMG_ENOMEM_WS, "workspace too small");
+    for (int g = 0; g < ngrids; g++) {
+        const size_t need = dim == 2 ? workspace2d_bytes(&descs[g], &params[g], true) : nmg_workspace_bytes(&descs[g], &params[g]);
+        if (need == 0) return NMG_EINVAL;   // the size query has set the message
+        if (ws_bytes < need) return fail(NMG_ENOMEM_WS, "workspace too small");
+    }
     hipStream_t s = (hipStream_t)stream;
     for (int g = ngrids - 1; g >= 0; g--) {
         if (g < ngrids - 1) {
