@@ -602,6 +602,11 @@ constexpr int kResPL = 1872;                     // cells, ring included (48 x 3
 template <typename T> struct ResCell;
 template <> struct ResCell<double> { double v[3]; };
 template <> struct alignas(16) ResCell<float> { float v[4]; };
+// the memory of a tile, first of its cells and then of the restriction's summands
+struct alignas(16) ResLds { double v[3 * kResPL]; };
+static_assert(alignof(ResLds) >= alignof(ResCell<float>) && alignof(ResLds) >= alignof(ResCell<double>) &&
+                  sizeof(ResLds) >= kResPL * sizeof(ResCell<float>) && sizeof(ResLds) >= kResPL * sizeof(ResCell<double>),
+              "a cell is read at its own alignment");
 constexpr int kResNT = 512;
 constexpr int kResHalo = 3;                      // halo cells a thread fetches at most
 
@@ -620,16 +625,16 @@ constexpr int kRes21Cells = kResNT / 64 * 21;    // cells a workgroup holds then
 
 // One smoothing phase of one level by the workgroups that share it; this one has tile (bi, bj).
 // HT: the type the rows are held in; EPT: cells per thread; SOLO: one workgroup has the whole
-// level (no halo, no mailbox).  lds: [3 kResPL] doubles; dead: set when a wait ran out.
+// level (no halo, no mailbox).  dead: set when a wait ran out.
 template <typename T, int NB, typename HT, int EPT, bool SOLO>
-__device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, int bi, int bj, double *lds, int &dead)
+__device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, int bi, int bj, ResLds &lds, int &dead)
 {
     constexpr int C = NB == 21 ? 9 : (NB == 9 ? 3 : 2), R = NB == 5 ? 1 : 2, NW = BoxWords<T>::n;
     constexpr int ROWS = NB == 21 ? 1 : 3;       // rows of a cell that a thread has
     static_assert(ROWS == 3 || EPT == 1, "a row a thread");
     constexpr int KB = NW == 3 ? 3 : 2;          // halo cells whose words a thread has in flight
     typedef ResCell<T> Cell;
-    Cell *const sz = (Cell *)lds;                // dU [rows + 4][ld]; the restriction's summands last
+    Cell *const sz = (Cell *)lds.v;              // dU [rows + 4][ld]; the restriction's summands last
     const Level2D &L = A.L;
     const int t = threadIdx.x, nx = L.nx, ny = L.ny;
     const int i0 = SOLO ? 0 : bi * A.tx, j0 = SOLO ? 0 : bj * A.ty;
@@ -943,7 +948,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
         }
     }
     __syncthreads();
-    double *sa = lds;                            // [3][tile cells]
+    double *sa = lds.v;                          // [3][tile cells]
 #pragma unroll
     for (int k = 0; k < EPT; k++) {
         if (!inside(k)) continue;
@@ -970,7 +975,7 @@ __device__ __forceinline__ void resident_level(T *mg, const Resident2DArgs &A, i
 template <typename T, int NB, typename HT, int EPT>
 __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 {
-    __shared__ double lds[3 * kResPL];
+    __shared__ ResLds lds;
     __shared__ int dead;
     if (A.state && !A.state->active) return;     // the same for every workgroup
     resident_level<T, NB, HT, EPT, false>(mg, A, blockIdx.x % A.gx, blockIdx.x / A.gx, lds, dead);
@@ -1647,7 +1652,7 @@ __global__ void __launch_bounds__(512) k_bottom2d(T *mg, Bottom2DArgs B)
     constexpr int MM = 3 * kMaxCoarse2D;
     __shared__ double A[MM * (MM + 1)];
     __shared__ __align__(16) double sum[144];
-    __shared__ double lds[3 * kResPL];
+    __shared__ ResLds lds;
     const int last = B.levels - 1;
     Resident2DArgs R;
     R.m = 1;
