@@ -490,9 +490,13 @@ MGArgs mg_args(const nmg_plan *P, char *ws, bool with_state)
 // Upload the tables with the device pointers of this workspace and these states.  The level
 // and tile tables depend only on the plan and the workspace and are uploaded once per
 // workspace; the instance table (which holds the state pointers) is uploaded on every call,
-// from pinned memory.
+// from pinned memory.  Refused under capture: a replay would read that memory later, when it holds
+// something else, and the next call would take tables as uploaded that never were.
 nmg_status upload_tables(nmg_plan *P, char *ws, double *const *U, hipStream_t s)
 {
+    bool captured = false;
+    HIP_TRY(being_captured(s, captured));
+    if (captured) return fail(NMG_EHIP, "a plan's tables cannot be uploaded on a stream that is being captured");
     const size_t isz = sizeof(Inst1D) * P->n;
     auto static_tables = [&](char *to, size_t base) {   // at their offsets less base
         memcpy(to + P->off_levs - base, P->levs.data(), sizeof(Level1D) * P->levs.size());

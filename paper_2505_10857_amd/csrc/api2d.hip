@@ -248,9 +248,9 @@ nmg_status use_resident(Plan2D &P, char *ws, size_t ws_bytes, hipStream_t s)
     P.resident = P.streamed = false;
     set_bottom(P);
     if (P.box_cells == 0 || ws_bytes < P.total) return NMG_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY2(hipStreamIsCapturing(s, &cap));
-    if (cap != hipStreamCaptureStatusNone) return NMG_OK;
+    bool captured = false;
+    HIP_TRY2(being_captured(s, captured));
+    if (captured) return NMG_OK;
     // the one-workgroup bottom reads a 21-cell level's rows in every pass: the level runs by itself
     if (P.bottom_first == 0 && P.L[0].nb == 21 && P.levels > 1) P.bottom_first = 1;
     for (int l = 0; l < P.bottom_first; l++) {

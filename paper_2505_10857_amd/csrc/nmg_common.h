@@ -258,6 +258,16 @@ struct Level2D {
     long long J, Dinv, rhs, dU;
 };
 
+// Whether work on the stream is being recorded into a graph (never on the null stream, which the
+// runtime does not capture)
+inline hipError_t being_captured(hipStream_t s, bool &yes)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = s ? hipStreamIsCapturing(s, &st) : hipSuccess;
+    yes = st != hipStreamCaptureStatusNone;
+    return e;
+}
+
 // ---- launchers (return hipError_t of the launch) ----------------------------------------
 
 // residual over tiles (batched: tiles index instances) or one instance (tiles == null)

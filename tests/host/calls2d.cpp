@@ -96,14 +96,14 @@ int main()
     p.tau = p.omega = 1.0;
     p.n_max = 10;
     p.check_every = 1;
-    void *const any = (void *)256;
+    void *const any = (void *)256;               // as are the buffers and the stream
     while (std::cin >> entry >> d.nx >> d.ny >> d.levels >> d.jac >> p.precision >> p.nu1 >> p.nu2 >> p.nu3 >> cut >>
            capturing >> g_cus) {
         g_capturing = capturing != 0;
         const size_t bytes = nmg::workspace2d_bytes(&d, &p) - (size_t)cut;
         nmg_status st;
-        if (entry == "step") st = nmg::newton2d_steps(&d, &p, any, bytes, (double *)any, 1, nullptr, nullptr);
-        else st = nmg::vcycle2d(&d, &p, any, bytes, any, any, any, entry == "setup", nullptr);
+        if (entry == "step") st = nmg::newton2d_steps(&d, &p, any, bytes, (double *)any, 1, nullptr, (hipStream_t)64);
+        else st = nmg::vcycle2d(&d, &p, any, bytes, any, any, any, entry == "setup", (hipStream_t)64);
         printf("end %d\n", (int)st);
     }
     return 0;
