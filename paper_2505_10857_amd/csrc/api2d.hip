@@ -48,7 +48,7 @@ struct Plan2D {
     size_t total = 0;
     // resident levels (use_resident): the tiling of each launched level, tx = 0 where it has none
     std::vector<Resident2D> res;
-    Resident2D stream;         // tiling of a finest level that is streamed (its order in memory, too)
+    Resident2D stream;         // tiling of a finest level that is streamed (and of its rows in memory)
     bool streamed = false;     // it is in this call
     long long box_cells = 0;   // cells of the largest level that may be resident or streamed
     bool resident = false;
@@ -132,8 +132,7 @@ void set_bottom(Plan2D &P)
         P.bottom_first--;
 }
 
-// plain: every level in the rows' colour order (no streamed finest level)
-nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_geometry = true, bool plain = false)
+nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_geometry = true)
 {
     nmg_status st = check2d(d, p, need_geometry);
     if (st != NMG_OK) return st;
@@ -163,9 +162,11 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
         L.nb = l == 0 ? d->jac : 5;
         // colours of the cross (3), the full stencil (9) or the five-point stencil (2)
         L.P = make_perm2d(L.nx, L.ny, l == 0 ? (d->jac == 21 ? 9 : 3) : 2);
-        if (l == 0 && P.levels > 1 && !P.sweeps && !plain) {
+        // by the problem alone: neither the workspace's size, nor a capture, nor the device may move the
+        // operator between a set-up call and the calls that reuse it
+        if (l == 0 && P.levels > 1 && !P.sweeps) {
             P.stream = streamed2d_plan(L, P.prec);
-            if (P.stream.tx > 0) L.P = make_perm2d_tiled(L.nx, L.ny, P.stream.tx, P.stream.ty);
+            if (P.stream.tx > 0) tile_rows(L.P, L.nx, P.stream.tx, P.stream.ty);
         }
         const long long n = L.P.M;
         L.J = e; e += (long long)L.nb * 9 * n;
@@ -194,19 +195,6 @@ nmg_status build2d(Plan2D &P, const nmg_desc *d, const nmg_params *p, bool need_
     o = al256(o + resident2d_box_bytes(P.box_cells, P.prec));
     P.total = o;
     return NMG_OK;
-}
-
-// the plan for a workspace of ws_bytes: without room for the mailbox a streamed level would run as
-// launches per pass, which read the rows' order faster than the tiled one (1024 x 512, FP64, three
-// cycles: 30.3 and 39.0 ms)
-nmg_status build2d_for(Plan2D &P, const nmg_desc *d, const nmg_params *p, size_t ws_bytes)
-{
-    nmg_status st = build2d(P, d, p);
-    if (st == NMG_OK && P.stream.tx > 0 && ws_bytes < P.total) {
-        P = Plan2D();
-        st = build2d(P, d, p, true, true);
-    }
-    return st;
 }
 
 // nu smoothing iterations on level l, each two symmetric multicolour steps (colours 0..C-1, then
@@ -359,7 +347,7 @@ nmg_status newton_step(const Plan2D &P, char *w, double *U, hipStream_t s)
 size_t workspace2d_bytes(const nmg_desc *d, const nmg_params *p, bool base)
 {
     Plan2D P;
-    if (build2d(P, d, p, false, base) != NMG_OK) return 0;
+    if (build2d(P, d, p, false) != NMG_OK) return 0;
     return base ? P.off_box : P.total;
 }
 
@@ -400,7 +388,7 @@ nmg_status vcycle2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
 {
     if (!ws || !rhs || !dU || (setup && !J)) return set_error(NMG_EINVAL, "null argument");
     Plan2D P;
-    nmg_status st = build2d_for(P, d, p, ws_bytes);
+    nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
     if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     if ((st = use_resident(P, (char *)ws, ws_bytes, s)) != NMG_OK) return st;
@@ -408,14 +396,14 @@ nmg_status vcycle2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
     const size_t vsz = P.prec == NMG_FP32_MG ? 4 : 8;
     const Level2D &L0 = P.L[0];
     if (setup) {
-        HIP_TRY2(launch_permute2d(J, NMG_FP64, mgb + vsz * L0.J, P.prec, L0, 9 * L0.nb, 1, s));
+        HIP_TRY2(launch_permute2d(J, NMG_FP64, mgb + vsz * L0.J, P.prec, L0, 9 * L0.nb, 1, 1, s));
         HIP_TRY2(launch_dinv2d((const double *)J, mgb + vsz * L0.Dinv, L0, P.prec, s));
         if ((st = coarsen_all(P, mgb, s)) != NMG_OK) return st;
     }
-    HIP_TRY2(launch_permute2d(rhs, P.prec, mgb + vsz * L0.rhs, P.prec, L0, 3, 1, s));
-    HIP_TRY2(launch_permute2d(dU, P.prec, mgb + vsz * L0.dU, P.prec, L0, 3, 1, s));
+    HIP_TRY2(launch_permute2d(rhs, P.prec, mgb + vsz * L0.rhs, P.prec, L0, 3, 1, 1, s));
+    HIP_TRY2(launch_permute2d(dU, P.prec, mgb + vsz * L0.dU, P.prec, L0, 3, 0, 1, s));
     if ((st = vcycle_from(P, mgb, 0, s)) != NMG_OK) return st;
-    HIP_TRY2(launch_permute2d(mgb + vsz * L0.dU, P.prec, dU, P.prec, L0, 3, 0, s));
+    HIP_TRY2(launch_permute2d(mgb + vsz * L0.dU, P.prec, dU, P.prec, L0, 3, 0, 0, s));
     return NMG_OK;
 }
 
@@ -432,7 +420,7 @@ nmg_status newton2d_begin(const nmg_desc *d, const nmg_params *p, void *ws, size
 {
     if (!ws || !U) return set_error(NMG_EINVAL, "null argument");
     Plan2D P;
-    nmg_status st = build2d_for(P, d, p, ws_bytes);
+    nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
     if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;
@@ -450,7 +438,7 @@ nmg_status newton2d_steps(const nmg_desc *d, const nmg_params *p, void *ws, size
     if (!ws || !U) return set_error(NMG_EINVAL, "null argument");
     if (steps < 0) return set_error(NMG_EINVAL, "steps must be >= 0");
     Plan2D P;
-    nmg_status st = build2d_for(P, d, p, ws_bytes);
+    nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
     if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;
@@ -470,17 +458,17 @@ nmg_status autotune2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t w
     nmg_params q = *p;
     q.schedule = 0;
     Plan2D P;
-    nmg_status st = build2d_for(P, d, &q, ws_bytes);
+    nmg_status st = build2d(P, d, &q);
     if (st != NMG_OK) return st;
     if (P.sweeps) return set_error(NMG_EINVAL, "the schedules concern the multicolour smoother");
     if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *mgb = (char *)ws + P.off_mg;
     const size_t vsz = P.prec == NMG_FP32_MG ? 4 : 8;
     const Level2D &L0 = P.L[0];
-    HIP_TRY2(launch_permute2d(J, NMG_FP64, mgb + vsz * L0.J, P.prec, L0, 9 * L0.nb, 1, s));
+    HIP_TRY2(launch_permute2d(J, NMG_FP64, mgb + vsz * L0.J, P.prec, L0, 9 * L0.nb, 1, 1, s));
     HIP_TRY2(launch_dinv2d(J, mgb + vsz * L0.Dinv, L0, P.prec, s));
     if ((st = coarsen_all(P, mgb, s)) != NMG_OK) return st;
-    HIP_TRY2(launch_permute2d(rhs, P.prec, mgb + vsz * L0.rhs, P.prec, L0, 3, 1, s));
+    HIP_TRY2(launch_permute2d(rhs, P.prec, mgb + vsz * L0.rhs, P.prec, L0, 3, 1, 1, s));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY2(hipEventCreate(&e0));
     struct Ev { hipEvent_t &a, &b; ~Ev() { if (a) (void)hipEventDestroy(a); if (b) (void)hipEventDestroy(b); } } guard{e0, e1};
@@ -512,7 +500,7 @@ nmg_status newton2d(const nmg_desc *d, const nmg_params *p, void *ws, size_t ws_
 {
     if (!ws || !U || !stats) return set_error(NMG_EINVAL, "null argument");
     Plan2D P;
-    nmg_status st = build2d_for(P, d, p, ws_bytes);
+    nmg_status st = build2d(P, d, p);
     if (st != NMG_OK) return st;
     if (ws_bytes < P.off_box) return set_error(NMG_ENOMEM_WS, "workspace too small");
     char *w = (char *)ws;

@@ -82,7 +82,7 @@ __device__ __forceinline__ void coarsen_block(T *mg, const Level2D &Lf, const Le
     if (P >= 0 && P < Lc.nx && Q >= 0 && Q < Lc.ny) {
 #pragma unroll
         for (int f = 0; f < 4; f++) {
-            const long long fc = perm2d(Lf.P, 2 * I + (f & 1), 2 * Jq + (f >> 1));
+            const long long fc = perm2d_rows(Lf.P, 2 * I + (f & 1), 2 * Jq + (f >> 1));
 #pragma unroll
             for (int g = 0; g < 4; g++) {
                 const int b = find_off(NB, 2 * dP + (g & 1) - (f & 1), 2 * dQ + (g >> 1) - (f >> 1));
@@ -116,32 +116,44 @@ __global__ void __launch_bounds__(64) k_coarsen2d(T *mg, Level2D Lf, Level2D Lc)
     }
 }
 
-// cell (i, j) of slot p of a colour's block on a level in the tiled order; false: an empty slot
-__device__ __forceinline__ bool tiled_cell(const Level2D &L, int colour, long long p, int &i, int &j)
+// A launch per colour pass over a level whose rows lie in tiles: a wavefront takes 64 rows of the tile
+// (column blockIdx.z, row blockIdx.x of tiles) and colour, the blockIdx.y-th 64 from a multiple of 16 on
+// (from anywhere else a load takes twice the accesses of the first-level cache).  dU is in the order
+// without tiles, and its cache lines cross from a tile to the next in its row: with blockIdx.x along the
+// column, the tiles of a row mostly fall to one XCD, whose L2 then writes whole lines (1024 x 512, a pass:
+// FP32 15.0 us with the row's tiles on all XCDs, 12.7 so; FP64 17.1 to 26.8, 16.8 to 25.7).
+// (i, j), row: the cell of lane p; false: the tile has none there.
+constexpr int kTileRows = 64, kRowAlign = 16;
+
+__device__ __forceinline__ bool tiled_cell(const Level2D &L, int colour, int p, int &i, int &j, int &row)
 {
-    const int tile = (int)(p / L.P.W), e = (int)(p - (long long)tile * L.P.W);
-    const int tj = tile / L.P.gx, i0 = (tile - tj * L.P.gx) * L.P.tw, j0 = tj * L.P.th;
-    const int w = L.nx - i0 < L.P.tw ? L.nx - i0 : L.P.tw, h = L.ny - j0 < L.P.th ? L.ny - j0 : L.P.th;
+    const int i0 = blockIdx.z * L.P.tw(), j0 = blockIdx.x * L.P.th();
+    const int w = L.nx - i0 < L.P.tw() ? L.nx - i0 : L.P.tw(), h = L.ny - j0 < L.P.th() ? L.ny - j0 : L.P.th();
+    const int start = (int)tile3_start(L.P, colour, i0, j0, h);
+    row = (start & -kRowAlign) + blockIdx.y * kTileRows + p;
+    const int e = row - start;
+    if (e < 0 || e >= tile3_count(colour, i0, j0, w, h)) return false;
     int il, jr;
     tile3_cell(colour, i0, j0, w, e, il, jr);
     i = i0 + il;
     j = j0 + jr;
-    return jr < h && il < w;
+    return true;
 }
 
 // `reps` consecutive passes of eq. (22) over the cells of one colour on one level with the
 // NB-block stencil (C = 3 colours (i + j) mod 3 for the nine-block cross, 2 for five points, 9
 // colours (i mod 3) + 3 (j mod 3) for the full 21 cells), thread p taking slot p of that colour's
-// block (row p / W, k-th cell of the colour in the row).  Passes
+// block (row p / W, k-th cell of the colour in the row; tiled_cell where the rows lie in tiles).  Passes
 // of one colour in a row see the same neighbour values, so the off-diagonal sum and D^{-1} r are
 // formed once and the relaxation is applied `reps` times, each result rounded to the storage
 // type as if it had been stored between the passes.  The stencil is unrolled so that every load
 // of the cell's row is issued up front; neighbours outside the grid read the cell's own slot and
 // are left out of the sum.
+// TILED: the level's rows lie in tiles (NB = 9)
 template <typename T, int NB, bool STREAM = false>
 __device__ __forceinline__ void smooth_slot21(T *mg, const Level2D &L, int colour, double omega, int reps, long long p);
 
-template <typename T, int NB, bool STREAM = false>
+template <typename T, int NB, bool STREAM = false, bool TILED = false>
 __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour, double omega, int reps, long long p)
 {
     if constexpr (NB == 21) {
@@ -151,15 +163,21 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
     constexpr int C = NB == 9 ? 3 : 2;
     const int W = L.P.W;
     int i, j;
-    if (NB == 9 && L.P.tw > 0) {
-        if (!tiled_cell(L, colour, p, i, j)) return;
+    long long cc, rr;                            // dU of the cell, its row
+    if constexpr (TILED) {
+        int row;
+        if (!tiled_cell(L, colour, (int)p, i, j, row)) return;
+        rr = row;
+        cc = perm2d_of<C>(L.P, i, j);
     } else {
+        if (p >= (long long)L.P.ny * W) return;
         j = (int)(p / W);
         i = ((colour - j) % C + C) % C + C * (int)(p - (long long)j * W);
         if (i >= L.nx) return;
+        cc = rr = (long long)colour * L.P.ny * W + p;
     }
-    const long long n = L.P.M, cc = (long long)colour * L.P.ny * W + p;
-    const T *Jr = mg + L.J + cc;
+    const long long n = L.P.M;
+    const T *Jr = mg + L.J + rr;
     const T *Ur = mg + L.dU;
     double x[NB][3];
     bool ok[NB];
@@ -169,11 +187,8 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
         stencil_off(NB, b, di, dj);
         const int pi = i + di, pj = j + dj;
         ok[b] = pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny;
-        const int c2 = ((pi + pj) % C + C) % C;
-        const int ic = ((c2 - pj) % C + C) % C;
-        const long long q = !ok[b] ? cc
-                            : NB == 9 && L.P.tw > 0 ? perm2d(L.P, pi, pj)
-                                                    : (long long)c2 * L.ny * W + (long long)pj * W + (pi - ic) / C;
+        const int c2 = (colour + di + dj + 2 * C) % C;           // the neighbour's colour, the same in every lane
+        const long long q = ok[b] ? (long long)c2 * L.ny * W + (long long)pj * W + pi / C : cc;
 #pragma unroll
         for (int c = 0; c < 3; c++) x[b][c] = (double)Ur[c * n + q];
     }
@@ -187,7 +202,7 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
     double r[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
-        r[c] = ld2(mg + L.rhs, c * n + cc);
+        r[c] = ld2(mg + L.rhs, c * n + rr);
 #pragma unroll
         for (int b = 1; b < NB; b++)
             if (ok[b]) r[c] = r[c] + a[b][c];
@@ -195,8 +210,8 @@ __device__ __forceinline__ void smooth_slot(T *mg, const Level2D &L, int colour,
     double t[3];
 #pragma unroll
     for (int c = 0; c < 3; c++)
-        t[c] = lds2<STREAM>(mg + L.Dinv + (c * 3 + 0) * n + cc) * r[0] + lds2<STREAM>(mg + L.Dinv + (c * 3 + 1) * n + cc) * r[1] +
-               lds2<STREAM>(mg + L.Dinv + (c * 3 + 2) * n + cc) * r[2];
+        t[c] = lds2<STREAM>(mg + L.Dinv + (c * 3 + 0) * n + rr) * r[0] + lds2<STREAM>(mg + L.Dinv + (c * 3 + 1) * n + rr) * r[1] +
+               lds2<STREAM>(mg + L.Dinv + (c * 3 + 2) * n + rr) * r[2];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         T d = mg[L.dU + c * n + cc];
@@ -215,6 +230,7 @@ template <typename T, int NB, bool STREAM>
 __device__ __forceinline__ void smooth_slot21(T *mg, const Level2D &L, int colour, double omega, int reps, long long p)
 {
     const int W = L.P.W;
+    if (p >= (long long)L.P.ny * W) return;
     const int jr = (int)(p / W), k = (int)(p - (long long)jr * W);
     const int i = 3 * k + colour % 3, j = 3 * jr + colour / 3;
     if (i >= L.nx || j >= L.ny) return;
@@ -252,12 +268,12 @@ __device__ __forceinline__ void smooth_slot21(T *mg, const Level2D &L, int colou
     }
 }
 
-template <typename T, int NB, bool STREAM>
-__global__ void __launch_bounds__(256) k_smooth2d_pass(T *mg, Level2D L, int colour, double omega, int reps)
+// (FP32 cross: at most 128 registers, for four wavefronts a SIMD; with rows in tiles 132 without the bound)
+template <typename T, int NB, bool STREAM, bool TILED = false>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 && NB == 9 ? 4 : 1) k_smooth2d_pass(T *mg, Level2D L, int colour, double omega, int reps)
 {
-    const long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (p >= (long long)L.P.ny * L.P.W) return;
-    smooth_slot<T, NB, STREAM>(mg, L, colour, omega, reps, p);
+    const long long first = TILED ? 0 : blockIdx.x * (long long)blockDim.x;
+    smooth_slot<T, NB, STREAM, TILED>(mg, L, colour, omega, reps, first + threadIdx.x);
 }
 
 // The same passes with each cell's three rows of eq. (22) on three lanes: wavefront c of a
@@ -268,33 +284,36 @@ __global__ void __launch_bounds__(256) k_smooth2d_pass(T *mg, Level2D L, int col
 // are identical; three times the threads of the per-cell form, and a third of its loads per
 // thread, keep more of a colour's cells in flight.
 constexpr int kSplitCells = 64;
+static_assert(kSplitCells == kTileRows, "one chunk of a tile's rows a workgroup");
 
-template <typename T, int NB, bool STREAM>
+template <typename T, int NB, bool STREAM, bool TILED = false>
 __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level2D L, int colour, double omega, int reps)
 {
     __shared__ double sr[3][kSplitCells];
     constexpr int C = NB == 9 ? 3 : (NB == 21 ? 9 : 2);
     const int c = threadIdx.x / kSplitCells, lane = threadIdx.x % kSplitCells;
-    const long long p = blockIdx.x * (long long)kSplitCells + lane;
     const int W = L.P.W;
-    bool valid = p < (long long)L.P.ny * W;
+    bool valid;
     int i = 0, j = 0;
-    if (valid) {
+    long long cc = 0, rr = 0;                    // dU of the cell, its row
+    if constexpr (TILED) {
+        int row;
+        valid = tiled_cell(L, colour, lane, i, j, row);
+        if (valid) { rr = row; cc = perm2d_of<3>(L.P, i, j); }
+    } else {
+        const long long p = blockIdx.x * (long long)kSplitCells + lane;
         const int jr = (int)(p / W), k = (int)(p - (long long)jr * W);
-        if (NB == 9 && L.P.tw > 0) {
-            valid = tiled_cell(L, colour, p, i, j);
-        } else {
-            if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
-            else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
-            valid = i < L.nx && j < L.ny;
-        }
+        if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
+        else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
+        valid = p < (long long)L.P.ny * W && i < L.nx && j < L.ny;
+        cc = rr = (long long)colour * L.P.ny * W + p;
     }
-    const long long n = L.P.M, cc = (long long)colour * L.P.ny * W + p;
+    const long long n = L.P.M;
     double r = 0.0;
     if (valid) {
-        const T *Jr = mg + L.J + cc;
+        const T *Jr = mg + L.J + rr;
         const T *Ur = mg + L.dU;
-        r = ld2(mg + L.rhs, c * n + cc);
+        r = ld2(mg + L.rhs, c * n + rr);
 #pragma unroll
         for (int b = 1; b < NB; b++) {
             int di, dj;
@@ -311,9 +330,9 @@ __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level
     sr[c][lane] = r;
     __syncthreads();
     if (!valid) return;
-    const double t = lds2<STREAM>(mg + L.Dinv + (c * 3 + 0) * n + cc) * sr[0][lane] +
-                     lds2<STREAM>(mg + L.Dinv + (c * 3 + 1) * n + cc) * sr[1][lane] +
-                     lds2<STREAM>(mg + L.Dinv + (c * 3 + 2) * n + cc) * sr[2][lane];
+    const double t = lds2<STREAM>(mg + L.Dinv + (c * 3 + 0) * n + rr) * sr[0][lane] +
+                     lds2<STREAM>(mg + L.Dinv + (c * 3 + 1) * n + rr) * sr[1][lane] +
+                     lds2<STREAM>(mg + L.Dinv + (c * 3 + 2) * n + rr) * sr[2][lane];
     T d = mg[L.dU + c * n + cc];
     for (int q = 0; q < reps; q++) d = (T)((1.0 - omega) * (double)d - omega * t);
     mg[L.dU + c * n + cc] = d;
@@ -421,7 +440,7 @@ template <typename T>
 __device__ __forceinline__ void restrict_child(const T *mg, const Level2D &Lf, int fi, int fj, double a[3])
 {
     const long long nf = Lf.P.M;
-    const long long fc = perm2d(Lf.P, fi, fj);
+    const long long fc = perm2d_rows(Lf.P, fi, fj);
 #pragma unroll
     for (int c = 0; c < 3; c++) a[c] = ld2(mg + Lf.rhs, c * nf + fc);
     for (int b = 0; b < Lf.nb; b++) {
@@ -989,7 +1008,7 @@ __global__ void __launch_bounds__(kResNT) k_resident2d(T *mg, Resident2DArgs A)
 // held: in registers (one FP64 or two FP32 rows a thread) and kLdsRows in LDS.  The symmetric schedule
 // passes over colour 1 every other time and over colours 0 and 2 every fourth, so colour 1 is held
 // first, after as many cells of colours 0 and 2 as leave each of them one streamed cell a thread.  The
-// rest is streamed in every pass, contiguously (tiled order), and that is the bound: about 7.6 TB/s
+// rest is streamed in every pass, contiguously (its rows lie in tiles), and that is the bound: about 7.6 TB/s
 // from the memory-side cache, which the streamed part fits (235 MB; all rows: 6.1-6.6 TB/s).
 // 1024 x 512 FP64: 25.8 us a pass as separate launches, 14.2 so; FP32 13.6, 5.7.
 constexpr int kStrCells = 2600;                  // LDS cells of a tile with a ring of two
@@ -1039,10 +1058,11 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
     if (t == 0) dead = 0;
 
     int cells[C], held[C], in_lds;
+    long long row0[C];                           // where the tile's rows begin
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        cells[c] = th / 3 * tw;
-        for (int jr = th - th % 3; jr < th; jr++) cells[c] += (tw - tile3_first(c, i0, j0, jr) + 2) / 3;
+        cells[c] = tile3_count(c, i0, j0, tw, th);
+        row0[c] = tile3_start(L.P, c, i0, j0, th);
     }
     streamed_split(cells, EPT * kResNT, held, in_lds);
     // place in LDS of cell e of colour c, with bit 16 set where other tiles read it and bit 16 + b where
@@ -1059,7 +1079,7 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         }
         return p;
     };
-    auto slot_of = [&](int c, int e) { return ((long long)c * L.P.ny + bj * A.gx + bi) * L.P.W + e; };
+    auto slot_of = [&](int c, int e) { return (c == 0 ? row0[0] : c == 1 ? row0[1] : row0[2]) + e; };
 
     // rows in registers: the slots k * 512 + t take colour 1's cells, then colour 0's, then colour 2's
     T Jb[EPT][NB][9], Di[HOLD ? EPT : 1][9], rh[HOLD ? EPT : 1][3];
@@ -1118,8 +1138,8 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
         const int r = e / ld, i = i0 - 2 + e - r * ld, j = j0 - 2 + r;
         Cell v = Cell{};
         if (i >= 0 && i < nx && j >= 0 && j < ny) {
-            const long long fc = perm2d(L.P, i, j);
-            const long long pc = A.prolong ? perm2d(A.Lc.P, i >> 1, j >> 1) : 0;
+            const long long fc = perm2d_of<C>(L.P, i, j);
+            const long long pc = A.prolong ? perm2d_of<2>(A.Lc.P, i >> 1, j >> 1) : 0;
 #pragma unroll
             for (int c = 0; c < 3; c++) {
                 v.v[c] = mg[L.dU + c * n + fc];
@@ -1308,10 +1328,10 @@ __global__ void __launch_bounds__(kResNT) k_streamed2d(T *mg, Resident2DArgs A)
     for (int c = 0; c < C; c++)
         for (int e = t; e < cells[c]; e += kResNT) {
             const int f = place(c, e), p = f & 0xffff, il = p % ld, jr = p / ld;
-            const long long cc = slot_of(c, e);
+            const long long cc = slot_of(c, e), uc = perm2d_of<C>(L.P, i0 + il, j0 + jr);
             const Cell *u = su + p;
 #pragma unroll
-            for (int x = 0; x < 3; x++) mg[L.dU + x * n + cc] = bad ? (T)__builtin_nan("") : u->v[x];
+            for (int x = 0; x < 3; x++) mg[L.dU + x * n + uc] = bad ? (T)__builtin_nan("") : u->v[x];
             if (!A.restr) continue;
             double a[3];
 #pragma unroll
@@ -1703,20 +1723,22 @@ __global__ void k_dinv2d(const double *J, T *Dinv, Level2D L0)
 #pragma unroll
         for (int e = 0; e < 9; e++) D[e] = J[e * n + c];
         inv3d(D, B);
-        const long long q = perm2d(L0.P, (int)(c % L0.nx), (int)(c / L0.nx));
+        const long long q = perm2d_rows(L0.P, (int)(c % L0.nx), (int)(c / L0.nx));
 #pragma unroll
         for (int e = 0; e < 9; e++) Dinv[e * L0.P.M + q] = (T)B[e];
     }
 }
 
-// per-cell entries between the natural order [nent][n] and a level's order [nent][M]
+// per-cell entries between the natural order [nent][n] and a level's order [nent][M], of rows (J, rhs)
+// or of dU
 template <typename S, typename D>
-__global__ void k_permute2d(const S *src, D *dst, Level2D L, int nent, int to_level)
+__global__ void k_permute2d(const S *src, D *dst, Level2D L, int nent, int rows, int to_level)
 {
     const long long n = (long long)L.nx * L.ny, total = n * nent;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
         const long long c = e % n, a = e / n;
-        const long long q = perm2d(L.P, (int)(c % L.nx), (int)(c / L.nx));
+        const int i = (int)(c % L.nx), j = (int)(c / L.nx);
+        const long long q = rows ? perm2d_rows(L.P, i, j) : perm2d(L.P, i, j);
         if (to_level) dst[a * L.P.M + q] = (D)src[e];
         else dst[e] = (D)src[a * L.P.M + q];
     }
@@ -1858,7 +1880,20 @@ template <typename T, int NB, bool STREAM>
 static void smooth2d_launch(T *mg, const Level2D &L, int colour, int reps, double omega, hipStream_t s, bool alt)
 {
     const long long slots = (long long)L.P.ny * L.P.W;
-    if ((NB == 21) != alt) {
+    const bool split = (NB == 21) != alt;
+    if constexpr (NB == 9) {
+        if (L.P.tw() > 0) {
+            // a tile has at most ceil(tw th / 3) cells of a colour
+            const int tw = L.P.tw(), th = L.P.th(), most = kRowAlign - 1 + (tw * th + 2) / 3;
+            const dim3 grid((L.ny + th - 1) / th, (most + kTileRows - 1) / kTileRows, (L.nx + tw - 1) / tw);
+            if (split)
+                hipLaunchKernelGGL((k_smooth2d_split<T, NB, STREAM, true>), grid, dim3(3 * kSplitCells), 0, s, mg, L, colour, omega, reps);
+            else
+                hipLaunchKernelGGL((k_smooth2d_pass<T, NB, STREAM, true>), grid, dim3(kTileRows), 0, s, mg, L, colour, omega, reps);
+            return;
+        }
+    }
+    if (split) {
         dim3 grid((unsigned)((slots + kSplitCells - 1) / kSplitCells));
         hipLaunchKernelGGL((k_smooth2d_split<T, NB, STREAM>), grid, dim3(3 * kSplitCells), 0, s, mg, L, colour, omega, reps);
     } else {
@@ -2014,7 +2049,7 @@ hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, cons
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s)
 {
-    if (G.tx < 2 || L.P.tw > 0 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
+    if (G.tx < 2 || L.P.tw() > 0 || L.P.C != (L.nb == 21 ? 9 : (L.nb == 9 ? 3 : 2))) return hipErrorInvalidValue;
     if (!phase_exchanges(L, G, nu, restr)) return hipErrorInvalidValue;
     Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
     void *args[] = {&mg, &A};
@@ -2051,7 +2086,7 @@ hipError_t launch_streamed2d(void *mg, const Level2D &L, const Level2D &Lc, cons
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s)
 {
-    if (G.tx < 2 || L.P.tw != G.tx || L.P.th != G.ty || L.P.gx != G.gx) return hipErrorInvalidValue;
+    if (G.tx < 2 || L.P.tw() != G.tx || L.P.th() != G.ty || L.P.nx() != L.nx) return hipErrorInvalidValue;
     if (!phase_exchanges(L, G, nu, restr)) return hipErrorInvalidValue;
     Resident2DArgs A = resident_args(L, Lc, G, nu, prolong, restr, tag, omega, box, cells, state);
     void *args[] = {&mg, &A};
@@ -2156,7 +2191,7 @@ hipError_t launch_dinv2d(const double *J, void *Dinv, const Level2D &L0, int pre
 }
 
 hipError_t launch_permute2d(const void *src, int src_prec, void *dst, int dst_prec, const Level2D &L, int nent,
-                            int to_level, hipStream_t s)
+                            int rows, int to_level, hipStream_t s)
 {
     const long long total = (long long)L.nx * L.ny * nent;
     int blocks = (int)std::min<long long>((total + 255) / 256, 16384);
@@ -2164,16 +2199,16 @@ hipError_t launch_permute2d(const void *src, int src_prec, void *dst, int dst_pr
     const bool s32 = src_prec == NMG_FP32_MG, d32 = dst_prec == NMG_FP32_MG;
     if (!s32 && !d32)
         hipLaunchKernelGGL((k_permute2d<double, double>), dim3(blocks), dim3(256), 0, s, (const double *)src,
-                           (double *)dst, L, nent, to_level);
+                           (double *)dst, L, nent, rows, to_level);
     else if (!s32)
         hipLaunchKernelGGL((k_permute2d<double, float>), dim3(blocks), dim3(256), 0, s, (const double *)src,
-                           (float *)dst, L, nent, to_level);
+                           (float *)dst, L, nent, rows, to_level);
     else if (!d32)
         hipLaunchKernelGGL((k_permute2d<float, double>), dim3(blocks), dim3(256), 0, s, (const float *)src,
-                           (double *)dst, L, nent, to_level);
+                           (double *)dst, L, nent, rows, to_level);
     else
         hipLaunchKernelGGL((k_permute2d<float, float>), dim3(blocks), dim3(256), 0, s, (const float *)src,
-                           (float *)dst, L, nent, to_level);
+                           (float *)dst, L, nent, rows, to_level);
     return hipGetLastError();
 }
 

@@ -139,17 +139,20 @@ struct Inst2D {
 
 // Colour-blocked cell order of a 2D level: the cells of one colour are stored together, row by
 // row, so that a colour pass of the smoother reads contiguous data.  C = 2 or 3: colour
-// c = (i + j) mod C, cell (i, j) at c*ny*W + j*W + (i - i_c(j)) / C, i_c(j) the first column of
-// colour c in row j and W = ceil(nx / C) slots per row and colour.  C = 9 (the full 21-cell
-// stencil): colour c = (i mod 3) + 3 (j mod 3), cell (i, j) at c*ceil(ny/3)*W + (j/3)*W + i/3 with
-// W = ceil(nx / 3).  C = 1 is the natural order j*nx + i.
-// Tiled order (tw > 0, C = 3): a colour's cells lie together tile by tile (tiles of tw x th cells, gx in
-// a row, W = ceil(tw th / 3) slots per tile and colour, ny = the number of tiles), within a tile row
-// by row without gaps, so that a workgroup that streams its tile's rows reads them contiguously.
+// c = (i + j) mod C, cell (i, j) at c*ny*W + j*W + floor(i / C), W = ceil(nx / C) slots per row and
+// colour.  C = 9 (the full 21-cell stencil): colour c = (i mod 3) + 3 (j mod 3), cell (i, j) at
+// c*ceil(ny/3)*W + (j/3)*W + i/3 with W = ceil(nx / 3).  C = 1 is the natural order j*nx + i.
+// With tiles (tw, th; C = 3) the operator's rows (J, D^{-1}, rhs; not dU) lie tile by tile in their
+// colour's slots, within a tile row by row, all without gaps, so that a workgroup that streams its
+// tile's rows reads them contiguously.  The order is the level's own, the same however a call runs: a
+// later call finds the operator as the set-up left it.
 struct Perm2D {
-    int C, W, ny, pad;  // ny: rows per colour (ny of the level, ceil(ny / 3) when C = 9)
-    long long M;       // slots per array: C * ny * W
-    int tw, th, gx, nx;
+    int C, W, ny;       // ny: rows per colour (ny of the level, ceil(ny / 3) when C = 9)
+    unsigned tile;      // tw | th << 8 | nx of the level << 16 (levels with tiles are at most 5120 cells wide), or 0
+    long long M;        // slots per array: C * ny * W
+    __host__ __device__ int tw() const { return tile & 0xff; }
+    __host__ __device__ int th() const { return tile >> 8 & 0xff; }
+    __host__ __device__ int nx() const { return tile >> 16; }
 };
 
 // Cells of one colour in a tile of w columns whose first cell is (i0, j0), C = 3: three rows in a row
@@ -162,11 +165,24 @@ __host__ __device__ inline int tile3_pos(int c, int i0, int j0, int w, int il, i
     for (int r = jr - jr % 3; r < jr; r++) pos += (w - tile3_first(c, i0, j0, r) + 2) / 3;
     return pos + (il - tile3_first(c, i0, j0, jr)) / 3;
 }
-// the cell at place p of colour c (the inverse); jr past the tile's last row when there is none
+// cells of colour c in w columns and h rows from (i0, j0)
+__host__ __device__ inline int tile3_count(int c, int i0, int j0, int w, int h)
+{
+    int n = h / 3 * w;
+    for (int r = h - h % 3; r < h; r++) n += (w - tile3_first(c, i0, j0, r) + 2) / 3;
+    return n;
+}
+// the cell at place p of colour c (the inverse of tile3_pos, p < tile3_count); the tiles are small
+// enough (p below 2^12, w below 2^7) for the quotient in FP32
 __host__ __device__ inline void tile3_cell(int c, int i0, int j0, int w, int p, int &il, int &jr)
 {
-    jr = p / w * 3;
-    int rem = p % w;
+#ifdef __HIP_DEVICE_COMPILE__
+    const int q = (int)(((float)p + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+#else
+    const int q = (int)(((float)p + 0.5f) * (1.0f / (float)w));
+#endif
+    jr = q * 3;
+    int rem = p - q * w;
     for (int x = 0; x < 2; x++) {
         const int m = (w - tile3_first(c, i0, j0, jr) + 2) / 3;
         if (rem < m) break;
@@ -176,9 +192,11 @@ __host__ __device__ inline void tile3_cell(int c, int i0, int j0, int w, int p, 
     il = tile3_first(c, i0, j0, jr) + 3 * rem;
 }
 
-// The orders without tiles where the number of colours is known: 9 for the full stencil's level, 3 for
-// the cross's, 2 below.  A level that a resident or one-workgroup kernel holds never has the tiled order;
-// without that case the kernels need fewer registers.
+// The order where the number of colours is known: 9 for the full stencil's level, 3 for the cross's, 2
+// below.  A level that a resident or one-workgroup kernel holds never has its rows in tiles; without
+// that case the kernels need fewer registers.  ((i - i_c) / C, i_c the first column of colour c in row j,
+// is floor(i / C); written so, the resident kernels are scheduled better: 128 x 64 with 21 cells, two
+// Newton steps, 13.97 against 14.15 ms.)
 constexpr int colours2d(int nb) { return nb == 21 ? 9 : (nb == 9 ? 3 : 2); }
 
 template <int C>
@@ -189,45 +207,42 @@ __host__ __device__ inline long long perm2d_of(const Perm2D &P, int i, int j)
     return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / C;
 }
 
+// dU of cell (i, j); without tiles its row, too
 __host__ __device__ inline long long perm2d(const Perm2D &P, int i, int j)
 {
-    if (P.tw > 0) {
-        const int c = (i + j) % P.C;
-        const int ti = i / P.tw, tj = j / P.th, i0 = ti * P.tw, j0 = tj * P.th;
-        const int w = P.nx - i0 < P.tw ? P.nx - i0 : P.tw;
-        return ((long long)c * P.ny + tj * P.gx + ti) * P.W + tile3_pos(c, i0, j0, w, i - i0, j - j0);
-    }
     if (P.C == 9) return perm2d_of<9>(P, i, j);
-    const int c = (i + j) % P.C, ic = ((c - j) % P.C + P.C) % P.C;
-    return (long long)c * P.ny * P.W + (long long)j * P.W + (i - ic) / P.C;
+    return (long long)((i + j) % P.C) * P.ny * P.W + (long long)j * P.W + i / P.C;
+}
+
+// where colour c's rows of the tile of w x h cells from (i0, j0) begin
+__host__ __device__ inline long long tile3_start(const Perm2D &P, int c, int i0, int j0, int h)
+{
+    return (long long)c * P.ny * P.W + tile3_count(c, 0, 0, P.nx(), j0) + tile3_count(c, 0, j0, i0, h);
+}
+
+// the row of cell (i, j)
+__host__ __device__ inline long long perm2d_rows(const Perm2D &P, int i, int j)
+{
+    if (P.tile == 0) return perm2d(P, i, j);
+    const int c = (i + j) % 3, i0 = i / P.tw() * P.tw(), j0 = j / P.th() * P.th();
+    const int w = P.nx() - i0 < P.tw() ? P.nx() - i0 : P.tw(), h = P.ny - j0 < P.th() ? P.ny - j0 : P.th();
+    return tile3_start(P, c, i0, j0, h) + tile3_pos(c, i0, j0, w, i - i0, j - j0);
 }
 
 inline Perm2D make_perm2d(int nx, int ny, int C)
 {
     Perm2D P;
     P.C = C;
+    P.tile = 0;
     P.W = C == 9 ? (nx + 2) / 3 : (nx + C - 1) / C;
     P.ny = C == 9 ? (ny + 2) / 3 : ny;
-    P.pad = 0;
     P.M = (long long)C * P.ny * P.W;
-    P.tw = P.th = P.gx = 0;
-    P.nx = nx;
     return P;
 }
 
-inline Perm2D make_perm2d_tiled(int nx, int ny, int tw, int th)
+inline void tile_rows(Perm2D &P, int nx, int tw, int th)
 {
-    Perm2D P;
-    P.C = 3;
-    P.W = (tw * th + 2) / 3;
-    P.gx = (nx + tw - 1) / tw;
-    P.ny = P.gx * ((ny + th - 1) / th);
-    P.pad = 0;
-    P.M = 3LL * P.ny * P.W;
-    P.tw = tw;
-    P.th = th;
-    P.nx = nx;
-    return P;
+    P.tile = (unsigned)(tw | th << 8 | nx << 16);
 }
 
 // Block b of a 2D stencil of nb blocks (closed forms, no tables): nb = 9, the cross of eq. (21)
@@ -249,8 +264,8 @@ __host__ __device__ constexpr int stencil_dy(int nb, int b)
     return ((b - 17) & 1) ? 2 : -2;
 }
 
-// One 2D multigrid level: blocks J [nb*9][M], Dinv [9][M], rhs [3][M], dU [3][M] in the level's
-// colour-blocked order (C = 3 on a nine-block finest level, 9 on a 21-block one, 2 on five-point
+// One 2D multigrid level: blocks J [nb*9][M], Dinv [9][M], rhs [3][M] (perm2d_rows) and dU [3][M]
+// (perm2d) in the level's colour-blocked order (C = 3 on a nine-block finest level, 9 on a 21-block one, 2 on five-point
 // levels); offsets in elements of the value type.
 struct Level2D {
     int nx, ny, nb, pad;
@@ -339,8 +354,8 @@ Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg);
 // workgroups of k_resident2d that can be resident at once on the current device (0: none)
 int resident2d_max_wg(int nb, int prec);
 // A cross-stencil level whose rows the registers of the chip do not hold all: the tiles of
-// launch_streamed2d (by size alone; tx = 0: the level is resident, or too large for it).  Such a level
-// is stored in the tiled order.
+// launch_streamed2d (by size alone; tx = 0: the level is resident, or too large for it).  Such a level's
+// rows lie in these tiles.
 Resident2D streamed2d_plan(const Level2D &L, int prec);
 int streamed2d_max_wg(int prec);
 hipError_t launch_streamed2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
@@ -377,9 +392,10 @@ hipError_t launch_fill(void *p, int prec, long long n, hipStream_t s);
 hipError_t launch_update2d(double *U, const void *mg, const Level2D &L0, double tau,
                            const NewtonState *state, int prec, hipStream_t s);
 hipError_t launch_dinv2d(const double *J, void *Dinv, const Level2D &L0, int prec, hipStream_t s);
-// nent per-cell entries between the natural order (src or dst, per `to_level`) and a level's order
+// nent per-cell entries between the natural order (src or dst, per `to_level`) and a level's order, its
+// rows' (J, rhs) or dU's
 hipError_t launch_permute2d(const void *src, int src_prec, void *dst, int dst_prec, const Level2D &L, int nent,
-                            int to_level, hipStream_t s);
+                            int rows, int to_level, hipStream_t s);
 hipError_t launch_state2d(const double *partial, int ntiles, long long ncells, double tol, int n_max,
                           NewtonState *state, double *hist, int max_hist, int init, hipStream_t s);
 constexpr int kMaxCoarse2D = 40;   // cells on the coarsest 2D level (dense solve in LDS)

@@ -744,7 +744,7 @@ __device__ __forceinline__ void interior_rows(const Inst2D &I, const Perm2D &Pm,
     if (row) {
         const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
         o.M = Pm.M;
-        o.slot = perm2d(Pm, i, j);
+        o.slot = perm2d_rows(Pm, i, j);
         o.R0 = I.R[cidx];
         o.R1 = I.R[n + cidx];
         o.R2 = I.R[2 * n + cidx];
@@ -1048,7 +1048,7 @@ __device__ __forceinline__ void border_rows(const Inst2D &I, const Perm2D &Pm, T
         const long long n = (long long)I.Nx * I.Ny, cidx = (long long)j * I.Nx + i;
         JacOut o;
         o.M = Pm.M;
-        o.slot = slot = perm2d(Pm, i, j);
+        o.slot = slot = perm2d_rows(Pm, i, j);
         o.R0 = I.R[cidx];
         o.R1 = I.R[n + cidx];
         o.R2 = I.R[2 * n + cidx];

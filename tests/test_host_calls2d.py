@@ -70,3 +70,31 @@ def test_every_phase_of_several_workgroups_exchanges(calls, prec, jac):
             assert gx * gy == 1 or done >= 1, f"{q}: {kind} {v} has no exchange"
             seen += 1
     assert seen > 1000
+
+
+# grids whose finest level is streamed: exact and ragged tiles, FP64 and FP32
+STREAMED = [(1024, 512, 8, 0), (1024, 512, 8, 1), (768, 384, 8, 0), (64, 2112, 7, 0), (128, 4224, 8, 1)]
+
+
+@pytest.mark.parametrize("nx,ny,levels,prec", STREAMED)
+def test_the_operator_lies_where_the_set_up_left_it(calls, nx, ny, levels, prec):
+    """A set-up call and a call that reuses its operator agree on the order of the rows, whatever
+    differs between them: the workspace's size, a capture, the device's compute units.  And each way
+    of a call runs as it is meant to: streamed where that is possible, else a launch a pass."""
+    ways = {(0, 0, 256): True, (1, 0, 256): False, (0, 1, 256): False, (0, 0, 64): False}
+    for entry in ("setup", "vcycle"):
+        for way, streams in ways.items():
+            (launches, status), = calls([(entry, nx, ny, levels, 9, prec, 2, 2, 3, *way)])
+            assert status == 0
+            assert any(kind == "streamed" for kind, *_ in launches) == streams
+            assert any(kind == "pass" and v[:2] == [nx, ny] for kind, *v in launches) == (not streams)
+            rows = [v[2] for kind, *v in launches if kind == "rows"]
+            assert len(rows) == (2 if entry == "setup" else 1) and set(rows) == {1}, (entry, way)
+
+
+def test_rows_in_tiles_have_a_slot_each(calls):
+    sizes = [(nx, ny, tw, th) for nx in (1, 2, 16, 31, 64, 90) for ny in (1, 3, 34, 47, 70)
+             for tw in (16, 17, 18, 32) for th in (4, 5, 6, 34)]
+    queries = [("order", *q) for q in sizes]
+    for q, (_, bad) in zip(sizes, calls(queries)):
+        assert bad == 0, (q, bad)
