@@ -335,8 +335,6 @@ hipError_t launch_interp_a3(const double *Uc, int nxc, int nyc, double *Uf, hipS
 // 2D
 int residual2d_tiles(int Nx, int Ny);
 hipError_t launch_residual2d(const Inst2D &I, double *partial, hipStream_t s);
-hipError_t launch_res2d_finalize(const double *partial, int ntiles, long long ncells, double *res,
-                                 hipStream_t s);
 // J, rhs, Dinv written in the cell order P (make_perm2d(Nx, Ny, 1) for the natural order)
 hipError_t launch_jacobian2d(const Inst2D &I, const Perm2D &P, void *J, void *rhs, void *Dinv, int prec,
                              hipStream_t s, int nb = 9);

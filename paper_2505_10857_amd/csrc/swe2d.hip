@@ -345,7 +345,6 @@ struct LdsStateT {
         return z[(j - j0 + 2) * kSX + (i - i0 + 2)];
     }
 };
-using LdsState = LdsStateT<false>;
 
 // state in global memory [3][Ny][Nx]; SURF: zavg [Ny+4][Nx+4] (cells -2..Nx+1 x -2..Ny+1)
 template <bool SURF>
@@ -453,19 +452,6 @@ NMG2D_INL void load_slopes(const Inst2D &I, int i, int j, double bx[4], double b
         bx[e] = I.bx[g + e];
         by[e] = I.by[g + e];
     }
-}
-
-// sum of the tile partials in a fixed order: res = sum / (Nx Ny)
-__global__ void __launch_bounds__(256) k_res2d_finalize(const double *partial, int ntiles, long long ncells,
-                                                        double *res)
-{
-    __shared__ double red[4];
-    double v = 0.0;
-    for (int k = threadIdx.x; k < ntiles; k += 256) v += partial[k];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) *res = (red[0] + red[1] + red[2] + red[3]) / (double)ncells;
 }
 
 // ---- Jacobian -------------------------------------------------------------------------------
@@ -1245,13 +1231,6 @@ hipError_t launch_residual2d(const Inst2D &I, double *partial, hipStream_t s)
 }
 
 int residual2d_tiles(int Nx, int Ny) { return ((Nx + kTX - 1) / kTX) * ((Ny + kTY - 1) / kTY); }
-
-hipError_t launch_res2d_finalize(const double *partial, int ntiles, long long ncells, double *res,
-                                 hipStream_t s)
-{
-    hipLaunchKernelGGL(k_res2d_finalize, dim3(1), dim3(256), 0, s, partial, ntiles, ncells, res);
-    return hipGetLastError();
-}
 
 template <typename T, int NB, bool SURF>
 static hipError_t jacobian2d_t(const Inst2D &I, const Perm2D &P, T *J, T *rhs, T *Dinv, hipStream_t s)
