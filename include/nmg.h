@@ -164,7 +164,10 @@ typedef struct {
  *     the rows that the schedule evicts before it returns to them, when its operator is larger
  *     than the memory-side cache);
  *   NMG_SCHED2D_SMALL_BOTTOM: the one-workgroup bottom of the V-cycle starts at levels of at
- *     most 128 cells instead of 512. */
+ *     most 128 cells instead of 512.
+ * The first three concern levels that run a launch per colour pass.  A level whose smoothing phase
+ * is one cooperative launch (every launched level of a cross-stencil grid of up to about 5e5 cells, and of
+ * a 21-cell grid of up to about 4e4, unless the stream is being captured) is the same under them. */
 #define NMG_SCHED2D_ALT_FINEST 1
 #define NMG_SCHED2D_ALT_COARSE 2
 #define NMG_SCHED2D_NO_STREAM 4
@@ -212,7 +215,8 @@ nmg_status nmg_jacobian_assemble_simplified(const nmg_desc *desc, const nmg_para
  * Jacobian J (layout above), multicolour block SOR smoothing (eq. 19/22), restriction and
  * coarse operators of eq. (17)/(24), injection prolongation (eq. 18/25) and a direct solve on
  * the coarsest grid.  setup = 1 copies J into the workspace and builds every coarse operator
- * and diagonal inverse (needed once per J); setup = 0 reuses them.  rhs and dU (in/out) are
+ * and diagonal inverse (needed once per J); setup = 0 reuses them, also where the two calls differ
+ * in the workspace size that they pass or in being captured.  rhs and dU (in/out) are
  * device arrays in the U layout; precision NMG_FP32_MG makes rhs/dU float arrays. */
 nmg_status nmg_mg_vcycle(const nmg_desc *desc, const nmg_params *params, void *ws, size_t ws_bytes,
                          const void *J, const void *rhs, void *dU, int32_t setup, void *stream);
@@ -222,7 +226,8 @@ nmg_status nmg_mg_vcycle(const nmg_desc *desc, const nmg_params *params, void *w
  * 0..NMG_TUNE2D_CANDIDATES-1 (params->schedule is ignored) runs one warm-up V-cycle and then
  * `cycles` timed V-cycles (HIP events on `stream`); ms[c] (host, NMG_TUNE2D_CANDIDATES entries)
  * receives the milliseconds per V-cycle and *best the fastest schedule, to be passed in
- * params->schedule.  2D only; synchronises `stream`; the workspace's correction is overwritten. */
+ * params->schedule.  Where every launched level smooths in cooperative launches, the candidates differ
+ * only by NMG_SCHED2D_SMALL_BOTTOM and *best is one of equals.  2D only; synchronises `stream`; the workspace's correction is overwritten. */
 nmg_status nmg_autotune2d(const nmg_desc *desc, const nmg_params *params, void *ws, size_t ws_bytes,
                           const double *J, const void *rhs, int32_t cycles, int32_t *best, double *ms,
                           void *stream);
@@ -306,7 +311,8 @@ nmg_status nmg_plan_solve(nmg_plan *plan, void *ws, size_t ws_bytes, double *con
 /* Run exactly `steps` Newton steps (or fewer for instances that stop earlier) without
  * re-initialising; nmg_plan_begin evaluates the initial residual.  For step-wise drivers such
  * as a serving loop.  active_out (host, length n; may be NULL) receives 1 for still-active
- * instances; stats (host, may be NULL) the per-instance state. */
+ * instances; stats (host, may be NULL) the per-instance state.  A plan cannot be begun on a stream
+ * that is being captured (NMG_EHIP, nothing enqueued): it uploads its tables. */
 nmg_status nmg_plan_begin(nmg_plan *plan, void *ws, size_t ws_bytes, double *const *U, void *stream);
 nmg_status nmg_plan_steps(nmg_plan *plan, void *ws, int32_t steps, int32_t use_graph,
                           int32_t *active_out, nmg_stats *stats, void *stream);
@@ -341,15 +347,16 @@ nmg_status nmg_plan_profile_read(nmg_plan *plan, double *ms, int32_t *launches);
  *     2048; the coarsest level always) run in the one-workgroup-per-instance bottom-of-cycle
  *     kernel, with two or four cells a thread; the larger levels run in the tiled smoothers.  A
  *     small value spreads more levels over the whole GPU, a large one saves launches and
- *     synchronisation.  Default 2048.  With every tunable at its default, a plan whose finest levels
- *     are covered by one round of workgroups takes several levels a launch above a bottom of at
- *     most 1024 cells instead.
+ *     synchronisation.  Default 2048.  With bottom_cells, smooth_tile and split_finest at their
+ *     defaults, a multigrid plan of one stencil width whose levels above the bottom take at most 512
+ *     workgroups runs several of them a launch, above a bottom of at most 1024 cells instead.
  *   smooth_tile: cells (= threads) per tile of the tiled smoother, 256 or 512 (0: 256).
  *   split_finest: 0 (default) runs the finest level's post-smoothing of one V-cycle and the
  *     pre-smoothing of the next in one launch where the plan allows it (multigrid plans with
  *     nu3 >= 2 whose instances all use the three-block Jacobian); 1 keeps them apart.
- *   fused_finest: reported by nmg_plan_get_options (1 when that fused launch is in use),
- *     ignored by nmg_plan_set_options.
+ *   fused_finest: reported by nmg_plan_get_options (1 when the options and the plan allow that fused
+ *     launch; a plan that runs several levels a launch, see bottom_cells, allows it and does not use
+ *     it), ignored by nmg_plan_set_options.
  *   split_residual: 0 (default) evaluates the residual of eq. (10) and its cell norms inside the
  *     Jacobian launch that ends each Newton step (the Jacobian the next step needs; an instance
  *     that then meets the stopping test leaves it unused); 1 ends each step with a separate

@@ -1953,7 +1953,9 @@ static const void *resident2d_kernel(int nb, int prec, int narrow)
 // estimated time per pass, out of those whose compute region fits the registers, whose halo fits
 // LDS and whose workgroups are all resident at once (one per compute unit).  The estimate: an
 // exchange 1.0 us, shared by m passes; a pass `lat` plus `work` per wavefront that a SIMD has to run;
-// and a little for every workgroup, so that small levels leave compute units to other streams.
+// and a little for every workgroup, so that small levels leave compute units to other streams.  It orders
+// the tilings and does not predict times: 64 x 32, FP32, gets 8 x 4 tiles and m = 5 at an estimated
+// 0.68 us a pass and takes 1.13.  (A phase may exchange more often than planned: phase2d.)
 Resident2D resident2d_plan(const Level2D &L, int prec, int max_wg)
 {
     Resident2D best;

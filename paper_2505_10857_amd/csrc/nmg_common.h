@@ -265,8 +265,8 @@ __host__ __device__ constexpr int stencil_dy(int nb, int b)
 }
 
 // One 2D multigrid level: blocks J [nb*9][M], Dinv [9][M], rhs [3][M] (perm2d_rows) and dU [3][M]
-// (perm2d) in the level's colour-blocked order (C = 3 on a nine-block finest level, 9 on a 21-block one, 2 on five-point
-// levels); offsets in elements of the value type.
+// (perm2d) in the level's colour-blocked order (C = 3 on a nine-block finest level, 9 on a 21-block
+// one, 2 on five-point levels); offsets in elements of the value type.
 struct Level2D {
     int nx, ny, nb, pad;
     Perm2D P;
@@ -285,10 +285,10 @@ inline hipError_t being_captured(hipStream_t s, bool &yes)
 
 // ---- launchers (return hipError_t of the launch) ----------------------------------------
 
-// residual over tiles (batched: tiles index instances) or one instance (tiles == null)
-// recon: the reconstruction of every instance in the launch (NMG_RECON_*)
 // whether a single instance's residual launch writes res itself (its `partial`)
 bool residual1d_sums(int N);
+// residual over tiles (batched: tiles index instances) or one instance (tiles == null)
+// recon: the reconstruction of every instance in the launch (NMG_RECON_*)
 hipError_t launch_residual1d(const Inst1D *insts_dev, const Tile *tiles, int ntiles,
                              const Inst1D *single, NewtonState *state, double *partial, int recon,
                              hipStream_t s);
@@ -303,9 +303,11 @@ hipError_t launch_jacobian1d(const Inst1D *insts_dev, const Tile *tiles, int nti
                              const Inst1D *single, double *J_single, const MGArgs &mg, int prec,
                              int nb_mask, int recon, hipStream_t s, double *fused_partial = nullptr);
 hipError_t launch_coarsen1d(const MGArgs &mg, const Tile *tiles, int ntiles, int prec, hipStream_t s);
-// nt: threads of the bottom workgroup (256, 512 or 1024); it handles levels of up to 2 nt cells
+// up to kGroupLevels levels of a tile in one launch; mode 0: down, 1: up; src_out as in launch_smooth1d, of
+// the group's first level
 hipError_t launch_group1d(const MGArgs &mg, const Tile *tiles, int ntiles, int mode, int zero_init, int final_update,
                           int src_out, int prec, hipStream_t s);
+// nt: half the cells of the largest level that it takes (256, 512 or 1024); the workgroup has 512 threads
 hipError_t launch_bottom(const MGArgs &mg, const int *inst_list, int n, int zero_init0, int final_update,
                          int prec, int nt, hipStream_t s);
 // mode 0: pre-smoothing + restriction; 1: prolongation + post-smoothing (+ update); 2: both,
@@ -367,9 +369,10 @@ size_t resident2d_box_bytes(long long cells, int prec);
 unsigned resident2d_exchanges(const Level2D &L, int nu, int m);
 // the tiling of one phase of nu >= 1 iterations: G with as many passes an exchange as leave the phase one
 Resident2D phase2d(const Level2D &L, const Resident2D &G, int nu, int restr);
-// [prolongation from Lc +] nu smoothing iterations [+ restriction to Lc] in one cooperative launch
 // an empty cooperative launch
 hipError_t open_cooperative_queue(hipStream_t s);
+// [prolongation from Lc +] nu smoothing iterations [+ restriction to Lc] in one cooperative launch, G as
+// phase2d gives it
 hipError_t launch_resident2d(void *mg, const Level2D &L, const Level2D &Lc, const Resident2D &G, int nu, int prolong,
                              int restr, unsigned tag, double omega, void *box, long long cells,
                              const NewtonState *state, int prec, hipStream_t s);
