@@ -246,7 +246,7 @@ __device__ __forceinline__ void smooth_slot21(T *mg, const Level2D &L, int colou
         stencil_off(21, b, di, dj);
         const int pi = i + di, pj = j + dj;
         const bool ok = pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny;
-        const long long q = ok ? perm2d(L.P, pi, pj) : cc;
+        const long long q = ok ? perm2d_of<9>(L.P, pi, pj) : cc;
         const double x0 = (double)Ur[q], x1 = (double)Ur[n + q], x2 = (double)Ur[2 * n + q];
 #pragma unroll
         for (int c = 0; c < 3; c++) {
@@ -292,21 +292,22 @@ __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level
     __shared__ double sr[3][kSplitCells];
     constexpr int C = NB == 9 ? 3 : (NB == 21 ? 9 : 2);
     const int c = threadIdx.x / kSplitCells, lane = threadIdx.x % kSplitCells;
+    const long long p = blockIdx.x * (long long)kSplitCells + lane;
     const int W = L.P.W;
-    bool valid;
+    bool valid = TILED || p < (long long)L.P.ny * W;
     int i = 0, j = 0;
-    long long cc = 0, rr = 0;                    // dU of the cell, its row
-    if constexpr (TILED) {
-        int row;
-        valid = tiled_cell(L, colour, lane, i, j, row);
-        if (valid) { rr = row; cc = perm2d_of<3>(L.P, i, j); }
-    } else {
-        const long long p = blockIdx.x * (long long)kSplitCells + lane;
-        const int jr = (int)(p / W), k = (int)(p - (long long)jr * W);
-        if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
-        else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
-        valid = p < (long long)L.P.ny * W && i < L.nx && j < L.ny;
-        cc = rr = (long long)colour * L.P.ny * W + p;
+    long long cc = (long long)colour * L.P.ny * W + p, rr = cc;  // dU of the cell, its row
+    if (valid) {
+        if constexpr (TILED) {
+            int row;
+            valid = tiled_cell(L, colour, lane, i, j, row);
+            if (valid) { rr = row; cc = perm2d_of<C>(L.P, i, j); }
+        } else {
+            const int jr = (int)(p / W), k = (int)(p - (long long)jr * W);
+            if (C == 9) { i = 3 * k + colour % 3; j = 3 * jr + colour / 3; }
+            else { j = jr; i = ((colour - j) % C + C) % C + C * k; }
+            valid = i < L.nx && j < L.ny;
+        }
     }
     const long long n = L.P.M;
     double r = 0.0;
@@ -320,7 +321,7 @@ __global__ void __launch_bounds__(3 * kSplitCells) k_smooth2d_split(T *mg, Level
             stencil_off(NB, b, di, dj);
             const int pi = i + di, pj = j + dj;
             const bool ok = pi >= 0 && pi < L.nx && pj >= 0 && pj < L.ny;
-            const long long q = ok ? perm2d(L.P, pi, pj) : cc;
+            const long long q = ok ? perm2d_of<C>(L.P, pi, pj) : cc;
             const double a = lds2<STREAM>(Jr + (b * 9 + c * 3 + 0) * n) * (double)Ur[q] +
                              lds2<STREAM>(Jr + (b * 9 + c * 3 + 1) * n) * (double)Ur[n + q] +
                              lds2<STREAM>(Jr + (b * 9 + c * 3 + 2) * n) * (double)Ur[2 * n + q];
