@@ -417,9 +417,11 @@ __global__ void __launch_bounds__(kTile) k_residual_batch(const Inst1D *insts, c
 }
 
 // One workgroup may take all tiles, one after the other: its sum in k_sum_res's order then is res, and
-// the call is one launch.  Up to kResTiles tiles that is the cheaper way: the host's launches are what
-// such a call costs (residual and Jacobian, 200 cells: 23.8 us with a launch for the sum, 20.5 without).
-constexpr int kResTiles = 4;
+// the call is one launch.  Up to kResTiles tiles that is the cheaper way: calls in a row cost what the host's
+// launches cost (11.5 us a call, 14.5 with a launch for the sum), and a call that is waited for gains a launch
+// and loses 1.4 us a further tile (1 / 2 / 3 / 4 tiles: 22.2 / 23.8 / 25.0 / 26.5 us, 25.0 with a
+// launch for the sum, whatever the tiles).
+constexpr int kResTiles = 3;
 
 template <bool SURF>
 __global__ void __launch_bounds__(kTile) k_residual_single(Inst1D I, double *res)
