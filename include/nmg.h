@@ -258,9 +258,10 @@ nmg_status nmg_newton2d_steps(const nmg_desc *desc, const nmg_params *params, vo
  * and harnesses that forbid hipMalloc.  nmg_newton_solve_static is nmg_newton_solve with the
  * library's own device workspace instead of the ws argument: a static array of
  * NMG_STATIC_WS_MIB MiB that every GPU the library runs on holds from the library's load until
- * the process ends.  Same arguments and results otherwise (the same kernels, launched without a
- * HIP graph; the result is bitwise that of nmg_newton_solve).  It calls no hipMalloc, hipFree,
- * pinned-memory or other allocating HIP routine.  A problem whose nmg_workspace_bytes exceeds
+ * the process ends.  Same arguments and results otherwise (launched without a HIP graph and, in 2D,
+ * with a launch per colour pass instead of cooperative phases; the result is bitwise that of
+ * nmg_newton_solve).  It calls no hipMalloc, hipFree, pinned-memory or other allocating HIP routine.  A
+ * problem whose workspace (nmg_workspace_bytes, in 2D less the cooperative phases' mailbox) exceeds
  * the array returns NMG_ENOMEM_WS (64 MiB covers 1D grids up to about 2e5 cells and 2D grids up
  * to 256 x 128 in FP64, 512 x 256 with NMG_FP32_MG).  Every call on one GPU uses that GPU's one
  * array and leaves its contents behind (each call initialises what it reads): calls that overlap
